@@ -134,9 +134,59 @@ struct NetGatherArgs {
   uint32_t* err;
 };
 
-// Synchronous activation over pattern blocks of 4 (one pattern per float4 component); state
-// buffers [pblocks][nodes] of float4, swapped after each step.
+// Synchronous activation. A genome whose node states fit the LDS runs all its steps in one
+// workgroup per block of 4 Q patterns (k_net_run); the others, and those whose edges would keep one
+// workgroup busy long after the rest of the chip, run one launch per step over state buffers
+// [pblocks][nodes] of float4 (4 patterns per block), swapped after each step.
+constexpr int kNetRunThreads = 1024;          // 16 waves: two workgroups fill a CU
+constexpr uint32_t kNetRunMaxQ = 4;           // float4 pattern groups of a workgroup, at most
+constexpr uint32_t kNetRunLds = 160u * 1024u;
+// LDS of a genome of n nodes: two state buffers of n * q float4 and n + 1 edge offsets.
+inline constexpr uint32_t net_run_lds(uint32_t n, uint32_t q) { return n * (32u * q + 4u) + 4u; }
+constexpr int kNetRanges = 8;                 // classes of genomes in a launch, at most
+constexpr uint32_t kNetStageFloats = 256;     // patterns and targets small enough for the kernarg
+
+// Patterns and targets passed by value to the device buffer the kernels read.
+struct NetStageArgs {
+  float* dst;
+  uint32_t n;
+  float v[kNetStageFloats];
+};
+
+struct NetRunArgs {
+  const uint32_t* order;       // genomes
+  const int64_t* node_offset;  // [n_genomes + 1]
+  const int32_t* node_in;
+  const int64_t* in_offset;
+  const uint32_t* in_src;
+  const float* in_w;
+  const float* patterns;       // [n_patterns * n_inputs]
+  const float* targets;        // [n_patterns] or NULL (fitness: one output, at most 4 patterns)
+  const int32_t* out_node;     // [n_outputs] substrate index of output o
+  float* outputs;              // [n_genomes * n_patterns * n_outputs] or NULL
+  float* fitness;              // [n_genomes] or NULL
+  int64_t nodes, edges;
+  uint32_t n_genomes;
+  uint32_t n_inputs, n_outputs, n_patterns;
+  uint32_t steps;
+  uint32_t lds_bytes;          // the launch's dynamic LDS
+  // class r: genomes order[first[r]] .. (count[r] of them), blocks[r] blocks of 4 q[r] patterns
+  uint32_t first[kNetRanges], count[kNetRanges], blocks[kNetRanges], q[kNetRanges];
+};
+
+// The genomes of a stepwise launch: up to kNetRanges runs of `order`.
+struct NetList {
+  const uint32_t* order;
+  uint32_t first[kNetRanges];  // run r: order[first[r]] ..
+  uint32_t count[kNetRanges];
+  uint32_t total;              // sum of the counts
+  uint32_t max_nodes;          // nodes of its largest genome
+  uint32_t n_genomes;
+};
+
 struct NetStateArgs {
+  NetList list;
+  const int64_t* node_offset;
   const int32_t* node_in;   // [nodes]
   const float* patterns;    // [n_patterns * n_inputs]
   float* state;             // [pblocks * nodes * 4]
@@ -147,6 +197,8 @@ struct NetStateArgs {
 };
 
 struct NetStepArgs {
+  NetList list;
+  const int64_t* node_offset;
   const int32_t* node_in;
   const int64_t* in_offset;
   const uint32_t* in_src;
@@ -158,6 +210,7 @@ struct NetStepArgs {
 };
 
 struct NetOutArgs {
+  NetList list;
   const int64_t* node_offset;  // [n_genomes + 1]
   const int32_t* out_node;     // [n_outputs] substrate index of output o
   const float* state;          // the final state
@@ -165,10 +218,8 @@ struct NetOutArgs {
   float* outputs;              // [n_genomes * n_patterns * n_outputs] or NULL
   float* fitness;              // [n_genomes] or NULL
   int64_t nodes;
-  uint32_t n_genomes;
   uint32_t n_outputs;
   uint32_t n_patterns;
-  uint32_t pblocks;
 };
 
 }  // namespace emr

@@ -4,12 +4,13 @@
 // kept nodes' numbering and their incoming edges grouped by destination, and synchronous
 // activation over a batch of input patterns with an optional XOR fitness.
 //
-// Work over edges runs one thread per edge across the whole population, and activation one wave
-// per (node, pattern block): genomes are very unequal (a genome with a high-frequency CPPN can
-// hold a large share of the population's edges), so no step may give one genome to one
-// workgroup when its cost grows with the genome's edges. Only steps whose cost follows a
-// genome's node count (its bitmap, its node numbering) run one workgroup per genome. Numbering
-// and layouts: network.h.
+// Work over edges runs one thread per edge across the whole population: genomes are very unequal (a
+// genome with a high-frequency CPPN can hold a large share of the population's edges), so no
+// step may give one genome to one workgroup when its cost grows with the genome's edges beyond
+// its share of the chip. Steps whose cost follows a genome's node count (its bitmap, its node
+// numbering) run one workgroup per genome, and activation one per (genome, pattern block) while
+// that block's edges stay below the chip's share (the rule is in networks.cpp). Numbering and
+// layouts: network.h.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -329,92 +330,281 @@ __global__ void __launch_bounds__(kNetThreads) k_net_gather(NetGatherArgs A) {
 }
 
 // ------------------------------------------------------------------------ activation
-// Initial state: input nodes hold their pattern values, every other node 0.
-__global__ void __launch_bounds__(kNetThreads) k_net_state(NetStateArgs A) {
-  const int64_t total = (int64_t)A.pblocks * A.nodes;
-  float4* st = reinterpret_cast<float4*>(A.state);
-  for (int64_t t = grid_thread(); t < total; t += grid_threads()) {
-    const uint32_t pb = (uint32_t)(t / A.nodes);
-    const int64_t i = t - (int64_t)pb * A.nodes;
-    const int32_t slot = A.node_in[i];
-    float c[4] = {0.f, 0.f, 0.f, 0.f};
-    if (slot >= 0 && (uint32_t)slot < A.n_inputs) {
+__global__ void __launch_bounds__(kNetThreads) k_net_stage(NetStageArgs A) {
+  if (threadIdx.x < A.n) A.dst[threadIdx.x] = A.v[threadIdx.x];
+}
+
+// Four patterns (block pb) of input slot `slot`.
+__device__ __forceinline__ float4 pattern4(const float* patterns, uint32_t n_patterns,
+                                           uint32_t n_inputs, int32_t slot, uint32_t pb) {
+  float c[4] = {0.f, 0.f, 0.f, 0.f};
+  if (slot >= 0 && (uint32_t)slot < n_inputs) {
 #pragma unroll
-      for (uint32_t q = 0; q < 4; ++q) {
-        const uint32_t p = 4u * pb + q;
-        c[q] = p < A.n_patterns ? A.patterns[(int64_t)p * A.n_inputs + (uint32_t)slot] : 0.0f;
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t p = 4u * pb + k;
+      c[k] = p < n_patterns ? patterns[(int64_t)p * n_inputs + (uint32_t)slot] : 0.0f;
+    }
+  }
+  return make_float4(c[0], c[1], c[2], c[3]);
+}
+
+__device__ __forceinline__ void add4(float4& a, const float4& b) {
+  a.x += b.x;
+  a.y += b.y;
+  a.z += b.z;
+  a.w += b.w;
+}
+// a and b exchanged between lane halves (rows of 16 in swap16) so that the sum of the two results
+// is, in the lower half (even rows), a plus its partner 32 (16) lanes away, and in the upper half
+// (odd rows) the same of b: one butterfly stage of two values in two instructions.
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// v plus v of the lane that the DPP control names.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+                 0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4E, kDppXor1 = 0xB1;
+
+// A node's incoming sum over one wave, for the 4 Q patterns whose states are x[source * Q + q]
+// (q = lane % Q). The sum is always the same 64 partial sums, partial k an fmaf chain over edges
+// k, k + 64, ... in list order, added in a fixed butterfly, so its bits depend neither on Q nor on
+// the run: lane group t = lane / Q holds partials t, t + S, t + 2 S, ... (S = 64 / Q), the high
+// bits of k are folded inside the lane and the low ones across lanes. The stages over 32 and 16
+// lanes leave one of the four patterns per row of 16 lanes, so the rest and the sigmoid run once
+// for all four: the lane returns the sum of pattern 4 q + lane / 16. The next 64 edges are loaded
+// while the current ones are summed.
+template <int Q>
+__device__ __forceinline__ float node_sum(const float4* x, const uint32_t* __restrict__ src,
+                                           const float* __restrict__ wt, uint32_t deg,
+                                           uint32_t base, uint32_t n, uint32_t lane) {
+  constexpr uint32_t S = kWave / Q;
+  const uint32_t q = lane % Q, t = lane / Q;
+  float4 acc[Q];
+  uint32_t s[Q];
+  float w[Q];
+#pragma unroll
+  for (int j = 0; j < Q; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // (src and wt step along the list, so a lane's offsets from them stay constant)
+  auto load = [&](uint32_t left) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const uint32_t k = S * (uint32_t)j + t;
+      s[j] = n;  // (no edge: adds nothing)
+      w[j] = 0.0f;
+      if (k < left) {
+        s[j] = src[k] - base;  // (below n: k_net_gather checked every source)
+        w[j] = wt[k];
       }
     }
-    st[t] = make_float4(c[0], c[1], c[2], c[3]);
-  }
-}
-
-// One synchronous step: one wave per (node, pattern block). An input node keeps its values; every
-// other node takes sigmoid of the sum of w * (the source's previous state) over its incoming
-// edges: lane k sums edges k, k + 64, ... of the node's list as an fmaf chain in list order, then
-// the 64 partial sums are added in a fixed butterfly (the same bits on every run).
-__global__ void __launch_bounds__(kNetThreads) k_net_step(NetStepArgs A) {
-  const int64_t item = (int64_t)blockIdx.x * (kNetThreads / kWave) + threadIdx.x / kWave;
-  const int64_t total = (int64_t)A.pblocks * A.nodes;
-  if (item >= total) return;
-  const uint32_t lane = threadIdx.x % kWave;
-  const uint32_t pb = (uint32_t)(item / A.nodes);
-  const int64_t i = item - (int64_t)pb * A.nodes;
-  const float4* cur = reinterpret_cast<const float4*>(A.cur) + (int64_t)pb * A.nodes;
-  float4* nxt = reinterpret_cast<float4*>(A.nxt) + (int64_t)pb * A.nodes;
-  if (A.node_in[i] >= 0) {
-    if (lane == 0) nxt[i] = cur[i];
-    return;
-  }
-  float zx = 0.f, zy = 0.f, zz = 0.f, zw = 0.f;
-  const int64_t e1 = A.in_offset[i + 1];
-  for (int64_t e = A.in_offset[i] + lane; e < e1; e += kWave) {
-    const uint32_t s = A.in_src[e];
-    if ((int64_t)s >= A.nodes) continue;  // (gather checked every source)
-    const float w = A.in_w[e];
-    const float4 x = cur[s];
-    zx = fmaf(w, x.x, zx);
-    zy = fmaf(w, x.y, zy);
-    zz = fmaf(w, x.z, zz);
-    zw = fmaf(w, x.w, zw);
+    src += kWave;
+    wt += kWave;
+  };
+  load(deg);
+  while (deg != 0u) {
+    float4 v[Q];
+    float u[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (s[j] < n) v[j] = x[s[j] * Q + q];
+      u[j] = w[j];
+    }
+    deg = deg > (uint32_t)kWave ? deg - kWave : 0u;
+    if (deg != 0u) load(deg);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      acc[j].x = fmaf(u[j], v[j].x, acc[j].x);
+      acc[j].y = fmaf(u[j], v[j].y, acc[j].y);
+      acc[j].z = fmaf(u[j], v[j].z, acc[j].z);
+      acc[j].w = fmaf(u[j], v[j].w, acc[j].w);
+    }
   }
 #pragma unroll
-  for (int o = kWave / 2; o >= 1; o >>= 1) {
-    zx += __shfl_xor(zx, o, kWave);
-    zy += __shfl_xor(zy, o, kWave);
-    zz += __shfl_xor(zz, o, kWave);
-    zw += __shfl_xor(zw, o, kWave);
-  }
-  if (lane == 0) nxt[i] = make_float4(sigmoid_f(zx), sigmoid_f(zy), sigmoid_f(zz), sigmoid_f(zw));
+  for (int h = Q / 2; h >= 1; h >>= 1)
+#pragma unroll
+    for (int j = 0; j < h; ++j) add4(acc[j], acc[j + h]);
+  float z = swap_add16(swap_add32(acc[0].x, acc[0].z), swap_add32(acc[0].y, acc[0].w));
+  static_assert(Q <= 4, "the stages over 8 and 4 lanes are always needed");
+  z = dpp_add<kDppRor8>(z);  // (a rotation by 8 of 16 lanes; by 4 of values of period 8)
+  z = dpp_add<kDppRor4>(z);
+  if constexpr (Q <= 2) z = dpp_add<kDppXor2>(z);
+  if constexpr (Q <= 1) z = dpp_add<kDppXor1>(z);
+  return z;
 }
 
-// Outputs of every (genome, pattern, output), and the XOR fitness of every genome (one output,
-// four patterns: 1 - the mean squared error against the targets).
-__global__ void __launch_bounds__(kNetThreads) k_net_out(NetOutArgs A) {
-  const float4* st = reinterpret_cast<const float4*>(A.state);
-  const int64_t per_g = (int64_t)A.n_patterns * A.n_outputs;
+// All steps of one genome for one block of 4 Q patterns. One launch per step over global states
+// gathers 16 bytes per edge and four patterns from L2 (150 networks, 0.51M edges, 1000 patterns, 4
+// steps: 2560 us); here the gathers are LDS reads, the edges are read once per 4 Q patterns and
+// the steps need no launches between them (468 us; bound by the instructions of the many small
+// nodes' sums and the latency of their edge loads, which 32 waves per CU hide). The states of its nodes live in two LDS
+// buffers (swapped by each step), one wave per node and step, the edges read from L2. An input
+// node holds its pattern values in both buffers. The node's first edge (bit 31: an input node) is
+// kept in LDS after the states.
+template <int Q>
+__device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_t block,
+                                        float4* lds) {
+  const int64_t n0 = A.node_offset[g];
+  const uint32_t n = (uint32_t)(A.node_offset[g + 1] - n0);
+  if (n0 < 0 || n0 + (int64_t)n > A.nodes || net_run_lds(n, Q) > A.lds_bytes) return;  // (never)
+  const int64_t e0 = A.in_offset[n0], e1 = A.in_offset[n0 + n];
+  if (e0 < 0 || e1 < e0 || e1 > A.edges || e1 - e0 > 0x7FFFFFFF) return;  // (host-checked)
+  const uint32_t edges = (uint32_t)(e1 - e0);
+  const uint32_t lane = threadIdx.x % kWave;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  float4* cur = lds;
+  float4* nxt = lds + n * Q;
+  uint32_t* first = reinterpret_cast<uint32_t*>(lds + 2u * n * Q);
+  for (uint32_t i = threadIdx.x; i < n * Q; i += kNetRunThreads) {
+    const float4 v =
+        pattern4(A.patterns, A.n_patterns, A.n_inputs, A.node_in[n0 + i / Q], block * Q + i % Q);
+    cur[i] = v;
+    nxt[i] = v;
+  }
+  for (uint32_t i = threadIdx.x; i <= n; i += kNetRunThreads) {
+    const int64_t e = A.in_offset[n0 + i] - e0;
+    const uint32_t f = e < 0 ? 0u : (e > (int64_t)edges ? edges : (uint32_t)e);
+    first[i] = f | (i < n && A.node_in[n0 + i] >= 0 ? 0x80000000u : 0u);
+  }
+  __syncthreads();
+  for (uint32_t step = 0; step < A.steps; ++step) {
+    for (uint32_t i = wave; i < n; i += kNetRunThreads / kWave) {
+      const uint32_t f = __builtin_amdgcn_readfirstlane(first[i]);
+      if (f >> 31) continue;
+      const uint32_t l = __builtin_amdgcn_readfirstlane(first[i + 1]) & 0x7FFFFFFFu;
+      const float z = node_sum<Q>(cur, A.in_src + e0 + f, A.in_w + e0 + f, l > f ? l - f : 0u,
+                                  (uint32_t)n0, n, lane);
+      if (lane % 16u < (uint32_t)Q)
+        reinterpret_cast<float*>(nxt + i * Q + lane % 16u)[lane / 16u] = sigmoid_f(z);
+    }
+    __syncthreads();
+    float4* s = cur;
+    cur = nxt;
+    nxt = s;
+  }
+  const float* c = reinterpret_cast<const float*>(cur);
   if (A.outputs) {
-    for (int64_t t = grid_thread(); t < (int64_t)A.n_genomes * per_g; t += grid_threads()) {
-      const uint32_t g = (uint32_t)(t / per_g);
-      const int64_t r = t - (int64_t)g * per_g;
+    const uint32_t np = min(A.n_patterns - block * 4u * Q, 4u * Q);
+    for (uint32_t i = threadIdx.x; i < np * A.n_outputs; i += kNetRunThreads) {
+      const uint32_t p = i / A.n_outputs, o = i % A.n_outputs;
+      const uint32_t node = (uint32_t)A.out_node[o];
+      if (node >= n) continue;  // (host-checked)
+      A.outputs[((int64_t)g * A.n_patterns + block * 4u * Q + p) * A.n_outputs + o] =
+          c[node * 4u * Q + p];
+    }
+  }
+  if (A.fitness && threadIdx.x == 0 && (uint32_t)A.out_node[0] < n) {
+    float se = 0.0f;
+    for (uint32_t k = 0; k < A.n_patterns && k < 4u; ++k) {
+      const float d = c[(uint32_t)A.out_node[0] * 4u * Q + k] - A.targets[k];
+      se = fmaf(d, d, se);
+    }
+    A.fitness[g] = 1.0f - se / (float)A.n_patterns;
+  }
+}
+
+__global__ void __launch_bounds__(kNetRunThreads, 8) k_net_run(NetRunArgs A) {
+  extern __shared__ float4 net_lds[];
+  uint32_t at = blockIdx.x;
+#pragma unroll
+  for (int r = 0; r < kNetRanges; ++r) {
+    const uint32_t blocks = A.blocks[r], all = A.count[r] * blocks;
+    if (at < all) {
+      const uint32_t g = A.order[A.first[r] + at / blocks], block = at % blocks;
+      if (g >= A.n_genomes) return;
+      switch (A.q[r]) {
+        case 1: net_run<1>(A, g, block, net_lds); break;
+        case 2: net_run<2>(A, g, block, net_lds); break;
+        default: net_run<4>(A, g, block, net_lds); break;
+      }
+      return;
+    }
+    at -= all;
+  }
+}
+
+// The k-th genome of a list (k < total).
+__device__ __forceinline__ uint32_t list_genome(const NetList& L, uint32_t k) {
+#pragma unroll
+  for (int r = 0; r < kNetRanges; ++r) {
+    if (k < L.count[r]) return L.order[L.first[r] + k];
+    k -= L.count[r];
+  }
+  return L.n_genomes;
+}
+
+// The stepwise kernels: blockIdx.y is the list's genome, blockIdx.z the block of four patterns.
+// Initial state: input nodes hold their pattern values, every other node 0.
+__global__ void __launch_bounds__(kNetThreads) k_net_state(NetStateArgs A) {
+  const uint32_t g = list_genome(A.list, blockIdx.y);
+  if (g >= A.list.n_genomes) return;
+  float4* st = reinterpret_cast<float4*>(A.state);
+  const int64_t n1 = A.node_offset[g + 1];
+  for (int64_t i = A.node_offset[g] + grid_thread(); i < n1; i += grid_threads())
+    for (uint32_t pb = blockIdx.z; pb < A.pblocks; pb += gridDim.z)
+      st[(int64_t)pb * A.nodes + i] =
+          pattern4(A.patterns, A.n_patterns, A.n_inputs, A.node_in[i], pb);
+}
+
+// One synchronous step: one wave per (node, pattern block).
+__global__ void __launch_bounds__(kNetThreads) k_net_step(NetStepArgs A) {
+  const uint32_t g = list_genome(A.list, blockIdx.y);
+  if (g >= A.list.n_genomes) return;
+  const uint32_t lane = threadIdx.x % kWave;
+  const int64_t n0 = A.node_offset[g];
+  const uint32_t n = (uint32_t)(A.node_offset[g + 1] - n0);
+  const uint32_t k = blockIdx.x * (kNetThreads / kWave) +
+                     __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (k >= n) return;
+  const int64_t i = n0 + k;
+  for (uint32_t pb = blockIdx.z; pb < A.pblocks; pb += gridDim.z) {
+    const float4* cur = reinterpret_cast<const float4*>(A.cur) + (int64_t)pb * A.nodes;
+    float4* nxt = reinterpret_cast<float4*>(A.nxt) + (int64_t)pb * A.nodes;
+    if (A.node_in[i] >= 0) {
+      if (lane == 0) nxt[i] = cur[i];
+      continue;
+    }
+    const int64_t e0 = A.in_offset[i];
+    const float z = node_sum<1>(cur + n0, A.in_src + e0, A.in_w + e0,
+                                 (uint32_t)(A.in_offset[i + 1] - e0), (uint32_t)n0, n, lane);
+    if (lane % 16u == 0u) reinterpret_cast<float*>(nxt + i)[lane / 16u] = sigmoid_f(z);
+  }
+}
+
+// Outputs of the list's (genome, pattern, output), or their XOR fitness (one output, four
+// patterns: 1 - the mean squared error against the targets).
+__global__ void __launch_bounds__(kNetThreads) k_net_out(NetOutArgs A) {
+  const uint32_t g = list_genome(A.list, blockIdx.y);
+  if (g >= A.list.n_genomes) return;
+  const float4* st = reinterpret_cast<const float4*>(A.state);
+  if (A.outputs) {
+    const int64_t per_g = (int64_t)A.n_patterns * A.n_outputs;
+    for (int64_t r = grid_thread(); r < per_g; r += grid_threads()) {
       const uint32_t p = (uint32_t)(r / A.n_outputs), o = (uint32_t)(r % A.n_outputs);
       const int64_t node = A.node_offset[g] + A.out_node[o];
       if (node >= A.node_offset[g + 1] || node >= A.nodes) continue;  // (host-checked)
-      A.outputs[t] = comp(st[(int64_t)(p / 4u) * A.nodes + node], p % 4u);
+      A.outputs[(int64_t)g * per_g + r] = comp(st[(int64_t)(p / 4u) * A.nodes + node], p % 4u);
     }
   }
-  if (A.fitness) {
-    for (int64_t g = grid_thread(); g < (int64_t)A.n_genomes; g += grid_threads()) {
-      const int64_t node = A.node_offset[g] + A.out_node[0];
-      if (node >= A.node_offset[g + 1] || node >= A.nodes) continue;
-      const float4 v = st[node];
-      float se = 0.0f;
-      for (uint32_t q = 0; q < A.n_patterns && q < 4u; ++q) {
-        const float d = comp(v, q) - A.targets[q];
-        se = fmaf(d, d, se);
-      }
-      A.fitness[g] = 1.0f - se / (float)A.n_patterns;
+  if (A.fitness && grid_thread() == 0) {
+    const int64_t node = A.node_offset[g] + A.out_node[0];
+    if (node >= A.node_offset[g + 1] || node >= A.nodes) return;
+    const float4 v = st[node];
+    float se = 0.0f;
+    for (uint32_t q = 0; q < A.n_patterns && q < 4u; ++q) {
+      const float d = comp(v, q) - A.targets[q];
+      se = fmaf(d, d, se);
     }
+    A.fitness[g] = 1.0f - se / (float)A.n_patterns;
   }
 }
 
@@ -427,10 +617,15 @@ uint32_t stride_blocks(int64_t n) {
   int64_t b = (n + emr::kNetThreads - 1) / emr::kNetThreads;
   return (uint32_t)(b < 1 ? 1 : (b > 16384 ? 16384 : b));
 }
+// (x: the caller's, y: the list's genomes, z: pattern blocks, at most 65535 with a stride loop)
+dim3 list_grid(const emr::NetList& L, uint32_t x, uint32_t pblocks) {
+  return dim3(x < 1 ? 1 : x, L.total, pblocks < 65535u ? pblocks : 65535u);
+}
 }  // namespace
 
 // Steps: 0 rank, 1 edges, 2 flags, 3 reach pass, 4 degrees, 5 kept counts, 6 nodes, 7 keys,
-// 8 gather, 9 initial state, 10 one activation step, 11 outputs / fitness.
+// 8 gather; activation: 9 initial state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns
+// by value, 13 all steps in LDS.
 extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, hipStream_t s) {
   using namespace emr;
   (void)work;
@@ -485,24 +680,46 @@ extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, h
     }
     case 9: {
       const auto& A = *static_cast<const NetStateArgs*>(args);
-      hipLaunchKernelGGL(k_net_state, dim3(stride_blocks((int64_t)A.pblocks * A.nodes)), blk, 0, s,
-                         A);
+      hipLaunchKernelGGL(k_net_state, list_grid(A.list, (A.list.max_nodes + kNetThreads - 1) /
+                                                            kNetThreads, A.pblocks),
+                         blk, 0, s, A);
       break;
     }
     case 10: {
       const auto& A = *static_cast<const NetStepArgs*>(args);
-      const int64_t waves = (int64_t)A.pblocks * A.nodes;
-      const int64_t b = (waves + kNetThreads / kWave - 1) / (kNetThreads / kWave);
-      if (b <= 0) return hipSuccess;
-      if (b > 0x7FFFFFFF) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(k_net_step, dim3((uint32_t)b), blk, 0, s, A);
+      constexpr uint32_t waves = kNetThreads / kWave;
+      hipLaunchKernelGGL(k_net_step,
+                         list_grid(A.list, (A.list.max_nodes + waves - 1) / waves, A.pblocks), blk,
+                         0, s, A);
       break;
     }
     case 11: {
       const auto& A = *static_cast<const NetOutArgs*>(args);
-      const int64_t items = A.outputs ? (int64_t)A.n_genomes * A.n_patterns * A.n_outputs
-                                      : (int64_t)A.n_genomes;
-      hipLaunchKernelGGL(k_net_out, dim3(stride_blocks(items)), blk, 0, s, A);
+      const uint32_t items = A.outputs ? A.n_patterns * A.n_outputs : 1u;
+      const uint32_t b = (items + kNetThreads - 1) / kNetThreads;
+      hipLaunchKernelGGL(k_net_out, list_grid(A.list, b < 256u ? b : 256u, 1u), blk, 0, s, A);
+      break;
+    }
+    case 12: {
+      const auto& A = *static_cast<const NetStageArgs*>(args);
+      if (A.n > kNetStageFloats || kNetStageFloats > (uint32_t)kNetThreads)
+        return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k_net_stage, dim3(1), blk, 0, s, A);
+      break;
+    }
+    case 13: {
+      const auto& A = *static_cast<const NetRunArgs*>(args);
+      uint64_t b = 0;
+      for (int r = 0; r < kNetRanges; ++r) {
+        if (A.count[r] == 0) continue;
+        if ((A.q[r] & (A.q[r] - 1)) != 0 || A.q[r] == 0 || A.q[r] > kNetRunMaxQ ||
+            A.blocks[r] == 0)
+          return hipErrorInvalidValue;
+        b += (uint64_t)A.count[r] * A.blocks[r];
+      }
+      if (b == 0) return hipSuccess;
+      if (b > 0x7FFFFFFFull || A.lds_bytes > kNetRunLds) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k_net_run, dim3((uint32_t)b), dim3(kNetRunThreads), A.lds_bytes, s, A);
       break;
     }
     default:

@@ -13,6 +13,7 @@
 // a count.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -281,6 +282,10 @@ struct emr_networks {
   Dev d_out_node;  // [n_out] substrate index of output o
   int64_t nodes = 0, edges = 0;
   Dev state, patterns;
+  // genomes in the order of the activation launches (order_genomes), with their node and edge counts
+  Dev order;
+  std::vector<int64_t> order_edges;
+  std::vector<uint32_t> order_host, order_nodes, class_first;
   // pinned staging of an activation's patterns and targets, and the event of its last copy
   void* pin = nullptr;
   size_t pin_bytes = 0;
@@ -303,7 +308,7 @@ struct emr_networks {
     if (pin) (void)hipHostFree(pin);
     for (auto& ph : phases) ph->release_idle();
     for (Dev* d : {&known, &node_offset, &node_cell, &node_in, &in_offset, &in_src, &in_w,
-                   &d_slots, &d_out_node, &state, &patterns})
+                   &d_slots, &d_out_node, &state, &patterns, &order})
       d->reset_idle();
   }
 };
@@ -419,6 +424,9 @@ emr_status express_phase(Build& B, Phase& P) {
   NET_TRY(emr_call_check(cws.p, P.ccap, &P.ctotal, nullptr, B.s));
   return EMR_OK;
 }
+
+emr_status order_genomes(emr_networks& N, const std::vector<int64_t>& node_off,
+                         const std::vector<int64_t>& edge_off, hipStream_t s);
 
 emr_status assemble(Build& B) {
   emr_networks& N = *B.net;
@@ -548,6 +556,7 @@ emr_status assemble(Build& B) {
   if (N.edges > e_raw)
     return failf(EMR_E_DEVICE, "networks: %lld kept edges of %lld", (long long)N.edges,
                  (long long)e_raw);
+  NET_TRY(order_genomes(N, node_off, edge_off, s));
   Dev d_edge_off, gid;
   NET_TRY(alloc(N.node_offset, (size_t)(G + 1) * 8, "network node offsets", s));
   NET_TRY(alloc(d_edge_off, (size_t)(G + 1) * 8, "network edge offsets", s));
@@ -603,6 +612,100 @@ emr_status assemble(Build& B) {
   return EMR_OK;
 }
 
+// The genomes in the order of the activation launches: by class of node count (the classes of
+// run_forward), the most edges first inside a class.
+struct RunClass {
+  uint32_t lds;  // LDS of the class's genomes, at most
+  uint32_t q;    // float4 pattern groups of a workgroup, at most
+};
+// The more patterns share one read of the edges the better, as long as two workgroups of 16 waves
+// share a CU's LDS: 80 KB at 4, 2 and then 1 float4 of patterns per node, else the whole
+// 160 KB. The last class holds what does not fit and always runs stepwise.
+constexpr RunClass kRunClass[] = {{80u << 10, 4}, {80u << 10, 2},
+                                  {80u << 10, 1}, {160u << 10, 1}, {0xFFFFFFFFu, 1}};
+constexpr int kRunClasses = sizeof kRunClass / sizeof kRunClass[0];
+static_assert(kRunClasses <= emr::kNetRanges && kRunClass[kRunClasses - 2].lds == emr::kNetRunLds,
+              "a range per class");
+
+emr_status order_genomes(emr_networks& N, const std::vector<int64_t>& node_off,
+                         const std::vector<int64_t>& edge_off, hipStream_t s) {
+  const uint32_t G = (uint32_t)N.n_genomes;
+  std::vector<uint32_t>& order = N.order_host;
+  order.resize(G);
+  std::vector<uint8_t> cls(G);
+  for (uint32_t g = 0; g < G; ++g) {
+    order[g] = g;
+    const int64_t n = node_off[g + 1] - node_off[g];
+    int c = 0;
+    while (c + 1 < kRunClasses &&
+           (n > (int64_t)emr::kNetRunLds / 32 || edge_off[g + 1] - edge_off[g] > INT32_MAX ||
+            emr::net_run_lds((uint32_t)n, kRunClass[c].q) > kRunClass[c].lds))
+      ++c;
+    cls[g] = (uint8_t)c;
+  }
+  auto edges = [&](uint32_t g) { return edge_off[g + 1] - edge_off[g]; };
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
+    return cls[a] != cls[b] ? cls[a] < cls[b] : edges(a) > edges(b);
+  });
+  N.order_edges.resize(G);
+  N.order_nodes.resize(G);
+  N.class_first.assign(kRunClasses + 1, 0);
+  for (uint32_t k = 0; k < G; ++k) {
+    N.order_edges[k] = edges(order[k]);
+    N.order_nodes[k] = (uint32_t)(node_off[order[k] + 1] - node_off[order[k]]);
+    ++N.class_first[cls[order[k]] + 1];
+  }
+  for (int c = 0; c < kRunClasses; ++c) N.class_first[c + 1] += N.class_first[c];
+  NET_TRY(alloc(N.order, (size_t)G * 4, "activation order", s));
+  return to_device(N.order.p, order.data(), (size_t)G * 4, s);
+}
+
+// The patterns (and targets) on the device: small ones as kernel arguments, others staged in
+// pinned memory and copied on the stream (the staging is rewritten only after the previous
+// call's copy has completed).
+emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
+                          const float* targets, size_t n_tgt, hipStream_t s) {
+  const size_t need = (n_pat + n_tgt) * 4;
+  if (M.patterns.bytes < need || !M.patterns.p)
+    NET_TRY(alloc(M.patterns, need, "input patterns", s));
+  if (n_pat + n_tgt <= emr::kNetStageFloats) {
+    emr::NetStageArgs a{};
+    a.dst = M.patterns.as<float>();
+    a.n = (uint32_t)(n_pat + n_tgt);
+    std::memcpy(a.v, patterns, n_pat * 4);
+    if (n_tgt) std::memcpy(a.v + n_pat, targets, n_tgt * 4);
+    NET_HIP(emr_launch_net(12, &a, 0, s));
+    return EMR_OK;
+  }
+  if (!M.pin_done) NET_HIP(hipEventCreateWithFlags(&M.pin_done, hipEventDisableTiming));
+  if (M.pin_pending) NET_HIP(hipEventSynchronize(M.pin_done));
+  M.pin_pending = false;
+  if (M.pin_bytes < need || !M.pin) {
+    if (M.pin) (void)hipHostFree(M.pin);
+    M.pin = nullptr;
+    M.pin_bytes = 0;
+    if (hipHostMalloc(&M.pin, need, hipHostMallocDefault) != hipSuccess) {
+      M.pin = nullptr;
+      (void)hipGetLastError();
+      return failf(EMR_E_NOMEM, "networks: cannot allocate %zu bytes of pinned staging", need);
+    }
+    M.pin_bytes = need;
+  }
+  std::memcpy(M.pin, patterns, n_pat * 4);
+  if (n_tgt) std::memcpy(static_cast<float*>(M.pin) + n_pat, targets, n_tgt * 4);
+  NET_HIP(hipMemcpyAsync(M.patterns.p, M.pin, need, hipMemcpyHostToDevice, s));
+  NET_HIP(hipEventRecord(M.pin_done, s));
+  M.pin_pending = true;
+  return EMR_OK;
+}
+
+// Smallest edge count that sends a genome to the stepwise kernels (below it the launches of the
+// steps cost more than one workgroup's longer run), and the most steps of a fused run (one launch
+// stays well below a second).
+constexpr int64_t kStepwiseEdges = 16384;
+constexpr int32_t kFusedSteps = 1024;
+constexpr int64_t kFusedWorkgroups = 256;  // half of those that the chip holds
+
 emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_patterns,
                        int32_t steps, float* outputs, float* fitness, const float* targets,
                        hipStream_t s) {
@@ -614,58 +717,125 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
   const int64_t pblocks = (n_patterns + 3) / 4;
   if (pblocks * (N->nodes ? N->nodes : 1) > ((int64_t)1 << 40))
     return failf(EMR_E_LIMIT, "networks: too many nodes x patterns");
-  // two state buffers of [pblocks][nodes] float4
-  const size_t half = (size_t)pblocks * (size_t)(N->nodes ? N->nodes : 1) * 16;
-  if (M.state.bytes < 2 * half) NET_TRY(alloc(M.state, 2 * half, "node states", s));
-  // patterns, then targets, staged in pinned memory and copied on the stream; the staging is
-  // rewritten only after the previous call's copy has completed
-  const size_t pat_bytes = (size_t)n_patterns * (size_t)N->n_in * 4;
-  const size_t tgt_bytes = targets ? (size_t)n_patterns * 4 : 0;
-  const size_t need = pat_bytes + tgt_bytes;
-  if (!M.pin_done) NET_HIP(hipEventCreateWithFlags(&M.pin_done, hipEventDisableTiming));
-  if (M.pin_pending) NET_HIP(hipEventSynchronize(M.pin_done));
-  M.pin_pending = false;
-  if (M.pin_bytes < need || !M.pin) {
-    if (M.pin) (void)hipHostFree(M.pin);
-    M.pin = nullptr;
-    M.pin_bytes = 0;
-    if (hipHostMalloc(&M.pin, need ? need : 16, hipHostMallocDefault) != hipSuccess) {
-      M.pin = nullptr;
-      (void)hipGetLastError();
-      return failf(EMR_E_NOMEM, "networks: cannot allocate %zu bytes of pinned staging", need);
+  const size_t n_pat = (size_t)n_patterns * (size_t)N->n_in;
+  NET_TRY(stage_patterns(M, patterns, n_pat, targets, targets ? (size_t)n_patterns : 0, s));
+  // A class's pattern groups per workgroup, no more than there are.
+  uint32_t q_of[kRunClasses];
+  for (int c = 0; c < kRunClasses; ++c) {
+    uint32_t q = 1;
+    while (q < kRunClass[c].q && (int64_t)q < pblocks) q *= 2;
+    q_of[c] = q;
+  }
+  // One workgroup runs a (genome, pattern block). A genome whose edges exceed twice the mean load
+  // of the workgroups that the chip holds would outlast all others, so it runs stepwise, spread
+  // over the chip (a prefix of its class, which is in descending edge order).
+  int64_t work = 0;
+  for (int c = 0; c < kRunClasses; ++c)
+    for (uint32_t k = N->class_first[c]; k < N->class_first[c + 1]; ++k)
+      work += N->order_edges[k] * ((pblocks + q_of[c] - 1) / q_of[c]);
+  const int64_t most = std::max(kStepwiseEdges, work / kFusedWorkgroups);
+  emr::NetList list{};
+  list.order = N->order.as<uint32_t>();
+  list.n_genomes = (uint32_t)N->n_genomes;
+  uint32_t fused_first[kRunClasses];
+  for (int c = 0; c < kRunClasses; ++c) {
+    const uint32_t k0 = N->class_first[c], k1 = N->class_first[c + 1];
+    uint32_t k = k0;
+    while (k < k1 && (c == kRunClasses - 1 || steps > kFusedSteps || N->order_edges[k] > most)) {
+      list.max_nodes = std::max(list.max_nodes, N->order_nodes[k]);
+      ++k;
     }
-    M.pin_bytes = need ? need : 16;
+    list.first[c] = k0;
+    list.count[c] = k - k0;
+    list.total += k - k0;
+    fused_first[c] = k;
   }
-  if (M.patterns.bytes < need || !M.patterns.p) NET_TRY(alloc(M.patterns, need, "input patterns", s));
-  std::memcpy(M.pin, patterns, pat_bytes);
-  if (tgt_bytes) std::memcpy(static_cast<char*>(M.pin) + pat_bytes, targets, tgt_bytes);
-  NET_HIP(hipMemcpyAsync(M.patterns.p, M.pin, need, hipMemcpyHostToDevice, s));
-  NET_HIP(hipEventRecord(M.pin_done, s));
-  M.pin_pending = true;
-  float* buf[2] = {M.state.as<float>(), reinterpret_cast<float*>(M.state.as<char>() + half)};
-  emr::NetStateArgs sa{N->node_in.as<int32_t>(), M.patterns.as<float>(), buf[0], N->nodes,
-                       (uint32_t)N->n_in, (uint32_t)n_patterns, (uint32_t)pblocks};
-  NET_HIP(emr_launch_net(9, &sa, 0, s));
-  int cur = 0;
-  for (int32_t t = 0; t < steps; ++t, cur ^= 1) {
-    emr::NetStepArgs st{N->node_in.as<int32_t>(), N->in_offset.as<int64_t>(),
-                        N->in_src.as<uint32_t>(), N->in_w.as<float>(), buf[cur], buf[cur ^ 1],
-                        N->nodes, (uint32_t)pblocks};
-    NET_HIP(emr_launch_net(10, &st, 0, s));
+  const float* d_targets = targets ? M.patterns.as<float>() + n_pat : nullptr;
+  emr::NetRunArgs ra{};
+  ra.order = N->order.as<uint32_t>();
+  ra.node_offset = N->node_offset.as<int64_t>();
+  ra.node_in = N->node_in.as<int32_t>();
+  ra.in_offset = N->in_offset.as<int64_t>();
+  ra.in_src = N->in_src.as<uint32_t>();
+  ra.in_w = N->in_w.as<float>();
+  ra.patterns = M.patterns.as<float>();
+  ra.targets = d_targets;
+  ra.out_node = N->d_out_node.as<int32_t>();
+  ra.outputs = outputs;
+  ra.fitness = fitness;
+  ra.nodes = N->nodes;
+  ra.edges = N->edges;
+  ra.n_genomes = (uint32_t)N->n_genomes;
+  ra.n_inputs = (uint32_t)N->n_in;
+  ra.n_outputs = (uint32_t)N->n_out;
+  ra.n_patterns = (uint32_t)n_patterns;
+  ra.steps = (uint32_t)steps;
+  // the classes of 80 KB in one launch, the largest genomes' (the longest workgroups) first; then
+  // the class that takes a whole CU's LDS
+  for (int part = 0; part < 2; ++part) {
+    const int lo = part == 0 ? 0 : kRunClasses - 2, hi = part == 0 ? kRunClasses - 2 : kRunClasses - 1;
+    uint64_t blocks = 0;
+    ra.lds_bytes = 0;
+    for (int r = 0; r < emr::kNetRanges; ++r) ra.count[r] = 0;
+    for (int c = hi - 1, r = 0; c >= lo; --c, ++r) {
+      ra.first[r] = fused_first[c];
+      ra.count[r] = N->class_first[c + 1] - fused_first[c];
+      ra.q[r] = q_of[c];
+      ra.blocks[r] = (uint32_t)((pblocks + q_of[c] - 1) / q_of[c]);
+      blocks += (uint64_t)ra.count[r] * ra.blocks[r];
+      for (uint32_t i = fused_first[c]; i < N->class_first[c + 1]; ++i)
+        ra.lds_bytes = std::max(ra.lds_bytes, emr::net_run_lds(N->order_nodes[i], q_of[c]));
+    }
+    if (blocks > 0x7FFFFFFFull)
+      return failf(EMR_E_LIMIT, "networks: too many genomes x patterns");
+    if (blocks > 0) NET_HIP(emr_launch_net(13, &ra, 0, s));
   }
-  emr::NetOutArgs oa{};
-  oa.node_offset = N->node_offset.as<int64_t>();
-  oa.out_node = N->d_out_node.as<int32_t>();
-  oa.state = buf[cur];
-  oa.targets = targets ? reinterpret_cast<const float*>(M.patterns.as<char>() + pat_bytes) : nullptr;
-  oa.outputs = outputs;
-  oa.fitness = fitness;
-  oa.nodes = N->nodes;
-  oa.n_genomes = (uint32_t)N->n_genomes;
-  oa.n_outputs = (uint32_t)N->n_out;
-  oa.n_patterns = (uint32_t)n_patterns;
-  oa.pblocks = (uint32_t)pblocks;
-  NET_HIP(emr_launch_net(11, &oa, 0, s));
+  if (list.total > 0) {
+    // two state buffers of [pblocks][nodes] float4
+    const size_t half = (size_t)pblocks * (size_t)(N->nodes ? N->nodes : 1) * 16;
+    if (M.state.bytes < 2 * half) NET_TRY(alloc(M.state, 2 * half, "node states", s));
+    float* buf[2] = {M.state.as<float>(), reinterpret_cast<float*>(M.state.as<char>() + half)};
+    // (a launch covers at most 65535 genomes)
+    const emr::NetList whole = list;
+    uint32_t done = 0;
+    while (done < whole.total) {
+      uint32_t skip = done, left = std::min(whole.total - done, 65535u);
+      list.total = left;
+      done += left;
+      for (int c = 0; c < kRunClasses; ++c) {
+        const uint32_t cut = std::min(skip, whole.count[c]);
+        const uint32_t n = std::min(whole.count[c] - cut, left);
+        list.first[c] = whole.first[c] + cut;
+        list.count[c] = n;
+        skip -= cut;
+        left -= n;
+      }
+      emr::NetStateArgs sa{list, N->node_offset.as<int64_t>(), N->node_in.as<int32_t>(),
+                           M.patterns.as<float>(), buf[0], N->nodes, (uint32_t)N->n_in,
+                           (uint32_t)n_patterns, (uint32_t)pblocks};
+      NET_HIP(emr_launch_net(9, &sa, 0, s));
+      int cur = 0;
+      for (int32_t t = 0; t < steps; ++t, cur ^= 1) {
+        emr::NetStepArgs st{list, N->node_offset.as<int64_t>(), N->node_in.as<int32_t>(),
+                            N->in_offset.as<int64_t>(), N->in_src.as<uint32_t>(),
+                            N->in_w.as<float>(), buf[cur], buf[cur ^ 1], N->nodes,
+                            (uint32_t)pblocks};
+        NET_HIP(emr_launch_net(10, &st, 0, s));
+      }
+      emr::NetOutArgs oa{};
+      oa.list = list;
+      oa.node_offset = N->node_offset.as<int64_t>();
+      oa.out_node = N->d_out_node.as<int32_t>();
+      oa.state = buf[cur];
+      oa.targets = d_targets;
+      oa.outputs = outputs;
+      oa.fitness = fitness;
+      oa.nodes = N->nodes;
+      oa.n_outputs = (uint32_t)N->n_out;
+      oa.n_patterns = (uint32_t)n_patterns;
+      NET_HIP(emr_launch_net(11, &oa, 0, s));
+    }
+  }
   if (!M.done) NET_HIP(hipEventCreateWithFlags(&M.done, hipEventDisableTiming));
   NET_HIP(hipEventRecord(M.done, s));
   M.done_pending = true;

@@ -334,10 +334,11 @@ emr_status discover_phase(Build& B, Phase& P) {
   NET_TRY(alloc(P.roffset, (size_t)(P.n_pairs + 1) * 8, "pair offsets", B.s));
   int64_t n_pos = 0, Q = 0;
   NET_TRY(emr_grid_count(N.depth, &n_pos, &Q));
-  // A first guess of 16M records (320 MB) holds the kept cells of every workload measured here,
-  // so the retry (which runs the phase's discovery a second time) stays the exception.
+  // A retry runs the phase's discovery a second time (and a heavy population's hidden phase is
+  // most of a generation), so the first guess is large: 64M records (1.3 GB, as much again for the
+  // pool). One random population of 1000 in ten keeps more than 16M.
   int64_t cap = P.n_pairs * Q;
-  if (cap > (int64_t)1 << 24) cap = (int64_t)1 << 24;
+  if (cap > (int64_t)1 << 26) cap = (int64_t)1 << 26;
   if (cap < 1) cap = 1;
   for (int attempt = 0;; ++attempt) {
     int64_t wsb = 0;

@@ -185,79 +185,97 @@ emr_status build_plan_tables(const ProgDesc* desc, const GenomeInfo* info, int32
   if (P.n_pairs > 0xFFFFFFFFll) return fail_msg(msg, EMR_E_LIMIT, "too many pairs");
 
   // Group each genome's sources by direction, in source order, into sets of <= max_group(window).
-  struct TmpGroup {
-    Group g;
+  // The full sets of a (genome, direction) and the remainder are runs of groups with one program
+  // and one S; order[] holds the sources, run after run.
+  struct Run {
+    uint32_t desc, first;  // its sources order[first] .. order[first + S * count - 1]
+    uint32_t count;        // groups
     int S, window;
-    uint32_t desc;
-    uint32_t src[kMaxGroup];
-    double cost;
+    double cost;  // cost-model slots per query of a group's source, its S sources walked together
   };
-  std::vector<TmpGroup> tmp;
+  std::vector<Run> runs;
+  std::vector<uint32_t> order;
+  runs.reserve(4 * (size_t)G);
+  // (shared sources are listed once per direction, each genome's own sources once)
+  std::vector<uint32_t> shared_of[2];
+  if (!offs)
+    for (int32_t j = 0; j < n_shared; ++j) shared_of[sources[j].dir].push_back((uint32_t)j);
+  const uint32_t shared_at[2] = {0u, (uint32_t)shared_of[0].size()};
+  if (!offs) {
+    order = shared_of[0];
+    order.insert(order.end(), shared_of[1].begin(), shared_of[1].end());
+  } else {
+    order.reserve((size_t)n_sources);
+  }
+  size_t n_groups = 0;
   for (int32_t g = 0; g < G; ++g) {
-    const int32_t lo = offs ? offs[g] : 0, hi = offs ? offs[g + 1] : n_shared;
     for (int dir = 0; dir < 2; ++dir) {
       const uint32_t di = 2u * (uint32_t)g + (uint32_t)dir;
-      const ProgDesc& d = desc[di];
       const int wb = window_bucket(info[di].window);
       if (wb < 0)
         return fail_msg(msg, EMR_E_LIMIT, "genome %d needs a value window of %d", g,
                         info[di].window);
-      const int gmax = max_group(wb);
-      TmpGroup cur{};
-      int n = 0;
-      auto flush = [&]() {
-        if (n == 0) return;
-        cur.S = n;
-        cur.window = wb;
-        cur.desc = di;
-        for (int s = n; s < kMaxGroup; ++s) cur.g.pair[s] = cur.g.pair[n - 1];
-        cur.g.var_off = d.var_off;
-        cur.g.n_rec = d.n_rec;
-        cur.g.n_steps = d.n_steps;
-        cur.g.flags = d.flags;
-        tmp.push_back(cur);
-        cur = TmpGroup{};
-        n = 0;
-      };
-      for (int32_t j = lo; j < hi; ++j) {
-        if (sources[j].dir != dir) continue;
-        const int64_t pair = offs ? (int64_t)j : (int64_t)g * n_shared + j;
-        cur.g.pair[n] = (uint32_t)pair;
-        cur.src[n] = (uint32_t)j;
-        if (++n == gmax) flush();
+      uint32_t first, n;
+      if (offs) {
+        first = (uint32_t)order.size();
+        for (int32_t j = offs[g]; j < offs[g + 1]; ++j)
+          if (sources[j].dir == dir) order.push_back((uint32_t)j);
+        n = (uint32_t)order.size() - first;
+      } else {
+        first = shared_at[dir];
+        n = (uint32_t)shared_of[dir].size();
       }
-      flush();
+      const uint32_t gmax = (uint32_t)max_group(wb), full = n / gmax, rest = n % gmax;
+      if (full) runs.push_back({di, first, full, (int)gmax, wb, query_slots(info[di], 4.0, (int)gmax)});
+      if (rest) runs.push_back({di, first + full * gmax, 1u, (int)rest, wb,
+                                query_slots(info[di], 4.0, (int)rest)});
+      n_groups += full + (rest ? 1 : 0);
     }
   }
   // Order groups by bucket; assign bias-table offsets and members. Within a bucket the most
   // expensive programs come first (the round-robin chunk shares of a first call then end with the
   // cheapest); output order does not depend on this order (each pair has its own totals and
   // offsets).
-  // per query of a group's source, its S sources walked together
-  for (TmpGroup& t : tmp) t.cost = query_slots(info[t.desc], 4.0, t.S);
-  auto cost = [](const TmpGroup& t) { return t.cost; };
-  std::stable_sort(tmp.begin(), tmp.end(), [&](const TmpGroup& a, const TmpGroup& b) {
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) {
     if (a.S != b.S) return a.S < b.S;
     if (a.window != b.window) return a.window < b.window;
-    return cost(a) > cost(b);
+    return a.cost > b.cost;
   });
-  P.groups.reserve(tmp.size());
+  P.groups.resize(n_groups);
+  P.group_member0.resize(n_groups);
+  P.group_cost.resize(n_groups);
+  P.members.resize((size_t)P.n_pairs);
   uint64_t bias = 0;
-  for (size_t i = 0; i < tmp.size(); ++i) {
-    TmpGroup& t = tmp[i];
-    if (P.buckets.empty() || P.buckets.back().S != t.S || P.buckets.back().window != t.window)
-      P.buckets.push_back({t.S, t.window, (uint32_t)i, 0, 0.0, 0});
-    P.buckets.back().count++;
-    if (t.g.flags & 1u) P.buckets.back().varying = P.buckets.back().count;
-    P.buckets.back().cost += t.S * cost(t);
-    t.g.bias_off = (uint32_t)bias;
-    P.group_member0.push_back((uint32_t)P.members.size());
-    const uint32_t rows = t.g.n_rec + 2;  // output row, one per record at most, prefetch row
-    for (int s = 0; s < t.S; ++s) P.members.push_back({t.desc, t.src[s], (uint32_t)(bias + s), rows});
-    bias += 4ull * rows;
-    if (bias > 0xFFFFFFFFull) return fail_msg(msg, EMR_E_LIMIT, "bias table too large");
-    P.groups.push_back(t.g);
-    P.group_cost.push_back((float)cost(t));
+  uint32_t gi = 0, mi = 0;
+  for (const Run& r : runs) {
+    const ProgDesc& d = desc[r.desc];
+    const int64_t pair0 = offs ? 0 : (int64_t)(r.desc / 2u) * n_shared;
+    const uint32_t rows = d.n_rec + 2;  // output row, one per record at most, prefetch row
+    if (P.buckets.empty() || P.buckets.back().S != r.S || P.buckets.back().window != r.window)
+      P.buckets.push_back({r.S, r.window, gi, 0, 0.0, 0});
+    PlanTables::Bucket& bk = P.buckets.back();
+    const uint32_t* src = order.data() + r.first;
+    for (uint32_t k = 0; k < r.count; ++k, ++gi, src += r.S) {
+      bk.count++;
+      if (d.flags & 1u) bk.varying = bk.count;
+      bk.cost += r.S * r.cost;
+      Group& q = P.groups[gi];
+      q = Group{};
+      q.var_off = d.var_off;
+      q.n_rec = d.n_rec;
+      q.n_steps = d.n_steps;
+      q.flags = d.flags;
+      q.bias_off = (uint32_t)bias;
+      P.group_member0[gi] = mi;
+      for (int s = 0; s < r.S; ++s) {
+        q.pair[s] = (uint32_t)(pair0 + src[s]);
+        P.members[mi++] = {r.desc, src[s], (uint32_t)(bias + s), rows};
+      }
+      for (int s = r.S; s < kMaxGroup; ++s) q.pair[s] = q.pair[r.S - 1];
+      P.group_cost[gi] = (float)r.cost;
+      bias += 4ull * rows;
+      if (bias > 0xFFFFFFFFull) return fail_msg(msg, EMR_E_LIMIT, "bias table too large");
+    }
   }
   // Part order within the launch: the costliest bucket first (its chunks are handed out first).
   std::stable_sort(P.buckets.begin(), P.buckets.end(),
@@ -272,10 +290,17 @@ emr_status build_plan_tables(const ProgDesc* desc, const GenomeInfo* info, int32
       const PlanTables::Bucket& b = P.buckets[bi];
       L.part[L.n_parts++] = (int)bi;
       L.cost += b.cost;
+      uint32_t last = 0xFFFFFFFFu;
+      double base = 0.0, trans = 0.0;
       for (uint32_t g = 0; g < b.count; ++g) {
-        const GenomeInfo& inf = info[P.members[P.group_member0[b.first + g]].desc];
-        L.slots_base += b.S * query_base(inf, b.S);
-        L.slots_trans += b.S * query_trans(inf, b.S);
+        const uint32_t di = P.members[P.group_member0[b.first + g]].desc;
+        if (di != last) {  // (the groups of a program follow each other)
+          base = b.S * query_base(info[di], b.S);
+          trans = b.S * query_trans(info[di], b.S);
+          last = di;
+        }
+        L.slots_base += base;
+        L.slots_trans += trans;
       }
       L.sources += (double)b.S * b.count;
     }
@@ -317,9 +342,10 @@ emr_status build_plan_tables(const ProgDesc* desc, const GenomeInfo* info, int32
       }
     }
   }
-  for (const Group& g : P.groups)
-    if (!(g.flags & 1u))
-      for (int s = 0; s < kMaxGroup; ++s) P.img[P.t_uniform + g.pair[s]] = 1;
+  for (const PlanTables::Bucket& b : P.buckets)  // (a bucket's uniform groups are its last)
+    for (uint32_t k = b.varying; k < b.count; ++k)
+      for (int s = 0; s < kMaxGroup; ++s)
+        P.img[P.t_uniform + P.groups[b.first + k].pair[s]] = 1;
   if (!P.groups.empty())
     std::memcpy(P.img.data() + P.t_groups, P.groups.data(), P.groups.size() * sizeof(Group));
   if (!P.members.empty())

@@ -204,6 +204,72 @@ emr_status stream_pool(StreamPool** out) {
   return EMR_OK;
 }
 
+// Pinned staging of the host tables' uploads: a copy from pageable memory holds the calling thread
+// for the whole transfer (75 us for a 200 KB table; 15 us into staging). A buffer is handed out
+// again once the event recorded after its copy has completed. At most kStagings buffers of at most
+// kStagingBytes each, kept for the process; a larger upload, or one that finds them all in flight
+// and the table full, copies from the caller's memory and waits.
+constexpr size_t kStagings = 4;
+constexpr size_t kStagingBytes = size_t(16) << 20;
+struct Staging {
+  int device;
+  void* p;
+  size_t size;
+  hipEvent_t done;
+  bool pending;
+};
+std::mutex g_staging_mu;
+std::vector<Staging> g_stagings;
+
+// Copies src to dst (device) on s. The source may be reused on return; the copy is complete only
+// in stream order.
+emr_status upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  if (bytes == 0) return EMR_OK;
+  int dev = 0;
+  HIP_OR_FAIL(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lock(g_staging_mu);
+  Staging* use = nullptr;
+  for (Staging& b : g_stagings) {
+    if (b.device != dev || b.size < bytes || use) continue;
+    if (b.pending) {
+      const hipError_t q = hipEventQuery(b.done);
+      if (q != hipSuccess) {
+        (void)hipGetLastError();  // (not ready is no error of the caller's)
+        continue;
+      }
+      b.pending = false;
+    }
+    use = &b;
+  }
+  if (!use && bytes <= kStagingBytes && g_stagings.size() < kStagings) {
+    Staging b{dev, nullptr, size_t(1) << 20, nullptr, false};
+    while (b.size < bytes) b.size *= 2;
+    if (hipHostMalloc(&b.p, b.size, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+    } else if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipHostFree(b.p);
+    } else {
+      g_stagings.push_back(b);
+      use = &g_stagings.back();
+    }
+  }
+  if (!use) {
+    HIP_OR_FAIL(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
+    HIP_OR_FAIL(hipStreamSynchronize(s));
+    return EMR_OK;
+  }
+  std::memcpy(use->p, src, bytes);
+  use->pending = true;
+  if (hipMemcpyAsync(dst, use->p, bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
+      hipEventRecord(use->done, s) != hipSuccess) {
+    (void)hipStreamSynchronize(s);
+    use->pending = false;
+    return fail(EMR_E_DEVICE, "upload of %zu bytes failed", bytes);
+  }
+  return EMR_OK;
+}
+
 // Per-thread profiling of the discover-kernel launches.
 struct Profiler {
   bool on = false;
@@ -293,6 +359,10 @@ struct Plan : emr::PlanTables {
   // The bias rows of the plan's groups (the bind kernel's output: every position-independent
   // contribution per (genome, source)), computed on the device once, on first use (dev_mu).
   mutable float* d_bias = nullptr;
+  // Recorded after the upload and the bind kernel; a call's stream waits for it until a query has
+  // found it complete (call_tables).
+  mutable hipEvent_t ready = nullptr;
+  mutable std::atomic<bool> ready_done{false};
   // The workgroups' chunk lists of the plan's launches (plan_schedule), one per launch shape, on
   // the device (dev_mu).
   struct Sched {
@@ -319,6 +389,11 @@ struct Plan : emr::PlanTables {
   Plan& operator=(const Plan&) = delete;
   ~Plan() {
     jit.reset();  // drains the device before the compiled tier's module goes
+    // (the tables may go before any call read them: their upload and bind kernel finish first)
+    if (ready) {
+      if (!ready_done.load()) (void)hipEventSynchronize(ready);
+      (void)hipEventDestroy(ready);
+    }
     if (d_tables) (void)hipFree(d_tables);
     if (d_bias) (void)hipFree(d_bias);
     for (const Sched& x : scheds) (void)hipFree(x.d);
@@ -389,30 +464,6 @@ emr_status plan_for(const emr_population* pop, const emr_source* sources, int32_
   return EMR_OK;
 }
 
-// The plan's tables on the device, uploaded (and waited for) on first use.
-emr_status plan_tables(const Plan& P, char** out) {
-  std::lock_guard<std::mutex> lock(P.dev_mu);
-  if (!P.d_tables) {
-    char* d = nullptr;
-    if (hipMalloc((void**)&d, P.img.size()) != hipSuccess)
-      return fail(EMR_E_NOMEM, "device tables of %zu bytes", P.img.size());
-    StreamPool* sp = nullptr;
-    emr_status st = stream_pool(&sp);
-    if (st == EMR_OK &&
-        (hipMemcpyAsync(d, P.img.data(), P.img.size(), hipMemcpyHostToDevice, sp->aux[0]) !=
-             hipSuccess ||
-         hipStreamSynchronize(sp->aux[0]) != hipSuccess))
-      st = fail(EMR_E_DEVICE, "upload of the call tables failed");
-    if (st != EMR_OK) {
-      (void)hipFree(d);
-      return st;
-    }
-    P.d_tables = d;
-  }
-  *out = P.d_tables;
-  return EMR_OK;
-}
-
 // Chunk cost estimates for the schedule, in lane-slots: the queries' cost-model slots (one tile is
 // kTile / kWave positions per lane, for each source of the walk), plus per walk (positions, the
 // variance, records) and per chunk (the group's tables) overheads. A position-independent group
@@ -428,7 +479,10 @@ double chunk_cost(const Plan& P, uint64_t gi, uint32_t S, double tpw, double nt)
   return S * q * nt * (emr::kTile / emr::kWave) + nt / tpw * kSchedWalkSlots + kSchedChunkSlots;
 }
 constexpr size_t kMaxScheds = 16;            // launch shapes a plan keeps lists for
-constexpr uint64_t kSchedMaxChunks = 1u << 22;
+// Placing a chunk costs the host about 0.4 us, and with hundreds of chunks per workgroup the
+// round-robin shares are balanced by their number alone (227 ms of placement before a launch of
+// 24 ms that did not need it), so larger launches run round-robin.
+constexpr uint64_t kSchedMaxChunks = 1u << 17;
 constexpr uint64_t kSchedMaxBytes = 64u << 20;
 
 // The waves' chunk lists of a discover launch with scalars sc on `grid` workgroups, made and
@@ -439,7 +493,9 @@ emr_status plan_schedule(const Plan& P, const emr::DiscoverScalars& sc, uint32_t
                          const uint32_t** d, uint32_t* stride) {
   *d = nullptr;
   *stride = 0;
-  if (grid == 0 || sc.n_chunks == 0 || sc.n_chunks > kSchedMaxChunks) return EMR_OK;
+  if (grid == 0 || sc.n_chunks == 0 || sc.n_chunks > kSchedMaxChunks ||
+      sc.n_chunks > (uint64_t)grid * emr::kListLds)
+    return EMR_OK;
   std::lock_guard<std::mutex> lock(P.dev_mu);
   for (const Plan::Sched& x : P.scheds)
     if (x.grid == grid && x.tiles == sc.tiles && x.n_parts == sc.n_parts &&
@@ -660,38 +716,51 @@ emr::BindArgs bind_args(const emr_population* pop, const Plan& P, const char* ta
   return b;
 }
 
-// The plan's bias rows on the device, computed on first use by the bind kernel on the library's
-// stream and waited for (a table error found then fails the call that needed them).
-emr_status plan_bias(const emr_population* pop, const Plan& P, const char* tables,
-                     const float** out) {
-  std::lock_guard<std::mutex> lock(P.dev_mu);
-  if (!P.d_bias) {
-    const size_t n = P.bias_table_floats();
-    float* d = nullptr;
-    if (hipMalloc((void**)&d, (n + 64) * sizeof(float)) != hipSuccess)
-      return fail(EMR_E_NOMEM, "bias rows of %zu floats", n);
-    uint32_t* err = (uint32_t*)(d + n);  // one word after the rows and their padding
-    StreamPool* sp = nullptr;
-    emr_status st = stream_pool(&sp);
-    uint32_t host_err = 0;
-    if (st == EMR_OK) {
-      const emr::BindArgs b = bind_args(pop, P, tables, d, err);
-      if (emr_launch_fill(d, (int64_t)n + 1, 0u, sp->aux[0]) != hipSuccess ||
-          emr_launch_bind(&b, sp->aux[0]) != hipSuccess ||
-          hipMemcpyAsync(&host_err, err, 4, hipMemcpyDeviceToHost, sp->aux[0]) != hipSuccess ||
-          hipStreamSynchronize(sp->aux[0]) != hipSuccess)
-        st = fail(EMR_E_DEVICE, "computing the bias rows failed");
-      else if (host_err)
-        st = fail(EMR_E_DEVICE, "the bind kernel reported error flags 0x%x (2: a table entry out "
-                  "of range)", host_err);
+// The plan's tables and bias rows on the device: on first use uploaded, and the rows computed by
+// the bind kernel, on the library's stream without waiting; the caller's stream s waits for them.
+// The bind kernel raises a table error into *err (the first call's flags, so that call's check
+// reports it; check_plan_tables has found none).
+emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, uint32_t* err) {
+  if (!P.ready_done.load(std::memory_order_acquire)) {
+    std::lock_guard<std::mutex> lock(P.dev_mu);
+    if (!P.d_bias) {
+      const size_t n = P.bias_table_floats();
+      char* d = nullptr;
+      float* bias = nullptr;
+      StreamPool* sp = nullptr;
+      emr_status st = stream_pool(&sp);
+      if (st != EMR_OK) return st;
+      if (hipMalloc((void**)&d, P.img.size()) != hipSuccess ||
+          hipMalloc((void**)&bias, n * sizeof(float)) != hipSuccess)
+        st = fail(EMR_E_NOMEM, "device tables of %zu bytes and bias rows of %zu floats",
+                  P.img.size(), n);
+      if (st == EMR_OK && !P.ready &&
+          hipEventCreateWithFlags(&P.ready, hipEventDisableTiming) != hipSuccess)
+        st = fail(EMR_E_DEVICE, "event of the call tables");
+      if (st == EMR_OK) st = upload(d, P.img.data(), P.img.size(), sp->aux[0]);
+      if (st == EMR_OK) {
+        const emr::BindArgs b = bind_args(pop, P, d, bias, err);
+        if (emr_launch_fill(bias, (int64_t)n, 0u, sp->aux[0]) != hipSuccess ||
+            emr_launch_bind(&b, sp->aux[0]) != hipSuccess ||
+            hipEventRecord(P.ready, sp->aux[0]) != hipSuccess)
+          st = fail(EMR_E_DEVICE, "computing the bias rows failed");
+      }
+      if (st != EMR_OK) {
+        (void)hipStreamSynchronize(sp->aux[0]);
+        if (d) (void)hipFree(d);
+        if (bias) (void)hipFree(bias);
+        return st;
+      }
+      P.d_tables = d;
+      P.d_bias = bias;
     }
-    if (st != EMR_OK) {
-      (void)hipFree(d);
-      return st;
+    if (hipEventQuery(P.ready) == hipSuccess) {
+      P.ready_done.store(true, std::memory_order_release);
+    } else {
+      (void)hipGetLastError();  // (not ready is no error of the caller's)
+      HIP_OR_FAIL(hipStreamWaitEvent(s, P.ready, 0));
     }
-    P.d_bias = d;
   }
-  *out = P.d_bias;
   return EMR_OK;
 }
 
@@ -1172,12 +1241,12 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
 
 // The plan's own device tables and bias rows and the depth's tile geometry table (each made on
 // first use).
-emr_status call_tables(const emr_population* pop, const Plan& P, CallTables* T) {
-  char* tables = nullptr;
-  emr_status st = plan_tables(P, &tables);
+emr_status call_tables(const emr_population* pop, const Plan& P, const CallFlags& f,
+                       CallTables* T) {
+  emr_status st = plan_device(pop, P, f.s, f.dev + emr::kFlagErr);
   if (st != EMR_OK) return st;
-  T->tables = tables;
-  if ((st = plan_bias(pop, P, tables, &T->bias)) != EMR_OK) return st;
+  T->tables = P.d_tables;
+  T->bias = P.d_bias;
   return tile_geo_table(P.depth, &T->geo, &T->geo_rows);
 }
 
@@ -1226,10 +1295,10 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   emr_status st = check_call_workspace(workspace, workspace_bytes,
                                        (int64_t)workspace_need(P, out ? out->capacity : 0));
   if (st != EMR_OK) return st;
-  CallTables T;
-  if ((st = call_tables(pop, P, &T)) != EMR_OK) return st;
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
+  CallTables T;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
   bool jit = false;
   if ((st = jit_use(pop, P, plan_slots(P), &jit)) != EMR_OK) return st;
   const bool records = out != nullptr && raw == nullptr;
@@ -1290,7 +1359,7 @@ emr_status pack_and_upload(int32_t n, const std::function<emr_genome(int32_t)>& 
   std::vector<emr::ProgDesc> desc;
   std::vector<emr::GenomeInfo> info;
   std::vector<uint32_t> words;
-  const int n_threads = std::max(1, std::min({WorkerPool::get().size(), 16, n / 32}));
+  const int n_threads = std::max(1, std::min({WorkerPool::get().size(), 16, n / 8}));
   std::string msg;
   int32_t bad = -1;
   emr_status pst = emr::pack_genomes(
@@ -1398,6 +1467,7 @@ emr_status emr_pack_population_flat(int32_t n, const int64_t* node_off, const ui
 
 void emr_free_population(emr_population* pop) {
   if (!pop) return;
+  pop->plan.reset();  // (its bind kernel, which reads the program words, has then finished)
   if (pop->d_blob) (void)hipFree(pop->d_blob);
   if (pop->d_desc) (void)hipFree(pop->d_desc);
   delete pop;
@@ -1824,13 +1894,12 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     R.counts_h_pairs = n_pairs + 1;
   }
 
-  CallTables T;
-  st = call_tables(pop, P, &T);
-  if (st != EMR_OK) return st;
   if ((st = check_call_workspace(R.ws, R.ws_bytes, ws_need)) != EMR_OK) return st;
   CallFlags f;  // the chunks raise into its words, handed over once at the end
   st = take_flags(nullptr, R.s, &f);
   if (st != EMR_OK) return st;
+  CallTables T;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
   bool jit = false;
   st = jit_use(pop, P, plan_slots(P) * (double)(total - start) / (double)total, &jit);
   if (st != EMR_OK) return st;
@@ -2036,13 +2105,13 @@ emr_status emr_hidden_sources(const emr_population* pop, const emr_source* sourc
   const HiddenLayout L(G, depth);
   if ((st = check_workspace(out->workspace, out->workspace_bytes, (int64_t)L.bytes)) != EMR_OK)
     return st;
-  CallTables T;
-  if ((st = call_tables(pop, P, &T)) != EMR_OK) return st;
-  R.pair_info = (const uint32_t*)(T.tables + P.t_pairinfo);
-  R.src_xy = (const float*)(T.tables + P.t_srcxy);
   const hipStream_t s = (hipStream_t)stream;
   CallFlags f;
   if ((st = take_flags(out->workspace, s, &f)) != EMR_OK) return st;
+  CallTables T;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
+  R.pair_info = (const uint32_t*)(T.tables + P.t_pairinfo);
+  R.src_xy = (const float*)(T.tables + P.t_srcxy);
   char* ws = (char*)out->workspace;
   emr::HiddenArgs A{};
   A.rec = R;
@@ -2090,13 +2159,13 @@ emr_status emr_express(const emr_population* pop, const emr_source* sources, int
   if ((st = check_workspace(out->workspace, out->workspace_bytes,
                             (int64_t)align256((size_t)P.n_pairs * 4))) != EMR_OK)
     return st;
-  CallTables T;
-  if ((st = call_tables(pop, P, &T)) != EMR_OK) return st;
-  R.pair_info = (const uint32_t*)(T.tables + P.t_pairinfo);
-  R.src_xy = (const float*)(T.tables + P.t_srcxy);
   const hipStream_t s = (hipStream_t)stream;
   CallFlags f;
   if ((st = take_flags(out->workspace, s, &f)) != EMR_OK) return st;
+  CallTables T;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
+  R.pair_info = (const uint32_t*)(T.tables + P.t_pairinfo);
+  R.src_xy = (const float*)(T.tables + P.t_srcxy);
   emr::ExpressArgs A{};
   A.rec = R;
   A.type_mask = (uint32_t)type_mask;
@@ -2149,15 +2218,14 @@ emr_status emr_band_values(const emr_population* pop, const emr_source* sources,
                                  G.bias_off + (uint32_t)k};
       }
     }
-  CallTables T;
-  if ((st = call_tables(pop, P, &T)) != EMR_OK) return st;
   const hipStream_t s = (hipStream_t)stream;
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
+  CallTables T;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
   if (P.n_pairs > 0) {
-    HIP_OR_FAIL(hipMemcpyAsync(workspace, bp.data(), bp.size() * sizeof(emr::BandPair),
-                               hipMemcpyHostToDevice, s));
-    HIP_OR_FAIL(hipStreamSynchronize(s));  // (bp is a host temporary)
+    if ((st = upload(workspace, bp.data(), bp.size() * sizeof(emr::BandPair), s)) != EMR_OK)
+      return st;
     emr::BandArgs A{};
     A.blob = pop->d_blob;
     A.bias = T.bias;

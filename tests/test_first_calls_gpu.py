@@ -1,0 +1,62 @@
+"""A plan's first calls: its tables and bias rows are uploaded without waiting, so calls that follow
+at once on other streams, other uses of the plan, and a population freed right after its first call
+is enqueued must all see them complete."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_27612_amd import workloads as W  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def emr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_27612_amd import emr as m
+    return m
+
+
+def bits(emr, res):
+    emr.emr_result_check(res)
+    n = int(res["pair_offset"][-1].item())
+    return (res["pair_offset"].cpu().numpy().copy(), res["parent"][:n].cpu().numpy().copy(),
+            res["w4"][:n].cpu().numpy().view(np.uint32).copy())
+
+
+# (more sources than fit one staging buffer of the uploads: 16 MB of tables)
+@pytest.mark.parametrize("genomes,n_src", [(40, 5), (150, 33), (3000, 200)])
+def test_first_calls_on_several_streams(emr, genomes, n_src):
+    flat = emr.flat_genomes(W.population(genomes, genomes, 12, 40))
+    subs = W.tabular_sources(n_src - 1)
+    depth = 3 if genomes > 1000 else 5
+    want = None
+    for _ in range(3):
+        pop = emr.emr_pack_population(flat)
+        cap = 1 << 20
+        bufs = [emr.alloc_result(pop, subs, depth, capacity=cap) for _ in range(4)]
+        streams = [torch.cuda.Stream() for _ in range(4)]
+        torch.cuda.synchronize()
+        for b, s in zip(bufs, streams):
+            emr.emr_discover(pop, subs, depth, 0.03, res=b, stream=s)
+        got = [bits(emr, b) for b in bufs]
+        want = want or got[0]
+        for g in got:
+            for x, y in zip(g, want):
+                np.testing.assert_array_equal(x, y)
+
+
+def test_population_freed_after_its_first_call(emr):
+    genomes = W.population(5, 100, 12, 40)
+    subs = W.xor_sources()
+    keep = emr.emr_pack_population(genomes)
+    want = bits(emr, emr.emr_discover(keep, subs, 6, 0.03))
+    for _ in range(5):
+        pop = emr.emr_pack_population(genomes)
+        res = emr.emr_discover(pop, subs, 6, 0.03)
+        del pop
+        for x, y in zip(bits(emr, res), want):
+            np.testing.assert_array_equal(x, y)

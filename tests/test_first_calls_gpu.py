@@ -36,7 +36,7 @@ def test_first_calls_on_several_streams(emr, genomes, n_src):
     want = None
     for _ in range(3):
         pop = emr.emr_pack_population(flat)
-        cap = 1 << 20
+        cap = 1 << 21
         bufs = [emr.alloc_result(pop, subs, depth, capacity=cap) for _ in range(4)]
         streams = [torch.cuda.Stream() for _ in range(4)]
         torch.cuda.synchronize()

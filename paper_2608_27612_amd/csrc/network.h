@@ -29,6 +29,35 @@ struct NetRankArgs {
   uint32_t n_genomes;
 };
 
+// One pair of a phase, for the edges of its connections: entry o of the raw edges is connection
+// o - delta, between raw node `node` (its source's, global; kNoNode: an internal error) and the
+// connection's grid cell in genome g.
+struct NetPair {
+  int64_t delta;
+  uint32_t g_dir;  // genome << 1 | direction (0: node -> cell, 1: cell -> node)
+  uint32_t node;
+};
+
+constexpr int kNetMaxPhases = 65;  // the substrate's and one per hidden-to-hidden iteration
+
+// Raw edges genome by genome: one workgroup turns the phases' connection counts per genome into
+// raw_edge and each phase's seg, and the hidden counts into raw_node.
+struct NetLayoutArgs {
+  const uint32_t* hidden;               // [n_genomes]
+  // phase k: its connections' offsets per pair and genome g's pairs src_offsets[g] ..
+  // src_offsets[g + 1] - 1 (NULL: g * n_sub ..)
+  const int64_t* const* conn_offset;    // [n_phases]
+  const int64_t* const* src_offsets;    // [n_phases]
+  int64_t* seg;                         // [n_phases * n_genomes] raw edge index of g's first edge
+  int64_t* raw_edge;                    // [n_genomes + 1]
+  int64_t* raw_node;                    // [n_genomes + 1]
+  int64_t n_raw, e_raw;                 // what the host expects the totals to be
+  uint32_t n_phases;
+  uint32_t n_sub;
+  uint32_t n_genomes;
+  uint32_t* err;
+};
+
 struct NetEdgeArgs {
   // one phase's expressed connections (CSR over its pairs)
   const int64_t* conn_offset;  // [n_pairs + 1]
@@ -50,33 +79,34 @@ struct NetEdgeArgs {
   const int64_t* seg;          // [n_genomes] raw edge index of genome g's first edge of this phase
   const int64_t* raw_edge;     // [n_genomes + 1]
   const int64_t* raw_node;     // [n_genomes + 1]
+  NetPair* pairs;              // [n_pairs] (k_net_pairs writes, k_net_edges reads)
   uint32_t* eu;                // [raw edges] global raw node numbers (raw_node[g] + local)
   uint32_t* ev;
   float* ew;
+  int64_t e_raw;
   uint32_t* err;
 };
 
-// Pruning. Flags per raw node (global numbering): reachable from an input (fwd), reaches an
-// output (bwd); kept edges counted into their destination's in-degree.
+// Pruning. Flags per raw node (global numbering): byte 0 reachable from an input, byte 1 reaches an
+// output.
 struct NetFlagArgs {
   const uint8_t* sub_dir;
   const int64_t* raw_node;  // [n_genomes + 1]
-  uint8_t* fwd;             // [raw nodes]
-  uint8_t* bwd;             // [raw nodes]
-  uint32_t* in_deg;         // [raw nodes] kept edges into the node
-  uint32_t* kept_nodes;     // [n_genomes] kept hidden nodes (k_net_kept)
-  uint32_t* kept_edges;     // [n_genomes] kept edges (k_net_kept)
+  uint16_t* flags;          // [raw nodes]
+  uint32_t* kept_nodes;     // [n_genomes] kept nodes, substrate nodes among them (k_net_kept)
+  int64_t* node_offset;     // [n_genomes + 1] (k_net_number)
   uint32_t n_sub;
   uint32_t n_genomes;
 };
 
+constexpr int kNetPasses = 6;  // reach passes enqueued before the host looks at them
+
 struct NetReachArgs {
   const uint32_t* eu;       // [raw edges] global raw node numbers, kNoNode: dropped
   const uint32_t* ev;
-  uint8_t* fwd;
-  uint8_t* bwd;
-  uint32_t* in_deg;         // k_net_degree only
-  uint32_t* changed;        // set to 1 by a pass that changed a flag (k_net_reach only)
+  uint16_t* flags;
+  uint32_t* changed;        // [kNetPasses] set to 1 by a pass that changed a flag
+  uint32_t pass;            // of the batch: returns at once when pass - 1 changed nothing
   int64_t edges;            // raw edges
   int64_t nodes;            // raw nodes
 };
@@ -86,51 +116,47 @@ struct NetNodeArgs {
   const uint32_t* rank;
   int64_t words;
   const int64_t* raw_node;
-  const uint8_t* fwd;
-  const uint8_t* bwd;
-  const uint32_t* in_deg;
+  const uint16_t* flags;
   const int32_t* in_slot;      // [n_sub] input number of a substrate node, or -1
   const int64_t* node_offset;  // [n_genomes + 1] kept nodes
-  const int64_t* edge_offset;  // [n_genomes + 1] kept edges
   uint32_t* gid;               // [raw nodes] kept node number (global), or kNoNode
   uint32_t* node_cell;         // [nodes] heap cell, kNoNode for substrate nodes
   int32_t* node_in;            // [nodes] input number of a substrate input node, else -1
-  int64_t* in_offset;          // [nodes + 1]
   uint32_t* err;
   uint32_t n_sub;
   uint32_t n_genomes;
 };
 
 // The kept edges grouped by destination, each group in raw order: a stable sort of the raw edges
-// by their destination's kept number (dropped edges get the key `sentinel` = nodes and sort
-// last), then a gather of the sorted edges' sources and weights.
+// by their destination's kept number (dropped edges get the key `sentinel`, above every kept
+// number, and sort last) that carries each edge's source and weight along.
 struct NetKeyArgs {
   const uint32_t* eu;
   const uint32_t* ev;
-  const uint8_t* fwd;
-  const uint8_t* bwd;
+  const float* ew;
+  const uint16_t* flags;
   const uint32_t* gid;
   uint32_t* key;            // [raw edges]
-  uint32_t* val;            // [raw edges] the raw edge index
+  uint64_t* val;            // [raw edges] source's kept number | weight bits << 32
   int64_t edges;            // raw edges
   int64_t nodes;            // raw nodes
-  uint32_t sentinel;        // kept nodes in all
+  uint32_t sentinel;        // raw nodes in all
   uint32_t* err;
 };
 
-struct NetGatherArgs {
-  const uint32_t* key;      // sorted
-  const uint32_t* val;      // sorted raw edge indices
-  const uint32_t* eu;
-  const float* ew;
-  const uint32_t* gid;
-  const int64_t* in_offset; // [nodes + 1]
-  uint32_t* in_src;         // [edges] global node number of the source
-  float* in_w;              // [edges]
-  int64_t edges;            // kept edges
+struct NetSplitArgs {
+  const uint32_t* key;        // sorted
+  const uint64_t* val;        // sorted
+  const int64_t* node_offset; // [n_genomes + 1]
+  int64_t* in_offset;         // [nodes + 1]
+  int64_t* summary;           // [2 (n_genomes + 1) + 1] for the host: node_offset, the genomes'
+                              // first kept edges, *err
+  uint32_t* in_src;           // [edges] global node number of the source
+  float* in_w;                // [edges]
   int64_t raw_edges;
   int64_t raw_nodes;
-  int64_t nodes;
+  uint32_t sentinel;
+  uint32_t n_genomes;
   uint32_t* err;
 };
 

@@ -54,6 +54,22 @@ __device__ __forceinline__ int64_t find_segment(const int64_t* off, int64_t n, i
   }
   return lo;
 }
+// The same from a segment lo with off[lo] <= i on: a gallop, then a search (i is close to lo).
+__device__ __forceinline__ int64_t find_segment_from(const int64_t* off, int64_t n, int64_t lo,
+                                                     int64_t i) {
+  int64_t step = 1, hi = lo + 1;
+  while (hi < n && off[hi] <= i) {
+    lo = hi;
+    step *= 2;
+    hi = n - lo > step ? lo + step : n;
+  }
+  while (hi - lo > 1) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    if (off[mid] <= i) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
 
 // Raw node number of heap cell `cell` in genome g (n_sub + its rank among the genome's hidden
 // cells), or kNoNode when the cell is not a hidden node.
@@ -112,63 +128,144 @@ __global__ void __launch_bounds__(kNetThreads) k_net_rank(NetRankArgs A) {
 }
 
 // ------------------------------------------------------------------------ raw edges
-// One thread per expressed connection of one phase.
-__global__ void __launch_bounds__(kNetThreads) k_net_edges(NetEdgeArgs A) {
-  for (int64_t i = grid_thread(); i < A.total; i += grid_threads()) {
-    const int64_t r = find_segment(A.conn_offset, A.n_pairs, i);
-    uint32_t g, sn, dir;
+// One workgroup: the exclusive sums of the genomes' raw nodes and edges, and each phase's segment
+// of a genome's edges. (These sums took the host a copy of every phase's offsets and a wait.)
+__global__ void __launch_bounds__(kNetThreads) k_net_layout(NetLayoutArgs A) {
+  __shared__ uint32_t part[kNetThreads / kWave];
+  __shared__ uint64_t wide[kNetThreads];
+  int64_t run_n = 0, run_e = 0;
+  for (uint32_t base = 0; base < A.n_genomes; base += kNetThreads) {
+    const uint32_t g = base + threadIdx.x;
+    int64_t edges = 0;
+    uint32_t n = 0;
+    if (g < A.n_genomes) {
+      n = A.n_sub + A.hidden[g];
+      for (uint32_t k = 0; k < A.n_phases; ++k) {
+        const int64_t* so = A.src_offsets[k];
+        const int64_t p0 = so ? so[g] : (int64_t)g * A.n_sub;
+        const int64_t p1 = so ? so[g + 1] : (int64_t)(g + 1) * A.n_sub;
+        const int64_t len = A.conn_offset[k][p1] - A.conn_offset[k][p0];
+        A.seg[(int64_t)k * A.n_genomes + g] = edges;  // (within the genome; its base added below)
+        edges += len;
+      }
+    }
+    uint32_t tn;
+    const int64_t en = block_excl_scan(n, part, &tn);
+    wide[threadIdx.x] = (uint64_t)edges;  // (a genome's edges can exceed 32 bits: a wide scan)
+    __syncthreads();
+    for (uint32_t o = 1; o < (uint32_t)kNetThreads; o <<= 1) {
+      const uint64_t y = threadIdx.x >= o ? wide[threadIdx.x - o] : 0ull;
+      __syncthreads();
+      wide[threadIdx.x] += y;
+      __syncthreads();
+    }
+    const int64_t te = (int64_t)wide[kNetThreads - 1];
+    const int64_t ee = (int64_t)wide[threadIdx.x] - edges;
+    if (g < A.n_genomes) {
+      A.raw_node[g] = run_n + en;
+      A.raw_edge[g] = run_e + ee;
+      for (uint32_t k = 0; k < A.n_phases; ++k) A.seg[(int64_t)k * A.n_genomes + g] += run_e + ee;
+    }
+    run_n += tn;
+    run_e += te;
+    __syncthreads();  // `wide` is free again
+  }
+  if (threadIdx.x == 0) {
+    A.raw_node[A.n_genomes] = run_n;
+    A.raw_edge[A.n_genomes] = run_e;
+    if (run_n != A.n_raw || run_e != A.e_raw) atomicOr(A.err, kNetErrIndex);
+  }
+}
+
+// One thread per pair of a phase: what its connections' edges have in common.
+__global__ void __launch_bounds__(kNetThreads) k_net_pairs(NetEdgeArgs A) {
+  for (int64_t r = grid_thread(); r < A.n_pairs; r += grid_threads()) {
+    uint32_t g, node, dir;
     int64_t first;
     if (A.src_offsets == nullptr) {
       g = (uint32_t)(r / A.n_sub);
-      const uint32_t j = (uint32_t)(r % A.n_sub);
-      sn = j;
-      dir = A.sub_dir[j];
+      node = (uint32_t)(r % A.n_sub);
+      dir = A.sub_dir[node];
       first = (int64_t)g * A.n_sub;
     } else {
       g = (uint32_t)find_segment(A.src_offsets, A.n_genomes, r);
       first = A.src_offsets[g];
-      sn = g < A.n_genomes ? node_of(A.known, A.rank, A.words, g, A.n_sub, A.src_cell[r]) : kNoNode;
+      node = g < A.n_genomes ? node_of(A.known, A.rank, A.words, g, A.n_sub, A.src_cell[r]) : kNoNode;
       dir = 0u;
     }
-    if (g >= A.n_genomes || sn == kNoNode) {
+    NetPair p{0, 0u, kNoNode};
+    if (g >= A.n_genomes || node == kNoNode ||
+        (int64_t)node >= A.raw_node[g + 1] - A.raw_node[g]) {
       atomicOr(A.err, kNetErrIndex);
-      continue;
-    }
-    const int64_t o = A.seg[g] + (i - A.conn_offset[first]);
-    if (o < A.raw_edge[g] || o >= A.raw_edge[g + 1]) {
-      atomicOr(A.err, kNetErrIndex);
-      continue;
-    }
-    const uint32_t cn = node_of(A.known, A.rank, A.words, g, A.n_sub, A.conn_cell[i]);
-    const int64_t nb = A.raw_node[g], n = A.raw_node[g + 1] - nb;
-    uint32_t u = dir == 0u ? sn : cn, v = dir == 0u ? cn : sn;
-    if (cn == kNoNode) {
-      u = v = kNoNode;  // the grid end is not a hidden node: dropped
-    } else if ((int64_t)u >= n || (int64_t)v >= n) {
-      atomicOr(A.err, kNetErrIndex);
-      u = v = kNoNode;
     } else {
-      u += (uint32_t)nb;  // (the host bounds the raw nodes below kNoNode)
-      v += (uint32_t)nb;
+      p.delta = A.seg[g] - A.conn_offset[first];
+      p.g_dir = g << 1 | dir;
+      p.node = node + (uint32_t)A.raw_node[g];  // (the host bounds the raw nodes below kNoNode)
     }
-    A.eu[o] = u;
-    A.ev[o] = v;
-    A.ew[o] = A.conn_w[i];
+    A.pairs[r] = p;
+  }
+}
+
+// The raw edge of connection i of pair P.
+__device__ __forceinline__ void net_edge(const NetEdgeArgs& A, const NetPair& P, int64_t i) {
+  const uint32_t g = P.g_dir >> 1;
+  const int64_t o = i + P.delta;
+  if (P.node == kNoNode || o < A.raw_edge[g] || o >= A.raw_edge[g + 1] || o >= A.e_raw) {
+    atomicOr(A.err, kNetErrIndex);
+    return;
+  }
+  const uint32_t cn = node_of(A.known, A.rank, A.words, g, A.n_sub, A.conn_cell[i]);
+  const uint32_t c = cn + (uint32_t)A.raw_node[g];
+  const bool in = (P.g_dir & 1u) != 0u;
+  uint32_t u = in ? c : P.node, v = in ? P.node : c;
+  if (cn == kNoNode) {
+    u = v = kNoNode;  // the grid end is not a hidden node: dropped
+  } else if ((int64_t)cn >= A.raw_node[g + 1] - A.raw_node[g]) {
+    atomicOr(A.err, kNetErrIndex);
+    u = v = kNoNode;
+  }
+  A.eu[o] = u;
+  A.ev[o] = v;
+  A.ew[o] = A.conn_w[i];
+}
+
+// Wave w takes the phase's connections [w kEdgeSpan, (w + 1) kEdgeSpan), 64 at a time. While they
+// belong to one pair (most do: a few heavy genomes hold most connections, hundreds per pair) the
+// pair is the wave's and only the grid end is looked up per lane; else each lane finds its pair
+// from the last one on. (A search of all pairs and genomes per connection: 455 us for 16.8M.)
+constexpr int64_t kEdgeSpan = 8 * kWave;
+__global__ void __launch_bounds__(kNetThreads) k_net_edges(NetEdgeArgs A) {
+  const uint32_t lane = threadIdx.x % kWave;
+  const int64_t wave = (int64_t)blockIdx.x * (kNetThreads / kWave) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int64_t n_waves = (int64_t)gridDim.x * (kNetThreads / kWave);
+  for (int64_t base = wave * kEdgeSpan; base < A.total; base += n_waves * kEdgeSpan) {
+    int64_t r = find_segment(A.conn_offset, A.n_pairs, base);
+    const int64_t end = base + kEdgeSpan < A.total ? base + kEdgeSpan : A.total;
+    for (int64_t b = base; b < end; b += kWave) {
+      r = find_segment_from(A.conn_offset, A.n_pairs, r, b);
+      const int64_t last = b + kWave < end ? b + kWave : end;
+      const int64_t i = b + lane;
+      if (A.conn_offset[r + 1] >= last) {
+        const NetPair P = A.pairs[r];
+        if (i < last) net_edge(A, P, i);
+      } else if (i < last) {
+        net_edge(A, A.pairs[find_segment_from(A.conn_offset, A.n_pairs, r, i)], i);
+      }
+    }
   }
 }
 
 // ------------------------------------------------------------------------ pruning
 // Flags of every raw node before the passes: substrate inputs reach themselves, substrate
-// outputs reach an output; no kept edge yet. One workgroup per genome (its nodes).
+// outputs reach an output. One workgroup per genome (its nodes).
+constexpr uint32_t kFwd = 1u, kBwd = 0x100u;  // a byte each: stored by themselves, read together
 __global__ void __launch_bounds__(kNetThreads) k_net_flags(NetFlagArgs A) {
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const int64_t nb = A.raw_node[g], n = A.raw_node[g + 1] - nb;
-    for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-      const bool sub = j < (int64_t)A.n_sub;
-      A.fwd[nb + j] = (uint8_t)(sub && A.sub_dir[j] == 0u);
-      A.bwd[nb + j] = (uint8_t)(sub && A.sub_dir[j] != 0u);
-      A.in_deg[nb + j] = 0u;
-    }
+    for (int64_t j = threadIdx.x; j < n; j += blockDim.x)
+      A.flags[nb + j] =
+          (uint16_t)(j >= (int64_t)A.n_sub ? 0u : (A.sub_dir[j] == 0u ? kFwd : kBwd));
   }
 }
 
@@ -176,76 +273,102 @@ __global__ void __launch_bounds__(kNetThreads) k_net_flags(NetFlagArgs A) {
 // forward (fwd[u] -> fwd[v]) and reachability of an output backward (bwd[v] -> bwd[u]). Flags only
 // go from 0 to 1, so a thread reading a flag another thread is setting sees either value; a pass
 // that changes nothing saw only values fixed since the launch began (every write of the previous
-// pass is visible at launch), which is the fixed point. The host repeats passes until one
-// reports no change.
-__global__ void __launch_bounds__(kNetThreads) k_net_reach(NetReachArgs A) {
+// pass is visible at launch), which is the fixed point. The host enqueues kNetPasses passes at a
+// time (a wait for each costs more than the pass) and goes on until the last one changed nothing;
+// a pass after one that changed nothing returns at once. Four edges per thread: the edges in two
+// 16-byte loads, eight flag reads in flight.
+__device__ __forceinline__ bool reach_edge(const NetReachArgs& A, uint32_t u, uint32_t v,
+                                           uint32_t fu, uint32_t fv) {
   bool ch = false;
-  for (int64_t e = grid_thread(); e < A.edges; e += grid_threads()) {
-    const uint32_t u = A.eu[e], v = A.ev[e];
-    if ((int64_t)u >= A.nodes || (int64_t)v >= A.nodes) continue;  // dropped edge
-    if (A.fwd[u] && !A.fwd[v]) {
-      A.fwd[v] = 1;
-      ch = true;
-    }
-    if (A.bwd[v] && !A.bwd[u]) {
-      A.bwd[u] = 1;
-      ch = true;
-    }
+  uint8_t* bytes = reinterpret_cast<uint8_t*>(A.flags);
+  if ((fu & kFwd) != 0u && (fv & kFwd) == 0u) {
+    bytes[2 * (int64_t)v] = 1;
+    ch = true;
   }
-  if (__ballot(ch) != 0ull && (threadIdx.x % kWave) == 0) *A.changed = 1u;
+  if ((fv & kBwd) != 0u && (fu & kBwd) == 0u) {
+    bytes[2 * (int64_t)u + 1] = 1;
+    ch = true;
+  }
+  return ch;
+}
+__global__ void __launch_bounds__(kNetThreads) k_net_reach(NetReachArgs A) {
+  if (A.pass > 0u && A.changed[A.pass - 1u] == 0u) return;
+  bool ch = false;
+  const int64_t quads = (A.edges + 3) / 4;
+  for (int64_t q = grid_thread(); q < quads; q += grid_threads()) {
+    uint32_t u[4], v[4], fu[4], fv[4];
+    if (4 * q + 4 <= A.edges) {
+      const uint4 a = reinterpret_cast<const uint4*>(A.eu)[q];
+      const uint4 b = reinterpret_cast<const uint4*>(A.ev)[q];
+      u[0] = a.x, u[1] = a.y, u[2] = a.z, u[3] = a.w;
+      v[0] = b.x, v[1] = b.y, v[2] = b.z, v[3] = b.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        u[k] = 4 * q + k < A.edges ? A.eu[4 * q + k] : kNoNode;
+        v[k] = 4 * q + k < A.edges ? A.ev[4 * q + k] : kNoNode;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool ok = (int64_t)u[k] < A.nodes && (int64_t)v[k] < A.nodes;  // else a dropped edge
+      fu[k] = ok ? A.flags[u[k]] : 0u;
+      fv[k] = ok ? A.flags[v[k]] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ch |= reach_edge(A, u[k], v[k], fu[k], fv[k]);
+  }
+  if (__ballot(ch) != 0ull && (threadIdx.x % kWave) == 0) A.changed[A.pass] = 1u;
 }
 
-// An edge u -> v is kept when an input reaches u and v reaches an output (then both ends are
-// kept nodes); each kept edge counts into its destination's in-degree.
-__global__ void __launch_bounds__(kNetThreads) k_net_degree(NetReachArgs A) {
-  for (int64_t e = grid_thread(); e < A.edges; e += grid_threads()) {
-    const uint32_t u = A.eu[e], v = A.ev[e];
-    if ((int64_t)u >= A.nodes || (int64_t)v >= A.nodes) continue;
-    if (A.fwd[u] && A.bwd[v]) atomicAdd(A.in_deg + v, 1u);
-  }
+__device__ __forceinline__ bool node_kept(uint32_t flags) {
+  return flags == (kFwd | kBwd);
 }
 
-// Per genome: kept hidden nodes (reached from an input and reaching an output) and kept edges
-// (the sum of the in-degrees). One workgroup per genome (its nodes).
+// Per genome: kept nodes (substrate nodes, and hidden ones reached from an input and reaching an
+// output). One workgroup per genome (its nodes).
 __global__ void __launch_bounds__(kNetThreads) k_net_kept(NetFlagArgs A) {
   __shared__ uint32_t part[kNetThreads / kWave];
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const int64_t nb = A.raw_node[g], n = A.raw_node[g + 1] - nb;
-    uint32_t kn = 0u, ke = 0u;
-    for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-      if (j >= (int64_t)A.n_sub && A.fwd[nb + j] && A.bwd[nb + j]) ++kn;
-      ke += A.in_deg[nb + j];
-    }
-    uint32_t tn, te;
+    uint32_t kn = 0u;
+    for (int64_t j = threadIdx.x; j < n; j += blockDim.x)
+      if (j < (int64_t)A.n_sub || node_kept(A.flags[nb + j])) ++kn;
+    uint32_t tn;
     block_excl_scan(kn, part, &tn);
-    block_excl_scan(ke, part, &te);
-    if (threadIdx.x == 0) {
-      A.kept_nodes[g] = tn;
-      A.kept_edges[g] = te;
-    }
+    if (threadIdx.x == 0) A.kept_nodes[g] = tn;
   }
 }
 
+// One workgroup: the kept nodes' exclusive sums.
+__global__ void __launch_bounds__(kNetThreads) k_net_number(NetFlagArgs A) {
+  __shared__ uint32_t part[kNetThreads / kWave];
+  int64_t run = 0;
+  for (uint32_t base = 0; base < A.n_genomes; base += kNetThreads) {
+    const uint32_t g = base + threadIdx.x;
+    uint32_t t;
+    const uint32_t e = block_excl_scan(g < A.n_genomes ? A.kept_nodes[g] : 0u, part, &t);
+    if (g < A.n_genomes) A.node_offset[g] = run + e;
+    run += t;
+  }
+  if (threadIdx.x == 0) A.node_offset[A.n_genomes] = run;
+}
+
 // ------------------------------------------------------------------------ kept nodes
-// One workgroup per genome: kept numbers in raw order, the kept nodes' first incoming edge and
-// input numbers, then the kept hidden nodes' heap cells.
+// One workgroup per genome: kept numbers in raw order and the input numbers, then the kept hidden
+// nodes' heap cells.
 __global__ void __launch_bounds__(kNetThreads) k_net_nodes(NetNodeArgs A) {
   __shared__ uint32_t part[kNetThreads / kWave];
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const int64_t nb = A.raw_node[g], n = A.raw_node[g + 1] - nb;
     const int64_t NB = A.node_offset[g], NE = A.node_offset[g + 1];
-    const int64_t EB = A.edge_offset[g];
-    uint32_t run_id = 0u, run_deg = 0u;
+    uint32_t run_id = 0u;
     for (int64_t base = 0; base < n; base += kNetThreads) {
       const int64_t j = base + threadIdx.x;
-      uint32_t keep = 0u, deg = 0u;
-      if (j < n) {
-        keep = (j < (int64_t)A.n_sub || (A.fwd[nb + j] && A.bwd[nb + j])) ? 1u : 0u;
-        deg = keep ? A.in_deg[nb + j] : 0u;
-      }
-      uint32_t tk, td;
+      const uint32_t keep =
+          j < n && (j < (int64_t)A.n_sub || node_kept(A.flags[nb + j])) ? 1u : 0u;
+      uint32_t tk;
       const uint32_t ek = block_excl_scan(keep, part, &tk);
-      const uint32_t ed = block_excl_scan(deg, part, &td);
       if (j < n) {
         const uint32_t id = run_id + ek;
         uint32_t gl = kNoNode;
@@ -253,8 +376,7 @@ __global__ void __launch_bounds__(kNetThreads) k_net_nodes(NetNodeArgs A) {
           if (NB + id >= NE) {
             atomicOr(A.err, kNetErrIndex);
           } else {
-            gl = (uint32_t)(NB + id);  // (the host bounds the kept nodes below kNoNode)
-            A.in_offset[NB + id] = EB + run_deg + ed;
+            gl = (uint32_t)(NB + id);  // (at most the raw nodes, which stay below kNoNode)
             const bool sub = j < (int64_t)A.n_sub;
             A.node_in[NB + id] = sub ? A.in_slot[j] : -1;
             if (sub) A.node_cell[NB + id] = kNoNode;
@@ -263,12 +385,8 @@ __global__ void __launch_bounds__(kNetThreads) k_net_nodes(NetNodeArgs A) {
         A.gid[nb + j] = gl;
       }
       run_id += tk;
-      run_deg += td;
     }
-    if (threadIdx.x == 0) {
-      if (NB + run_id != NE || EB + run_deg != A.edge_offset[g + 1]) atomicOr(A.err, kNetErrIndex);
-      if (g == A.n_genomes - 1) A.in_offset[NE] = A.edge_offset[g + 1];
-    }
+    if (threadIdx.x == 0 && NB + run_id != NE) atomicOr(A.err, kNetErrIndex);
     __syncthreads();  // gid of the whole genome before the cell pass
     const uint32_t* kw = A.known + (int64_t)g * A.words;
     const uint32_t* rk = A.rank + (int64_t)g * A.words;
@@ -293,39 +411,70 @@ __global__ void __launch_bounds__(kNetThreads) k_net_nodes(NetNodeArgs A) {
 }
 
 // ------------------------------------------------------------------------ incoming edges
-// Sort keys of the raw edges: a kept edge's destination's kept number (sentinel: dropped).
+// An edge u -> v is kept when an input reaches u and v reaches an output (then both ends are kept
+// nodes). Sort keys of the raw edges: a kept edge's destination's kept number (sentinel: dropped);
+// the values carry its source and weight, so that nothing is gathered after the sort (a gather of
+// 15M edges by their raw index took 250 us).
 __global__ void __launch_bounds__(kNetThreads) k_net_keys(NetKeyArgs A) {
   for (int64_t e = grid_thread(); e < A.edges; e += grid_threads()) {
     const uint32_t u = A.eu[e], v = A.ev[e];
-    uint32_t key = A.sentinel;
-    if ((int64_t)u < A.nodes && (int64_t)v < A.nodes && A.fwd[u] && A.bwd[v]) {
-      const uint32_t gu = A.gid[u], gv = A.gid[v];
+    const uint32_t w = __float_as_uint(A.ew[e]);
+    uint32_t key = A.sentinel, gu = 0u;
+    if ((int64_t)u < A.nodes && (int64_t)v < A.nodes && (A.flags[u] & kFwd) != 0u &&
+        (A.flags[v] & kBwd) != 0u) {
+      gu = A.gid[u];
+      const uint32_t gv = A.gid[v];
       if (gu >= A.sentinel || gv >= A.sentinel) atomicOr(A.err, kNetErrIndex);
       else key = gv;
     }
     A.key[e] = key;
-    A.val[e] = (uint32_t)e;  // (the host bounds the raw edges below 2^32)
+    A.val[e] = (uint64_t)w << 32 | gu;
   }
 }
 
-// The sorted kept edges (the first `edges` entries) to their CSR slots: entry i holds the edge
-// at slot i, whose destination's range must contain i.
-__global__ void __launch_bounds__(kNetThreads) k_net_gather(NetGatherArgs A) {
-  for (int64_t i = grid_thread(); i < A.edges; i += grid_threads()) {
-    const uint32_t k = A.key[i], e = A.val[i];
-    if ((int64_t)k >= A.nodes || (int64_t)e >= A.raw_edges || i < A.in_offset[k] ||
-        i >= A.in_offset[k + 1]) {
+// The first i with key[i] >= k (n: none).
+__device__ __forceinline__ int64_t first_key(const uint32_t* key, int64_t n, uint32_t k) {
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    if (key[mid] < k) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// in_offset of every kept node (and one past the last), and the genomes' first edges, by searches of
+// the sorted keys. (Counting the in-degrees instead took an atomic per edge: 190 us for 15M.)
+__global__ void __launch_bounds__(kNetThreads) k_net_offsets(NetSplitArgs A) {
+  const int64_t nodes = A.node_offset[A.n_genomes], G1 = (int64_t)A.n_genomes + 1;
+  if (nodes > A.raw_nodes) {  // (never: k_net_number sums k_net_kept's counts)
+    if (grid_thread() == 0) atomicOr(A.err, kNetErrIndex);
+    return;
+  }
+  for (int64_t t = grid_thread(); t <= nodes + G1; t += grid_threads()) {
+    const int64_t k = t <= nodes ? t : A.node_offset[t - nodes - 1];
+    const int64_t e = first_key(A.key, A.raw_edges, k < nodes ? (uint32_t)k : A.sentinel);
+    if (t <= nodes) {
+      A.in_offset[t] = e;
+    } else {
+      A.summary[t - nodes - 1] = k;
+      A.summary[G1 + t - nodes - 1] = e;
+    }
+  }
+}
+
+// The sorted kept edges' sources and weights.
+__global__ void __launch_bounds__(kNetThreads) k_net_split(NetSplitArgs A) {
+  const int64_t nodes = A.node_offset[A.n_genomes];
+  for (int64_t i = grid_thread(); i < A.raw_edges; i += grid_threads()) {
+    if (A.key[i] >= A.sentinel) return;  // (the dropped edges are the last)
+    const uint64_t v = A.val[i];
+    if ((int64_t)(uint32_t)v >= nodes) {
       atomicOr(A.err, kNetErrIndex);
       continue;
     }
-    const uint32_t u = A.eu[e];
-    const uint32_t gu = (int64_t)u < A.raw_nodes ? A.gid[u] : kNoNode;
-    if ((int64_t)gu >= A.nodes) {
-      atomicOr(A.err, kNetErrIndex);
-      continue;
-    }
-    A.in_src[i] = gu;
-    A.in_w[i] = A.ew[e];
+    A.in_src[i] = (uint32_t)v;
+    A.in_w[i] = __uint_as_float((uint32_t)(v >> 32));
   }
 }
 
@@ -608,6 +757,9 @@ __global__ void __launch_bounds__(kNetThreads) k_net_out(NetOutArgs A) {
   }
 }
 
+// After every other kernel of the build: the error word to the host's summary.
+__global__ void k_net_end(NetSplitArgs A) { A.summary[2 * ((int64_t)A.n_genomes + 1)] = *A.err; }
+
 }  // namespace emr
 
 namespace {
@@ -623,9 +775,9 @@ dim3 list_grid(const emr::NetList& L, uint32_t x, uint32_t pblocks) {
 }
 }  // namespace
 
-// Steps: 0 rank, 1 edges, 2 flags, 3 reach pass, 4 degrees, 5 kept counts, 6 nodes, 7 keys,
-// 8 gather; activation: 9 initial state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns
-// by value, 13 all steps in LDS.
+// Steps: 0 rank, 1 layout, 2 pairs of a phase, 3 its edges, 4 flags, 5 reach pass, 6 kept counts
+// and their sums, 7 nodes, 8 keys; after the sort, 14 offsets and edges. Activation: 9 initial
+// state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns by value, 13 all steps in LDS.
 extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, hipStream_t s) {
   using namespace emr;
   (void)work;
@@ -637,45 +789,60 @@ extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, h
       break;
     }
     case 1: {
-      const auto& A = *static_cast<const NetEdgeArgs*>(args);
-      if (A.total <= 0) return hipSuccess;
-      hipLaunchKernelGGL(k_net_edges, dim3(stride_blocks(A.total)), blk, 0, s, A);
+      const auto& A = *static_cast<const NetLayoutArgs*>(args);
+      hipLaunchKernelGGL(k_net_layout, dim3(1), blk, 0, s, A);
       break;
     }
     case 2: {
+      const auto& A = *static_cast<const NetEdgeArgs*>(args);
+      if (A.n_pairs <= 0) return hipSuccess;
+      hipLaunchKernelGGL(k_net_pairs, dim3(stride_blocks(A.n_pairs)), blk, 0, s, A);
+      break;
+    }
+    case 3: {
+      const auto& A = *static_cast<const NetEdgeArgs*>(args);
+      if (A.total <= 0) return hipSuccess;
+      hipLaunchKernelGGL(k_net_edges, dim3(stride_blocks((A.total + kEdgeSpan - 1) / kEdgeSpan *
+                                                         kWave)),
+                         blk, 0, s, A);
+      break;
+    }
+    case 4: {
       const auto& A = *static_cast<const NetFlagArgs*>(args);
       hipLaunchKernelGGL(k_net_flags, dim3(genome_blocks(A.n_genomes)), blk, 0, s, A);
       break;
     }
-    case 3: {
-      const auto& A = *static_cast<const NetReachArgs*>(args);
-      hipLaunchKernelGGL(k_net_reach, dim3(stride_blocks(A.edges)), blk, 0, s, A);
-      break;
-    }
-    case 4: {
-      const auto& A = *static_cast<const NetReachArgs*>(args);
-      hipLaunchKernelGGL(k_net_degree, dim3(stride_blocks(A.edges)), blk, 0, s, A);
-      break;
-    }
     case 5: {
-      const auto& A = *static_cast<const NetFlagArgs*>(args);
-      hipLaunchKernelGGL(k_net_kept, dim3(genome_blocks(A.n_genomes)), blk, 0, s, A);
+      const auto& A = *static_cast<const NetReachArgs*>(args);
+      if (A.pass >= (uint32_t)kNetPasses || ((uintptr_t)A.eu & 15) != 0 || ((uintptr_t)A.ev & 15) != 0)
+        return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k_net_reach, dim3(stride_blocks((A.edges + 3) / 4)), blk, 0, s, A);
       break;
     }
     case 6: {
+      const auto& A = *static_cast<const NetFlagArgs*>(args);
+      hipLaunchKernelGGL(k_net_kept, dim3(genome_blocks(A.n_genomes)), blk, 0, s, A);
+      hipLaunchKernelGGL(k_net_number, dim3(1), blk, 0, s, A);
+      break;
+    }
+    case 7: {
       const auto& A = *static_cast<const NetNodeArgs*>(args);
       hipLaunchKernelGGL(k_net_nodes, dim3(genome_blocks(A.n_genomes)), blk, 0, s, A);
       break;
     }
-    case 7: {
+    case 8: {
       const auto& A = *static_cast<const NetKeyArgs*>(args);
+      if (A.edges <= 0) return hipSuccess;
       hipLaunchKernelGGL(k_net_keys, dim3(stride_blocks(A.edges)), blk, 0, s, A);
       break;
     }
-    case 8: {
-      const auto& A = *static_cast<const NetGatherArgs*>(args);
-      if (A.edges <= 0) return hipSuccess;
-      hipLaunchKernelGGL(k_net_gather, dim3(stride_blocks(A.edges)), blk, 0, s, A);
+    case 14: {
+      const auto& A = *static_cast<const NetSplitArgs*>(args);
+      hipLaunchKernelGGL(k_net_offsets, dim3(stride_blocks(A.raw_nodes + A.n_genomes + 2)), blk, 0,
+                         s, A);
+      if (A.raw_edges > 0)
+        hipLaunchKernelGGL(k_net_split, dim3(stride_blocks(A.raw_edges)), blk, 0, s, A);
+      hipLaunchKernelGGL(k_net_end, dim3(1), dim3(1), 0, s, A);
       break;
     }
     case 9: {

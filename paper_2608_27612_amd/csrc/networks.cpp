@@ -9,8 +9,8 @@
 // until no genome finds a new one. The network kernels (network.hip) then number the nodes, map
 // every expressed connection to an edge, prune to the input-to-output paths (passes over every
 // edge of the population until one changes nothing) and group each kept node's incoming edges (a
-// stable sort of the edges by destination). Every step synchronizes with the host where it needs
-// a count.
+// stable sort of the edges by destination). The host waits where it needs a count: a phase's
+// records, its new nodes and connections, the pruning's end, and the networks' offsets.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,7 +32,7 @@ emr_status set_error(emr_status st, const std::string& msg);
 }
 extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, hipStream_t s);
 extern "C" hipError_t emr_net_sort(void* tmp, size_t* bytes, const uint32_t* kin, uint32_t* kout,
-                                   const uint32_t* vin, uint32_t* vout, uint32_t n, int bits,
+                                   const uint64_t* vin, uint64_t* vout, uint32_t n, int bits,
                                    hipStream_t s);
 
 namespace {
@@ -233,6 +233,11 @@ emr_status to_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
   return EMR_OK;
 }
 
+constexpr int32_t kMaxSubstrate = 1024;
+constexpr int32_t kMaxIterations = 64;
+constexpr int32_t kMaxSteps = 1 << 20;
+constexpr int32_t kMaxPatterns = 1 << 16;
+
 // One phase: its sources, discovery, and expressed connections.
 struct Phase {
   std::vector<emr_source> sources;
@@ -242,13 +247,16 @@ struct Phase {
   int64_t rcap = 0, rtotal = 0;
   Dev cell, w, ccount, coffset;
   int64_t ccap = 0, ctotal = 0;
+  // the hidden-node call (until it is checked) and the new nodes it found
+  Dev hws, hsrc, hcell, hoff, cws;
+  int64_t hcap = 0, n_new = 0;
   Dev src_cell;   // [sources] heap cells of the queried hidden nodes
   Dev src_offs;   // [n_genomes + 1] int64 copy of offs
   Dev ws;         // the discovery's workspace, released after the phase
 
   void release_idle() {
     for (Dev* d : {&parent, &w4, &rcount, &roffset, &cell, &w, &ccount, &coffset, &src_cell,
-                   &src_offs, &ws})
+                   &src_offs, &ws, &hws, &hsrc, &hcell, &hoff, &cws})
       d->reset_idle();
   }
 
@@ -360,53 +368,36 @@ emr_status discover_phase(Build& B, Phase& P) {
   }
 }
 
-// The phase's new hidden nodes (or-ed into the bitmap); on return *out holds them for the next
-// phase: host sources and offsets, device cells and offsets.
-emr_status hidden_phase(Build& B, Phase& P, Phase* next, int64_t* n_new) {
+// Enqueues the phase's new hidden nodes (or-ed into the bitmap).
+emr_status hidden_phase(Build& B, Phase& P) {
   emr_networks& N = *B.net;
-  const int64_t cap = P.rtotal * 4 > 0 ? P.rtotal * 4 : 1;  // every record adds 4 cells at most
+  P.hcap = P.rtotal * 4 > 0 ? P.rtotal * 4 : 1;  // every record adds 4 cells at most
   int64_t hb = 0;
   NET_TRY(emr_hidden_workspace_bytes(N.n_genomes, N.depth, &hb));
-  Dev hws, hsrc, hcell, hoff;
-  NET_TRY(alloc(hws, (size_t)hb, "hidden-node workspace", B.s));
-  NET_TRY(alloc(hsrc, (size_t)cap * sizeof(emr_source), "hidden sources", B.s));
-  NET_TRY(alloc(hcell, (size_t)cap * 4, "hidden cells", B.s));
-  NET_TRY(alloc(hoff, (size_t)(N.n_genomes + 1) * 8, "hidden offsets", B.s));
+  NET_TRY(alloc(P.hws, (size_t)hb, "hidden-node workspace", B.s));
+  NET_TRY(alloc(P.hsrc, (size_t)P.hcap * sizeof(emr_source), "hidden sources", B.s));
+  NET_TRY(alloc(P.hcell, (size_t)P.hcap * 4, "hidden cells", B.s));
+  NET_TRY(alloc(P.hoff, (size_t)(N.n_genomes + 1) * 8, "hidden offsets", B.s));
   emr_hidden h;
-  h.sources = hsrc.as<emr_source>();
-  h.cell = hcell.as<uint32_t>();
-  h.capacity = cap;
-  h.offsets = hoff.as<int64_t>();
+  h.sources = P.hsrc.as<emr_source>();
+  h.cell = P.hcell.as<uint32_t>();
+  h.capacity = P.hcap;
+  h.offsets = P.hoff.as<int64_t>();
   h.known = N.known.as<uint32_t>();
-  h.workspace = hws.p;
+  h.workspace = P.hws.p;
   h.workspace_bytes = hb;
   const emr_result r = P.result();
-  NET_TRY(emr_hidden_sources(B.pop, P.sources.data(), (int32_t)P.sources.size(), P.offs_ptr(),
-                             P.n_shared(), N.depth, &r, &h, B.s));
-  int64_t total = 0;
-  NET_TRY(emr_call_check(hws.p, cap, &total, nullptr, B.s));
-  *n_new = total;
-  if (!next || total == 0) return EMR_OK;
-  if (total > INT32_MAX) return failf(EMR_E_LIMIT, "networks: %lld hidden sources in one phase",
-                                      (long long)total);
-  next->sources.resize((size_t)total);
-  std::vector<int64_t> off((size_t)N.n_genomes + 1);
-  NET_TRY(to_host(next->sources.data(), hsrc.p, (size_t)total * sizeof(emr_source), B.s));
-  NET_TRY(to_host(off.data(), hoff.p, off.size() * 8, B.s));
-  next->offs.resize(off.size());
-  for (size_t g = 0; g < off.size(); ++g) next->offs[g] = (int32_t)off[g];
-  next->src_cell.take(hcell);
-  next->src_offs.take(hoff);
-  return EMR_OK;
+  return emr_hidden_sources(B.pop, P.sources.data(), (int32_t)P.sources.size(), P.offs_ptr(),
+                            P.n_shared(), N.depth, &r, &h, B.s);
 }
 
+// Enqueues the phase's connections.
 emr_status express_phase(Build& B, Phase& P) {
   emr_networks& N = *B.net;
   P.ccap = P.rtotal * 4 > 0 ? P.rtotal * 4 : 1;  // four children per record at most
   int64_t eb = 0;
   NET_TRY(emr_express_workspace_bytes(P.n_pairs, &eb));
-  Dev cws;
-  NET_TRY(alloc(cws, (size_t)eb, "connection workspace", B.s));
+  NET_TRY(alloc(P.cws, (size_t)eb, "connection workspace", B.s));
   NET_TRY(alloc(P.cell, (size_t)P.ccap * 4, "connections", B.s));
   NET_TRY(alloc(P.w, (size_t)P.ccap * 4, "connections", B.s));
   NET_TRY(alloc(P.ccount, (size_t)P.n_pairs * 8, "connection counts", B.s));
@@ -417,87 +408,113 @@ emr_status express_phase(Build& B, Phase& P) {
   c.capacity = P.ccap;
   c.pair_count = P.ccount.as<int64_t>();
   c.pair_offset = P.coffset.as<int64_t>();
-  c.workspace = cws.p;
+  c.workspace = P.cws.p;
   c.workspace_bytes = eb;
   const emr_result r = P.result();
-  NET_TRY(emr_express(B.pop, P.sources.data(), (int32_t)P.sources.size(), P.offs_ptr(),
-                      P.n_shared(), N.depth, &r, B.type_mask, B.w_min, &c, B.s));
-  NET_TRY(emr_call_check(cws.p, P.ccap, &P.ctotal, nullptr, B.s));
+  return emr_express(B.pop, P.sources.data(), (int32_t)P.sources.size(), P.offs_ptr(),
+                     P.n_shared(), N.depth, &r, B.type_mask, B.w_min, &c, B.s);
+}
+
+// Checks both calls; `next`, when given, receives the new hidden nodes to query: host sources and
+// offsets, device cells and offsets.
+emr_status finish_phase(Build& B, Phase& P, Phase* next) {
+  emr_networks& N = *B.net;
+  NET_TRY(emr_call_check(P.hws.p, P.hcap, &P.n_new, nullptr, B.s));
+  if (next && P.n_new > 0) {
+    if (P.n_new > INT32_MAX)
+      return failf(EMR_E_LIMIT, "networks: %lld hidden sources in one phase", (long long)P.n_new);
+    next->sources.resize((size_t)P.n_new);
+    std::vector<int64_t> off((size_t)N.n_genomes + 1);
+    NET_HIP(hipMemcpyAsync(next->sources.data(), P.hsrc.p, (size_t)P.n_new * sizeof(emr_source),
+                           hipMemcpyDeviceToHost, B.s));
+    NET_TRY(to_host(off.data(), P.hoff.p, off.size() * 8, B.s));
+    next->offs.resize(off.size());
+    for (size_t g = 0; g < off.size(); ++g) next->offs[g] = (int32_t)off[g];
+    next->src_cell.take(P.hcell);
+    next->src_offs.take(P.hoff);
+  }
+  NET_TRY(emr_call_check(P.cws.p, P.ccap, &P.ctotal, nullptr, B.s));
+  for (Dev* d : {&P.hws, &P.hsrc, &P.hcell, &P.hoff, &P.cws}) d->reset();
   return EMR_OK;
 }
 
-emr_status order_genomes(emr_networks& N, const std::vector<int64_t>& node_off,
-                         const std::vector<int64_t>& edge_off, hipStream_t s);
+emr_status order_genomes(emr_networks& N, const int64_t* node_off, const int64_t* edge_off,
+                         hipStream_t s);
 
+// Numbers the nodes, maps the connections to edges, prunes, and groups the kept edges by
+// destination. The sizes that the host needs are known or bounded beforehand (the phases' hidden
+// nodes and connections), so it waits only for the reach passes and once at the end.
 emr_status assemble(Build& B) {
   emr_networks& N = *B.net;
   const uint32_t G = (uint32_t)N.n_genomes;
   const hipStream_t s = B.s;
-  Dev rank, hidden, err;
-  NET_TRY(alloc(rank, (size_t)G * (size_t)N.words * 4, "bitmap ranks", s));
-  NET_TRY(alloc(hidden, (size_t)G * 4, "hidden counts", s));
-  NET_TRY(alloc(err, 8, "error and pass words", s));
-  NET_HIP(hipMemsetAsync(err.p, 0, 8, s));
-  uint32_t* d_err = err.as<uint32_t>();
-  uint32_t* d_changed = d_err + 1;
-  emr::NetRankArgs ra{N.known.as<uint32_t>(), rank.as<uint32_t>(), hidden.as<uint32_t>(), N.words,
-                      G};
-  NET_HIP(emr_launch_net(0, &ra, 0, s));
-  std::vector<uint32_t> hid(G);
-  NET_TRY(to_host(hid.data(), hidden.p, (size_t)G * 4, s));
-  std::vector<int64_t> raw_node(G + 1, 0);
-  for (uint32_t g = 0; g < G; ++g) raw_node[g + 1] = raw_node[g] + N.n_sub + hid[g];
-  // raw edges: genome by genome, each genome's phases in order
   const size_t K = N.phases.size();
-  std::vector<std::vector<int64_t>> len(K, std::vector<int64_t>(G));
-  for (size_t k = 0; k < K; ++k) {
-    Phase& P = *N.phases[k];
-    std::vector<int64_t> off((size_t)P.n_pairs + 1);
-    NET_TRY(to_host(off.data(), P.coffset.p, off.size() * 8, s));
-    for (uint32_t g = 0; g < G; ++g) {
-      const int64_t p0 = P.shared() ? (int64_t)g * N.n_sub : P.offs[g];
-      const int64_t p1 = P.shared() ? (int64_t)(g + 1) * N.n_sub : P.offs[g + 1];
-      len[k][g] = off[p1] - off[p0];
-    }
+  static_assert(kMaxIterations + 1 <= emr::kNetMaxPhases, "phases of a build");
+  int64_t n_raw = (int64_t)G * N.n_sub, e_raw = 0;
+  for (const auto& p : N.phases) {
+    n_raw += p->n_new;
+    e_raw += p->ctotal;
   }
-  std::vector<int64_t> raw_edge(G + 1, 0);
-  std::vector<std::vector<int64_t>> seg(K, std::vector<int64_t>(G));
-  for (uint32_t g = 0; g < G; ++g) {
-    int64_t e = raw_edge[g];
-    for (size_t k = 0; k < K; ++k) {
-      seg[k][g] = e;
-      e += len[k][g];
-    }
-    raw_edge[g + 1] = e;
-  }
-  const int64_t n_raw = raw_node[G], e_raw = raw_edge[G];
   // raw node and edge numbers are u32 (kNoNode, the largest, marks a dropped edge)
   if (n_raw >= (int64_t)emr::kNoNode)
     return failf(EMR_E_LIMIT, "networks: %lld raw nodes (at most 2^32 - 2)", (long long)n_raw);
   if (e_raw >= (int64_t)emr::kNoNode)
     return failf(EMR_E_LIMIT, "networks: %lld raw edges (at most 2^32 - 2)", (long long)e_raw);
-  Dev d_raw_node, d_raw_edge, d_dir, eu, ev, ew, fwd, bwd, in_deg, kept_n, kept_e;
-  std::vector<Dev> d_seg(K);
-  NET_TRY(alloc(d_raw_node, (size_t)(G + 1) * 8, "node offsets", s));
-  NET_TRY(alloc(d_raw_edge, (size_t)(G + 1) * 8, "edge offsets", s));
-  NET_TRY(alloc(d_dir, (size_t)N.n_sub, "substrate directions", s));
+  // the host's small tables in one upload: the phases' offset tables, then the substrate directions
+  std::vector<uint64_t> tab(2 * K + ((size_t)N.n_sub + 7) / 8);
+  for (size_t k = 0; k < K; ++k) {
+    Phase& P = *N.phases[k];
+    tab[k] = (uint64_t)(uintptr_t)P.coffset.p;
+    tab[K + k] = P.shared() ? 0 : (uint64_t)(uintptr_t)P.src_offs.p;
+  }
+  uint8_t* dir = reinterpret_cast<uint8_t*>(tab.data() + 2 * K);
+  for (int32_t j = 0; j < N.n_sub; ++j) dir[j] = N.substrate[j].dir == EMR_DIR_OUT ? 0 : 1;
+  Dev rank, hidden, err, d_tab, raw_node, raw_edge, seg, eu, ev, ew, flags, kept_n, gid, sum;
+  NET_TRY(alloc(rank, (size_t)G * (size_t)N.words * 4, "bitmap ranks", s));
+  NET_TRY(alloc(hidden, (size_t)G * 4, "hidden counts", s));
+  NET_TRY(alloc(err, 4 * (1 + emr::kNetPasses), "error and pass words", s));
+  NET_TRY(alloc(d_tab, tab.size() * 8, "phase tables", s));
+  NET_TRY(alloc(raw_node, (size_t)(G + 1) * 8, "node offsets", s));
+  NET_TRY(alloc(raw_edge, (size_t)(G + 1) * 8, "edge offsets", s));
+  NET_TRY(alloc(seg, K * (size_t)G * 8, "phase segments", s));
   NET_TRY(alloc(eu, (size_t)e_raw * 4, "edges", s));
   NET_TRY(alloc(ev, (size_t)e_raw * 4, "edges", s));
   NET_TRY(alloc(ew, (size_t)e_raw * 4, "edges", s));
-  NET_TRY(alloc(fwd, (size_t)n_raw, "node flags", s));
-  NET_TRY(alloc(bwd, (size_t)n_raw, "node flags", s));
-  NET_TRY(alloc(in_deg, (size_t)n_raw * 4, "in-degrees", s));
+  NET_TRY(alloc(flags, (size_t)n_raw * 2, "node flags", s));
   NET_TRY(alloc(kept_n, (size_t)G * 4, "kept counts", s));
-  NET_TRY(alloc(kept_e, (size_t)G * 4, "kept counts", s));
-  std::vector<uint8_t> dir(N.n_sub);
-  for (int32_t j = 0; j < N.n_sub; ++j) dir[j] = N.substrate[j].dir == EMR_DIR_OUT ? 0 : 1;
-  NET_TRY(to_device(d_raw_node.p, raw_node.data(), raw_node.size() * 8, s));
-  NET_TRY(to_device(d_raw_edge.p, raw_edge.data(), raw_edge.size() * 8, s));
-  NET_TRY(to_device(d_dir.p, dir.data(), dir.size(), s));
+  NET_TRY(alloc(gid, (size_t)n_raw * 4, "node numbers", s));
+  NET_TRY(alloc(sum, (size_t)(2 * (G + 1) + 1) * 8, "network offsets", s));
+  NET_TRY(alloc(N.node_offset, (size_t)(G + 1) * 8, "network node offsets", s));
+  NET_TRY(alloc(N.node_cell, (size_t)n_raw * 4, "network nodes", s));
+  NET_TRY(alloc(N.node_in, (size_t)n_raw * 4, "network input numbers", s));
+  NET_TRY(alloc(N.in_offset, (size_t)(n_raw + 1) * 8, "network edge offsets", s));
+  NET_TRY(alloc(N.in_src, (size_t)e_raw * 4, "network edges", s));
+  NET_TRY(alloc(N.in_w, (size_t)e_raw * 4, "network edges", s));
+  NET_HIP(hipMemsetAsync(err.p, 0, 4 * (1 + emr::kNetPasses), s));
+  NET_TRY(to_device(d_tab.p, tab.data(), tab.size() * 8, s));
+  uint32_t* d_err = err.as<uint32_t>();
+  const uint8_t* d_dir = reinterpret_cast<const uint8_t*>(d_tab.as<uint64_t>() + 2 * K);
+  emr::NetRankArgs ra{N.known.as<uint32_t>(), rank.as<uint32_t>(), hidden.as<uint32_t>(), N.words,
+                      G};
+  NET_HIP(emr_launch_net(0, &ra, 0, s));
+  emr::NetLayoutArgs la{};
+  la.hidden = hidden.as<uint32_t>();
+  la.conn_offset = d_tab.as<const int64_t*>();
+  la.src_offsets = d_tab.as<const int64_t*>() + K;
+  la.seg = seg.as<int64_t>();
+  la.raw_edge = raw_edge.as<int64_t>();
+  la.raw_node = raw_node.as<int64_t>();
+  la.n_raw = n_raw;
+  la.e_raw = e_raw;
+  la.n_phases = (uint32_t)K;
+  la.n_sub = (uint32_t)N.n_sub;
+  la.n_genomes = G;
+  la.err = d_err;
+  NET_HIP(emr_launch_net(1, &la, 0, s));
   for (size_t k = 0; k < K; ++k) {
     Phase& P = *N.phases[k];
-    NET_TRY(alloc(d_seg[k], (size_t)G * 8, "phase segments", s));
-    NET_TRY(to_device(d_seg[k].p, seg[k].data(), (size_t)G * 8, s));
+    Dev pairs;
+    NET_TRY(alloc(pairs, (size_t)P.n_pairs * sizeof(emr::NetPair), "pair table", s));
     emr::NetEdgeArgs ea{};
     ea.conn_offset = P.coffset.as<int64_t>();
     ea.conn_cell = P.cell.as<uint32_t>();
@@ -506,111 +523,85 @@ emr_status assemble(Build& B) {
     ea.total = P.ctotal;
     ea.src_offsets = P.shared() ? nullptr : P.src_offs.as<int64_t>();
     ea.src_cell = P.shared() ? nullptr : P.src_cell.as<uint32_t>();
-    ea.sub_dir = d_dir.as<uint8_t>();
+    ea.sub_dir = d_dir;
     ea.n_sub = (uint32_t)N.n_sub;
     ea.n_genomes = G;
     ea.known = N.known.as<uint32_t>();
     ea.rank = rank.as<uint32_t>();
     ea.words = N.words;
-    ea.seg = d_seg[k].as<int64_t>();
-    ea.raw_edge = d_raw_edge.as<int64_t>();
-    ea.raw_node = d_raw_node.as<int64_t>();
+    ea.seg = seg.as<int64_t>() + k * G;
+    ea.raw_edge = raw_edge.as<int64_t>();
+    ea.raw_node = raw_node.as<int64_t>();
+    ea.pairs = pairs.as<emr::NetPair>();
     ea.eu = eu.as<uint32_t>();
     ea.ev = ev.as<uint32_t>();
     ea.ew = ew.as<float>();
+    ea.e_raw = e_raw;
     ea.err = d_err;
-    NET_HIP(emr_launch_net(1, &ea, 0, s));
+    NET_HIP(emr_launch_net(2, &ea, 0, s));
+    NET_HIP(emr_launch_net(3, &ea, 0, s));
   }
   // pruning: flags, then passes over every edge until one changes nothing
-  emr::NetFlagArgs fa{d_dir.as<uint8_t>(), d_raw_node.as<int64_t>(), fwd.as<uint8_t>(),
-                      bwd.as<uint8_t>(), in_deg.as<uint32_t>(), kept_n.as<uint32_t>(),
-                      kept_e.as<uint32_t>(), (uint32_t)N.n_sub, G};
-  NET_HIP(emr_launch_net(2, &fa, 0, s));
-  emr::NetReachArgs rr{eu.as<uint32_t>(), ev.as<uint32_t>(), fwd.as<uint8_t>(), bwd.as<uint8_t>(),
-                       in_deg.as<uint32_t>(), d_changed, e_raw, n_raw};
+  emr::NetFlagArgs fa{d_dir, raw_node.as<int64_t>(), flags.as<uint16_t>(), kept_n.as<uint32_t>(),
+                      N.node_offset.as<int64_t>(), (uint32_t)N.n_sub, G};
+  NET_HIP(emr_launch_net(4, &fa, 0, s));
+  emr::NetReachArgs rr{eu.as<uint32_t>(), ev.as<uint32_t>(), flags.as<uint16_t>(), d_err + 1, 0u,
+                       e_raw, n_raw};
   // a pass that changes something sets at least one more flag: 2 n_raw passes bound the loop
   const int64_t max_pass = 2 * n_raw + 2;
-  for (int64_t pass = 0;; ++pass) {
+  for (int64_t pass = 0; e_raw > 0; pass += emr::kNetPasses) {
     if (pass > max_pass)
       return failf(EMR_E_DEVICE, "networks: pruning did not settle in %lld passes",
                    (long long)max_pass);
-    NET_HIP(hipMemsetAsync(d_changed, 0, 4, s));
-    NET_HIP(emr_launch_net(3, &rr, 0, s));
+    if (pass > 0) NET_HIP(hipMemsetAsync(d_err + 1, 0, 4 * emr::kNetPasses, s));
+    for (rr.pass = 0; rr.pass < (uint32_t)emr::kNetPasses; ++rr.pass)
+      NET_HIP(emr_launch_net(5, &rr, 0, s));
     uint32_t ch = 0;
-    NET_TRY(to_host(&ch, d_changed, 4, s));
+    NET_TRY(to_host(&ch, d_err + emr::kNetPasses, 4, s));
     if (ch == 0) break;
   }
-  NET_HIP(emr_launch_net(4, &rr, 0, s));
-  NET_HIP(emr_launch_net(5, &fa, 0, s));
-  std::vector<uint32_t> kn(G), ke(G);
-  NET_TRY(to_host(kn.data(), kept_n.p, (size_t)G * 4, s));
-  NET_TRY(to_host(ke.data(), kept_e.p, (size_t)G * 4, s));
-  std::vector<int64_t> node_off(G + 1, 0), edge_off(G + 1, 0);
-  for (uint32_t g = 0; g < G; ++g) {
-    node_off[g + 1] = node_off[g] + N.n_sub + kn[g];
-    edge_off[g + 1] = edge_off[g] + ke[g];
-  }
-  N.nodes = node_off[G];
-  N.edges = edge_off[G];
-  if (N.nodes >= (int64_t)emr::kNoNode)
-    return failf(EMR_E_LIMIT, "networks: %lld nodes in all (at most 2^32 - 2)", (long long)N.nodes);
-  if (N.edges > e_raw)
-    return failf(EMR_E_DEVICE, "networks: %lld kept edges of %lld", (long long)N.edges,
-                 (long long)e_raw);
-  NET_TRY(order_genomes(N, node_off, edge_off, s));
-  Dev d_edge_off, gid;
-  NET_TRY(alloc(N.node_offset, (size_t)(G + 1) * 8, "network node offsets", s));
-  NET_TRY(alloc(d_edge_off, (size_t)(G + 1) * 8, "network edge offsets", s));
-  NET_TRY(alloc(N.node_cell, (size_t)N.nodes * 4, "network nodes", s));
-  NET_TRY(alloc(N.node_in, (size_t)N.nodes * 4, "network input numbers", s));
-  NET_TRY(alloc(N.in_offset, (size_t)(N.nodes + 1) * 8, "network edge offsets", s));
-  NET_TRY(alloc(N.in_src, (size_t)N.edges * 4, "network edges", s));
-  NET_TRY(alloc(N.in_w, (size_t)N.edges * 4, "network edges", s));
-  NET_TRY(alloc(gid, (size_t)n_raw * 4, "node numbers", s));
-  NET_TRY(to_device(N.node_offset.p, node_off.data(), node_off.size() * 8, s));
-  NET_TRY(to_device(d_edge_off.p, edge_off.data(), edge_off.size() * 8, s));
+  NET_HIP(emr_launch_net(6, &fa, 0, s));
   emr::NetNodeArgs na{N.known.as<uint32_t>(), rank.as<uint32_t>(), N.words,
-                      d_raw_node.as<int64_t>(), fwd.as<uint8_t>(), bwd.as<uint8_t>(),
-                      in_deg.as<uint32_t>(), N.d_slots.as<int32_t>(),
-                      N.node_offset.as<int64_t>(), d_edge_off.as<int64_t>(), gid.as<uint32_t>(),
-                      N.node_cell.as<uint32_t>(), N.node_in.as<int32_t>(),
-                      N.in_offset.as<int64_t>(), d_err, (uint32_t)N.n_sub, G};
-  NET_HIP(emr_launch_net(6, &na, 0, s));
+                      raw_node.as<int64_t>(), flags.as<uint16_t>(), N.d_slots.as<int32_t>(),
+                      N.node_offset.as<int64_t>(), gid.as<uint32_t>(), N.node_cell.as<uint32_t>(),
+                      N.node_in.as<int32_t>(), d_err, (uint32_t)N.n_sub, G};
+  NET_HIP(emr_launch_net(7, &na, 0, s));
   // kept edges grouped by destination, each group in raw order: a stable sort by destination
-  if (N.edges > 0) {
-    Dev keys, vals, skeys, svals, tmp;
-    NET_TRY(alloc(keys, (size_t)e_raw * 4, "edge keys", s));
-    NET_TRY(alloc(vals, (size_t)e_raw * 4, "edge keys", s));
-    NET_TRY(alloc(skeys, (size_t)e_raw * 4, "edge keys", s));
-    NET_TRY(alloc(svals, (size_t)e_raw * 4, "edge keys", s));
-    emr::NetKeyArgs ka{eu.as<uint32_t>(), ev.as<uint32_t>(), fwd.as<uint8_t>(), bwd.as<uint8_t>(),
-                       gid.as<uint32_t>(), keys.as<uint32_t>(), vals.as<uint32_t>(), e_raw, n_raw,
-                       (uint32_t)N.nodes, d_err};
-    NET_HIP(emr_launch_net(7, &ka, 0, s));
+  const uint32_t sentinel = (uint32_t)n_raw;
+  Dev keys, vals, skeys, svals, tmp;
+  NET_TRY(alloc(keys, (size_t)e_raw * 4, "edge keys", s));
+  NET_TRY(alloc(vals, (size_t)e_raw * 8, "edge values", s));
+  NET_TRY(alloc(skeys, (size_t)e_raw * 4, "edge keys", s));
+  NET_TRY(alloc(svals, (size_t)e_raw * 8, "edge values", s));
+  if (e_raw > 0) {
+    emr::NetKeyArgs ka{eu.as<uint32_t>(), ev.as<uint32_t>(), ew.as<float>(), flags.as<uint16_t>(),
+                       gid.as<uint32_t>(), keys.as<uint32_t>(), vals.as<uint64_t>(), e_raw, n_raw,
+                       sentinel, d_err};
+    NET_HIP(emr_launch_net(8, &ka, 0, s));
     int bits = 1;
-    while (bits < 32 && ((uint64_t)1 << bits) <= (uint64_t)N.nodes) ++bits;  // keys <= nodes
+    while (bits < 32 && ((uint64_t)1 << bits) <= (uint64_t)sentinel) ++bits;  // keys <= sentinel
     size_t tb = 0;
     NET_HIP(emr_net_sort(nullptr, &tb, keys.as<uint32_t>(), skeys.as<uint32_t>(),
-                         vals.as<uint32_t>(), svals.as<uint32_t>(), (uint32_t)e_raw, bits, s));
+                         vals.as<uint64_t>(), svals.as<uint64_t>(), (uint32_t)e_raw, bits, s));
     NET_TRY(alloc(tmp, tb, "sort storage", s));
     NET_HIP(emr_net_sort(tmp.p, &tb, keys.as<uint32_t>(), skeys.as<uint32_t>(),
-                         vals.as<uint32_t>(), svals.as<uint32_t>(), (uint32_t)e_raw, bits, s));
-    emr::NetGatherArgs ga{skeys.as<uint32_t>(), svals.as<uint32_t>(), eu.as<uint32_t>(),
-                          ew.as<float>(), gid.as<uint32_t>(), N.in_offset.as<int64_t>(),
-                          N.in_src.as<uint32_t>(), N.in_w.as<float>(), N.edges, e_raw, n_raw,
-                          N.nodes, d_err};
-    NET_HIP(emr_launch_net(8, &ga, 0, s));
-    uint32_t e = 0;
-    NET_TRY(to_host(&e, d_err, 4, s));  // (the sort's buffers are released after this sync)
-    if (e != 0)
-      return failf(EMR_E_DEVICE, "networks: a network kernel flagged an internal error (0x%x)", e);
-    return EMR_OK;
+                         vals.as<uint64_t>(), svals.as<uint64_t>(), (uint32_t)e_raw, bits, s));
   }
-  uint32_t e = 0;
-  NET_TRY(to_host(&e, d_err, 4, s));
-  if (e != 0)
-    return failf(EMR_E_DEVICE, "networks: a network kernel flagged an internal error (0x%x)", e);
-  return EMR_OK;
+  emr::NetSplitArgs sa{skeys.as<uint32_t>(), svals.as<uint64_t>(), N.node_offset.as<int64_t>(),
+                       N.in_offset.as<int64_t>(), sum.as<int64_t>(), N.in_src.as<uint32_t>(),
+                       N.in_w.as<float>(), e_raw, n_raw, sentinel, G, d_err};
+  NET_HIP(emr_launch_net(14, &sa, 0, s));
+  std::vector<int64_t> off(2 * ((size_t)G + 1) + 1);
+  NET_TRY(to_host(off.data(), sum.p, off.size() * 8, s));
+  if (off.back() != 0)
+    return failf(EMR_E_DEVICE, "networks: a network kernel flagged an internal error (0x%llx)",
+                 (unsigned long long)off.back());
+  N.nodes = off[G];
+  N.edges = off[2 * (size_t)G + 1];
+  if (N.nodes < 0 || N.nodes > n_raw || N.edges < 0 || N.edges > e_raw)
+    return failf(EMR_E_DEVICE, "networks: %lld nodes of %lld, %lld kept edges of %lld",
+                 (long long)N.nodes, (long long)n_raw, (long long)N.edges, (long long)e_raw);
+  return order_genomes(N, off.data(), off.data() + G + 1, s);
 }
 
 // The genomes in the order of the activation launches: by class of node count (the classes of
@@ -628,8 +619,8 @@ constexpr int kRunClasses = sizeof kRunClass / sizeof kRunClass[0];
 static_assert(kRunClasses <= emr::kNetRanges && kRunClass[kRunClasses - 2].lds == emr::kNetRunLds,
               "a range per class");
 
-emr_status order_genomes(emr_networks& N, const std::vector<int64_t>& node_off,
-                         const std::vector<int64_t>& edge_off, hipStream_t s) {
+emr_status order_genomes(emr_networks& N, const int64_t* node_off, const int64_t* edge_off,
+                         hipStream_t s) {
   const uint32_t G = (uint32_t)N.n_genomes;
   std::vector<uint32_t>& order = N.order_host;
   order.resize(G);
@@ -863,22 +854,17 @@ emr_status build_all(Build& B, int32_t n_substrate, int32_t iterations) {
     NET_TRY(discover_phase(B, P));
     const bool more = it < iterations;
     auto next = more ? std::make_unique<Phase>() : nullptr;
-    int64_t n_new = 0;
-    NET_TRY(hidden_phase(B, P, next.get(), &n_new));
+    NET_TRY(hidden_phase(B, P));
     NET_TRY(express_phase(B, P));
+    NET_TRY(finish_phase(B, P, next.get()));
     P.ws.reset();
-    if (!more || n_new == 0) break;
+    if (!more || P.n_new == 0) break;
     N.phases.push_back(std::move(next));
   }
   NET_TRY(assemble(B));
   NET_HIP(hipStreamSynchronize(B.s));
   return EMR_OK;
 }
-
-constexpr int32_t kMaxSubstrate = 1024;
-constexpr int32_t kMaxIterations = 64;
-constexpr int32_t kMaxSteps = 1 << 20;
-constexpr int32_t kMaxPatterns = 1 << 16;
 
 }  // namespace
 

@@ -274,6 +274,10 @@ constexpr uint32_t kChunkTilesMax = 16;
 // Group marks of the compaction: a range of more than kNzMinGroups groups of 64 tiles has
 // nz_words(tiles) words of marks per pair, one bit per group.
 constexpr uint32_t kNzMinGroups = 2;
+// Ranges of at most this many pairs compact in one kernel (k_compact): each of its workgroups sums
+// the totals of the pairs before its own, which for more pairs would read more than k_scan's
+// launch costs (at 16384 pairs 16 reads per thread).
+constexpr uint32_t kCompactPairs = 16384;
 EMR_HD constexpr uint32_t nz_words(uint32_t tiles) { return ((tiles + 63u) / 64u + 63u) / 64u; }
 // Rows of zeros after the last tile of the tile geometry table: a walk of TPW <= 4 tiles loads
 // the next walk's TPW rows, up to 2 TPW - 1 rows past its first tile, with no bound per load.
@@ -316,6 +320,7 @@ struct DiscoverArgs {
 // workgroup) then k_move (one wave per pair).
 struct ScanArgs {
   uint32_t* pair_total;  // [n_pairs] per-pair totals of the range (cleared by k_scan after use)
+  uint32_t* clear_total; // k_compact: [n_pairs] the previous call's totals, cleared for the next
   int64_t* pair_count;   // [n_pairs] out
   int64_t* pair_offset;  // [n_pairs + 1] out
   uint32_t* flags;       // the call's flag words (kFlag*)

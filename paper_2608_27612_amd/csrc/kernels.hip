@@ -67,7 +67,7 @@ __device__ __forceinline__ float act_apply(uint32_t a, float z) {
 // After a record-mode discover launch every tile of the range has left its status word (pool
 // offset << 8 | count) and every pair its total. k_scan turns the totals into output offsets
 // (pairs back to back in pair order: CSR), k_move gathers each pair's records from the pool to its
-// offset: tiles in increasing order, each tile's records in increasing lane (parent) order, so
+// offset (k_compact does both for the usual numbers of pairs): tiles in increasing order, each tile's records in increasing lane (parent) order, so
 // each pair's records come out in ascending parent order. Records whose pool or output index is
 // beyond `cap`, or beyond their pair's count, are not moved (an overflowing call reports its
 // total, which exceeds the capacity; a pair whose tiles were skipped after a table error gets no
@@ -95,7 +95,9 @@ __global__ void k_finalize(uint32_t* flags, uint32_t* host) {
 }
 
 constexpr int kScanThreads = 1024;
-constexpr int kScanPer = 4;  // consecutive pairs per thread and round
+// Consecutive pairs per thread and round: a round costs a trip to memory and two barriers (4 us),
+// so long tables take 16 (40,000 pairs: 41 us at 4); short ones keep to few registers and stores.
+constexpr int kScanPerShort = 4, kScanPerLong = 16;
 
 // One workgroup: pairs in rounds of kScanThreads * kScanPer, thread t taking the kScanPer pairs
 // from round + kScanPer t (their loads issued together). Writes pair_count, pair_offset
@@ -105,6 +107,7 @@ constexpr int kScanPer = 4;  // consecutive pairs per thread and round
 // call's kernels are ordered on its stream and this is the only writer of the largest count), so
 // thread 0 reads the words it needs together with the first round's totals and writes the final
 // values without reading them again: the kernel waits for memory once before its stores.
+template <int kScanPer>
 __global__ void __launch_bounds__(kScanThreads) k_scan(ScanArgs A) {
   __shared__ uint64_t wsum[kScanThreads / kWave];
   __shared__ uint32_t wmax[kScanThreads / kWave];
@@ -200,12 +203,45 @@ __device__ __forceinline__ uint32_t wave_incl_scan7(uint32_t c) {
 
 // Moves the records of one group of up to 64 tiles (lane l holds tile l's status word w and count
 // c, incl their inclusive scan): the group's rank q (the pair's rank at + q) goes from its tile's
-// pool segment to base + at + q, in batches of 64 ranks, lane l moving the batch's l-th record.
+// pool segment to base + at + q. A few records scattered over the tiles go in batches of 64 ranks,
+// lane l moving the batch's l-th record (a batch looks through every tile that has any); more than
+// two batches go tile by tile, a tile's records being consecutive on both sides, with four tiles'
+// loads in flight (a batch's search through 64 tiles made one pair of 4700 records a wave of 43 us).
 __device__ __forceinline__ void move_group(const MoveArgs& A, uint64_t w, uint32_t c, uint32_t incl,
                                            int64_t base, uint32_t at, uint32_t count,
                                            uint32_t lane) {
   const uint32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
   const uint64_t has = ballot(c != 0u);
+  if (total > 2 * kWave) {
+    for (uint64_t m = has; m != 0ull;) {
+      uint32_t parent[4];
+      float4 v[4];
+      int64_t dst[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        dst[k] = -1;
+        if (m == 0ull) continue;
+        const uint32_t i = (uint32_t)__builtin_ctzll(m);
+        m &= m - 1ull;
+        const uint32_t n = __builtin_amdgcn_readlane(c, i);
+        const uint32_t q = __builtin_amdgcn_readlane(incl, i) - n + lane;
+        const uint64_t src = (read_lane64(w, i) >> kStatusCountBits) + lane;
+        const int64_t d = base + at + q;
+        if (lane < n && at + q < count && src < (uint64_t)A.cap && d < A.cap) {
+          dst[k] = d;
+          parent[k] = A.pool_parent[src];
+          v[k] = reinterpret_cast<const float4*>(A.pool_w4)[src];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (dst[k] >= 0) {
+          A.parent[dst[k]] = parent[k];
+          reinterpret_cast<float4*>(A.w4)[dst[k]] = v[k];
+        }
+    }
+    return;
+  }
   for (uint32_t b = 0; b < total; b += kWave) {
     const uint32_t q = b + lane;
     uint64_t src = ~0ull;
@@ -248,9 +284,33 @@ __device__ __forceinline__ void for_marked_groups(const MoveArgs& A, uint32_t pa
   }
 }
 
+// One pair's records to base, tile group by tile group (a range of at most two groups reads both
+// groups' status words at once, w0 and w1; a longer one visits only its marked groups).
+__device__ __forceinline__ void move_short(const MoveArgs& A, uint64_t w0, uint64_t w1,
+                                           int64_t base, uint32_t count, uint32_t lane) {
+  const uint32_t c0 = status_count(w0), c1 = status_count(w1);
+  const uint32_t incl0 = wave_incl_scan7(c0), incl1 = wave_incl_scan7(c1);
+  move_group(A, w0, c0, incl0, base, 0u, count, lane);
+  if (A.tiles > (uint32_t)kWave)
+    move_group(A, w1, c1, incl1, base, __builtin_amdgcn_readlane(incl0, kWave - 1), count, lane);
+}
+__device__ __forceinline__ void move_long(const MoveArgs& A, uint32_t pair, int64_t base,
+                                          uint32_t count, uint32_t lane) {
+  const uint64_t* row = A.status + (int64_t)pair * A.tiles;
+  uint32_t at = 0;
+  for_marked_groups(A, pair, lane, [&](uint32_t g) {
+    if (count == 0u) return;
+    const uint32_t t = g * kWave + lane;
+    const uint64_t w = t < A.tiles ? row[t] : 0ull;
+    const uint32_t c = status_count(w);
+    const uint32_t incl = wave_incl_scan7(c);
+    move_group(A, w, c, incl, base, at, count, lane);
+    at += __builtin_amdgcn_readlane(incl, kWave - 1);
+  });
+}
+
 // Each wave takes pairs wave, wave + n_waves, ...: the pair's count and offset from k_scan, then
-// its tiles' records group by group (a range of at most two groups reads both groups' status
-// words at once; a longer one visits only its marked groups).
+// its tiles' records.
 constexpr int kMoveWaves = 4;
 
 __global__ void __launch_bounds__(kMoveWaves * kWave) k_move(MoveArgs A) {
@@ -261,49 +321,128 @@ __global__ void __launch_bounds__(kMoveWaves * kWave) k_move(MoveArgs A) {
   // A pair's loads are issued together, before any of them is used: its skip mark (read from a
   // valid stand-in address when the call skips no pair), count and offset, and for a short range
   // its status words (read even when the pair has no records: they lie inside the status table).
-  auto skipped = [&](uint32_t pair) -> const uint8_t* {
-    return A.skip != nullptr ? A.skip + pair : (const uint8_t*)(A.pair_count + pair);
-  };
-  if (n_groups <= kNzMinGroups) {
-    for (uint32_t pair = first; pair < A.n_pairs; pair += n_waves) {
-      const uint64_t* row = A.status + (int64_t)pair * A.tiles;
-      const uint8_t sv = *skipped(pair);
-      const int64_t count64 = A.pair_count[pair];
-      const int64_t base = A.pair_offset[pair];
-      const uint64_t w0 = lane < A.tiles ? row[lane] : 0ull;
-      const uint64_t w1 = n_groups > 1 && kWave + lane < A.tiles ? row[kWave + lane] : 0ull;
-      const uint32_t count = (uint32_t)min(count64, (int64_t)0xFFFFFFFFll);
-      if ((A.skip != nullptr && sv != 0) || count == 0u) continue;  // no records
-      const uint32_t c0 = status_count(w0), c1 = status_count(w1);
-      const uint32_t incl0 = wave_incl_scan7(c0), incl1 = wave_incl_scan7(c1);
-      move_group(A, w0, c0, incl0, base, 0u, count, lane);
-      if (n_groups > 1)
-        move_group(A, w1, c1, incl1, base, __builtin_amdgcn_readlane(incl0, kWave - 1), count,
-                   lane);
-    }
-    return;
-  }
   for (uint32_t pair = first; pair < A.n_pairs; pair += n_waves) {
-    const uint8_t sv = *skipped(pair);
+    const uint64_t* row = A.status + (int64_t)pair * A.tiles;
+    const uint8_t sv = *(A.skip != nullptr ? A.skip + pair : (const uint8_t*)(A.pair_count + pair));
     const int64_t count64 = A.pair_count[pair];
     const int64_t base = A.pair_offset[pair];
+    uint64_t w0 = 0ull, w1 = 0ull;
+    if (n_groups <= kNzMinGroups) {
+      w0 = lane < A.tiles ? row[lane] : 0ull;
+      w1 = kWave + lane < A.tiles ? row[kWave + lane] : 0ull;
+    }
     // (the count and offset are used before the skip test, so that their loads go out with the
     // mark's instead of after the branch)
     asm volatile("" ::"v"(count64), "v"(base));
     if (A.skip != nullptr && sv != 0) continue;  // no records, no marks
     const uint32_t count = (uint32_t)min(count64, (int64_t)0xFFFFFFFFll);
-    const uint64_t* row = A.status + (int64_t)pair * A.tiles;
-    uint32_t at = 0;
-    for_marked_groups(A, pair, lane, [&](uint32_t g) {
-      if (count == 0u) return;
-      const uint32_t t = g * kWave + lane;
-      const uint64_t w = t < A.tiles ? row[t] : 0ull;
-      const uint32_t c = status_count(w);
-      const uint32_t incl = wave_incl_scan7(c);
-      move_group(A, w, c, incl, base, at, count, lane);
-      at += __builtin_amdgcn_readlane(incl, kWave - 1);
-    });
+    if (n_groups > kNzMinGroups)
+      move_long(A, pair, base, count, lane);
+    else if (count != 0u)
+      move_short(A, w0, w1, base, count, lane);
   }
+}
+
+// Both at once, for at most kCompactPairs pairs: every workgroup (4 pairs, one wave each) sums the
+// totals of the pairs before its own (at most 16 loads of 16 bytes per thread, from L2, in flight
+// together with its pairs' status words), so no kernel has to run before it; the last workgroup
+// has then seen every total and does what k_scan does at its end. The totals stay as they are
+// while other workgroups still read them: the call's other set, which the previous call used, is
+// cleared for the next one instead. (4000 pairs, one of them with 4700 records: k_scan and k_move
+// 6.2 + 43 us and a gap between the launches, this kernel with the tile-by-tile move 16 us.)
+__global__ void __launch_bounds__(kMoveWaves * kWave) k_compact(ScanArgs S, MoveArgs A) {
+  static_assert(kMoveWaves == 4, "a workgroup's totals are one 16-byte load");
+  __shared__ uint64_t wsum[kMoveWaves];
+  __shared__ uint32_t wmax[kMoveWaves];
+  const uint32_t lane = lane_id(), t = threadIdx.x;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(t / kWave);
+  const uint32_t pair0 = blockIdx.x * kMoveWaves, pair = pair0 + wv;
+  const uint32_t n_groups = (A.tiles + kWave - 1) / kWave;
+  const bool last = blockIdx.x == gridDim.x - 1;
+  const bool mine = pair < A.n_pairs;
+  uint32_t f_err = 0, f_max = 0;
+  if (last && t == 0) {
+    f_err = __hip_atomic_load(S.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    f_max = __hip_atomic_load(S.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const uint64_t* row = A.status + (int64_t)pair * A.tiles;
+  uint8_t sv = 0;
+  uint64_t w0 = 0ull, w1 = 0ull;
+  if (mine) {
+    if (A.skip != nullptr) sv = A.skip[pair];
+    if (n_groups <= kNzMinGroups) {
+      w0 = lane < A.tiles ? row[lane] : 0ull;
+      w1 = kWave + lane < A.tiles ? row[kWave + lane] : 0ull;
+    }
+  }
+  uint32_t own[kMoveWaves];
+#pragma unroll
+  for (int k = 0; k < kMoveWaves; ++k)
+    own[k] = pair0 + k < S.n_pairs ? S.pair_total[pair0 + k] : 0u;
+  uint64_t sum = 0;
+  uint32_t mx = 0;
+  const uint4* before = reinterpret_cast<const uint4*>(S.pair_total);  // 4 pairs per workgroup
+  for (uint32_t i = t; i < blockIdx.x; i += kMoveWaves * kWave) {
+    const uint4 v = before[i];
+    sum += (uint64_t)v.x + v.y + v.z + v.w;
+    mx = max(max(mx, max(v.x, v.y)), max(v.z, v.w));
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    sum += __shfl_xor(sum, off, kWave);
+    mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, kWave));
+  }
+  if (lane == 0) {
+    wsum[wv] = sum;
+    wmax[wv] = mx;
+  }
+  __syncthreads();
+  uint64_t base = 0;
+#pragma unroll
+  for (int k = 0; k < kMoveWaves; ++k) base += wsum[k];
+  uint64_t total = base;  // after this workgroup's pairs
+#pragma unroll
+  for (int k = 0; k < kMoveWaves; ++k) {
+    if ((uint32_t)k < wv) base += own[k];
+    total += own[k];
+  }
+  uint32_t count = own[0];
+#pragma unroll
+  for (int k = 1; k < kMoveWaves; ++k) count = wv == (uint32_t)k ? own[k] : count;
+  if (mine && lane == 0) {
+    S.clear_total[pair] = 0u;
+    S.pair_count[pair] = count;
+    if (S.host_counts) S.host_counts[pair] = count;
+    S.pair_offset[pair] = (int64_t)base;
+  }
+  if (last && t == 0) {
+    uint32_t m = f_max;
+#pragma unroll
+    for (int k = 0; k < kMoveWaves; ++k) m = max(m, max(wmax[k], own[k]));
+    S.pair_offset[S.n_pairs] = (int64_t)total;
+    if (S.host_counts) S.host_counts[S.n_pairs] = f_err;
+    if (S.host) {
+      // the call's last flag writes (see k_scan)
+      S.host[kFlagErr] = f_err;
+      S.host[kFlagMax] = m;
+      S.host[kFlagTotal] = (uint32_t)total;
+      S.host[kFlagTotal + 1] = (uint32_t)(total >> 32);
+#pragma unroll
+      for (int k = 0; k < kFlagWords; ++k)
+        __hip_atomic_store(S.flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      __hip_atomic_store(S.flags + kFlagMax, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store((uint64_t*)(S.flags + kFlagTotal), total, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store((uint64_t*)(S.flags + kFlagPool), 0ull, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (!mine || (A.skip != nullptr && sv != 0)) return;
+  if (n_groups > kNzMinGroups)
+    move_long(A, pair, (int64_t)base, count, lane);
+  else if (count != 0u)
+    move_short(A, w0, w1, (int64_t)base, count, lane);
 }
 
 // The interpreting discover kernel: one launch covers every part of a call.
@@ -671,7 +810,10 @@ extern "C" hipError_t emr_launch_discover(const emr::DiscoverArgs* a, int mode, 
 
 // Offsets of a CSR output from per-pair (or per-genome) totals, one workgroup.
 extern "C" hipError_t emr_launch_scan(const emr::ScanArgs* S, hipStream_t s) {
-  hipLaunchKernelGGL(emr::k_scan, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
+  if (S->n_pairs > (uint32_t)(emr::kScanThreads * emr::kScanPerShort))
+    hipLaunchKernelGGL(emr::k_scan<emr::kScanPerLong>, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
+  else
+    hipLaunchKernelGGL(emr::k_scan<emr::kScanPerShort>, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
   return hipGetLastError();
 }
 
@@ -680,10 +822,17 @@ extern "C" hipError_t emr_launch_scan(const emr::ScanArgs* S, hipStream_t s) {
 extern "C" hipError_t emr_launch_compact(const emr::ScanArgs* S, const emr::MoveArgs* M,
                                          hipStream_t s) {
   if (S->n_pairs == 0) return hipSuccess;
-  hipLaunchKernelGGL(emr::k_scan, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   uint32_t blocks = (M->n_pairs + emr::kMoveWaves - 1) / emr::kMoveWaves;
+  if (S->n_pairs <= emr::kCompactPairs) {
+    if (S->n_pairs != M->n_pairs || !S->clear_total || S->clear_total == S->pair_total ||
+        (((uintptr_t)S->pair_total | (uintptr_t)S->clear_total) & 15) != 0)
+      return hipErrorInvalidValue;
+    hipLaunchKernelGGL(emr::k_compact, dim3(blocks), dim3(emr::kMoveWaves * emr::kWave), 0, s, *S,
+                       *M);
+    return hipGetLastError();
+  }
+  const hipError_t e = emr_launch_scan(S, s);
+  if (e != hipSuccess) return e;
   if (blocks > 8192) blocks = 8192;  // waves loop over pairs beyond this
   hipLaunchKernelGGL(emr::k_move, dim3(blocks), dim3(emr::kMoveWaves * emr::kWave), 0, s, *M);
   return hipGetLastError();

@@ -1085,6 +1085,8 @@ bool cached_split_parts(const Plan& P, const Plan::Launch& L, bool skip_uniform,
 // before the discover launch, once every argument of that launch is ready on the host.
 // flags: the call's device flag words (error bits, largest count); flags_host: their pinned words
 // (device view) for that hand-over.
+// turn: which of the workspace's two sets of totals the range uses (the other is cleared for the
+// next call).
 // may_alloc: the call may allocate on first use: the thread's launch profiling (its events) and
 // the launch's chunk schedule apply (off for the allocation-free call, which runs its chunks
 // round-robin). A compiled-tier launch gets its workgroups' chunk lists once its plan runs again
@@ -1095,7 +1097,8 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
                         float theta, const emr_result* out, float* raw, void* workspace,
                         hipStream_t s, int64_t tile_lo, int64_t n_tiles, bool jit,
                         uint32_t* flags, uint32_t* flags_host, bool finalize, bool clear,
-                        bool may_alloc = true, int64_t* host_counts = nullptr) {
+                        bool may_alloc = true, int64_t* host_counts = nullptr,
+                        uint32_t turn = 0) {
   char* ws = (char*)workspace;
   const char* tables = T.tables;
   const uint32_t* geo_tab = T.geo;
@@ -1136,7 +1139,7 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     a.err = flags;
     a.pool_parent = pool_parent;
     a.pool_w4 = pool_w4;
-    a.pair_total = records ? (uint32_t*)(ws + P.off_ptotal) : nullptr;
+    a.pair_total = records ? (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride) : nullptr;
     a.raw = raw;
     a.cap = cap;
     a.n_pos = emr::n_positions(P.depth);
@@ -1210,7 +1213,8 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     HIP_OR_FAIL(emr_launch_fill(ws + P.off_nz, P.clear_words, 0u, s));
   if (records && P.n_pairs > 0) {
     emr::ScanArgs S{};
-    S.pair_total = (uint32_t*)(ws + P.off_ptotal);
+    S.pair_total = (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride);
+    S.clear_total = (uint32_t*)(ws + P.off_ptotal + (1 - turn) * P.ptotal_stride);
     S.pair_count = out->pair_count;
     S.pair_offset = out->pair_offset;
     S.flags = flags;
@@ -1250,24 +1254,31 @@ emr_status call_tables(const emr_population* pop, const Plan& P, const CallFlags
   return tile_geo_table(P.depth, &T->geo, &T->geo_rows);
 }
 
-// Workspaces whose counters a record call left cleared: its k_scan zeroes every pair total and
-// its k_move every tile-group mark, so the next record call of the same plan on the same stream
-// (stream order puts it after those kernels) needs no clearing launch. Any other call with the
-// workspace forgets it. (A few entries: the latest workspaces of the process.)
+// Workspaces whose counters a record call left cleared: its compaction zeroes every tile-group mark
+// and the pair totals that the next record call will use (its own, or the other of two sets, taken
+// in turn), so the next record call of the same plan on the same stream (stream order puts it
+// after those kernels) needs no clearing launch. Any other call with the workspace forgets it. (A
+// few entries: the latest workspaces of the process.)
 struct CleanWorkspace {
   const void* ws;
   uint64_t plan;
   hipStream_t s;
   int64_t capacity;
+  uint32_t turn;  // the set of totals that the next call uses
 };
 std::mutex g_clean_mu;
 std::vector<CleanWorkspace> g_clean;
 constexpr size_t kCleanEntries = 64;
 
-bool workspace_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity) {
+bool workspace_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity,
+                     uint32_t* turn) {
   std::lock_guard<std::mutex> lock(g_clean_mu);
+  *turn = 0;
   for (const CleanWorkspace& c : g_clean)
-    if (c.ws == ws) return c.plan == P.id && c.s == s && c.capacity == capacity;
+    if (c.ws == ws && c.plan == P.id && c.s == s && c.capacity == capacity) {
+      *turn = c.turn;
+      return true;
+    }
   return false;
 }
 void workspace_forget(const void* ws) {
@@ -1278,15 +1289,16 @@ void workspace_forget(const void* ws) {
       return;
     }
 }
-void workspace_mark_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity) {
+void workspace_mark_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity,
+                          uint32_t turn) {
   std::lock_guard<std::mutex> lock(g_clean_mu);
   for (CleanWorkspace& c : g_clean)
     if (c.ws == ws) {
-      c = CleanWorkspace{ws, P.id, s, capacity};
+      c = CleanWorkspace{ws, P.id, s, capacity, turn};
       return;
     }
   if (g_clean.size() >= kCleanEntries) g_clean.erase(g_clean.begin());
-  g_clean.push_back(CleanWorkspace{ws, P.id, s, capacity});
+  g_clean.push_back(CleanWorkspace{ws, P.id, s, capacity, turn});
 }
 
 // Enqueue a whole call: take a flag slot, then every tile of every pair.
@@ -1303,12 +1315,13 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   if ((st = jit_use(pop, P, plan_slots(P), &jit)) != EMR_OK) return st;
   const bool records = out != nullptr && raw == nullptr;
   const int64_t capacity = records ? out->capacity : -1;
-  const bool clean = records && workspace_clean(workspace, P, s, capacity);
+  uint32_t turn = 0;
+  const bool clean = records && workspace_clean(workspace, P, s, capacity, &turn);
   workspace_forget(workspace);
   st = launch_range(pop, P, T, theta, out, raw, workspace, s, 0, P.tiles, jit, f.dev, f.host_dev,
-                    true, !clean);
+                    true, !clean, true, nullptr, turn);
   if (st != EMR_OK) return st;
-  if (records) workspace_mark_clean(workspace, P, s, capacity);
+  if (records) workspace_mark_clean(workspace, P, s, capacity, P.ptotal_stride ? 1 - turn : 0);
   f.ok = true;
   return EMR_OK;
 }

@@ -3,6 +3,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "emr_internal.h"
+
 namespace emr {
 
 // One pair's program as the band kernel walks it (16 bytes per pair, built by the host from the
@@ -38,8 +40,7 @@ struct BandSelectArgs {
   const float* band;
   int64_t in_cap;
   float theta_band;
-  uint32_t* totals;           // [n_pairs]
-  const int64_t* out_offset;  // [n_pairs + 1] from k_scan
+  FilterSpans spans;
   uint32_t* out_cell;
   float* out_w;
   int64_t out_cap;

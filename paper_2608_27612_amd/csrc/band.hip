@@ -2,8 +2,11 @@
 // Theorem 1 names beside the variance threshold; ES-HyperNEAT's pruning step defines it): for
 // connection (pair, cell C, weight w), the pair's CPPN at the four same-level neighbour centres
 // of C, one cell side d away along x and y, and band = max(min(|w - left|, |w - right|),
-// min(|w - down|, |w - up|)). One wave per pair: its program runs through the interpreter's record
-// step (one source per walk), each lane holding P / 4 connections and their 4 neighbours each.
+// min(|w - down|, |w - up|)). The pair's program runs through the interpreter's record step (one
+// source per walk), each lane holding P / 4 connections and their 4 neighbours each. kBandParts waves
+// share a pair, each taking every kBandParts-th walk: a high-frequency CPPN's pair has thousands of
+// connections (one wave per pair: 131 us for 300,000 connections of 4950 pairs, the heaviest
+// pair's wave), and a wave that finds no walk ends after reading the pair's offsets.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -16,13 +19,14 @@ namespace emr {
 
 // The walks of one pair over its connections [lo, hi): connection i = b + 64 k + lane holds
 // instances 4k .. 4k + 3 (left, right, down, up).
+constexpr uint32_t kBandParts = 8;
 template <int W>
 __device__ __forceinline__ void band_walks(const BandArgs& A, const BandPair& bp, int64_t lo,
-                                           int64_t hi, uint32_t lane) {
+                                           int64_t hi, uint32_t part, uint32_t lane) {
   constexpr int P = positions_per_lane(1, W);
   constexpr int C = P / 4;
   const int64_t n_pos = n_positions(A.depth);
-  for (int64_t b = lo; b < hi; b += (int64_t)kWave * C) {
+  for (int64_t b = lo + (int64_t)part * kWave * C; b < hi; b += (int64_t)kBandParts * kWave * C) {
     float px[P], py[P], wc[C];
     bool live[C];
 #pragma unroll
@@ -69,7 +73,7 @@ __device__ __forceinline__ void band_walks(const BandArgs& A, const BandPair& bp
 }
 
 __global__ void __launch_bounds__(256) k_band(BandArgs A) {
-  const uint32_t lane = lane_id();
+  const uint32_t lane = lane_id(), part = blockIdx.y;
   for (uint32_t pair = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) +
                                                       threadIdx.x / kWave);
        pair < A.n_pairs; pair += gridDim.x * (blockDim.x / kWave)) {
@@ -89,10 +93,10 @@ __global__ void __launch_bounds__(256) k_band(BandArgs A) {
     lo = lo < 0 ? 0 : (lo > A.cap ? A.cap : lo);
     hi = hi > A.cap ? A.cap : (hi < lo ? lo : hi);
     switch (bp.window) {
-      case 4u: band_walks<4>(A, bp, lo, hi, lane); break;
-      case 8u: band_walks<8>(A, bp, lo, hi, lane); break;
-      case 16u: band_walks<16>(A, bp, lo, hi, lane); break;
-      default: band_walks<32>(A, bp, lo, hi, lane); break;
+      case 4u: band_walks<4>(A, bp, lo, hi, part, lane); break;
+      case 8u: band_walks<8>(A, bp, lo, hi, part, lane); break;
+      case 16u: band_walks<16>(A, bp, lo, hi, part, lane); break;
+      default: band_walks<32>(A, bp, lo, hi, part, lane); break;
     }
   }
 }
@@ -102,6 +106,6 @@ __global__ void __launch_bounds__(256) k_band(BandArgs A) {
 extern "C" hipError_t emr_launch_band(const emr::BandArgs* A, hipStream_t s) {
   uint32_t b = (A->n_pairs + 3) / 4;
   b = b == 0 ? 1 : (b > 8192 ? 8192 : b);
-  hipLaunchKernelGGL(emr::k_band, dim3(b), dim3(256), 0, s, *A);
+  hipLaunchKernelGGL(emr::k_band, dim3(b, emr::kBandParts), dim3(256), 0, s, *A);
   return hipGetLastError();
 }

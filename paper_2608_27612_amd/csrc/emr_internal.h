@@ -372,12 +372,25 @@ struct HiddenArgs {
   uint32_t n_genomes;
 };
 
+// The filters over CSR entries (connections of records, band selection, the chain rule) run as
+// spans of consecutive entries, one wave each, whatever pairs they belong to: kFilterSpans spans
+// at most, of a multiple of 64 entries. The first kernel leaves each span's kept entries, the
+// second sums the spans before its own and writes the output and the pairs' offsets, the third
+// (one workgroup) the counts, the total and the flags.
+constexpr uint32_t kFilterSpans = 8192;
+struct FilterSpans {
+  uint32_t* kept;       // [kFilterSpans] (workspace)
+  int64_t* out_offset;  // [n_pairs + 1]
+  int64_t* out_count;   // [n_pairs]
+  uint32_t* flags;      // the call's flag words and their pinned copy
+  uint32_t* host;
+};
+
 struct ExpressArgs {
   RecordsIn rec;
+  FilterSpans spans;
   uint32_t type_mask;
   float w_min;
-  uint32_t* totals;           // [n_pairs]
-  const int64_t* out_offset;  // [n_pairs + 1] from k_scan
   uint32_t* out_cell;
   float* out_w;
   int64_t cap;
@@ -387,8 +400,7 @@ struct ChainArgs {
   RecordsIn rec;
   uint32_t* member;           // [n_pairs * qwords] bit P: parent P is a record of the pair
   int64_t qwords;
-  uint32_t* totals;           // [n_pairs]
-  const int64_t* out_offset;  // [n_pairs + 1] from k_scan
+  FilterSpans spans;
   uint32_t* out_parent;
   float* out_w4;
   int64_t cap;

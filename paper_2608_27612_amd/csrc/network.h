@@ -34,8 +34,10 @@ struct NetRankArgs {
 // connection's grid cell in genome g.
 struct NetPair {
   int64_t delta;
+  int64_t lo, hi;  // the genome's raw edges
   uint32_t g_dir;  // genome << 1 | direction (0: node -> cell, 1: cell -> node)
   uint32_t node;
+  uint32_t base, n;  // the genome's raw nodes
 };
 
 constexpr int kNetMaxPhases = 65;  // the substrate's and one per hidden-to-hidden iteration

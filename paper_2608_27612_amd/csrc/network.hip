@@ -193,14 +193,18 @@ __global__ void __launch_bounds__(kNetThreads) k_net_pairs(NetEdgeArgs A) {
       node = g < A.n_genomes ? node_of(A.known, A.rank, A.words, g, A.n_sub, A.src_cell[r]) : kNoNode;
       dir = 0u;
     }
-    NetPair p{0, 0u, kNoNode};
+    NetPair p{0, 0, 0, 0u, kNoNode, 0u, 0u};
     if (g >= A.n_genomes || node == kNoNode ||
         (int64_t)node >= A.raw_node[g + 1] - A.raw_node[g]) {
       atomicOr(A.err, kNetErrIndex);
     } else {
       p.delta = A.seg[g] - A.conn_offset[first];
       p.g_dir = g << 1 | dir;
-      p.node = node + (uint32_t)A.raw_node[g];  // (the host bounds the raw nodes below kNoNode)
+      p.lo = A.raw_edge[g];
+      p.hi = A.raw_edge[g + 1];
+      p.base = (uint32_t)A.raw_node[g];  // (the host bounds the raw nodes below kNoNode)
+      p.n = (uint32_t)(A.raw_node[g + 1] - A.raw_node[g]);
+      p.node = node + p.base;
     }
     A.pairs[r] = p;
   }
@@ -210,17 +214,17 @@ __global__ void __launch_bounds__(kNetThreads) k_net_pairs(NetEdgeArgs A) {
 __device__ __forceinline__ void net_edge(const NetEdgeArgs& A, const NetPair& P, int64_t i) {
   const uint32_t g = P.g_dir >> 1;
   const int64_t o = i + P.delta;
-  if (P.node == kNoNode || o < A.raw_edge[g] || o >= A.raw_edge[g + 1] || o >= A.e_raw) {
+  if (P.node == kNoNode || o < P.lo || o >= P.hi || o >= A.e_raw) {
     atomicOr(A.err, kNetErrIndex);
     return;
   }
   const uint32_t cn = node_of(A.known, A.rank, A.words, g, A.n_sub, A.conn_cell[i]);
-  const uint32_t c = cn + (uint32_t)A.raw_node[g];
+  const uint32_t c = cn + P.base;
   const bool in = (P.g_dir & 1u) != 0u;
   uint32_t u = in ? c : P.node, v = in ? P.node : c;
   if (cn == kNoNode) {
     u = v = kNoNode;  // the grid end is not a hidden node: dropped
-  } else if ((int64_t)cn >= A.raw_node[g + 1] - A.raw_node[g]) {
+  } else if (cn >= P.n) {
     atomicOr(A.err, kNetErrIndex);
     u = v = kNoNode;
   }
@@ -229,30 +233,33 @@ __device__ __forceinline__ void net_edge(const NetEdgeArgs& A, const NetPair& P,
   A.ew[o] = A.conn_w[i];
 }
 
-// Wave w takes the phase's connections [w kEdgeSpan, (w + 1) kEdgeSpan), 64 at a time. While they
-// belong to one pair (most do: a few heavy genomes hold most connections, hundreds per pair) the
-// pair is the wave's and only the grid end is looked up per lane; else each lane finds its pair
-// from the last one on. (A search of all pairs and genomes per connection: 455 us for 16.8M.)
-constexpr int64_t kEdgeSpan = 8 * kWave;
-__global__ void __launch_bounds__(kNetThreads) k_net_edges(NetEdgeArgs A) {
+// Wave w takes the phase's connections [w span, (w + 1) span), 64 at a time. While they belong to
+// one pair (most do: a few heavy genomes hold most connections, hundreds per pair) the pair is the
+// wave's and only the grid end is looked up per lane; else each lane finds its pair from the step's
+// first on. (A search of all pairs and genomes per connection: 455 us for 16.8M.)
+__global__ void __launch_bounds__(kNetThreads) k_net_edges(NetEdgeArgs A, int64_t span) {
   const uint32_t lane = threadIdx.x % kWave;
   const int64_t wave = (int64_t)blockIdx.x * (kNetThreads / kWave) +
                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int64_t n_waves = (int64_t)gridDim.x * (kNetThreads / kWave);
-  for (int64_t base = wave * kEdgeSpan; base < A.total; base += n_waves * kEdgeSpan) {
-    int64_t r = find_segment(A.conn_offset, A.n_pairs, base);
-    const int64_t end = base + kEdgeSpan < A.total ? base + kEdgeSpan : A.total;
-    for (int64_t b = base; b < end; b += kWave) {
-      r = find_segment_from(A.conn_offset, A.n_pairs, r, b);
-      const int64_t last = b + kWave < end ? b + kWave : end;
-      const int64_t i = b + lane;
-      if (A.conn_offset[r + 1] >= last) {
-        const NetPair P = A.pairs[r];
-        if (i < last) net_edge(A, P, i);
-      } else if (i < last) {
-        net_edge(A, A.pairs[find_segment_from(A.conn_offset, A.n_pairs, r, i)], i);
-      }
+  const int64_t base = wave * span, end = base + span < A.total ? base + span : A.total;
+  if (base >= end) return;
+  uint32_t r = __builtin_amdgcn_readfirstlane(
+      (uint32_t)find_segment(A.conn_offset, A.n_pairs, base));  // (pairs number below 2^32)
+  int64_t r1 = A.conn_offset[r + 1];
+  NetPair P = A.pairs[r];
+  for (int64_t b = base; b < end; b += kWave) {
+    if (b >= r1) {
+      r = __builtin_amdgcn_readfirstlane(
+          (uint32_t)find_segment_from(A.conn_offset, A.n_pairs, r, b));
+      r1 = A.conn_offset[r + 1];
+      P = A.pairs[r];
     }
+    const int64_t i = b + lane;
+    if (i >= end) continue;
+    if (i < r1)
+      net_edge(A, P, i);
+    else
+      net_edge(A, A.pairs[find_segment_from(A.conn_offset, A.n_pairs, r, i)], i);
   }
 }
 
@@ -802,9 +809,12 @@ extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, h
     case 3: {
       const auto& A = *static_cast<const NetEdgeArgs*>(args);
       if (A.total <= 0) return hipSuccess;
-      hipLaunchKernelGGL(k_net_edges, dim3(stride_blocks((A.total + kEdgeSpan - 1) / kEdgeSpan *
-                                                         kWave)),
-                         blk, 0, s, A);
+      // 16384 waves at most (two rounds of the chip's wave slots), whole steps of 64 connections
+      const int64_t steps = (A.total + kWave - 1) / kWave;
+      const int64_t span = (steps + 16383) / 16384 * kWave;
+      const int64_t waves = (A.total + span - 1) / span;
+      constexpr int64_t per = kNetThreads / kWave;
+      hipLaunchKernelGGL(k_net_edges, dim3((uint32_t)((waves + per - 1) / per)), blk, 0, s, A, span);
       break;
     }
     case 4: {

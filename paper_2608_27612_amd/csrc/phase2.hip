@@ -8,7 +8,8 @@
 //     connection, kept by its type and weight magnitude;
 //   Eq. 2 read literally: a record stays when every ancestor of its cell is a record of the pair;
 //   the band filter: the connections whose band value (band.hip) exceeds a threshold.
-// Each output is CSR (k_scan in kernels.hip turns per-pair or per-genome totals into offsets).
+// Each output is CSR. A pair's entries number from none to hundreds of thousands (a high-frequency
+// CPPN keeps every cell), so no kernel gives a pair to a wave: entries go to the waves in spans.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -30,30 +31,7 @@ __device__ __forceinline__ void cell_centre(uint32_t p, float* x, float* y) {
   *y = __builtin_fmaf((float)(2u * compact_even(m >> 1) + 1u), sc, -1.0f);
 }
 
-// Each wave takes pairs wave, wave + n_waves, ...
-#define FOR_EACH_PAIR_WAVE(pair, n)                                                              \
-  for (uint32_t pair = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) +        \
-                                                      threadIdx.x / kWave);                      \
-       pair < (n); pair += gridDim.x * (blockDim.x / kWave))
-
-// The pair's records [lo, hi) within the buffers' capacity.
-__device__ __forceinline__ void pair_range(const RecordsIn& R, uint32_t pair, int64_t* lo,
-                                           int64_t* hi) {
-  const int64_t off = R.offset[pair], cnt = R.count[pair];
-  *lo = off < 0 ? 0 : (off > R.cap ? R.cap : off);
-  const int64_t end = off + (cnt < 0 ? 0 : cnt);
-  *hi = end > R.cap ? R.cap : (end < *lo ? *lo : end);
-}
-
-// ------------------------------------------------------------------------ hidden nodes
-// The call's records in parallel (a pair's records can number from none to hundreds of
-// thousands, so they are spread by record, not by pair): wave w takes the records
-// [w kMarkSpan, (w + 1) kMarkSpan) and lane l the records w kMarkSpan + l, + 64, ...; a record's
-// pair is the last pair whose offset is at most the record's index (a binary search for the
-// lane's first record, then a gallop forward from the pair before, the indices only growing).
-// A record outside the range of the pair found (offsets out of order) marks nothing.
-constexpr uint32_t kMarkSpan = 16 * kWave;
-
+// ------------------------------------------------------------------------ spans of entries
 // The last q in [lo, hi) with off[q] <= r, given off[lo] <= r and (hi = n or off[hi] > r).
 __device__ __forceinline__ uint32_t last_at_most(const int64_t* off, uint32_t lo, uint32_t hi,
                                                  int64_t r) {
@@ -66,52 +44,218 @@ __device__ __forceinline__ uint32_t last_at_most(const int64_t* off, uint32_t lo
   }
   return lo;
 }
+// The last q >= lo with off[q] <= r, given off[lo] <= r: a gallop, then a search.
+__device__ __forceinline__ uint32_t last_from(const int64_t* off, uint32_t lo, uint32_t n,
+                                              int64_t r) {
+  uint32_t step = 1u, hi = lo + 1u;
+  while (hi < n && off[hi] <= r) {
+    lo = hi;
+    step = step < (1u << 30) ? 2u * step : step;
+    hi = n - lo > step ? lo + step : n;
+  }
+  return last_at_most(off, lo, hi, r);
+}
 
+// Entries per span when `held` entries go to n_spans spans: a multiple of 64.
+__device__ __forceinline__ int64_t span_length(int64_t held, uint32_t n_spans) {
+  const int64_t steps = (held + kWave - 1) / kWave;
+  return (steps + n_spans - 1) / n_spans * kWave;
+}
+
+// Calls f(i, pair, start) for the wave's entries [base, end) of a CSR table (off[n + 1]), 64 at a
+// time, every lane of the wave taking part (i < end is the lane's own test): pair is the entry's,
+// start = off[pair]. Most steps lie inside one pair, which the wave then follows without a search;
+// in the others each lane searches on from the pair of the step's first entry.
+template <typename F>
+__device__ __forceinline__ void for_span(const int64_t* off, uint32_t n, int64_t base, int64_t end,
+                                         uint32_t lane, F&& f) {
+  if (base >= end) return;
+  uint32_t p = __builtin_amdgcn_readfirstlane(last_at_most(off, 0u, n, base));
+  int64_t p0 = off[p], p1 = off[p + 1];
+  for (int64_t b = base; b < end; b += kWave) {
+    if (b >= p1) {
+      p = __builtin_amdgcn_readfirstlane(last_from(off, p, n, b));
+      p0 = off[p];
+      p1 = off[p + 1];
+    }
+    const int64_t i = b + lane;
+    uint32_t q = p;
+    int64_t q0 = p0;
+    if (p1 < (b + kWave < end ? b + kWave : end) && i >= p1 && i < end) {
+      q = last_from(off, p, n, i);
+      q0 = off[q];
+    }
+    f(i, q, q0);
+  }
+}
+
+// The wave's span index, and the launches' workgroups: 4 spans each.
+__device__ __forceinline__ uint32_t span_index() {
+  return __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+}
+
+// Sum over the wave of a per-lane count c < 8 (bit-sliced ballots).
+__device__ __forceinline__ uint32_t wave_sum3(uint32_t c) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) t += popc64(ballot((c >> b) & 1u)) << b;
+  return t;
+}
+__device__ __forceinline__ uint32_t wave_excl3(uint32_t c) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) t += mbcnt64(ballot((c >> b) & 1u)) << b;
+  return t;
+}
+
+// A filter over a CSR table: Op has off() (the table's offsets), pairs(), cap() (entries held), keep
+// (entry, pair) -> a mask of the entry's kept items (up to 4) and emit(entry, pair, item, place).
+template <typename Op>
+__global__ void __launch_bounds__(256) k_filter_count(Op op) {
+  const uint32_t lane = lane_id(), span = span_index();
+  const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
+  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
+  const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
+  uint32_t total = 0;
+  if (op.off()[0] <= 0)  // (else not a CSR offset table)
+    for_span(op.off(), n, base, min(base + len, held), lane,
+             [&](int64_t i, uint32_t pair, int64_t) {
+               const uint32_t m = i < min(base + len, held) ? op.keep(i, pair) : 0u;
+               total += wave_sum3((uint32_t)__builtin_popcount(m));
+             });
+  if (lane == 0) op.spans.kept[span] = total;
+}
+
+// The kept entries of the spans before this one (n_spans at most kFilterSpans, read by the
+// workgroup: 32 loads per thread at most).
+__device__ __forceinline__ uint64_t spans_before(const uint32_t* kept, uint64_t* wsum) {
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  const uint32_t first = blockIdx.x * waves;
+  uint64_t sum = 0;
+  for (uint32_t k = threadIdx.x; k < first; k += blockDim.x) sum += kept[k];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+  if (lane == 0) wsum[wv] = sum;
+  __syncthreads();
+  uint64_t t = 0;
+  for (uint32_t k = 0; k < waves; ++k) t += wsum[k];
+  for (uint32_t k = first; k < first + wv; ++k) t += kept[k];
+  return t;
+}
+
+// Writes the kept items in order, and the offset of every pair whose first entry the span holds.
+template <typename Op>
+__global__ void __launch_bounds__(256) k_filter_emit(Op op) {
+  __shared__ uint64_t wsum[256 / kWave];
+  const uint32_t lane = lane_id(), span = span_index();
+  const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
+  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
+  const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
+  int64_t at0 = (int64_t)spans_before(op.spans.kept, wsum);
+  if (op.off()[0] > 0) return;
+  for_span(op.off(), n, base, min(base + len, held), lane,
+           [&](int64_t i, uint32_t pair, int64_t start) {
+             const bool mine = i < min(base + len, held);
+             const uint32_t m = mine ? op.keep(i, pair) : 0u;
+             const uint32_t c = (uint32_t)__builtin_popcount(m);
+             int64_t at = at0 + wave_excl3(c);
+             if (mine && i == start) op.spans.out_offset[pair] = at;
+#pragma unroll
+             for (int k = 0; k < 4; ++k)
+               if ((m >> k) & 1u) op.emit(i, pair, k, at++);
+             at0 += wave_sum3(c);
+           });
+}
+
+// One workgroup, after k_filter_emit: the offsets of the empty pairs (their next pair's that has an
+// entry) and of those whose entries lie beyond the ones held (the total), every pair's count, and
+// the call's last flag words (see k_scan).
+constexpr int kEndThreads = 1024;
+template <typename Op>
+__global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op, uint32_t n_spans) {
+  __shared__ uint64_t wsum[kEndThreads / kWave];
+  __shared__ uint32_t wmax[kEndThreads / kWave];
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  const uint32_t n = op.pairs();
+  const FilterSpans& F = op.spans;
+  uint32_t f_err = 0, f_max = 0;
+  if (threadIdx.x == 0) {
+    f_err = __hip_atomic_load(F.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    f_max = __hip_atomic_load(F.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
+  uint64_t sum = 0;
+  for (uint32_t k = threadIdx.x; k < n_spans; k += kEndThreads) sum += F.kept[k];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+  if (lane == 0) wsum[wv] = sum;
+  __syncthreads();
+  uint64_t total = 0;
+#pragma unroll
+  for (int k = 0; k < kEndThreads / kWave; ++k) total += wsum[k];
+  uint32_t mx = 0;
+  // the offset of the first kept item at or after entry i, the first of pair p or of a later one
+  auto offset_at = [&](int64_t i, uint32_t p) {
+    return i >= held ? (int64_t)total : F.out_offset[last_from(op.off(), p, n, i)];
+  };
+  for (uint32_t p = threadIdx.x; p < n; p += kEndThreads) {
+    const int64_t i0 = op.off()[p], i1 = op.off()[p + 1];
+    int64_t c = 0;
+    if (i0 < i1 && i0 < held) {
+      const int64_t o0 = F.out_offset[p];
+      const int64_t o1 = p + 1 == n ? (int64_t)total : offset_at(i1, p + 1);
+      c = o1 > o0 ? o1 - o0 : 0;
+    } else {
+      F.out_offset[p] = offset_at(i0, p);
+    }
+    F.out_count[p] = c;
+    mx = max(mx, (uint32_t)min(c, (int64_t)0xFFFFFFFFll));
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
+  if (lane == 0) wmax[wv] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t m = f_max;
+    for (int k = 0; k < kEndThreads / kWave; ++k) m = max(m, wmax[k]);
+    F.out_offset[n] = (int64_t)total;
+    F.host[kFlagErr] = f_err;
+    F.host[kFlagMax] = m;
+    F.host[kFlagTotal] = (uint32_t)total;
+    F.host[kFlagTotal + 1] = (uint32_t)(total >> 32);
+#pragma unroll
+    for (int k = 0; k < kFlagWords; ++k)
+      __hip_atomic_store(F.flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// ------------------------------------------------------------------------ hidden nodes
+// Each record's four cells. A record outside the range of the pair found (offsets out of order)
+// marks nothing. (One lane per record with a search of its own took 261 us for 6M records.)
 __global__ void __launch_bounds__(256) k_hidden_mark(HiddenArgs A) {
   const uint32_t lane = lane_id();
   const int64_t Q = n_parents(A.rec.depth);
   const uint32_t np = A.rec.n_pairs;
   if (np == 0u) return;
   const int64_t* off = A.rec.offset;
-  const int64_t total = min(max(off[np], (int64_t)0), A.rec.cap);  // the call's records held
-  if (off[0] > 0) return;                                           // not a CSR offset table
-  const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  for (int64_t base = (int64_t)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * kMarkSpan;
-       base < total; base += n_waves * kMarkSpan) {
-    uint32_t p = 0u;
-    bool first = true;
-    for (uint32_t j = 0; j < kMarkSpan / kWave; ++j) {
-      const int64_t r = base + (int64_t)j * kWave + lane;
-      if (r >= total) break;
-      if (first) {
-        p = last_at_most(off, 0u, np, r);
-        first = false;
-      } else {
-        // off[p] <= an earlier index < r: widen [p, hi) until off[hi] > r, then search it
-        uint32_t lo = p, step = 1u, hi = p + 1u;
-        while (hi < np && off[hi] <= r) {
-          lo = hi;
-          step = step < (1u << 30) ? 2u * step : step;
-          hi = np - lo > step ? lo + step : np;
-        }
-        p = last_at_most(off, lo, hi, r);
-      }
-      int64_t lo_r, hi_r;
-      pair_range(A.rec, p, &lo_r, &hi_r);
-      if (r < lo_r || r >= hi_r) continue;
-      const uint32_t info = A.rec.pair_info[2 * p];
-      const uint32_t g = info >> 1;
-      if ((info & 1u) != 0u || g >= A.n_genomes) continue;  // incoming pairs add no hidden node
-      const uint32_t P = A.rec.parent[r];
-      if ((int64_t)P >= Q) continue;
-      // grid positions 4P .. 4P+3; the many pairs of one genome mostly mark cells already marked,
-      // so a plain read first keeps them from queueing atomics on the same words
-      uint32_t* bits = A.fresh + (int64_t)g * A.words;
-      const uint32_t m = 0xFu << (4u * (P % 8u));
-      if ((__hip_atomic_load(bits + P / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
-        atomicOr(bits + P / 8u, m);
-    }
-  }
+  const int64_t held = min(max(off[np], (int64_t)0), A.rec.cap);  // the call's records held
+  if (off[0] > 0) return;                                          // not a CSR offset table
+  const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
+  const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
+  for_span(off, np, base, end, lane, [&](int64_t i, uint32_t p, int64_t start) {
+    if (i >= end || i < start || i >= start + A.rec.count[p]) return;
+    const uint32_t info = A.rec.pair_info[2 * p];
+    const uint32_t g = info >> 1;
+    if ((info & 1u) != 0u || g >= A.n_genomes) return;  // incoming pairs add no hidden node
+    const uint32_t P = A.rec.parent[i];
+    if ((int64_t)P >= Q) return;
+    // grid positions 4P .. 4P+3; the many pairs of one genome mostly mark cells already marked,
+    // so a plain read first keeps them from queueing atomics on the same words
+    uint32_t* bits = A.fresh + (int64_t)g * A.words;
+    const uint32_t m = 0xFu << (4u * (P % 8u));
+    if ((__hip_atomic_load(bits + P / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
+      atomicOr(bits + P / 8u, m);
+  });
 }
 
 // One workgroup per genome: its new cells (found now, not known before).
@@ -191,172 +335,111 @@ __device__ __forceinline__ uint32_t conn_type(float ax, float ay, float bx, floa
   return EMR_CONN_LATERAL;
 }
 
-// Bit k of the result: child k of record i is an expressed connection of its pair.
-__device__ __forceinline__ uint32_t expressed(const ExpressArgs& A, int64_t i, float sx, float sy,
-                                              bool incoming) {
-  const uint32_t P = A.rec.parent[i];
-  if ((int64_t)P >= n_parents(A.rec.depth)) return 0u;
-  const float4 w = reinterpret_cast<const float4*>(A.rec.w4)[i];
-  const float wk[4] = {w.x, w.y, w.z, w.w};
-  uint32_t m = 0;
+// The children of a pair's record that are expressed connections.
+struct ExpressOp : ExpressArgs {
+  __device__ const int64_t* off() const { return rec.offset; }
+  __device__ uint32_t pairs() const { return rec.n_pairs; }
+  __device__ int64_t cap() const { return rec.cap; }
+  __device__ uint32_t keep(int64_t i, uint32_t pair) const {
+    if (i >= rec.offset[pair] + rec.count[pair]) return 0u;
+    const uint32_t P = rec.parent[i];
+    if ((int64_t)P >= n_parents(rec.depth)) return 0u;
+    const bool incoming = (rec.pair_info[2 * pair] & 1u) != 0u;
+    const uint32_t j = rec.pair_info[2 * pair + 1];
+    const float sx = rec.src_xy[2 * j], sy = rec.src_xy[2 * j + 1];
+    const float4 w = reinterpret_cast<const float4*>(rec.w4)[i];
+    const float wk[4] = {w.x, w.y, w.z, w.w};
+    // Eq. 1: the four children are one aligned quad of their level
+    float x0, y0;
+    cell_centre(4u * P, &x0, &y0);
+    const float side = 2.0f * pow2_neg(level_of(4u * P));  // (exact: so are the centres)
+    uint32_t m = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    float cx, cy;
-    cell_centre(4u * P + (uint32_t)k, &cx, &cy);
-    const uint32_t t = incoming ? conn_type(cx, cy, sx, sy) : conn_type(sx, sy, cx, cy);
-    if ((t & A.type_mask) != 0u && __builtin_fabsf(wk[k]) > A.w_min) m |= 1u << k;
-  }
-  return m;
-}
-
-// Sum over the wave of a per-lane count c < 8 (bit-sliced ballots).
-__device__ __forceinline__ uint32_t wave_sum3(uint32_t c) {
-  uint32_t t = 0;
-#pragma unroll
-  for (int b = 0; b < 3; ++b) t += popc64(ballot((c >> b) & 1u)) << b;
-  return t;
-}
-__device__ __forceinline__ uint32_t wave_excl3(uint32_t c) {
-  uint32_t t = 0;
-#pragma unroll
-  for (int b = 0; b < 3; ++b) t += mbcnt64(ballot((c >> b) & 1u)) << b;
-  return t;
-}
-
-template <bool EMIT>
-__global__ void __launch_bounds__(256) k_express(ExpressArgs A) {
-  const uint32_t lane = lane_id();
-  FOR_EACH_PAIR_WAVE(pair, A.rec.n_pairs) {
-    const uint32_t info = A.rec.pair_info[2 * pair], j = A.rec.pair_info[2 * pair + 1];
-    const float sx = A.rec.src_xy[2 * j], sy = A.rec.src_xy[2 * j + 1];
-    int64_t lo, hi;
-    pair_range(A.rec, pair, &lo, &hi);
-    uint32_t total = 0;
-    const int64_t base = EMIT ? A.out_offset[pair] : 0;
-    for (int64_t b = lo; b < hi; b += kWave) {
-      const int64_t i = b + lane;
-      const uint32_t m = i < hi ? expressed(A, i, sx, sy, (info & 1u) != 0u) : 0u;
-      const uint32_t c = (uint32_t)__builtin_popcount(m);
-      if constexpr (EMIT) {
-        int64_t at = base + total + wave_excl3(c);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if ((m >> k) & 1u) {
-            if (at < A.cap) {
-              A.out_cell[at] = 4u * A.rec.parent[i] + 1u + (uint32_t)k;
-              A.out_w[at] = A.rec.w4[4 * i + k];
-            }
-            ++at;
-          }
-      }
-      total += wave_sum3(c);
+    for (int k = 0; k < 4; ++k) {
+      const float cx = (k & 1) ? x0 + side : x0, cy = (k & 2) ? y0 + side : y0;
+      const uint32_t t = incoming ? conn_type(cx, cy, sx, sy) : conn_type(sx, sy, cx, cy);
+      if ((t & type_mask) != 0u && __builtin_fabsf(wk[k]) > w_min) m |= 1u << k;
     }
-    if (!EMIT && lane == 0) A.totals[pair] = total;
+    return m;
   }
-}
+  __device__ void emit(int64_t i, uint32_t, int k, int64_t at) const {
+    if (at >= ExpressArgs::cap) return;
+    out_cell[at] = 4u * rec.parent[i] + 1u + (uint32_t)k;
+    out_w[at] = rec.w4[4 * i + k];
+  }
+};
 
 // ------------------------------------------------------------------------ band filter
-// Per pair (one wave): the connections with band > theta_band (strict; a NaN band never passes),
-// counted, then emitted in order at the pair's offset.
-template <bool EMIT>
-__global__ void __launch_bounds__(256) k_band_select(BandSelectArgs A) {
-  const uint32_t lane = lane_id();
-  FOR_EACH_PAIR_WAVE(pair, A.n_pairs) {
-    int64_t lo = A.in_offset[pair], hi = A.in_offset[pair + 1];
-    lo = lo < 0 ? 0 : (lo > A.in_cap ? A.in_cap : lo);
-    hi = hi > A.in_cap ? A.in_cap : (hi < lo ? lo : hi);
-    uint32_t total = 0;
-    const int64_t base = EMIT ? A.out_offset[pair] : 0;
-    for (int64_t b = lo; b < hi; b += kWave) {
-      const int64_t i = b + lane;
-      const bool keep = i < hi && A.band[i] > A.theta_band;
-      const uint64_t m = ballot(keep);
-      if constexpr (EMIT) {
-        const int64_t at = base + total + mbcnt64(m);
-        if (keep && at < A.out_cap) {
-          A.out_cell[at] = A.in_cell[i];
-          A.out_w[at] = A.in_w[i];
-        }
-      }
-      total += popc64(m);
-    }
-    if (!EMIT && lane == 0) A.totals[pair] = total;
+// The connections with band > theta_band (strict; a NaN band never passes), in order.
+struct BandOp : BandSelectArgs {
+  __device__ const int64_t* off() const { return in_offset; }
+  __device__ uint32_t pairs() const { return n_pairs; }
+  __device__ int64_t cap() const { return in_cap; }
+  __device__ uint32_t keep(int64_t i, uint32_t) const { return band[i] > theta_band ? 1u : 0u; }
+  __device__ void emit(int64_t i, uint32_t, int, int64_t at) const {
+    if (at >= out_cap) return;
+    out_cell[at] = in_cell[i];
+    out_w[at] = in_w[i];
   }
-}
+};
 
 // ------------------------------------------------------------------------ Eq. 2 chain rule
 __global__ void __launch_bounds__(256) k_chain_mark(ChainArgs A) {
   const uint32_t lane = lane_id();
   const int64_t Q = n_parents(A.rec.depth);
-  FOR_EACH_PAIR_WAVE(pair, A.rec.n_pairs) {
-    int64_t lo, hi;
-    pair_range(A.rec, pair, &lo, &hi);
-    uint32_t* bits = A.member + (int64_t)pair * A.qwords;
-    for (int64_t i = lo + lane; i < hi; i += kWave) {
-      const uint32_t P = A.rec.parent[i];
-      if ((int64_t)P < Q) atomicOr(bits + P / 32u, 1u << (P % 32u));
-    }
-  }
+  const uint32_t np = A.rec.n_pairs;
+  const int64_t* off = A.rec.offset;
+  const int64_t held = min(max(off[np], (int64_t)0), A.rec.cap);
+  if (off[0] > 0) return;
+  const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
+  const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
+  for_span(off, np, base, end, lane, [&](int64_t i, uint32_t p, int64_t start) {
+    if (i >= end || i < start || i >= start + A.rec.count[p]) return;
+    const uint32_t P = A.rec.parent[i];
+    if ((int64_t)P < Q) atomicOr(A.member + (int64_t)p * A.qwords + P / 32u, 1u << (P % 32u));
+  });
 }
 
-// Record i of a pair (member: the pair's bitmap) passes when every ancestor of its cell is a
-// record of the pair (the root is its own ancestor line's start).
-__device__ __forceinline__ bool chain_kept(const ChainArgs& A, const uint32_t* member, int64_t i) {
-  uint32_t P = A.rec.parent[i];
-  if ((int64_t)P >= n_parents(A.rec.depth)) return false;
-  bool ok = true;
-  while (P > 0u) {
-    P = (P - 1u) / 4u;
-    ok = ok && ((member[P / 32u] >> (P % 32u)) & 1u) != 0u;
-  }
-  return ok;
-}
-
-template <bool EMIT>
-__global__ void __launch_bounds__(256) k_chain(ChainArgs A) {
-  const uint32_t lane = lane_id();
-  FOR_EACH_PAIR_WAVE(pair, A.rec.n_pairs) {
-    int64_t lo, hi;
-    pair_range(A.rec, pair, &lo, &hi);
-    const uint32_t* member = A.member + (int64_t)pair * A.qwords;
-    uint32_t total = 0;
-    const int64_t base = EMIT ? A.out_offset[pair] : 0;
-    for (int64_t b = lo; b < hi; b += kWave) {
-      const int64_t i = b + lane;
-      const bool keep = i < hi && chain_kept(A, member, i);
-      const uint64_t kb = ballot(keep);
-      if constexpr (EMIT) {
-        const int64_t at = base + total + mbcnt64(kb);
-        if (keep && at < A.cap) {
-          A.out_parent[at] = A.rec.parent[i];
-          reinterpret_cast<float4*>(A.out_w4)[at] = reinterpret_cast<const float4*>(A.rec.w4)[i];
-        }
-      }
-      total += popc64(kb);
+// A pair's record (its members: the pair's bitmap) stays when every ancestor of its cell is a record
+// of the pair (the root is its own ancestor line's start).
+struct ChainOp : ChainArgs {
+  __device__ const int64_t* off() const { return rec.offset; }
+  __device__ uint32_t pairs() const { return rec.n_pairs; }
+  __device__ int64_t cap() const { return rec.cap; }
+  __device__ uint32_t keep(int64_t i, uint32_t pair) const {
+    if (i >= rec.offset[pair] + rec.count[pair]) return 0u;
+    uint32_t P = rec.parent[i];
+    if ((int64_t)P >= n_parents(rec.depth)) return 0u;
+    const uint32_t* bits = member + (int64_t)pair * qwords;
+    while (P > 0u) {
+      P = (P - 1u) / 4u;
+      if (((bits[P / 32u] >> (P % 32u)) & 1u) == 0u) return 0u;
     }
-    if (!EMIT && lane == 0) A.totals[pair] = total;
+    return 1u;
   }
-}
+  __device__ void emit(int64_t i, uint32_t, int, int64_t at) const {
+    if (at >= ChainArgs::cap) return;
+    out_parent[at] = rec.parent[i];
+    reinterpret_cast<float4*>(out_w4)[at] = reinterpret_cast<const float4*>(rec.w4)[i];
+  }
+};
 
 }  // namespace emr
 
 // ------------------------------------------------------------------------ launchers
-static uint32_t wave_blocks(uint32_t n) {  // workgroups of 4 waves, one wave per item (capped)
-  uint32_t b = (n + 3) / 4;
-  return b == 0 ? 1 : (b > 8192 ? 8192 : b);
+// Workgroups of 4 waves, one span each, for at most `cap` entries (the entries are counted on the
+// device: spans beyond them do nothing).
+static uint32_t span_blocks(int64_t cap) {
+  const int64_t steps = (cap + emr::kWave - 1) / emr::kWave;
+  return (uint32_t)((std::min<int64_t>(std::max<int64_t>(steps, 1), emr::kFilterSpans) + 3) / 4);
 }
 
 extern "C" hipError_t emr_launch_hidden(const emr::HiddenArgs* A, int step, hipStream_t s) {
   const uint32_t gb = A->n_genomes == 0 ? 1 : (A->n_genomes > 65535 ? 65535 : A->n_genomes);
   switch (step) {
-    case 0: {
-      // waves of kMarkSpan records over the records the buffers can hold (the waves loop when
-      // there are more)
-      const int64_t spans = (A->rec.cap + emr::kMarkSpan - 1) / emr::kMarkSpan;
-      const uint32_t blocks = (uint32_t)std::min<int64_t>(std::max<int64_t>((spans + 3) / 4, 1), 2048);
-      hipLaunchKernelGGL(emr::k_hidden_mark, dim3(blocks), dim3(256), 0, s, *A);
+    case 0:
+      hipLaunchKernelGGL(emr::k_hidden_mark, dim3(span_blocks(A->rec.cap)), dim3(256), 0, s, *A);
       break;
-    }
     case 1: hipLaunchKernelGGL(emr::k_hidden_count, dim3(gb), dim3(256), 0, s, *A); break;
     case 2: hipLaunchKernelGGL(emr::k_hidden_emit, dim3(gb), dim3(256), 0, s, *A); break;
     default: return hipErrorInvalidValue;
@@ -364,30 +447,28 @@ extern "C" hipError_t emr_launch_hidden(const emr::HiddenArgs* A, int step, hipS
   return hipGetLastError();
 }
 
-extern "C" hipError_t emr_launch_express(const emr::ExpressArgs* A, int emit, hipStream_t s) {
-  if (emit)
-    hipLaunchKernelGGL(emr::k_express<true>, dim3(wave_blocks(A->rec.n_pairs)), dim3(256), 0, s, *A);
-  else
-    hipLaunchKernelGGL(emr::k_express<false>, dim3(wave_blocks(A->rec.n_pairs)), dim3(256), 0, s, *A);
+namespace {
+template <typename Op>
+hipError_t launch_filter(const Op& op, int64_t cap, hipStream_t s) {
+  const uint32_t blocks = span_blocks(cap);
+  hipLaunchKernelGGL(emr::k_filter_count<Op>, dim3(blocks), dim3(256), 0, s, op);
+  hipLaunchKernelGGL(emr::k_filter_emit<Op>, dim3(blocks), dim3(256), 0, s, op);
+  hipLaunchKernelGGL(emr::k_filter_end<Op>, dim3(1), dim3(emr::kEndThreads), 0, s, op, 4 * blocks);
   return hipGetLastError();
 }
+}  // namespace
 
-extern "C" hipError_t emr_launch_band_select(const emr::BandSelectArgs* A, int emit,
-                                              hipStream_t s) {
-  if (emit)
-    hipLaunchKernelGGL(emr::k_band_select<true>, dim3(wave_blocks(A->n_pairs)), dim3(256), 0, s, *A);
-  else
-    hipLaunchKernelGGL(emr::k_band_select<false>, dim3(wave_blocks(A->n_pairs)), dim3(256), 0, s, *A);
-  return hipGetLastError();
+// The filters over at least one pair.
+extern "C" hipError_t emr_launch_express(const emr::ExpressArgs* A, hipStream_t s) {
+  return launch_filter(emr::ExpressOp{*A}, A->rec.cap, s);
 }
 
-extern "C" hipError_t emr_launch_chain(const emr::ChainArgs* A, int step, hipStream_t s) {
-  const dim3 grid(wave_blocks(A->rec.n_pairs));
-  switch (step) {
-    case 0: hipLaunchKernelGGL(emr::k_chain_mark, grid, dim3(256), 0, s, *A); break;
-    case 1: hipLaunchKernelGGL(emr::k_chain<false>, grid, dim3(256), 0, s, *A); break;
-    case 2: hipLaunchKernelGGL(emr::k_chain<true>, grid, dim3(256), 0, s, *A); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+extern "C" hipError_t emr_launch_band_select(const emr::BandSelectArgs* A, hipStream_t s) {
+  return launch_filter(emr::BandOp{*A}, A->in_cap, s);
+}
+
+extern "C" hipError_t emr_launch_chain(const emr::ChainArgs* A, hipStream_t s) {
+  hipLaunchKernelGGL(emr::k_chain_mark, dim3(span_blocks(A->rec.cap)), dim3(256), 0, s, *A);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_filter(emr::ChainOp{*A}, A->rec.cap, s);
 }

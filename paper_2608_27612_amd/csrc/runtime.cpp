@@ -36,11 +36,10 @@ extern "C" hipError_t emr_launch_compact(const emr::ScanArgs* S, const emr::Move
 extern "C" hipError_t emr_launch_finalize(uint32_t* flags, uint32_t* host, hipStream_t s);
 extern "C" hipError_t emr_launch_scan(const emr::ScanArgs* S, hipStream_t s);
 extern "C" hipError_t emr_launch_hidden(const emr::HiddenArgs* A, int step, hipStream_t s);
-extern "C" hipError_t emr_launch_express(const emr::ExpressArgs* A, int emit, hipStream_t s);
-extern "C" hipError_t emr_launch_chain(const emr::ChainArgs* A, int step, hipStream_t s);
+extern "C" hipError_t emr_launch_express(const emr::ExpressArgs* A, hipStream_t s);
+extern "C" hipError_t emr_launch_chain(const emr::ChainArgs* A, hipStream_t s);
 extern "C" hipError_t emr_launch_band(const emr::BandArgs* A, hipStream_t s);
-extern "C" hipError_t emr_launch_band_select(const emr::BandSelectArgs* A, int emit,
-                                              hipStream_t s);
+extern "C" hipError_t emr_launch_band_select(const emr::BandSelectArgs* A, hipStream_t s);
 extern "C" hipError_t emr_launch_tile_geo(uint32_t* out, uint32_t tiles, uint32_t rows,
                                           hipStream_t s);
 extern "C" hipError_t emr_noalloc_scratch(void** out);
@@ -2040,8 +2039,9 @@ emr_status check_workspace(const void* ws, int64_t bytes, int64_t need) {
 
 int64_t cell_words(int32_t depth) { return (emr::n_positions(depth) + 31) / 32; }
 
-// Workspace layouts: hidden nodes (fresh bitmap, per-genome totals and counts), expression (per-pair
-// totals), chain (membership bitmap, per-pair totals).
+// Workspace layouts: hidden nodes (fresh bitmap, per-genome totals and counts), expression and the
+// band filter (the spans' kept counts), chain (membership bitmap, the spans' kept counts).
+constexpr size_t kFilterBytes = emr::kFilterSpans * 4;
 struct HiddenLayout {
   size_t fresh = 0, totals = 0, counts = 0, bytes = 0;
   HiddenLayout(int64_t G, int32_t depth) {
@@ -2052,24 +2052,30 @@ struct HiddenLayout {
   }
 };
 struct ChainLayout {
-  size_t member = 0, totals = 0, bytes = 0;
+  size_t member = 0, spans = 0, bytes = 0;
   int64_t qwords = 0;
   ChainLayout(int64_t n_pairs, int32_t depth) {
     qwords = (emr::n_parents(depth) + 31) / 32;
-    totals = align256((size_t)n_pairs * (size_t)qwords * 4);
-    bytes = align256(totals + (size_t)n_pairs * 4);
+    spans = align256((size_t)n_pairs * (size_t)qwords * 4);
+    bytes = align256(spans + kFilterBytes);
   }
 };
 
-// The offsets of a phase-2 output (k_scan over per-pair or per-genome totals), which also hands the
-// call's flags over.
+// The output of a filter over no pairs: offset 0, and the flags handed over.
+emr_status no_pairs(int64_t* offsets, const CallFlags& f, hipStream_t s) {
+  HIP_OR_FAIL(emr_launch_fill(offsets, 2, 0u, s));
+  HIP_OR_FAIL(emr_launch_finalize(f.dev, f.host_dev, s));
+  return EMR_OK;
+}
+emr::FilterSpans filter_spans(void* kept, int64_t* offsets, int64_t* counts, const CallFlags& f) {
+  return emr::FilterSpans{(uint32_t*)kept, offsets, counts, f.dev, f.host_dev};
+}
+
+// The offsets of the hidden nodes (k_scan over per-genome totals), which also hands the call's
+// flags over.
 emr_status scan_totals(uint32_t* totals, int64_t* counts, int64_t* offsets, int64_t n,
                        const CallFlags& f, hipStream_t s) {
-  if (n == 0) {
-    HIP_OR_FAIL(emr_launch_fill(offsets, 2, 0u, s));
-    HIP_OR_FAIL(emr_launch_finalize(f.dev, f.host_dev, s));
-    return EMR_OK;
-  }
+  if (n == 0) return no_pairs(offsets, f, s);
   emr::ScanArgs S{};
   S.pair_total = totals;
   S.pair_count = counts;
@@ -2149,7 +2155,7 @@ emr_status emr_hidden_sources(const emr_population* pop, const emr_source* sourc
 
 emr_status emr_express_workspace_bytes(int64_t n_pairs, int64_t* bytes) {
   if (n_pairs < 0 || !bytes) return fail(EMR_E_INVAL, "bad arguments");
-  *bytes = (int64_t)align256((size_t)n_pairs * 4);
+  *bytes = (int64_t)kFilterBytes;
   return EMR_OK;
 }
 
@@ -2169,8 +2175,7 @@ emr_status emr_express(const emr_population* pop, const emr_source* sources, int
   if (out->capacity < 0 || !out->pair_offset || (P.n_pairs > 0 && !out->pair_count) ||
       (out->capacity > 0 && (!out->cell || !out->w)))
     return fail(EMR_E_INVAL, "bad connection output buffers");
-  if ((st = check_workspace(out->workspace, out->workspace_bytes,
-                            (int64_t)align256((size_t)P.n_pairs * 4))) != EMR_OK)
+  if ((st = check_workspace(out->workspace, out->workspace_bytes, (int64_t)kFilterBytes)) != EMR_OK)
     return st;
   const hipStream_t s = (hipStream_t)stream;
   CallFlags f;
@@ -2183,15 +2188,14 @@ emr_status emr_express(const emr_population* pop, const emr_source* sources, int
   A.rec = R;
   A.type_mask = (uint32_t)type_mask;
   A.w_min = w_min;
-  A.totals = (uint32_t*)out->workspace;
-  A.out_offset = out->pair_offset;
+  A.spans = filter_spans(out->workspace, out->pair_offset, out->pair_count, f);
   A.out_cell = out->cell;
   A.out_w = out->w;
   A.cap = out->capacity;
-  if (P.n_pairs > 0) HIP_OR_FAIL(emr_launch_express(&A, 0, s));
-  if ((st = scan_totals(A.totals, out->pair_count, out->pair_offset, P.n_pairs, f, s)) != EMR_OK)
+  if (P.n_pairs > 0)
+    HIP_OR_FAIL(emr_launch_express(&A, s));
+  else if ((st = no_pairs(out->pair_offset, f, s)) != EMR_OK)
     return st;
-  if (P.n_pairs > 0) HIP_OR_FAIL(emr_launch_express(&A, 1, s));
   f.ok = true;
   return EMR_OK;
 }
@@ -2271,8 +2275,7 @@ emr_status emr_band_filter(const emr_connections* in, const float* band, int64_t
   if (out->capacity < 0 || !out->pair_offset || (n_pairs > 0 && !out->pair_count) ||
       (out->capacity > 0 && (!out->cell || !out->w)))
     return fail(EMR_E_INVAL, "bad output connections");
-  emr_status st = check_workspace(out->workspace, out->workspace_bytes,
-                                  (int64_t)align256((size_t)n_pairs * 4));
+  emr_status st = check_workspace(out->workspace, out->workspace_bytes, (int64_t)kFilterBytes);
   if (st != EMR_OK) return st;
   const hipStream_t s = (hipStream_t)stream;
   CallFlags f;
@@ -2284,16 +2287,15 @@ emr_status emr_band_filter(const emr_connections* in, const float* band, int64_t
   A.band = band;
   A.in_cap = in->capacity;
   A.theta_band = theta_band;
-  A.totals = (uint32_t*)out->workspace;
-  A.out_offset = out->pair_offset;
+  A.spans = filter_spans(out->workspace, out->pair_offset, out->pair_count, f);
   A.out_cell = out->cell;
   A.out_w = out->w;
   A.out_cap = out->capacity;
   A.n_pairs = (uint32_t)n_pairs;
-  if (n_pairs > 0) HIP_OR_FAIL(emr_launch_band_select(&A, 0, s));
-  if ((st = scan_totals(A.totals, out->pair_count, out->pair_offset, n_pairs, f, s)) != EMR_OK)
+  if (n_pairs > 0)
+    HIP_OR_FAIL(emr_launch_band_select(&A, s));
+  else if ((st = no_pairs(out->pair_offset, f, s)) != EMR_OK)
     return st;
-  if (n_pairs > 0) HIP_OR_FAIL(emr_launch_band_select(&A, 1, s));
   f.ok = true;
   return EMR_OK;
 }
@@ -2325,19 +2327,16 @@ emr_status emr_chain_filter(const emr_result* rec, int64_t n_pairs, int32_t dept
   A.rec = R;
   A.member = (uint32_t*)(ws + L.member);
   A.qwords = L.qwords;
-  A.totals = (uint32_t*)(ws + L.totals);
-  A.out_offset = out->pair_offset;
+  A.spans = filter_spans(ws + L.spans, out->pair_offset, out->pair_count, f);
   A.out_parent = out->parent;
   A.out_w4 = out->w4;
   A.cap = out->capacity;
   if (n_pairs > 0) {
     HIP_OR_FAIL(emr_launch_fill(A.member, n_pairs * L.qwords, 0u, s));
-    HIP_OR_FAIL(emr_launch_chain(&A, 0, s));
-    HIP_OR_FAIL(emr_launch_chain(&A, 1, s));
-  }
-  if ((st = scan_totals(A.totals, out->pair_count, out->pair_offset, n_pairs, f, s)) != EMR_OK)
+    HIP_OR_FAIL(emr_launch_chain(&A, s));
+  } else if ((st = no_pairs(out->pair_offset, f, s)) != EMR_OK) {
     return st;
-  if (n_pairs > 0) HIP_OR_FAIL(emr_launch_chain(&A, 2, s));
+  }
   f.ok = true;
   return EMR_OK;
 }

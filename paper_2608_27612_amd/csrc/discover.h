@@ -4,7 +4,7 @@
 // once (Section 3.1, the batched query W), reduces the four siblings to their variance in
 // registers, applies var > theta (Section 3.2, Eq. 2), and writes the kept cells to a record pool
 // (one reservation per walk that keeps any), leaving each tile's pool offset and count in its
-// status word and each chunk's counts in its pairs' totals; k_scan and k_move then place every
+// status word and each chunk's counts in its pairs' totals; k_compact then places every
 // pair's records contiguously in ascending parent order.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -181,7 +181,7 @@ struct DiscoverScalars {
   float theta16;  // 16 theta
   uint32_t code_bytes;  // compiled tier: size of the code area (0 for the interpreter)
   // Records over more than 2 groups of 64 tiles: bit g % 64 of nz[pair * nz_words + g / 64]
-  // marks a group g of the range that kept a cell (k_move visits only those).
+  // marks a group g of the range that kept a cell (k_compact visits only those).
   uint64_t* nz;
   uint32_t nz_words;
   uint32_t blob_words, n_pairs;
@@ -215,7 +215,7 @@ constexpr uint32_t kListLds = 2048;  // the longest list: a discover workgroup h
 
 // Output modes: raw CPPN outputs; records of kept cells, each walk's reserved in a pool with one
 // atomic, each tile's pool offset and count left in its status word and each chunk's count added
-// to its pair's total, for k_scan (pair offsets) and k_move (per-pair contiguous lists).
+// to its pair's total, for k_compact (pair offsets and per-pair contiguous lists).
 constexpr int kModeRaw = 0, kModeRecords = 1;
 
 // A tile's status word in record mode: its records' pool offset << 8 | their count (<= 64).
@@ -275,9 +275,18 @@ constexpr uint32_t kChunkTilesMax = 16;
 // nz_words(tiles) words of marks per pair, one bit per group.
 constexpr uint32_t kNzMinGroups = 2;
 // Ranges of at most this many pairs compact in one kernel (k_compact): each of its workgroups sums
-// the totals of the pairs before its own, which for more pairs would read more than k_scan's
-// launch costs (at 16384 pairs 16 reads per thread).
+// the totals of the pairs before its own (at 16384 pairs 16 reads per thread). More pairs take a
+// kernel before it that sums buckets of kBucketPairs pairs.
 constexpr uint32_t kCompactPairs = 16384;
+constexpr uint32_t kBucketPairs = 1024;
+struct PairBucket {
+  uint64_t sum;
+  uint32_t largest;
+  uint32_t pad;
+};
+inline constexpr uint64_t n_buckets(uint64_t n_pairs) {
+  return n_pairs <= kCompactPairs ? 0 : (n_pairs + kBucketPairs - 1) / kBucketPairs;
+}
 EMR_HD constexpr uint32_t nz_words(uint32_t tiles) { return ((tiles + 63u) / 64u + 63u) / 64u; }
 // Rows of zeros after the last tile of the tile geometry table: a walk of TPW <= 4 tiles loads
 // the next walk's TPW rows, up to 2 TPW - 1 rows past its first tile, with no bound per load.
@@ -316,16 +325,17 @@ struct DiscoverArgs {
   uint32_t sched_stride, sched_lists;
 };
 
-// Arguments of the compaction of one record-mode range: k_scan (the pairs' offsets, one
-// workgroup) then k_move (one wave per pair).
+// Arguments of the compaction of one record-mode range (k_compact: ScanArgs for the offsets,
+// MoveArgs for the records; a wave per pair) and of k_scan (offsets of a call's genomes).
 struct ScanArgs {
   uint32_t* pair_total;  // [n_pairs] per-pair totals of the range (cleared by k_scan after use)
   uint32_t* clear_total; // k_compact: [n_pairs] the previous call's totals, cleared for the next
+  PairBucket* buckets;   // k_compact: [n_buckets(n_pairs)]
   int64_t* pair_count;   // [n_pairs] out
   int64_t* pair_offset;  // [n_pairs + 1] out
   uint32_t* flags;       // the call's flag words (kFlag*)
-  uint32_t* host;        // non-NULL: the call's pinned flag words (device view); k_scan then
-                         // hands the flags over and clears them (the call's last flag writer)
+  uint32_t* host;        // non-NULL: the call's pinned flag words (device view); the kernel
+                         // then hands the flags over and clears them (the call's last flag writer)
   int64_t* host_counts;  // non-NULL: pinned words (device view) that also get the counts, and at
                          // [n_pairs] the call's error bits (a streamed chunk's check before its
                          // delivery)
@@ -337,8 +347,6 @@ struct MoveArgs {
   const float* pool_w4;
   uint32_t* parent;
   float* w4;
-  const int64_t* pair_count;
-  const int64_t* pair_offset;
   uint64_t* nz;
   const uint8_t* skip;   // per pair: 1 = its groups were left out of the launch (no records)
   int64_t cap;
@@ -375,11 +383,13 @@ struct HiddenArgs {
 // The filters over CSR entries (connections of records, band selection, the chain rule) run as
 // spans of consecutive entries, one wave each, whatever pairs they belong to: kFilterSpans spans
 // at most, of a multiple of 64 entries. The first kernel leaves each span's kept entries, the
-// second sums the spans before its own and writes the output and the pairs' offsets, the third
-// (one workgroup) the counts, the total and the flags.
+// second sums the spans before its own and writes the output and the pairs' offsets, the third the
+// counts and the flags.
 constexpr uint32_t kFilterSpans = 8192;
+constexpr uint32_t kFilterWords = kFilterSpans + 4;
 struct FilterSpans {
-  uint32_t* kept;       // [kFilterSpans] (workspace)
+  uint32_t* kept;       // [kFilterWords] (workspace): each span's kept entries, then the count of
+                        // k_filter_end's finished workgroups, padding, and the total (u64)
   int64_t* out_offset;  // [n_pairs + 1]
   int64_t* out_count;   // [n_pairs]
   uint32_t* flags;      // the call's flag words and their pinned copy

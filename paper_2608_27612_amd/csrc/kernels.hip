@@ -10,10 +10,12 @@
 //               in registers, applies var > theta (Section 3.2, Eq. 2), and writes the kept cells
 //               to a record pool (one reservation per walk), each tile's pool offset and count to
 //               its status word.
-//   k_scan      one workgroup: the pairs' output offsets (exclusive scan of their totals), the
-//               call's total and largest count, and the hand-over of the call's flags.
-//   k_move      one wave per pair: gathers its records from the pool into its place in the
-//               call's output (pairs back to back, CSR), in ascending parent order.
+//   k_compact   one wave per pair: the pair's output offset (from the totals of the pairs before
+//               it, in buckets by k_buckets when they are many), its records gathered from the
+//               pool into their place in the call's output (pairs back to back, CSR) in ascending
+//               parent order; the last workgroup hands over the call's total, largest count and
+//               flags.
+//   k_scan      one workgroup: the offsets of a call's genomes (exclusive scan of their totals).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -65,9 +67,9 @@ __device__ __forceinline__ float act_apply(uint32_t a, float z) {
 
 // ------------------------------------------------------------------------ compaction
 // After a record-mode discover launch every tile of the range has left its status word (pool
-// offset << 8 | count) and every pair its total. k_scan turns the totals into output offsets
-// (pairs back to back in pair order: CSR), k_move gathers each pair's records from the pool to its
-// offset (k_compact does both for the usual numbers of pairs): tiles in increasing order, each tile's records in increasing lane (parent) order, so
+// offset << 8 | count) and every pair its total. k_compact turns the totals into output offsets
+// (pairs back to back in pair order: CSR) and gathers each pair's records from the pool to its
+// offset: tiles in increasing order, each tile's records in increasing lane (parent) order, so
 // each pair's records come out in ascending parent order. Records whose pool or output index is
 // beyond `cap`, or beyond their pair's count, are not moved (an overflowing call reports its
 // total, which exceeds the capacity; a pair whose tiles were skipped after a table error gets no
@@ -88,18 +90,17 @@ __device__ __forceinline__ void hand_over_flags(uint32_t* flags, uint32_t* host)
     __hip_atomic_store(flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The call's last kernel when k_scan does not hand over its flags (raw outputs, streamed calls).
+// The call's last kernel when k_compact does not hand over its flags (raw outputs, streamed calls).
 __global__ void k_finalize(uint32_t* flags, uint32_t* host) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   hand_over_flags(flags, host);
 }
 
 constexpr int kScanThreads = 1024;
-// Consecutive pairs per thread and round: a round costs a trip to memory and two barriers (4 us),
-// so long tables take 16 (40,000 pairs: 41 us at 4); short ones keep to few registers and stores.
-constexpr int kScanPerShort = 4, kScanPerLong = 16;
+constexpr int kScanPer = 4;  // consecutive entries per thread and round
 
-// One workgroup: pairs in rounds of kScanThreads * kScanPer, thread t taking the kScanPer pairs
+// One workgroup, for the tables of a call's genomes: entries in rounds of kScanThreads * kScanPer,
+// thread t taking the kScanPer
 // from round + kScanPer t (their loads issued together). Writes pair_count, pair_offset
 // (exclusive scan, pair_offset[n_pairs] = the total), clears the totals for the next launch,
 // resets the pool counter, raises the largest count and stores the total in the flags, and, with
@@ -107,7 +108,6 @@ constexpr int kScanPerShort = 4, kScanPerLong = 16;
 // call's kernels are ordered on its stream and this is the only writer of the largest count), so
 // thread 0 reads the words it needs together with the first round's totals and writes the final
 // values without reading them again: the kernel waits for memory once before its stores.
-template <int kScanPer>
 __global__ void __launch_bounds__(kScanThreads) k_scan(ScanArgs A) {
   __shared__ uint64_t wsum[kScanThreads / kWave];
   __shared__ uint32_t wmax[kScanThreads / kWave];
@@ -309,44 +309,51 @@ __device__ __forceinline__ void move_long(const MoveArgs& A, uint32_t pair, int6
   });
 }
 
-// Each wave takes pairs wave, wave + n_waves, ...: the pair's count and offset from k_scan, then
-// its tiles' records.
 constexpr int kMoveWaves = 4;
 
-__global__ void __launch_bounds__(kMoveWaves * kWave) k_move(MoveArgs A) {
-  const uint32_t lane = lane_id();
-  const uint32_t n_waves = gridDim.x * kMoveWaves;
-  const uint32_t n_groups = (A.tiles + kWave - 1) / kWave;
-  const uint32_t first = __builtin_amdgcn_readfirstlane(blockIdx.x * kMoveWaves + threadIdx.x / kWave);
-  // A pair's loads are issued together, before any of them is used: its skip mark (read from a
-  // valid stand-in address when the call skips no pair), count and offset, and for a short range
-  // its status words (read even when the pair has no records: they lie inside the status table).
-  for (uint32_t pair = first; pair < A.n_pairs; pair += n_waves) {
-    const uint64_t* row = A.status + (int64_t)pair * A.tiles;
-    const uint8_t sv = *(A.skip != nullptr ? A.skip + pair : (const uint8_t*)(A.pair_count + pair));
-    const int64_t count64 = A.pair_count[pair];
-    const int64_t base = A.pair_offset[pair];
-    uint64_t w0 = 0ull, w1 = 0ull;
-    if (n_groups <= kNzMinGroups) {
-      w0 = lane < A.tiles ? row[lane] : 0ull;
-      w1 = kWave + lane < A.tiles ? row[kWave + lane] : 0ull;
+// The sum and the largest of each bucket of kBucketPairs totals (a workgroup each, 4 per thread).
+__global__ void __launch_bounds__(kBucketPairs / 4) k_buckets(ScanArgs S) {
+  __shared__ uint64_t wsum[kBucketPairs / 4 / kWave];
+  __shared__ uint32_t wmax[kBucketPairs / 4 / kWave];
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  const uint32_t i = blockIdx.x * kBucketPairs + 4 * threadIdx.x;
+  uint32_t c[4] = {0u, 0u, 0u, 0u};
+  if (i + 4 <= S.n_pairs) {
+    const uint4 v = *reinterpret_cast<const uint4*>(S.pair_total + i);
+    c[0] = v.x, c[1] = v.y, c[2] = v.z, c[3] = v.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k < S.n_pairs) c[k] = S.pair_total[i + k];
+  }
+  uint64_t sum = (uint64_t)c[0] + c[1] + c[2] + c[3];
+  uint32_t mx = max(max(c[0], c[1]), max(c[2], c[3]));
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    sum += __shfl_xor(sum, off, kWave);
+    mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, kWave));
+  }
+  if (lane == 0) {
+    wsum[wv] = sum;
+    wmax[wv] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    PairBucket b{0ull, 0u, 0u};
+    for (uint32_t k = 0; k < kBucketPairs / 4 / kWave; ++k) {
+      b.sum += wsum[k];
+      b.largest = max(b.largest, wmax[k]);
     }
-    // (the count and offset are used before the skip test, so that their loads go out with the
-    // mark's instead of after the branch)
-    asm volatile("" ::"v"(count64), "v"(base));
-    if (A.skip != nullptr && sv != 0) continue;  // no records, no marks
-    const uint32_t count = (uint32_t)min(count64, (int64_t)0xFFFFFFFFll);
-    if (n_groups > kNzMinGroups)
-      move_long(A, pair, base, count, lane);
-    else if (count != 0u)
-      move_short(A, w0, w1, base, count, lane);
+    S.buckets[blockIdx.x] = b;
   }
 }
 
-// Both at once, for at most kCompactPairs pairs: every workgroup (4 pairs, one wave each) sums the
-// totals of the pairs before its own (at most 16 loads of 16 bytes per thread, from L2, in flight
-// together with its pairs' status words), so no kernel has to run before it; the last workgroup
-// has then seen every total and does what k_scan does at its end. The totals stay as they are
+// The offsets and the move at once: every workgroup (4 pairs, one wave each) sums the totals of the
+// pairs before its own (at most 16 loads of 16 bytes per thread, from L2, in flight together with
+// its pairs' status words), so for at most kCompactPairs pairs no kernel has to run before it; with
+// more, it sums the buckets before its own and the totals inside its bucket (40,000 pairs: k_scan,
+// one workgroup, took 41 us). The last workgroup has then seen every total and does what k_scan
+// does at its end. The totals stay as they are
 // while other workgroups still read them: the call's other set, which the previous call used, is
 // cleared for the next one instead. (4000 pairs, one of them with 4700 records: k_scan and k_move
 // 6.2 + 43 us and a gap between the launches, this kernel with the tile-by-tile move 16 us.)
@@ -381,8 +388,17 @@ __global__ void __launch_bounds__(kMoveWaves * kWave) k_compact(ScanArgs S, Move
     own[k] = pair0 + k < S.n_pairs ? S.pair_total[pair0 + k] : 0u;
   uint64_t sum = 0;
   uint32_t mx = 0;
+  uint32_t from = 0u;  // the first workgroup whose pairs are summed one by one
+  if (n_buckets(S.n_pairs) != 0) {
+    const uint32_t mine_b = pair0 / kBucketPairs;
+    for (uint32_t i = t; i < mine_b; i += kMoveWaves * kWave) {
+      sum += S.buckets[i].sum;
+      mx = max(mx, S.buckets[i].largest);
+    }
+    from = mine_b * (kBucketPairs / kMoveWaves);
+  }
   const uint4* before = reinterpret_cast<const uint4*>(S.pair_total);  // 4 pairs per workgroup
-  for (uint32_t i = t; i < blockIdx.x; i += kMoveWaves * kWave) {
+  for (uint32_t i = from + t; i < blockIdx.x; i += kMoveWaves * kWave) {
     const uint4 v = before[i];
     sum += (uint64_t)v.x + v.y + v.z + v.w;
     mx = max(max(mx, max(v.x, v.y)), max(v.z, v.w));
@@ -810,10 +826,7 @@ extern "C" hipError_t emr_launch_discover(const emr::DiscoverArgs* a, int mode, 
 
 // Offsets of a CSR output from per-pair (or per-genome) totals, one workgroup.
 extern "C" hipError_t emr_launch_scan(const emr::ScanArgs* S, hipStream_t s) {
-  if (S->n_pairs > (uint32_t)(emr::kScanThreads * emr::kScanPerShort))
-    hipLaunchKernelGGL(emr::k_scan<emr::kScanPerLong>, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
-  else
-    hipLaunchKernelGGL(emr::k_scan<emr::kScanPerShort>, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
+  hipLaunchKernelGGL(emr::k_scan, dim3(1), dim3(emr::kScanThreads), 0, s, *S);
   return hipGetLastError();
 }
 
@@ -822,19 +835,15 @@ extern "C" hipError_t emr_launch_scan(const emr::ScanArgs* S, hipStream_t s) {
 extern "C" hipError_t emr_launch_compact(const emr::ScanArgs* S, const emr::MoveArgs* M,
                                          hipStream_t s) {
   if (S->n_pairs == 0) return hipSuccess;
-  uint32_t blocks = (M->n_pairs + emr::kMoveWaves - 1) / emr::kMoveWaves;
-  if (S->n_pairs <= emr::kCompactPairs) {
-    if (S->n_pairs != M->n_pairs || !S->clear_total || S->clear_total == S->pair_total ||
-        (((uintptr_t)S->pair_total | (uintptr_t)S->clear_total) & 15) != 0)
-      return hipErrorInvalidValue;
-    hipLaunchKernelGGL(emr::k_compact, dim3(blocks), dim3(emr::kMoveWaves * emr::kWave), 0, s, *S,
-                       *M);
-    return hipGetLastError();
-  }
-  const hipError_t e = emr_launch_scan(S, s);
-  if (e != hipSuccess) return e;
-  if (blocks > 8192) blocks = 8192;  // waves loop over pairs beyond this
-  hipLaunchKernelGGL(emr::k_move, dim3(blocks), dim3(emr::kMoveWaves * emr::kWave), 0, s, *M);
+  const uint32_t blocks = (M->n_pairs + emr::kMoveWaves - 1) / emr::kMoveWaves;
+  const uint32_t buckets = (uint32_t)emr::n_buckets(S->n_pairs);
+  if (S->n_pairs != M->n_pairs || !S->clear_total || S->clear_total == S->pair_total ||
+      (((uintptr_t)S->pair_total | (uintptr_t)S->clear_total) & 15) != 0 ||
+      (buckets > 0 && (!S->buckets || ((uintptr_t)S->buckets & 15) != 0)))
+    return hipErrorInvalidValue;
+  if (buckets > 0)
+    hipLaunchKernelGGL(emr::k_buckets, dim3(buckets), dim3(emr::kBucketPairs / 4), 0, s, *S);
+  hipLaunchKernelGGL(emr::k_compact, dim3(blocks), dim3(emr::kMoveWaves * emr::kWave), 0, s, *S, *M);
   return hipGetLastError();
 }
 

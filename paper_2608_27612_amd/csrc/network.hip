@@ -81,9 +81,11 @@ __device__ __forceinline__ uint32_t node_of(const uint32_t* known, const uint32_
   const int64_t w = (int64_t)(p >> 5);
   if (w >= words) return kNoNode;
   const uint32_t word = known[(int64_t)g * words + w];
+  const uint32_t before = rank[(int64_t)g * words + w];  // (both reads go out together)
   const uint32_t b = p & 31u;
-  if (((word >> b) & 1u) == 0u) return kNoNode;
-  return n_sub + rank[(int64_t)g * words + w] + (uint32_t)__builtin_popcount(word & ((1u << b) - 1u));
+  return ((word >> b) & 1u) == 0u
+             ? kNoNode
+             : n_sub + before + (uint32_t)__builtin_popcount(word & ((1u << b) - 1u));
 }
 
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
@@ -210,27 +212,42 @@ __global__ void __launch_bounds__(kNetThreads) k_net_pairs(NetEdgeArgs A) {
   }
 }
 
-// The raw edge of connection i of pair P.
-__device__ __forceinline__ void net_edge(const NetEdgeArgs& A, const NetPair& P, int64_t i) {
+// The raw edges of N connections i[k] of pair P (i[k] < 0: none), their reads in flight together.
+template <int N>
+__device__ __forceinline__ void net_edges(const NetEdgeArgs& A, const NetPair& P,
+                                          const int64_t (&i)[N]) {
   const uint32_t g = P.g_dir >> 1;
-  const int64_t o = i + P.delta;
-  if (P.node == kNoNode || o < P.lo || o >= P.hi || o >= A.e_raw) {
-    atomicOr(A.err, kNetErrIndex);
-    return;
+  uint32_t cell[N], cn[N];
+  float w[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    cell[k] = i[k] >= 0 ? A.conn_cell[i[k]] : 0u;
+    w[k] = i[k] >= 0 ? A.conn_w[i[k]] : 0.0f;
   }
-  const uint32_t cn = node_of(A.known, A.rank, A.words, g, A.n_sub, A.conn_cell[i]);
-  const uint32_t c = cn + P.base;
-  const bool in = (P.g_dir & 1u) != 0u;
-  uint32_t u = in ? c : P.node, v = in ? P.node : c;
-  if (cn == kNoNode) {
-    u = v = kNoNode;  // the grid end is not a hidden node: dropped
-  } else if (cn >= P.n) {
-    atomicOr(A.err, kNetErrIndex);
-    u = v = kNoNode;
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    cn[k] = node_of(A.known, A.rank, A.words, g, A.n_sub, cell[k]);  // (cell 0: none)
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    if (i[k] < 0) continue;
+    const int64_t o = i[k] + P.delta;
+    if (P.node == kNoNode || o < P.lo || o >= P.hi || o >= A.e_raw) {
+      atomicOr(A.err, kNetErrIndex);
+      continue;
+    }
+    const uint32_t c = cn[k] + P.base;
+    const bool in = (P.g_dir & 1u) != 0u;
+    uint32_t u = in ? c : P.node, v = in ? P.node : c;
+    if (cn[k] == kNoNode) {
+      u = v = kNoNode;  // the grid end is not a hidden node: dropped
+    } else if (cn[k] >= P.n) {
+      atomicOr(A.err, kNetErrIndex);
+      u = v = kNoNode;
+    }
+    A.eu[o] = u;
+    A.ev[o] = v;
+    A.ew[o] = w[k];
   }
-  A.eu[o] = u;
-  A.ev[o] = v;
-  A.ew[o] = A.conn_w[i];
 }
 
 // Wave w takes the phase's connections [w span, (w + 1) span), 64 at a time. While they belong to
@@ -255,11 +272,17 @@ __global__ void __launch_bounds__(kNetThreads) k_net_edges(NetEdgeArgs A, int64_
       P = A.pairs[r];
     }
     const int64_t i = b + lane;
-    if (i >= end) continue;
-    if (i < r1)
-      net_edge(A, P, i);
+    if (b + 4 * kWave <= r1 && b + 4 * kWave <= end) {
+      const int64_t four[4] = {i, i + kWave, i + 2 * kWave, i + 3 * kWave};
+      net_edges<4>(A, P, four);
+      b += 3 * kWave;
+      continue;
+    }
+    const int64_t one[1] = {i < end ? i : -1};
+    if (i < r1 || i >= end)
+      net_edges<1>(A, P, one);
     else
-      net_edge(A, A.pairs[find_segment_from(A.conn_offset, A.n_pairs, r, i)], i);
+      net_edges<1>(A, A.pairs[find_segment_from(A.conn_offset, A.n_pairs, r, i)], one);
   }
 }
 

@@ -62,30 +62,37 @@ __device__ __forceinline__ int64_t span_length(int64_t held, uint32_t n_spans) {
   return (steps + n_spans - 1) / n_spans * kWave;
 }
 
-// Calls f(i, pair, start) for the wave's entries [base, end) of a CSR table (off[n + 1]), 64 at a
-// time, every lane of the wave taking part (i < end is the lane's own test): pair is the entry's,
-// start = off[pair]. Most steps lie inside one pair, which the wave then follows without a search;
-// in the others each lane searches on from the pair of the step's first entry.
-template <typename F>
+// Calls f(i, pair, ctx) for the wave's entries [base, end) of a CSR table (off[n + 1]), 64 at a
+// time, every lane of the wave taking part (i < end is the lane's own test): pair is the entry's
+// and ctx = make(pair) what its entries need of it. Most steps lie inside one pair, which the wave
+// then follows without a search or another load of its context (a step that loaded it again took
+// five trips to memory, one after the other); in the others each lane searches on from the pair of
+// the step's first entry.
+template <typename M, typename F>
 __device__ __forceinline__ void for_span(const int64_t* off, uint32_t n, int64_t base, int64_t end,
-                                         uint32_t lane, F&& f) {
+                                         uint32_t lane, M&& make, F&& f) {
   if (base >= end) return;
   uint32_t p = __builtin_amdgcn_readfirstlane(last_at_most(off, 0u, n, base));
-  int64_t p0 = off[p], p1 = off[p + 1];
+  int64_t p1 = off[p + 1];
+  auto ctx = make(p);
   for (int64_t b = base; b < end; b += kWave) {
     if (b >= p1) {
       p = __builtin_amdgcn_readfirstlane(last_from(off, p, n, b));
-      p0 = off[p];
       p1 = off[p + 1];
+      ctx = make(p);
     }
     const int64_t i = b + lane;
-    uint32_t q = p;
-    int64_t q0 = p0;
-    if (p1 < (b + kWave < end ? b + kWave : end) && i >= p1 && i < end) {
-      q = last_from(off, p, n, i);
-      q0 = off[q];
+    if (p1 >= (b + kWave < end ? b + kWave : end)) {
+      f(i, p, ctx);
+    } else {
+      uint32_t q = p;
+      auto c = ctx;
+      if (i >= p1 && i < end) {
+        q = last_from(off, p, n, i);
+        c = make(q);
+      }
+      f(i, q, c);
     }
-    f(i, q, q0);
   }
 }
 
@@ -108,8 +115,9 @@ __device__ __forceinline__ uint32_t wave_excl3(uint32_t c) {
   return t;
 }
 
-// A filter over a CSR table: Op has off() (the table's offsets), pairs(), cap() (entries held), keep
-// (entry, pair) -> a mask of the entry's kept items (up to 4) and emit(entry, pair, item, place).
+// A filter over a CSR table: Op has off() (the table's offsets), pairs(), cap() (entries held),
+// context(pair) (with the pair's first entry in `start`), keep(entry, context) -> a mask of the
+// entry's kept items (up to 4) and emit(entry, item, place).
 template <typename Op>
 __global__ void __launch_bounds__(256) k_filter_count(Op op) {
   const uint32_t lane = lane_id(), span = span_index();
@@ -118,12 +126,15 @@ __global__ void __launch_bounds__(256) k_filter_count(Op op) {
   const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
   uint32_t total = 0;
   if (op.off()[0] <= 0)  // (else not a CSR offset table)
-    for_span(op.off(), n, base, min(base + len, held), lane,
-             [&](int64_t i, uint32_t pair, int64_t) {
-               const uint32_t m = i < min(base + len, held) ? op.keep(i, pair) : 0u;
-               total += wave_sum3((uint32_t)__builtin_popcount(m));
-             });
+    for_span(
+        op.off(), n, base, min(base + len, held), lane,
+        [&](uint32_t pair) { return op.context(pair); },
+        [&](int64_t i, uint32_t, const auto& c) {
+          const uint32_t m = i < min(base + len, held) ? op.keep(i, c) : 0u;
+          total += wave_sum3((uint32_t)__builtin_popcount(m));
+        });
   if (lane == 0) op.spans.kept[span] = total;
+  if (span == 0 && lane == 0) op.spans.kept[kFilterSpans] = 0u;  // k_filter_end's counter
 }
 
 // The kept entries of the spans before this one (n_spans at most kFilterSpans, read by the
@@ -152,53 +163,41 @@ __global__ void __launch_bounds__(256) k_filter_emit(Op op) {
   const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
   const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
   int64_t at0 = (int64_t)spans_before(op.spans.kept, wsum);
-  if (op.off()[0] > 0) return;
-  for_span(op.off(), n, base, min(base + len, held), lane,
-           [&](int64_t i, uint32_t pair, int64_t start) {
-             const bool mine = i < min(base + len, held);
-             const uint32_t m = mine ? op.keep(i, pair) : 0u;
-             const uint32_t c = (uint32_t)__builtin_popcount(m);
-             int64_t at = at0 + wave_excl3(c);
-             if (mine && i == start) op.spans.out_offset[pair] = at;
+  if (op.off()[0] <= 0)
+    for_span(
+        op.off(), n, base, min(base + len, held), lane,
+        [&](uint32_t pair) { return op.context(pair); },
+        [&](int64_t i, uint32_t pair, const auto& ctx) {
+          const bool mine = i < min(base + len, held);
+          const uint32_t m = mine ? op.keep(i, ctx) : 0u;
+          const uint32_t c = (uint32_t)__builtin_popcount(m);
+          int64_t at = at0 + wave_excl3(c);
+          if (mine && i == ctx.start) op.spans.out_offset[pair] = at;
 #pragma unroll
-             for (int k = 0; k < 4; ++k)
-               if ((m >> k) & 1u) op.emit(i, pair, k, at++);
-             at0 += wave_sum3(c);
-           });
+          for (int k = 0; k < 4; ++k)
+            if ((m >> k) & 1u) op.emit(i, k, at++);
+          at0 += wave_sum3(c);
+        });
+  if (span == n_spans - 1 && lane == 0)
+    *reinterpret_cast<uint64_t*>(op.spans.kept + kFilterSpans + 2) = (uint64_t)at0;  // the total
 }
 
-// One workgroup, after k_filter_emit: the offsets of the empty pairs (their next pair's that has an
-// entry) and of those whose entries lie beyond the ones held (the total), every pair's count, and
-// the call's last flag words (see k_scan).
-constexpr int kEndThreads = 1024;
+// After k_filter_emit: the offsets of the empty pairs (their next pair's that has an entry) and of
+// those whose entries lie beyond the ones held (the total), and every pair's count; the workgroup
+// that ends last hands the call's flags over (see k_scan).
+constexpr int kEndThreads = 256;
 template <typename Op>
-__global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op, uint32_t n_spans) {
-  __shared__ uint64_t wsum[kEndThreads / kWave];
-  __shared__ uint32_t wmax[kEndThreads / kWave];
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+__global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op) {
   const uint32_t n = op.pairs();
   const FilterSpans& F = op.spans;
-  uint32_t f_err = 0, f_max = 0;
-  if (threadIdx.x == 0) {
-    f_err = __hip_atomic_load(F.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    f_max = __hip_atomic_load(F.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
   const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
-  uint64_t sum = 0;
-  for (uint32_t k = threadIdx.x; k < n_spans; k += kEndThreads) sum += F.kept[k];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-  if (lane == 0) wsum[wv] = sum;
-  __syncthreads();
-  uint64_t total = 0;
-#pragma unroll
-  for (int k = 0; k < kEndThreads / kWave; ++k) total += wsum[k];
+  const uint64_t total = *reinterpret_cast<const uint64_t*>(F.kept + kFilterSpans + 2);
   uint32_t mx = 0;
   // the offset of the first kept item at or after entry i, the first of pair p or of a later one
   auto offset_at = [&](int64_t i, uint32_t p) {
     return i >= held ? (int64_t)total : F.out_offset[last_from(op.off(), p, n, i)];
   };
-  for (uint32_t p = threadIdx.x; p < n; p += kEndThreads) {
+  for (uint32_t p = blockIdx.x * kEndThreads + threadIdx.x; p < n; p += gridDim.x * kEndThreads) {
     const int64_t i0 = op.off()[p], i1 = op.off()[p + 1];
     int64_t c = 0;
     if (i0 < i1 && i0 < held) {
@@ -213,21 +212,29 @@ __global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op, uint32_t n_sp
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
-  if (lane == 0) wmax[wv] = mx;
+  if (lane_id() == 0 && mx != 0u) raise_max(F.flags + kFlagMax, mx);
+  __threadfence();  // (the raised word before the count below)
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t m = f_max;
-    for (int k = 0; k < kEndThreads / kWave; ++k) m = max(m, wmax[k]);
-    F.out_offset[n] = (int64_t)total;
-    F.host[kFlagErr] = f_err;
-    F.host[kFlagMax] = m;
-    F.host[kFlagTotal] = (uint32_t)total;
-    F.host[kFlagTotal + 1] = (uint32_t)(total >> 32);
+  if (threadIdx.x != 0 || atomicAdd(F.kept + kFilterSpans, 1u) != gridDim.x - 1u) return;
+  __threadfence();
+  F.out_offset[n] = (int64_t)total;
+  F.host[kFlagErr] =
+      __hip_atomic_load(F.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  F.host[kFlagMax] =
+      __hip_atomic_load(F.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  F.host[kFlagTotal] = (uint32_t)total;
+  F.host[kFlagTotal + 1] = (uint32_t)(total >> 32);
 #pragma unroll
-    for (int k = 0; k < kFlagWords; ++k)
-      __hip_atomic_store(F.flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  for (int k = 0; k < kFlagWords; ++k)
+    __hip_atomic_store(F.flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// What a record's entry needs of its pair.
+struct RecordPair {
+  int64_t start, end;  // its records
+  uint32_t info;       // genome << 1 | direction
+  float sx, sy;        // its source
+};
 
 // ------------------------------------------------------------------------ hidden nodes
 // Each record's four cells. A record outside the range of the pair found (offsets out of order)
@@ -242,29 +249,39 @@ __global__ void __launch_bounds__(256) k_hidden_mark(HiddenArgs A) {
   if (off[0] > 0) return;                                          // not a CSR offset table
   const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
   const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
-  for_span(off, np, base, end, lane, [&](int64_t i, uint32_t p, int64_t start) {
-    if (i >= end || i < start || i >= start + A.rec.count[p]) return;
-    const uint32_t info = A.rec.pair_info[2 * p];
-    const uint32_t g = info >> 1;
-    if ((info & 1u) != 0u || g >= A.n_genomes) return;  // incoming pairs add no hidden node
-    const uint32_t P = A.rec.parent[i];
-    if ((int64_t)P >= Q) return;
-    // grid positions 4P .. 4P+3; the many pairs of one genome mostly mark cells already marked,
-    // so a plain read first keeps them from queueing atomics on the same words
-    uint32_t* bits = A.fresh + (int64_t)g * A.words;
-    const uint32_t m = 0xFu << (4u * (P % 8u));
-    if ((__hip_atomic_load(bits + P / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
-      atomicOr(bits + P / 8u, m);
-  });
+  for_span(
+      off, np, base, end, lane,
+      [&](uint32_t p) {
+        return RecordPair{off[p], off[p] + A.rec.count[p], A.rec.pair_info[2 * p], 0.0f, 0.0f};
+      },
+      [&](int64_t i, uint32_t, const RecordPair& c) {
+        const uint32_t g = c.info >> 1;
+        if (i >= end || i < c.start || i >= c.end) return;
+        if ((c.info & 1u) != 0u || g >= A.n_genomes) return;  // incoming pairs add no hidden node
+        const uint32_t P = A.rec.parent[i];
+        if ((int64_t)P >= Q) return;
+        // grid positions 4P .. 4P+3; the many pairs of one genome mostly mark cells already
+        // marked, so a plain read first keeps them from queueing atomics on the same words
+        uint32_t* bits = A.fresh + (int64_t)g * A.words;
+        const uint32_t m = 0xFu << (4u * (P % 8u));
+        if ((__hip_atomic_load(bits + P / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
+          atomicOr(bits + P / 8u, m);
+      });
 }
 
-// One workgroup per genome: its new cells (found now, not known before).
-__global__ void __launch_bounds__(256) k_hidden_count(HiddenArgs A) {
-  __shared__ uint32_t part[256 / kWave];
+// One workgroup per genome: its new cells (found now, not known before). A deep grid's bitmap is
+// long (43,691 words at depth 10) and a call's genomes may be few, so a genome gets 16 waves there
+// (and 4 of them a bitmap of at most kShortWords words).
+constexpr int kHiddenThreads = 1024;
+constexpr int64_t kShortWords = 1024;
+__global__ void __launch_bounds__(kHiddenThreads) k_hidden_count(HiddenArgs A) {
+  __shared__ uint32_t part[kHiddenThreads / kWave];
+  const uint32_t waves = blockDim.x / kWave;
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const uint32_t* f = A.fresh + (int64_t)g * A.words;
     const uint32_t* k = A.known ? A.known + (int64_t)g * A.words : nullptr;
     uint32_t c = 0;
+#pragma unroll 4
     for (int64_t w = threadIdx.x; w < A.words; w += blockDim.x)
       c += __builtin_popcount(f[w] & (k ? ~k[w] : ~0u));
 #pragma unroll
@@ -273,56 +290,67 @@ __global__ void __launch_bounds__(256) k_hidden_count(HiddenArgs A) {
     __syncthreads();
     if (threadIdx.x == 0) {
       uint32_t t = 0;
-      for (int i = 0; i < 256 / kWave; ++i) t += part[i];
+      for (uint32_t i = 0; i < waves; ++i) t += part[i];
       A.totals[g] = t;
     }
     __syncthreads();
   }
 }
 
-// One workgroup per genome: thread t owns a contiguous run of bitmap words, so the genome's new
-// cells come out in ascending order at offsets[g] + (cells of the runs before) + rank in the run;
-// then the genome's known bits take the new cells.
-__global__ void __launch_bounds__(256) k_hidden_emit(HiddenArgs A) {
-  __shared__ uint32_t part[256];
+// One workgroup per genome, four consecutive bitmap words per thread and round: the genome's new
+// cells come out in ascending order at offsets[g] + (cells of the rounds and threads before) + rank
+// in the thread's words; then the genome's known bits take the new cells. (A thread per run of
+// words / 256, scanned by one thread: 280 to 650 us for 100 genomes at depth 10.)
+__global__ void __launch_bounds__(kHiddenThreads) k_hidden_emit(HiddenArgs A) {
+  __shared__ uint32_t part[kHiddenThreads / kWave];
   const int64_t n_pos = n_positions(A.rec.depth);
-  const int64_t per = (A.words + 255) / 256;
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, waves = blockDim.x / kWave;
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const uint32_t* f = A.fresh + (int64_t)g * A.words;
     uint32_t* k = A.known ? A.known + (int64_t)g * A.words : nullptr;
-    const int64_t w0 = (int64_t)threadIdx.x * per;
-    const int64_t w1 = w0 + per < A.words ? w0 + per : A.words;
-    uint32_t c = 0;
-    for (int64_t w = w0; w < w1; ++w) c += __builtin_popcount(f[w] & (k ? ~k[w] : ~0u));
-    part[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {  // exclusive scan of the 256 runs
-      uint32_t run = 0;
-      for (int i = 0; i < 256; ++i) {
-        const uint32_t v = part[i];
-        part[i] = run;
-        run += v;
+    int64_t at0 = A.offsets[g];
+    for (int64_t round = 0; round < A.words; round += 4 * (int64_t)blockDim.x) {
+      const int64_t w0 = round + 4 * (int64_t)threadIdx.x;
+      uint32_t fw[4], kw[4], c = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        fw[q] = w0 + q < A.words ? f[w0 + q] : 0u;
+        kw[q] = k && w0 + q < A.words ? k[w0 + q] : 0u;
+        c += __builtin_popcount(fw[q] & ~kw[q]);
       }
-    }
-    __syncthreads();
-    int64_t at = A.offsets[g] + part[threadIdx.x];
-    for (int64_t w = w0; w < w1; ++w) {
-      const uint32_t kw = k ? k[w] : 0u;
-      for (uint32_t b = f[w] & ~kw; b != 0u; b &= b - 1u) {
-        const int64_t p = w * 32 + __builtin_ctz(b);
-        if (p < n_pos && at < A.cap) {
-          float x, y;
-          cell_centre((uint32_t)p, &x, &y);
-          A.out_src[3 * at] = __float_as_uint(x);
-          A.out_src[3 * at + 1] = __float_as_uint(y);
-          A.out_src[3 * at + 2] = (uint32_t)EMR_DIR_OUT;
-          if (A.out_cell) A.out_cell[at] = (uint32_t)(p + 1);
+      uint32_t incl = c;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl, off, kWave);
+        if (lane >= (uint32_t)off) incl += v;
+      }
+      if (lane == kWave - 1) part[wv] = incl;
+      __syncthreads();
+      uint32_t before = 0, total = 0;
+      for (uint32_t i = 0; i < waves; ++i) {
+        before += i < wv ? part[i] : 0u;
+        total += part[i];
+      }
+      int64_t at = at0 + before + incl - c;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        for (uint32_t b = fw[q] & ~kw[q]; b != 0u; b &= b - 1u) {
+          const int64_t p = (w0 + q) * 32 + __builtin_ctz(b);
+          if (p < n_pos && at < A.cap) {
+            float x, y;
+            cell_centre((uint32_t)p, &x, &y);
+            A.out_src[3 * at] = __float_as_uint(x);
+            A.out_src[3 * at + 1] = __float_as_uint(y);
+            A.out_src[3 * at + 2] = (uint32_t)EMR_DIR_OUT;
+            if (A.out_cell) A.out_cell[at] = (uint32_t)(p + 1);
+          }
+          ++at;
         }
-        ++at;
+        if (k && w0 + q < A.words && (fw[q] & ~kw[q]) != 0u) k[w0 + q] = kw[q] | fw[q];
       }
-      if (k) k[w] = kw | f[w];
+      at0 += total;
+      __syncthreads();  // part is rewritten for the next round
     }
-    __syncthreads();  // part is rewritten for the next genome
   }
 }
 
@@ -338,15 +366,20 @@ __device__ __forceinline__ uint32_t conn_type(float ax, float ay, float bx, floa
 // The children of a pair's record that are expressed connections.
 struct ExpressOp : ExpressArgs {
   __device__ const int64_t* off() const { return rec.offset; }
-  __device__ uint32_t pairs() const { return rec.n_pairs; }
+  __host__ __device__ uint32_t pairs() const { return rec.n_pairs; }
   __device__ int64_t cap() const { return rec.cap; }
-  __device__ uint32_t keep(int64_t i, uint32_t pair) const {
-    if (i >= rec.offset[pair] + rec.count[pair]) return 0u;
+  __device__ RecordPair context(uint32_t pair) const {
+    const uint32_t j = rec.pair_info[2 * pair + 1];
+    const int64_t start = rec.offset[pair];
+    return {start, start + rec.count[pair], rec.pair_info[2 * pair], rec.src_xy[2 * j],
+            rec.src_xy[2 * j + 1]};
+  }
+  __device__ uint32_t keep(int64_t i, const RecordPair& c) const {
+    if (i < c.start || i >= c.end) return 0u;
     const uint32_t P = rec.parent[i];
     if ((int64_t)P >= n_parents(rec.depth)) return 0u;
-    const bool incoming = (rec.pair_info[2 * pair] & 1u) != 0u;
-    const uint32_t j = rec.pair_info[2 * pair + 1];
-    const float sx = rec.src_xy[2 * j], sy = rec.src_xy[2 * j + 1];
+    const bool incoming = (c.info & 1u) != 0u;
+    const float sx = c.sx, sy = c.sy;
     const float4 w = reinterpret_cast<const float4*>(rec.w4)[i];
     const float wk[4] = {w.x, w.y, w.z, w.w};
     // Eq. 1: the four children are one aligned quad of their level
@@ -362,7 +395,7 @@ struct ExpressOp : ExpressArgs {
     }
     return m;
   }
-  __device__ void emit(int64_t i, uint32_t, int k, int64_t at) const {
+  __device__ void emit(int64_t i, int k, int64_t at) const {
     if (at >= ExpressArgs::cap) return;
     out_cell[at] = 4u * rec.parent[i] + 1u + (uint32_t)k;
     out_w[at] = rec.w4[4 * i + k];
@@ -373,10 +406,13 @@ struct ExpressOp : ExpressArgs {
 // The connections with band > theta_band (strict; a NaN band never passes), in order.
 struct BandOp : BandSelectArgs {
   __device__ const int64_t* off() const { return in_offset; }
-  __device__ uint32_t pairs() const { return n_pairs; }
+  __host__ __device__ uint32_t pairs() const { return n_pairs; }
   __device__ int64_t cap() const { return in_cap; }
-  __device__ uint32_t keep(int64_t i, uint32_t) const { return band[i] > theta_band ? 1u : 0u; }
-  __device__ void emit(int64_t i, uint32_t, int, int64_t at) const {
+  __device__ RecordPair context(uint32_t pair) const { return {in_offset[pair], 0, 0u, 0.0f, 0.0f}; }
+  __device__ uint32_t keep(int64_t i, const RecordPair&) const {
+    return band[i] > theta_band ? 1u : 0u;
+  }
+  __device__ void emit(int64_t i, int, int64_t at) const {
     if (at >= out_cap) return;
     out_cell[at] = in_cell[i];
     out_w[at] = in_w[i];
@@ -393,31 +429,38 @@ __global__ void __launch_bounds__(256) k_chain_mark(ChainArgs A) {
   if (off[0] > 0) return;
   const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
   const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
-  for_span(off, np, base, end, lane, [&](int64_t i, uint32_t p, int64_t start) {
-    if (i >= end || i < start || i >= start + A.rec.count[p]) return;
-    const uint32_t P = A.rec.parent[i];
-    if ((int64_t)P < Q) atomicOr(A.member + (int64_t)p * A.qwords + P / 32u, 1u << (P % 32u));
-  });
+  for_span(
+      off, np, base, end, lane,
+      [&](uint32_t p) { return RecordPair{off[p], off[p] + A.rec.count[p], 0u, 0.0f, 0.0f}; },
+      [&](int64_t i, uint32_t p, const RecordPair& c) {
+        if (i >= end || i < c.start || i >= c.end) return;
+        const uint32_t P = A.rec.parent[i];
+        if ((int64_t)P < Q) atomicOr(A.member + (int64_t)p * A.qwords + P / 32u, 1u << (P % 32u));
+      });
 }
 
 // A pair's record (its members: the pair's bitmap) stays when every ancestor of its cell is a record
 // of the pair (the root is its own ancestor line's start).
 struct ChainOp : ChainArgs {
   __device__ const int64_t* off() const { return rec.offset; }
-  __device__ uint32_t pairs() const { return rec.n_pairs; }
+  __host__ __device__ uint32_t pairs() const { return rec.n_pairs; }
   __device__ int64_t cap() const { return rec.cap; }
-  __device__ uint32_t keep(int64_t i, uint32_t pair) const {
-    if (i >= rec.offset[pair] + rec.count[pair]) return 0u;
+  __device__ RecordPair context(uint32_t pair) const {
+    const int64_t start = rec.offset[pair];
+    return {start, start + rec.count[pair], pair, 0.0f, 0.0f};  // (info: the pair itself)
+  }
+  __device__ uint32_t keep(int64_t i, const RecordPair& c) const {
+    if (i < c.start || i >= c.end) return 0u;
     uint32_t P = rec.parent[i];
     if ((int64_t)P >= n_parents(rec.depth)) return 0u;
-    const uint32_t* bits = member + (int64_t)pair * qwords;
+    const uint32_t* bits = member + (int64_t)c.info * qwords;
     while (P > 0u) {
       P = (P - 1u) / 4u;
       if (((bits[P / 32u] >> (P % 32u)) & 1u) == 0u) return 0u;
     }
     return 1u;
   }
-  __device__ void emit(int64_t i, uint32_t, int, int64_t at) const {
+  __device__ void emit(int64_t i, int, int64_t at) const {
     if (at >= ChainArgs::cap) return;
     out_parent[at] = rec.parent[i];
     reinterpret_cast<float4*>(out_w4)[at] = reinterpret_cast<const float4*>(rec.w4)[i];
@@ -436,12 +479,13 @@ static uint32_t span_blocks(int64_t cap) {
 
 extern "C" hipError_t emr_launch_hidden(const emr::HiddenArgs* A, int step, hipStream_t s) {
   const uint32_t gb = A->n_genomes == 0 ? 1 : (A->n_genomes > 65535 ? 65535 : A->n_genomes);
+  const uint32_t threads = A->words <= emr::kShortWords ? 256 : emr::kHiddenThreads;
   switch (step) {
     case 0:
       hipLaunchKernelGGL(emr::k_hidden_mark, dim3(span_blocks(A->rec.cap)), dim3(256), 0, s, *A);
       break;
-    case 1: hipLaunchKernelGGL(emr::k_hidden_count, dim3(gb), dim3(256), 0, s, *A); break;
-    case 2: hipLaunchKernelGGL(emr::k_hidden_emit, dim3(gb), dim3(256), 0, s, *A); break;
+    case 1: hipLaunchKernelGGL(emr::k_hidden_count, dim3(gb), dim3(threads), 0, s, *A); break;
+    case 2: hipLaunchKernelGGL(emr::k_hidden_emit, dim3(gb), dim3(threads), 0, s, *A); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -453,7 +497,9 @@ hipError_t launch_filter(const Op& op, int64_t cap, hipStream_t s) {
   const uint32_t blocks = span_blocks(cap);
   hipLaunchKernelGGL(emr::k_filter_count<Op>, dim3(blocks), dim3(256), 0, s, op);
   hipLaunchKernelGGL(emr::k_filter_emit<Op>, dim3(blocks), dim3(256), 0, s, op);
-  hipLaunchKernelGGL(emr::k_filter_end<Op>, dim3(1), dim3(emr::kEndThreads), 0, s, op, 4 * blocks);
+  const uint32_t ends = (op.pairs() + emr::kEndThreads - 1) / emr::kEndThreads;
+  hipLaunchKernelGGL(emr::k_filter_end<Op>, dim3(ends < 256u ? ends : 256u), dim3(emr::kEndThreads), 0,
+                     s, op);
   return hipGetLastError();
 }
 }  // namespace

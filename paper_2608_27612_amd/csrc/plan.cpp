@@ -322,11 +322,11 @@ emr_status build_plan_tables(const ProgDesc* desc, const GenomeInfo* info, int32
   P.off_nz = align256(P.off_status + P.status_bytes);
   P.nz_bytes = (size_t)P.n_pairs * nz_words((uint32_t)P.tiles) * 8;
   P.off_ptotal = align256(P.off_nz + P.nz_bytes);
-  // (one set of totals when k_scan clears it, else two that the calls use in turn)
-  P.ptotal_stride = P.n_pairs <= (int64_t)kCompactPairs ? align256((size_t)P.n_pairs * 4) : 0;
-  const size_t totals = P.ptotal_stride ? 2 * P.ptotal_stride : (size_t)P.n_pairs * 4;
-  P.total = align256(P.off_ptotal + totals);
-  P.clear_words = (int64_t)((P.off_ptotal + totals - P.off_nz + 3) / 4);
+  // (two sets of totals, used by the calls in turn; then the compaction's buckets of pairs)
+  P.ptotal_stride = align256((size_t)P.n_pairs * 4);
+  P.off_buckets = P.off_ptotal + 2 * P.ptotal_stride;
+  P.total = align256(P.off_buckets + (size_t)n_buckets((uint64_t)P.n_pairs) * sizeof(PairBucket));
+  P.clear_words = (int64_t)((P.off_buckets - P.off_nz) / 4);
   // tables
   P.t_groups = 0;
   P.t_members = align256(P.groups.size() * sizeof(Group));
@@ -469,8 +469,9 @@ bool check_plan_tables(const PlanTables& P, const ProgDesc* desc, uint64_t blob_
   }
   // The workspace regions follow each other, and the cleared words cover the marks and totals.
   if (P.off_status + P.status_bytes > P.off_nz || P.off_nz + P.nz_bytes > P.off_ptotal ||
-      P.off_ptotal + P.ptotal_stride + n_pairs * 4 > P.total || P.off_ptotal % 16 != 0 ||
-      P.ptotal_stride % 16 != 0 || (P.ptotal_stride != 0 && P.ptotal_stride < n_pairs * 4) ||
+      P.off_ptotal + P.ptotal_stride + n_pairs * 4 > P.off_buckets || P.off_ptotal % 16 != 0 ||
+      P.ptotal_stride % 16 != 0 || P.ptotal_stride < n_pairs * 4 || P.off_buckets % 16 != 0 ||
+      P.off_buckets + n_buckets(n_pairs) * sizeof(PairBucket) > P.total ||
       (uint64_t)P.clear_words * 4 < P.off_ptotal + P.ptotal_stride + n_pairs * 4 - P.off_nz ||
       P.off_nz + (uint64_t)P.clear_words * 4 > P.total)
     return check_fail(msg, "workspace regions overlap or overflow");

@@ -100,7 +100,8 @@ struct PlanTables {
   size_t status_bytes = 0;
   size_t off_nz = 0, nz_bytes = 0;
   size_t off_ptotal = 0;
-  size_t ptotal_stride = 0;  // bytes to the second set of per-pair totals (0: one set)
+  size_t ptotal_stride = 0;  // bytes to the second set of per-pair totals
+  size_t off_buckets = 0;
   int64_t clear_words = 0;
   // Floats of a bias table: the groups' rows plus 16 floats of padding (the compiled tier loads a
   // group's rows 1 .. 4 at once).

@@ -573,7 +573,7 @@ emr_status plan_schedule(const Plan& P, const emr::DiscoverScalars& sc, uint32_t
 // ------------------------------------------------------------------ call flags
 // Each call's kernels raise their error bits (word 0) and largest pair count (word 1) into a slot
 // of a library-owned ring in device memory. A slot is zero when a call takes it; the call's last
-// kernel (k_scan for a record call, k_finalize otherwise) writes the words to the slot's pinned
+// kernel (k_compact for a record call, k_finalize otherwise) writes the words to the slot's pinned
 // host words and clears them again. So
 // no copy of the flags goes either way, and the caller's workspace keeps no state from one call
 // to the next.
@@ -1078,7 +1078,7 @@ bool cached_split_parts(const Plan& P, const Plan::Launch& L, bool skip_uniform,
 // records go to `out` pair after pair (pair_offset, pair_count), its capacity also bounding the
 // pool in the workspace; raw outputs go to raw[r * N(D) + p].
 // jit: run the plan's compiled programs (jit_use said so) instead of the interpreter. With
-// `finalize`, the range's last kernel (k_scan for records, k_finalize for raw outputs) then hands
+// `finalize`, the range's last kernel (k_compact for records, k_finalize for raw outputs) then hands
 // the call's flags to their pinned words.
 // With `clear` (record mode), the workspace's group marks and per-pair totals are cleared right
 // before the discover launch, once every argument of that launch is ready on the host.
@@ -1214,10 +1214,11 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     emr::ScanArgs S{};
     S.pair_total = (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride);
     S.clear_total = (uint32_t*)(ws + P.off_ptotal + (1 - turn) * P.ptotal_stride);
+    S.buckets = (emr::PairBucket*)(ws + P.off_buckets);
     S.pair_count = out->pair_count;
     S.pair_offset = out->pair_offset;
     S.flags = flags;
-    S.host = finalize ? flags_host : nullptr;  // k_scan then ends the call's flag writes
+    S.host = finalize ? flags_host : nullptr;  // k_compact then ends the call's flag writes
     S.host_counts = host_counts;
     S.n_pairs = (uint32_t)P.n_pairs;
     emr::MoveArgs M{};
@@ -1226,8 +1227,6 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     M.pool_w4 = pool_w4;
     M.parent = out->parent;
     M.w4 = out->w4;
-    M.pair_count = out->pair_count;
-    M.pair_offset = out->pair_offset;
     M.nz = (uint64_t*)(ws + P.off_nz);
     M.skip = skip_uniform ? (const uint8_t*)(tables + P.t_uniform) : nullptr;
     M.cap = cap;
@@ -1320,7 +1319,7 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   st = launch_range(pop, P, T, theta, out, raw, workspace, s, 0, P.tiles, jit, f.dev, f.host_dev,
                     true, !clean, true, nullptr, turn);
   if (st != EMR_OK) return st;
-  if (records) workspace_mark_clean(workspace, P, s, capacity, P.ptotal_stride ? 1 - turn : 0);
+  if (records) workspace_mark_clean(workspace, P, s, capacity, 1 - turn);
   f.ok = true;
   return EMR_OK;
 }
@@ -1762,7 +1761,7 @@ struct StreamSet {
   uint32_t* g_parent[2] = {};       // each chunk's records (CSR), double buffered
   float* g_w4[2] = {};
   int64_t* counts_h[2] = {};        // pinned: a chunk's counts, then its error flags (one word)
-  int64_t* counts_h_dev[2] = {};    // the same words, device view (k_scan writes them)
+  int64_t* counts_h_dev[2] = {};    // the same words, device view (k_compact writes them)
   uint32_t* stage_parent[2] = {};   // pinned staging of a chunk's records
   float* stage_w4[2] = {};
   int64_t stage_cap[2] = {0, 0};
@@ -1924,7 +1923,7 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     const int64_t tile_lo = c * tpc, n = std::min<int64_t>(tpc, P.tiles - tile_lo);
     emr_result chunk_out{R.g_parent[b], R.g_w4[b], records, R.counts, R.offsets, R.ws,
                          R.ws_bytes};
-    // k_scan also writes the chunk's counts and the call's error bits to the pinned words
+    // k_compact also writes the chunk's counts and the call's error bits to the pinned words
     emr_status e = launch_range(pop, P, T, theta, &chunk_out, nullptr, R.ws, R.s, tile_lo, n, jit,
                                 f.dev, f.host_dev, false, true, true, R.counts_h_dev[b]);
     if (e != EMR_OK) return e;
@@ -2041,7 +2040,7 @@ int64_t cell_words(int32_t depth) { return (emr::n_positions(depth) + 31) / 32; 
 
 // Workspace layouts: hidden nodes (fresh bitmap, per-genome totals and counts), expression and the
 // band filter (the spans' kept counts), chain (membership bitmap, the spans' kept counts).
-constexpr size_t kFilterBytes = emr::kFilterSpans * 4;
+const size_t kFilterBytes = align256(emr::kFilterWords * 4);
 struct HiddenLayout {
   size_t fresh = 0, totals = 0, counts = 0, bytes = 0;
   HiddenLayout(int64_t G, int32_t depth) {

@@ -1,4 +1,4 @@
-"""Compaction: one kernel for at most 16384 pairs, two above; tile groups with a few records and with
+"""Compaction: one kernel for at most 16384 pairs, buckets of pairs above; tile groups with a few records and with
 every record; ranges of one, two and more groups of 64 tiles; the two sets of totals taken in turn.
 A pair's records are compared bit for bit with the raw outputs of its grid."""
 
@@ -60,7 +60,7 @@ def test_records_are_the_grid_s(emr, genomes, inputs, depth, theta):
 
 
 def test_one_kernel_and_two_agree(emr):
-    """4096 genomes of 4 sources are the last call of one kernel; 4097 take two."""
+    """4096 genomes of 4 sources are the last call of one kernel; 4097 take buckets of pairs."""
     genomes = W.population(11, 4097, 8, 24)
     subs = W.xor_sources()
     out = []

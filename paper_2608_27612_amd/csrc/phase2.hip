@@ -255,17 +255,29 @@ __global__ void __launch_bounds__(256) k_hidden_mark(HiddenArgs A) {
         return RecordPair{off[p], off[p] + A.rec.count[p], A.rec.pair_info[2 * p], 0.0f, 0.0f};
       },
       [&](int64_t i, uint32_t, const RecordPair& c) {
+        // grid positions 4P .. 4P+3 (incoming pairs add no hidden node)
         const uint32_t g = c.info >> 1;
-        if (i >= end || i < c.start || i >= c.end) return;
-        if ((c.info & 1u) != 0u || g >= A.n_genomes) return;  // incoming pairs add no hidden node
-        const uint32_t P = A.rec.parent[i];
-        if ((int64_t)P >= Q) return;
-        // grid positions 4P .. 4P+3; the many pairs of one genome mostly mark cells already
-        // marked, so a plain read first keeps them from queueing atomics on the same words
-        uint32_t* bits = A.fresh + (int64_t)g * A.words;
-        const uint32_t m = 0xFu << (4u * (P % 8u));
-        if ((__hip_atomic_load(bits + P / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
-          atomicOr(bits + P / 8u, m);
+        const bool mine = i < end && i >= c.start && i < c.end && (c.info & 1u) == 0u &&
+                          g < A.n_genomes;
+        const uint32_t P = mine ? A.rec.parent[i] : 0u;
+        const bool ok = mine && (int64_t)P < Q;
+        int64_t key = ok ? (int64_t)g * A.words + P / 8u : -1 - (int64_t)lane;
+        uint32_t m = 0xFu << (4u * (P % 8u));
+        // A pair's parents ascend, so the lanes of one bitmap word follow each other: the first of
+        // them (and every eighth lane: small pairs' runs can be longer) takes the bits of up to
+        // eight. Bits already marked by the genome's other pairs (most are)
+        // cost a read only; the read and the atomic both go to the memory side, past the L2s.
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+          const int64_t k2 = __shfl_down(key, d, kWave);
+          const uint32_t m2 = (uint32_t)__shfl_down((int)m, d, kWave);
+          if (lane + (uint32_t)d < (uint32_t)kWave && k2 == key) m |= m2;
+        }
+        const int64_t before = __shfl_up(key, 1, kWave);
+        if (!ok || (lane % 8u != 0u && before == key)) return;
+        uint32_t* bits = A.fresh + key;
+        if ((__hip_atomic_load(bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
+          atomicOr(bits, m);
       });
 }
 

@@ -83,6 +83,13 @@ __device__ __forceinline__ void raise_max(uint32_t* p, uint32_t v) {
   if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
 }
 
+// Raises the one error bit of the discover and bind kernels. A plain store, since a raw call's error
+// word is the call's pinned host word (no kernel then has to hand it over), where an atomic's
+// read-modify-write might not reach.
+__device__ __forceinline__ void raise_table_error(uint32_t* err) {
+  __hip_atomic_store(err, kErrTable, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ------------------------------------------------------------------------ discover kernel
 // Pointers are passed as separate restrict-qualified parameters so the compiler can prove that
 // the program, group and bias tables are never written by the kernel and read them with scalar
@@ -235,7 +242,7 @@ __device__ __forceinline__ void discover_chunk(uint32_t c, const DiscoverPart& p
     // a compiled program lies inside the code area (its end is checked by the host)
     if constexpr (JIT) ok = ok && G.code_off < a.code_bytes && (G.code_off & 3u) == 0;
     if (!ok) {
-      if (lane == 0) atomicOr(d.err, kErrTable);
+      if (lane == 0) raise_table_error(d.err);
       return;
     }
   }
@@ -506,7 +513,7 @@ __device__ __forceinline__ void discover_body(const uint32_t* __restrict__ geo_t
     // a round-robin entry's index is inside its part by the scan)
     const uint32_t k = entry >> kEntryPartShift, cl = entry & ((1u << kEntryPartShift) - 1u);
     if (k >= a.n_parts) {
-      if (lane == 0) atomicOr(err, kErrTable);
+      if (lane == 0) raise_table_error(err);
       break;
     }
     const DiscoverPart pt = a.part[k];
@@ -521,7 +528,7 @@ __device__ __forceinline__ void discover_body(const uint32_t* __restrict__ geo_t
       case 16 * 4 + 1: discover_chunk<1, 16, MODE, JIT>(cl, pt, a, d, geo, lane, code_base); break;
       case 32 * 4 + 1: discover_chunk<1, 32, MODE, JIT>(cl, pt, a, d, geo, lane, code_base); break;
       default:
-        if (lane == 0) atomicOr(err, kErrTable);
+        if (lane == 0) raise_table_error(err);
     }
   }
 }

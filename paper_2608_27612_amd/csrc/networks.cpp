@@ -694,7 +694,7 @@ emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
 // Smallest edge count that sends a genome to the stepwise kernels (below it the launches of the
 // steps cost more than one workgroup's longer run), and the most steps of a fused run (one launch
 // stays well below a second).
-constexpr int64_t kStepwiseEdges = 16384;
+constexpr int64_t kStepwiseEdges = 6144;
 constexpr int32_t kFusedSteps = 1024;
 constexpr int64_t kFusedWorkgroups = 256;  // half of those that the chip holds
 

@@ -281,14 +281,12 @@ __global__ void __launch_bounds__(256) k_hidden_mark(HiddenArgs A) {
       });
 }
 
-// One workgroup per genome: its new cells (found now, not known before). A deep grid's bitmap is
-// long (43,691 words at depth 10) and a call's genomes may be few, so a genome gets 16 waves there
-// (and 4 of them a bitmap of at most kShortWords words).
+// One workgroup of 16 waves per genome: its new cells (found now, not known before). A deep grid's
+// bitmap is long (43,691 words at depth 10) and a call's genomes may be few.
 constexpr int kHiddenThreads = 1024;
-constexpr int64_t kShortWords = 1024;
 __global__ void __launch_bounds__(kHiddenThreads) k_hidden_count(HiddenArgs A) {
   __shared__ uint32_t part[kHiddenThreads / kWave];
-  const uint32_t waves = blockDim.x / kWave;
+  constexpr uint32_t waves = kHiddenThreads / kWave;
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const uint32_t* f = A.fresh + (int64_t)g * A.words;
     const uint32_t* k = A.known ? A.known + (int64_t)g * A.words : nullptr;
@@ -309,26 +307,35 @@ __global__ void __launch_bounds__(kHiddenThreads) k_hidden_count(HiddenArgs A) {
   }
 }
 
-// One workgroup per genome, four consecutive bitmap words per thread and round: the genome's new
+// One workgroup per genome, four consecutive bitmap items per thread and round: the genome's new
 // cells come out in ascending order at offsets[g] + (cells of the rounds and threads before) + rank
-// in the thread's words; then the genome's known bits take the new cells. (A thread per run of
-// words / 256, scanned by one thread: 280 to 650 us for 100 genomes at depth 10.)
+// in the thread's items; then the genome's known bits take the new cells. An item is a word of a
+// long bitmap, which is sparse, and a nibble (the four children of one parent) of a short one,
+// where a thread with four dense words would write 128 cells one after the other (26 us for 43
+// words). (A thread per run of words / 256, scanned by one thread: 280 to 650 us for 100 genomes
+// at depth 10.)
+constexpr int64_t kShortWords = 1024;
+template <int BITS>
 __global__ void __launch_bounds__(kHiddenThreads) k_hidden_emit(HiddenArgs A) {
+  constexpr int PER = 32 / BITS;  // items per word
+  constexpr int ITEMS = BITS == 32 ? 4 : 1;
   __shared__ uint32_t part[kHiddenThreads / kWave];
-  const int64_t n_pos = n_positions(A.rec.depth);
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  const int64_t n_pos = n_positions(A.rec.depth), items = A.words * PER;
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
   for (uint32_t g = blockIdx.x; g < A.n_genomes; g += gridDim.x) {
     const uint32_t* f = A.fresh + (int64_t)g * A.words;
     uint32_t* k = A.known ? A.known + (int64_t)g * A.words : nullptr;
     int64_t at0 = A.offsets[g];
-    for (int64_t round = 0; round < A.words; round += 4 * (int64_t)blockDim.x) {
-      const int64_t w0 = round + 4 * (int64_t)threadIdx.x;
-      uint32_t fw[4], kw[4], c = 0;
+    for (int64_t round = 0; round < items; round += ITEMS * kHiddenThreads) {
+      const int64_t i0 = round + ITEMS * (int64_t)threadIdx.x;
+      uint32_t fresh[ITEMS], c = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        fw[q] = w0 + q < A.words ? f[w0 + q] : 0u;
-        kw[q] = k && w0 + q < A.words ? k[w0 + q] : 0u;
-        c += __builtin_popcount(fw[q] & ~kw[q]);
+      for (int q = 0; q < ITEMS; ++q) {
+        const int64_t w = (i0 + q) / PER;
+        fresh[q] = w < A.words ? f[w] & (k ? ~k[w] : ~0u) : 0u;
+        if constexpr (BITS < 32)
+          fresh[q] = (fresh[q] >> (BITS * (uint32_t)((i0 + q) % PER))) & ((1u << BITS) - 1u);
+        c += __builtin_popcount(fresh[q]);
       }
       uint32_t incl = c;
 #pragma unroll
@@ -339,15 +346,16 @@ __global__ void __launch_bounds__(kHiddenThreads) k_hidden_emit(HiddenArgs A) {
       if (lane == kWave - 1) part[wv] = incl;
       __syncthreads();
       uint32_t before = 0, total = 0;
-      for (uint32_t i = 0; i < waves; ++i) {
-        before += i < wv ? part[i] : 0u;
+#pragma unroll
+      for (int i = 0; i < kHiddenThreads / kWave; ++i) {
+        before += (uint32_t)i < wv ? part[i] : 0u;
         total += part[i];
       }
       int64_t at = at0 + before + incl - c;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        for (uint32_t b = fw[q] & ~kw[q]; b != 0u; b &= b - 1u) {
-          const int64_t p = (w0 + q) * 32 + __builtin_ctz(b);
+      for (int q = 0; q < ITEMS; ++q)
+        for (uint32_t b = fresh[q]; b != 0u; b &= b - 1u) {
+          const int64_t p = (i0 + q) * BITS + __builtin_ctz(b);
           if (p < n_pos && at < A.cap) {
             float x, y;
             cell_centre((uint32_t)p, &x, &y);
@@ -358,10 +366,17 @@ __global__ void __launch_bounds__(kHiddenThreads) k_hidden_emit(HiddenArgs A) {
           }
           ++at;
         }
-        if (k && w0 + q < A.words && (fw[q] & ~kw[q]) != 0u) k[w0 + q] = kw[q] | fw[q];
-      }
       at0 += total;
-      __syncthreads();  // part is rewritten for the next round
+      __syncthreads();  // part is rewritten for the next round, and every known word was read
+      if (k && c != 0u) {
+        if constexpr (BITS == 32) {
+#pragma unroll
+          for (int q = 0; q < ITEMS; ++q)
+            if (fresh[q] != 0u) k[i0 + q] |= fresh[q];
+        } else {
+          atomicOr(k + i0 / PER, fresh[0] << (BITS * (uint32_t)(i0 % PER)));
+        }
+      }
     }
   }
 }
@@ -491,13 +506,19 @@ static uint32_t span_blocks(int64_t cap) {
 
 extern "C" hipError_t emr_launch_hidden(const emr::HiddenArgs* A, int step, hipStream_t s) {
   const uint32_t gb = A->n_genomes == 0 ? 1 : (A->n_genomes > 65535 ? 65535 : A->n_genomes);
-  const uint32_t threads = A->words <= emr::kShortWords ? 256 : emr::kHiddenThreads;
   switch (step) {
     case 0:
       hipLaunchKernelGGL(emr::k_hidden_mark, dim3(span_blocks(A->rec.cap)), dim3(256), 0, s, *A);
       break;
-    case 1: hipLaunchKernelGGL(emr::k_hidden_count, dim3(gb), dim3(threads), 0, s, *A); break;
-    case 2: hipLaunchKernelGGL(emr::k_hidden_emit, dim3(gb), dim3(threads), 0, s, *A); break;
+    case 1:
+      hipLaunchKernelGGL(emr::k_hidden_count, dim3(gb), dim3(emr::kHiddenThreads), 0, s, *A);
+      break;
+    case 2:
+      if (A->words <= emr::kShortWords)
+        hipLaunchKernelGGL(emr::k_hidden_emit<4>, dim3(gb), dim3(emr::kHiddenThreads), 0, s, *A);
+      else
+        hipLaunchKernelGGL(emr::k_hidden_emit<32>, dim3(gb), dim3(emr::kHiddenThreads), 0, s, *A);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -1105,6 +1105,8 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
   const int cus = device_cu_count();
   const bool records = out != nullptr && raw == nullptr;
   const int mode = records ? emr::kModeRecords : emr::kModeRaw;
+  // a raw call's only flag is its error word, which its kernels raise in the pinned word itself
+  const bool hand_over = records || !finalize;
   // With theta >= 0 a position-independent output keeps no cell (its variance is exactly 0): the
   // record mode leaves those groups (the last of each part) out of the launch, and the
   // compaction gives their pairs no records without reading their counts.
@@ -1135,7 +1137,7 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     a.bias_tab = T.bias;
     a.status = (uint64_t*)(ws + P.off_status);
     a.nz = (uint64_t*)(ws + P.off_nz);
-    a.err = flags;
+    a.err = hand_over ? flags : flags_host;
     a.pool_parent = pool_parent;
     a.pool_w4 = pool_w4;
     a.pair_total = records ? (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride) : nullptr;
@@ -1237,15 +1239,15 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     return EMR_OK;
   }
   if (records) HIP_OR_FAIL(emr_launch_fill(out->pair_offset, 2, 0u, s));  // no pairs: offset 0
-  if (finalize) HIP_OR_FAIL(emr_launch_finalize(flags, flags_host, s));
+  if (hand_over && finalize) HIP_OR_FAIL(emr_launch_finalize(flags, flags_host, s));
   return EMR_OK;
 }
 
 // The plan's own device tables and bias rows and the depth's tile geometry table (each made on
 // first use).
 emr_status call_tables(const emr_population* pop, const Plan& P, const CallFlags& f,
-                       CallTables* T) {
-  emr_status st = plan_device(pop, P, f.s, f.dev + emr::kFlagErr);
+                       CallTables* T, bool raw = false) {
+  emr_status st = plan_device(pop, P, f.s, (raw ? f.host_dev : f.dev) + emr::kFlagErr);
   if (st != EMR_OK) return st;
   T->tables = P.d_tables;
   T->bias = P.d_bias;
@@ -1308,7 +1310,7 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
   CallTables T;
-  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
+  if ((st = call_tables(pop, P, f, &T, out == nullptr || raw != nullptr)) != EMR_OK) return st;
   bool jit = false;
   if ((st = jit_use(pop, P, plan_slots(P), &jit)) != EMR_OK) return st;
   const bool records = out != nullptr && raw == nullptr;
@@ -1620,7 +1622,8 @@ emr_status emr_eval_raw_noalloc(const emr_population* pop, const emr_source* sou
   const size_t off_geo = align256(P.img.size());
   const size_t off_bias = align256(off_geo + (size_t)geo_rows * 16);
   const size_t off_ws = align256(off_bias + P.bias_table_floats() * sizeof(float));
-  const size_t need = off_ws + P.total;
+  // (the workspace of a raw call: what precedes the second set of totals; nothing is written there)
+  const size_t need = off_ws + align256(P.off_ptotal + (size_t)P.n_pairs * 4);
   if (need > (size_t)EMR_NOALLOC_SCRATCH_BYTES)
     return fail(EMR_E_LIMIT, "the call needs %zu bytes of scratch; the allocation-free scratch "
                 "holds %d", need, EMR_NOALLOC_SCRATCH_BYTES);
@@ -1915,6 +1918,8 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
   st = jit_use(pop, P, plan_slots(P) * (double)(total - start) / (double)total, &jit);
   if (st != EMR_OK) return st;
 
+  bool cleared = false;
+  uint32_t turn = 0;
   // Chunk c on the compute stream: discover + compact over its tiles into buffer c & 1, then its
   // counts and the call's error word to pinned memory.
   auto enqueue = [&](int64_t c) -> emr_status {
@@ -1924,8 +1929,11 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     emr_result chunk_out{R.g_parent[b], R.g_w4[b], records, R.counts, R.offsets, R.ws,
                          R.ws_bytes};
     // k_compact also writes the chunk's counts and the call's error bits to the pinned words
+    // (each chunk's compaction clears the marks and the other set of totals for the next chunk)
     emr_status e = launch_range(pop, P, T, theta, &chunk_out, nullptr, R.ws, R.s, tile_lo, n, jit,
-                                f.dev, f.host_dev, false, true, true, R.counts_h_dev[b]);
+                                f.dev, f.host_dev, false, !cleared, true, R.counts_h_dev[b], turn);
+    cleared = true;
+    turn = 1 - turn;
     if (e != EMR_OK) return e;
     HIP_OR_FAIL(hipEventRecord(R.ev_count[b], R.s));
     return EMR_OK;

@@ -83,7 +83,7 @@ def test_stepwise_and_fused_agree(built):
     """The heaviest genome runs stepwise in a call of 4 patterns and fused in one of 16384; a call
     of 1025 steps runs every genome stepwise, one of 1024 none of the small ones."""
     net, nets = built
-    assert max(len(n["src"]) for n in nets) > 16384
+    assert max(len(n["src"]) for n in nets) > 16384  # (twice the least that runs stepwise)
     x = np.random.default_rng(9).uniform(-1, 1, (16384, 5)).astype(np.float32)
     many = net.activate(x, 2)[:, :4, 0].copy()
     few = net.activate(x[:4], 2)[:, :, 0].copy()

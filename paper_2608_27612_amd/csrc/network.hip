@@ -560,52 +560,77 @@ constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4E, kDppXor1 = 0x
 // the run: lane group t = lane / Q holds partials t, t + S, t + 2 S, ... (S = 64 / Q), the high
 // bits of k are folded inside the lane and the low ones across lanes. The stages over 32 and 16
 // lanes leave one of the four patterns per row of 16 lanes, so the rest and the sigmoid run once
-// for all four: the lane returns the sum of pattern 4 q + lane / 16. The next 64 edges are loaded
-// while the current ones are summed.
-template <int Q>
-__device__ __forceinline__ float node_sum(const float4* x, const uint32_t* __restrict__ src,
-                                           const float* __restrict__ wt, uint32_t deg,
-                                           uint32_t base, uint32_t n, uint32_t lane) {
+// for all four: the lane returns the sum of pattern 4 q + lane / 16.
+//
+// The vector unit is what bounds these kernels, so the loop over whole batches of 64 edges holds
+// only the multiply-adds and one address each: no bounds (x(s) reads the state of node s for the
+// lane's q: from LDS, where an index outside would read zero, or checked, from memory) and no
+// selects. AHEAD loads the next batch's sources and weights into a second register set: the
+// stepwise kernel, whose batches wait for two trips to memory, needs it (55 -> 38 us a step); 32
+// waves per CU hide the fused kernel's loads, and there the second set spilled (396 against 366
+// us). The last, partial batch masks its lanes.
+template <int Q, bool AHEAD, typename X>
+__device__ __forceinline__ float node_sum(X&& x, const uint32_t* __restrict__ src,
+                                          const float* __restrict__ wt, uint32_t deg,
+                                          uint32_t lane) {
   constexpr uint32_t S = kWave / Q;
-  const uint32_t q = lane % Q, t = lane / Q;
+  const uint32_t t = lane / Q;
   float4 acc[Q];
-  uint32_t s[Q];
-  float w[Q];
 #pragma unroll
   for (int j = 0; j < Q; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-  // (src and wt step along the list, so a lane's offsets from them stay constant)
-  auto load = [&](uint32_t left) {
+  auto add = [&](const uint32_t (&s)[Q], const float (&w)[Q]) {
+    float4 v[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) v[j] = x(s[j]);
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-      const uint32_t k = S * (uint32_t)j + t;
-      s[j] = n;  // (no edge: adds nothing)
-      w[j] = 0.0f;
-      if (k < left) {
-        s[j] = src[k] - base;  // (below n: k_net_gather checked every source)
-        w[j] = wt[k];
-      }
+      acc[j].x = fmaf(w[j], v[j].x, acc[j].x);
+      acc[j].y = fmaf(w[j], v[j].y, acc[j].y);
+      acc[j].z = fmaf(w[j], v[j].z, acc[j].z);
+      acc[j].w = fmaf(w[j], v[j].w, acc[j].w);
+    }
+  };
+  // (src and wt step along the list, so a lane's offsets from them stay constant)
+  auto load = [&](uint32_t (&s)[Q], float (&w)[Q]) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      s[j] = src[S * (uint32_t)j + t];
+      w[j] = wt[S * (uint32_t)j + t];
     }
     src += kWave;
     wt += kWave;
   };
-  load(deg);
-  while (deg != 0u) {
-    float4 v[Q];
-    float u[Q];
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (s[j] < n) v[j] = x[s[j] * Q + q];
-      u[j] = w[j];
+  uint32_t s0[Q], s1[Q];
+  float w0[Q], w1[Q];
+  uint32_t whole = deg / kWave;
+  if constexpr (AHEAD) {
+    if (whole != 0u) load(s0, w0);
+    while (whole >= 2u) {
+      load(s1, w1);
+      add(s0, w0);
+      if (whole >= 3u) load(s0, w0);
+      add(s1, w1);
+      whole -= 2u;
     }
-    deg = deg > (uint32_t)kWave ? deg - kWave : 0u;
-    if (deg != 0u) load(deg);
+    if (whole != 0u) add(s0, w0);
+  } else {
+    for (; whole != 0u; --whole) {
+      load(s0, w0);
+      add(s0, w0);
+    }
+  }
+  const uint32_t left = deg % kWave;
 #pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      acc[j].x = fmaf(u[j], v[j].x, acc[j].x);
-      acc[j].y = fmaf(u[j], v[j].y, acc[j].y);
-      acc[j].z = fmaf(u[j], v[j].z, acc[j].z);
-      acc[j].w = fmaf(u[j], v[j].w, acc[j].w);
+  for (int j = 0; j < Q; ++j) {
+    if (S * (uint32_t)j >= left) break;  // (the wave's)
+    const uint32_t k = S * (uint32_t)j + t;
+    if (k < left) {
+      const float4 v = x(src[k]);
+      const float w = wt[k];
+      acc[j].x = fmaf(w, v.x, acc[j].x);
+      acc[j].y = fmaf(w, v.y, acc[j].y);
+      acc[j].z = fmaf(w, v.z, acc[j].z);
+      acc[j].w = fmaf(w, v.w, acc[j].w);
     }
   }
 #pragma unroll
@@ -624,8 +649,8 @@ __device__ __forceinline__ float node_sum(const float4* x, const uint32_t* __res
 // All steps of one genome for one block of 4 Q patterns. One launch per step over global states
 // gathers 16 bytes per edge and four patterns from L2 (150 networks, 0.51M edges, 1000 patterns, 4
 // steps: 2560 us); here the gathers are LDS reads, the edges are read once per 4 Q patterns and
-// the steps need no launches between them (468 us; bound by the instructions of the many small
-// nodes' sums and the latency of their edge loads, which 32 waves per CU hide). The states of its nodes live in two LDS
+// the steps need no launches between them (366 us; bound by the vector instructions: a node's sum
+// and sigmoid beside its few edges). The states of its nodes live in two LDS
 // buffers (swapped by each step), one wave per node and step, the edges read from L2. An input
 // node holds its pattern values in both buffers. The node's first edge (bit 31: an input node) is
 // kept in LDS after the states.
@@ -656,12 +681,13 @@ __device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_
   }
   __syncthreads();
   for (uint32_t step = 0; step < A.steps; ++step) {
+    const float4* mine = cur + lane % Q;  // the lane's patterns
     for (uint32_t i = wave; i < n; i += kNetRunThreads / kWave) {
       const uint32_t f = __builtin_amdgcn_readfirstlane(first[i]);
       if (f >> 31) continue;
       const uint32_t l = __builtin_amdgcn_readfirstlane(first[i + 1]) & 0x7FFFFFFFu;
-      const float z = node_sum<Q>(cur, A.in_src + e0 + f, A.in_w + e0 + f, l > f ? l - f : 0u,
-                                  (uint32_t)n0, n, lane);
+      const float z = node_sum<Q, false>([&](uint32_t s) { return mine[(s - (uint32_t)n0) * Q]; },
+                                  A.in_src + e0 + f, A.in_w + e0 + f, l > f ? l - f : 0u, lane);
       if (lane % 16u < (uint32_t)Q)
         reinterpret_cast<float*>(nxt + i * Q + lane % 16u)[lane / 16u] = sigmoid_f(z);
     }
@@ -753,8 +779,11 @@ __global__ void __launch_bounds__(kNetThreads) k_net_step(NetStepArgs A) {
       continue;
     }
     const int64_t e0 = A.in_offset[i];
-    const float z = node_sum<1>(cur + n0, A.in_src + e0, A.in_w + e0,
-                                 (uint32_t)(A.in_offset[i + 1] - e0), (uint32_t)n0, n, lane);
+    const float z = node_sum<1, true>(
+        [&](uint32_t s) {
+          return (int64_t)s < A.nodes ? cur[s] : make_float4(0.f, 0.f, 0.f, 0.f);
+        },
+        A.in_src + e0, A.in_w + e0, (uint32_t)(A.in_offset[i + 1] - e0), lane);
     if (lane % 16u == 0u) reinterpret_cast<float*>(nxt + i)[lane / 16u] = sigmoid_f(z);
   }
 }

@@ -1931,7 +1931,8 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     // k_compact also writes the chunk's counts and the call's error bits to the pinned words
     // (each chunk's compaction clears the marks and the other set of totals for the next chunk)
     emr_status e = launch_range(pop, P, T, theta, &chunk_out, nullptr, R.ws, R.s, tile_lo, n, jit,
-                                f.dev, f.host_dev, false, !cleared, true, R.counts_h_dev[b], turn);
+                                f.dev, f.host_dev, c == n_chunks - 1, !cleared, true,
+                                R.counts_h_dev[b], turn);
     cleared = true;
     turn = 1 - turn;
     if (e != EMR_OK) return e;
@@ -1999,13 +2000,9 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     }
     if (next) *next = (c + 1) * n_pairs;
   }
-  HIP_OR_FAIL(emr_launch_finalize(f.dev, f.host_dev, R.s));
-  HIP_OR_FAIL(hipStreamSynchronize(R.s));
+  // (the last chunk's compaction handed the call's flags over, and every chunk was waited for and
+  // its errors checked above)
   f.ok = true;
-  const uint32_t err = f.host[emr::kFlagErr];
-  if (err)
-    return fail(EMR_E_DEVICE, "kernel reported error flags 0x%x (2: a table entry out of "
-                "range)", err);
   return EMR_OK;
 }
 

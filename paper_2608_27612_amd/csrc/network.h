@@ -99,6 +99,7 @@ struct NetFlagArgs {
   int64_t* node_offset;     // [n_genomes + 1] (k_net_number)
   uint32_t n_sub;
   uint32_t n_genomes;
+  int64_t* total;           // node_offset[n_genomes] once more, beside the pass words
 };
 
 constexpr int kNetPasses = 6;  // reach passes enqueued before the host looks at them
@@ -142,7 +143,7 @@ struct NetKeyArgs {
   uint64_t* val;            // [raw edges] source's kept number | weight bits << 32
   int64_t edges;            // raw edges
   int64_t nodes;            // raw nodes
-  uint32_t sentinel;        // raw nodes in all
+  uint32_t sentinel;        // kept nodes in all
   uint32_t* err;
 };
 

@@ -381,7 +381,10 @@ __global__ void __launch_bounds__(kNetThreads) k_net_number(NetFlagArgs A) {
     if (g < A.n_genomes) A.node_offset[g] = run + e;
     run += t;
   }
-  if (threadIdx.x == 0) A.node_offset[A.n_genomes] = run;
+  if (threadIdx.x == 0) {
+    A.node_offset[A.n_genomes] = run;
+    *A.total = run;
+  }
 }
 
 // ------------------------------------------------------------------------ kept nodes

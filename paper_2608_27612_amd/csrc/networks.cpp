@@ -472,7 +472,11 @@ emr_status assemble(Build& B) {
   Dev rank, hidden, err, d_tab, raw_node, raw_edge, seg, eu, ev, ew, flags, kept_n, gid, sum;
   NET_TRY(alloc(rank, (size_t)G * (size_t)N.words * 4, "bitmap ranks", s));
   NET_TRY(alloc(hidden, (size_t)G * 4, "hidden counts", s));
-  NET_TRY(alloc(err, 4 * (1 + emr::kNetPasses), "error and pass words", s));
+  // the error word, the pass words and, after the last of them, the kept node count: the host reads
+  // the last pass word and the count in one copy
+  static_assert((2 + emr::kNetPasses) % 2 == 0, "the count is 8-byte aligned");
+  const size_t err_bytes = 4 * (2 + emr::kNetPasses) + 8;
+  NET_TRY(alloc(err, err_bytes, "error and pass words", s));
   NET_TRY(alloc(d_tab, tab.size() * 8, "phase tables", s));
   NET_TRY(alloc(raw_node, (size_t)(G + 1) * 8, "node offsets", s));
   NET_TRY(alloc(raw_edge, (size_t)(G + 1) * 8, "edge offsets", s));
@@ -490,7 +494,7 @@ emr_status assemble(Build& B) {
   NET_TRY(alloc(N.in_offset, (size_t)(n_raw + 1) * 8, "network edge offsets", s));
   NET_TRY(alloc(N.in_src, (size_t)e_raw * 4, "network edges", s));
   NET_TRY(alloc(N.in_w, (size_t)e_raw * 4, "network edges", s));
-  NET_HIP(hipMemsetAsync(err.p, 0, 4 * (1 + emr::kNetPasses), s));
+  NET_HIP(hipMemsetAsync(err.p, 0, err_bytes, s));
   NET_TRY(to_device(d_tab.p, tab.data(), tab.size() * 8, s));
   uint32_t* d_err = err.as<uint32_t>();
   const uint8_t* d_dir = reinterpret_cast<const uint8_t*>(d_tab.as<uint64_t>() + 2 * K);
@@ -543,12 +547,24 @@ emr_status assemble(Build& B) {
   }
   // pruning: flags, then passes over every edge until one changes nothing
   emr::NetFlagArgs fa{d_dir, raw_node.as<int64_t>(), flags.as<uint16_t>(), kept_n.as<uint32_t>(),
-                      N.node_offset.as<int64_t>(), (uint32_t)N.n_sub, G};
+                      N.node_offset.as<int64_t>(), (uint32_t)N.n_sub, G,
+                      reinterpret_cast<int64_t*>(d_err + 2 + emr::kNetPasses)};
   NET_HIP(emr_launch_net(4, &fa, 0, s));
   emr::NetReachArgs rr{eu.as<uint32_t>(), ev.as<uint32_t>(), flags.as<uint16_t>(), d_err + 1, 0u,
                        e_raw, n_raw};
   // a pass that changes something sets at least one more flag: 2 n_raw passes bound the loop
   const int64_t max_pass = 2 * n_raw + 2;
+  emr::NetNodeArgs na{N.known.as<uint32_t>(), rank.as<uint32_t>(), N.words,
+                      raw_node.as<int64_t>(), flags.as<uint16_t>(), N.d_slots.as<int32_t>(),
+                      N.node_offset.as<int64_t>(), gid.as<uint32_t>(), N.node_cell.as<uint32_t>(),
+                      N.node_in.as<int32_t>(), d_err, (uint32_t)N.n_sub, G};
+  // Each batch of passes ends with the numbering its flags give, which stands if the batch settled:
+  // the wait that looks at the passes then brings the kept node count too.
+  int64_t kept_nodes = (int64_t)G * N.n_sub;  // (without edges nothing but the substrate is kept)
+  if (e_raw == 0) {
+    NET_HIP(emr_launch_net(6, &fa, 0, s));
+    NET_HIP(emr_launch_net(7, &na, 0, s));
+  }
   for (int64_t pass = 0; e_raw > 0; pass += emr::kNetPasses) {
     if (pass > max_pass)
       return failf(EMR_E_DEVICE, "networks: pruning did not settle in %lld passes",
@@ -556,18 +572,22 @@ emr_status assemble(Build& B) {
     if (pass > 0) NET_HIP(hipMemsetAsync(d_err + 1, 0, 4 * emr::kNetPasses, s));
     for (rr.pass = 0; rr.pass < (uint32_t)emr::kNetPasses; ++rr.pass)
       NET_HIP(emr_launch_net(5, &rr, 0, s));
-    uint32_t ch = 0;
-    NET_TRY(to_host(&ch, d_err + emr::kNetPasses, 4, s));
-    if (ch == 0) break;
+    NET_HIP(emr_launch_net(6, &fa, 0, s));
+    NET_HIP(emr_launch_net(7, &na, 0, s));
+    struct { uint32_t changed, unused; int64_t kept; } seen;
+    static_assert(sizeof seen == 16, "the last pass word, a word between, the count");
+    NET_TRY(to_host(&seen, d_err + emr::kNetPasses, sizeof seen, s));
+    if (seen.changed != 0) continue;
+    if (seen.kept < 0 || seen.kept > n_raw)
+      return failf(EMR_E_DEVICE, "networks: %lld kept nodes of %lld", (long long)seen.kept,
+                   (long long)n_raw);
+    kept_nodes = seen.kept;
+    break;
   }
-  NET_HIP(emr_launch_net(6, &fa, 0, s));
-  emr::NetNodeArgs na{N.known.as<uint32_t>(), rank.as<uint32_t>(), N.words,
-                      raw_node.as<int64_t>(), flags.as<uint16_t>(), N.d_slots.as<int32_t>(),
-                      N.node_offset.as<int64_t>(), gid.as<uint32_t>(), N.node_cell.as<uint32_t>(),
-                      N.node_in.as<int32_t>(), d_err, (uint32_t)N.n_sub, G};
-  NET_HIP(emr_launch_net(7, &na, 0, s));
-  // kept edges grouped by destination, each group in raw order: a stable sort by destination
-  const uint32_t sentinel = (uint32_t)n_raw;
+  // kept edges grouped by destination, each group in raw order: a stable sort by destination. The
+  // dropped edges' key is the kept node count: a key past the raw node count would cost a third
+  // radix pass where 17 bits number the raw nodes and 16 the kept ones.
+  const uint32_t sentinel = (uint32_t)kept_nodes;
   Dev keys, vals, skeys, svals, tmp;
   NET_TRY(alloc(keys, (size_t)e_raw * 4, "edge keys", s));
   NET_TRY(alloc(vals, (size_t)e_raw * 8, "edge values", s));

@@ -60,3 +60,28 @@ def test_population_freed_after_its_first_call(emr):
         del pop
         for x, y in zip(bits(emr, res), want):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("default,roomy", [(1 << 16, 1 << 17),   # the usual buffers hold the records
+                                           (100, 1 << 17),       # only the roomy ones do
+                                           (100, 200)])          # neither does
+def test_roomy_first_run(emr, monkeypatch, default, roomy):
+    """emr_discover_all of a long call: the same records, capacity and later checks as of a short
+    one, which runs a second time at the total that it found."""
+    genomes, sources = W.population(12, 80, 20, 60), W.xor_sources()
+    pop = emr.emr_pack_population(genomes)
+    monkeypatch.setattr(emr, "DEFAULT_CAPACITY", default)
+    want = emr.emr_discover_all(pop, sources, 6, 0.01)
+    total = int(want["pair_offset"][-1].item())
+    assert 200 < total < (1 << 16)
+    monkeypatch.setattr(emr, "ROOMY_POSITIONS", 1)
+    monkeypatch.setattr(emr, "ROOMY_CAPACITY", roomy)
+    got = emr.emr_discover_all(pop, sources, 6, 0.01)
+    assert got["capacity"] == want["capacity"] == max(total, default)
+    assert got["parent"].shape == want["parent"].shape and got["w4"].shape == want["w4"].shape
+    assert emr.emr_result_check(got)[0] == total
+    for key, n in (("pair_count", None), ("pair_offset", None), ("parent", total), ("w4", total)):
+        assert torch.equal(got[key][:n], want[key][:n]), key
+    again = emr.emr_discover(pop, sources, 6, 0.01, res=got)  # the result's buffers, used again
+    assert emr.emr_result_check(again)[0] == total
+    assert torch.equal(again["w4"][:total], want["w4"][:total])

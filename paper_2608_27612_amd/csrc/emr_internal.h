@@ -328,7 +328,8 @@ struct DiscoverArgs {
 // Arguments of the compaction of one record-mode range (k_compact: ScanArgs for the offsets,
 // MoveArgs for the records; a wave per pair) and of k_scan (offsets of a call's genomes).
 struct ScanArgs {
-  uint32_t* pair_total;  // [n_pairs] per-pair totals of the range (cleared by k_scan after use)
+  uint32_t* pair_total;  // [n_pairs] totals of the range's pairs (k_compact: the next call clears
+                         // them), or of a call's genomes (k_scan clears them after use)
   uint32_t* clear_total; // k_compact: [n_pairs] the previous call's totals, cleared for the next
   PairBucket* buckets;   // k_compact: [n_buckets(n_pairs)]
   int64_t* pair_count;   // [n_pairs] out

@@ -418,12 +418,14 @@ def emr_result_check(res, stream=None):
 
 # A call of this many parent positions or more runs for milliseconds, and finding more than
 # DEFAULT_CAPACITY records it would run a second time: emr_discover_all gives it room for
-# ROOMY_CAPACITY records (3 GB while it runs) and then moves the records into buffers of the usual
-# size. Two populations of 100 CPPNs whose hidden nodes at depth 10 find more than that: 37.1 -> 19.8
+# ROOMY_CAPACITY records (3 GB while it runs, of which the 1.3 GB workspace stays with the result) and
+# then moves the records into buffers of the usual size. Two populations of 100 CPPNs whose hidden nodes at depth 10 find more than that: 37.1 -> 19.8
 # and 78.5 -> 41.1 ms; one that finds less pays a copy (9.4 -> 9.5 ms). Shorter calls keep the small
-# buffers: their second run is cheap.
+# buffers: their second run is cheap. So do calls on a device with less than ROOMY_FREE bytes to
+# spare (a program that keeps many results).
 ROOMY_POSITIONS = 1 << 27
 ROOMY_CAPACITY = 1 << 26
+ROOMY_FREE = 24 << 30
 
 
 def _roomy_result(pop, sources, depth, src_offsets):
@@ -431,7 +433,7 @@ def _roomy_result(pop, sources, depth, src_offsets):
     import torch
     _, q = emr_grid_count(depth)
     cap = n_pairs_of(pop, sources, src_offsets) * q
-    if cap < ROOMY_POSITIONS:
+    if cap < ROOMY_POSITIONS or torch.cuda.mem_get_info()[0] < ROOMY_FREE:
         return None
     try:
         return alloc_result(pop, sources, depth, src_offsets, min(cap, ROOMY_CAPACITY))

@@ -138,12 +138,13 @@ __global__ void __launch_bounds__(256) k_filter_count(Op op) {
 }
 
 // The kept entries of the spans before this one (n_spans at most kFilterSpans, read by the
-// workgroup: 32 loads per thread at most).
-__device__ __forceinline__ uint64_t spans_before(const uint32_t* kept, uint64_t* wsum) {
+// workgroup: 32 loads per thread at most; the spans from `used` on hold no entries).
+__device__ __forceinline__ uint64_t spans_before(const uint32_t* kept, uint32_t used,
+                                                 uint64_t* wsum) {
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, waves = blockDim.x / kWave;
-  const uint32_t first = blockIdx.x * waves;
+  const uint32_t first = blockIdx.x * waves, read = min(first, used);
   uint64_t sum = 0;
-  for (uint32_t k = threadIdx.x; k < first; k += blockDim.x) sum += kept[k];
+  for (uint32_t k = threadIdx.x; k < read; k += blockDim.x) sum += kept[k];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
   if (lane == 0) wsum[wv] = sum;
@@ -162,7 +163,12 @@ __global__ void __launch_bounds__(256) k_filter_emit(Op op) {
   const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
   const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
   const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
-  int64_t at0 = (int64_t)spans_before(op.spans.kept, wsum);
+  // The spans are those of the capacity: of a light call's, most workgroups have no entries and
+  // leave before the sums (the last one writes the total): the filters of a tabular result 344 ->
+  // 338 us, of 432 records 262 -> 252 us.
+  const uint32_t used = len > 0 ? (uint32_t)((held + len - 1) / len) : 0u;
+  if (blockIdx.x + 1 < gridDim.x && blockIdx.x * (blockDim.x / kWave) >= used) return;
+  int64_t at0 = (int64_t)spans_before(op.spans.kept, used, wsum);
   if (op.off()[0] <= 0)
     for_span(
         op.off(), n, base, min(base + len, held), lane,

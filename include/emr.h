@@ -166,10 +166,9 @@ typedef struct {
  * tile-group marks and per-pair record totals, the folded per-(genome, source) biases, and a
  * record pool of `capacity` records (20 bytes each) that the discover kernel fills in any order
  * and the compaction gathers from. A call's error flags, largest count and total live in a
- * library-owned slot (see emr_result_check). A record call leaves the workspace's counters cleared,
- * and the next record call with the same workspace, plan (population, sources, depth), capacity
- * and stream does not clear them again: do not write into a workspace between calls (any other
- * call with it, or a change of any of those, makes the next call clear it first). EMR_E_INVAL for
+ * library-owned slot (see emr_result_check), and the marks and totals that consecutive calls leave
+ * cleared for each other in memory of the population's plan: the workspace keeps nothing from one
+ * call to the next, so its memory may be used for anything once a call has completed. EMR_E_INVAL for
  * a capacity outside [0, 2^32 - 1]. Host only. (The grouping
  * tables of a call live with the population: it keeps those of its last sources and depth on the
  * device, and a call with different ones replaces them.) */

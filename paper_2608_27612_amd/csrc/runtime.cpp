@@ -347,11 +347,27 @@ struct JitModule {
 
 // Everything one discover / raw-eval call needs besides the population: the host-built tables
 // (emr::PlanTables) and their device copies, schedules and compiled tier.
-std::atomic<uint64_t> g_plan_ids{0};
+struct FlagRing;
+
+// The counters of record calls in flight one after the other: the tile-group marks and two sets of
+// per-pair totals, laid out as in a workspace. A call's compaction clears the marks and the totals
+// that the next call will use (the other of the two sets), so calls on one stream need no clearing
+// launch between them. They lie in the plan's own memory, which nothing else writes: a workspace is
+// the caller's, and what it held after a call says nothing about what it holds at the next.
+struct CounterSet {
+  char* d = nullptr;
+  bool own = false;        // its own allocation (the first set follows the plan's bias rows)
+  bool busy = false;       // a call is being enqueued with it
+  bool clean = false;      // the marks and the totals of `turn` are zero in stream order
+  uint32_t turn = 0;       // the set of totals that the next call uses
+  hipStream_t s = nullptr; // the last call's stream and flag slot
+  FlagRing* ring = nullptr;
+  int slot = -1;
+  uint64_t seq = 0;
+};
+constexpr size_t kCounterSets = 8;  // of a plan, at most
 
 struct Plan : emr::PlanTables {
-  // Distinct for every plan the process builds (a freed plan's address may be reused).
-  const uint64_t id = ++g_plan_ids;
   mutable std::mutex dev_mu;
   // The tables' device copy, uploaded on first use and freed with the plan.
   mutable char* d_tables = nullptr;
@@ -383,6 +399,9 @@ struct Plan : emr::PlanTables {
   };
   mutable std::mutex split_mu;
   mutable std::vector<Split> splits;
+  // The plan's counter sets (take_counters).
+  mutable std::mutex counters_mu;
+  mutable std::vector<CounterSet> counters;
   Plan() = default;
   Plan(const Plan&) = delete;
   Plan& operator=(const Plan&) = delete;
@@ -396,7 +415,11 @@ struct Plan : emr::PlanTables {
     if (d_tables) (void)hipFree(d_tables);
     if (d_bias) (void)hipFree(d_bias);
     for (const Sched& x : scheds) (void)hipFree(x.d);
+    for (const CounterSet& x : counters)
+      if (x.own) (void)hipFree(x.d);
   }
+  // Bytes of a counter set: a workspace's group marks and two sets of totals.
+  size_t counter_bytes() const { return off_buckets - off_nz; }
   // The compiled tier (jit_use): built at most once per plan, under jit_mu.
   mutable std::mutex jit_mu;
   mutable std::unique_ptr<JitModule> jit;
@@ -646,6 +669,7 @@ struct CallFlags {
   uint32_t* host_dev = nullptr;  // the pinned words (device view)
   hipStream_t s = nullptr;
   const void* ws = nullptr;
+  uint64_t seq = 0;
   bool ok = false;  // the call's last kernel is enqueued
   CallFlags() = default;
   CallFlags(const CallFlags&) = delete;
@@ -656,7 +680,6 @@ struct CallFlags {
     // the slot's next user waits for whatever this call enqueued
     ring->pending[slot] = hipEventRecord(ring->done[slot], s) == hipSuccess;
     ring->ws[slot] = ok ? ws : nullptr;
-    ring->seq[slot] = ++ring->calls;
     ring->dirty[slot] = !ok;
   }
 };
@@ -674,6 +697,7 @@ emr_status take_flags(const void* workspace, hipStream_t s, CallFlags* f) {
   R->ws[k] = nullptr;
   f->ring = R;
   f->slot = k;
+  f->seq = R->seq[k] = ++R->calls;
   f->dev = R->dev + (size_t)k * kSlotWords;
   f->host = R->host + (size_t)k * kSlotWords;
   f->host_dev = R->host_dev + (size_t)k * kSlotWords;
@@ -723,23 +747,25 @@ emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, 
   if (!P.ready_done.load(std::memory_order_acquire)) {
     std::lock_guard<std::mutex> lock(P.dev_mu);
     if (!P.d_bias) {
-      const size_t n = P.bias_table_floats();
+      // the bias rows, then the plan's first counter set: one allocation, cleared by one launch
+      const size_t n = P.bias_table_floats(), off_set = align256(n * sizeof(float));
+      const size_t bytes = off_set + P.counter_bytes();
       char* d = nullptr;
       float* bias = nullptr;
       StreamPool* sp = nullptr;
       emr_status st = stream_pool(&sp);
       if (st != EMR_OK) return st;
       if (hipMalloc((void**)&d, P.img.size()) != hipSuccess ||
-          hipMalloc((void**)&bias, n * sizeof(float)) != hipSuccess)
-        st = fail(EMR_E_NOMEM, "device tables of %zu bytes and bias rows of %zu floats",
-                  P.img.size(), n);
+          hipMalloc((void**)&bias, bytes) != hipSuccess)
+        st = fail(EMR_E_NOMEM, "device tables of %zu bytes, bias rows and counters of %zu",
+                  P.img.size(), bytes);
       if (st == EMR_OK && !P.ready &&
           hipEventCreateWithFlags(&P.ready, hipEventDisableTiming) != hipSuccess)
         st = fail(EMR_E_DEVICE, "event of the call tables");
       if (st == EMR_OK) st = upload(d, P.img.data(), P.img.size(), sp->aux[0]);
       if (st == EMR_OK) {
         const emr::BindArgs b = bind_args(pop, P, d, bias, err);
-        if (emr_launch_fill(bias, (int64_t)n, 0u, sp->aux[0]) != hipSuccess ||
+        if (emr_launch_fill(bias, (int64_t)(bytes / 4), 0u, sp->aux[0]) != hipSuccess ||
             emr_launch_bind(&b, sp->aux[0]) != hipSuccess ||
             hipEventRecord(P.ready, sp->aux[0]) != hipSuccess)
           st = fail(EMR_E_DEVICE, "computing the bias rows failed");
@@ -752,6 +778,12 @@ emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, 
       }
       P.d_tables = d;
       P.d_bias = bias;
+      CounterSet first;
+      first.d = (char*)bias + off_set;
+      first.clean = true;  // (every call's stream waits for the fill)
+      std::lock_guard<std::mutex> sets(P.counters_mu);
+      P.counters.reserve(kCounterSets);
+      P.counters.push_back(first);
     }
     if (hipEventQuery(P.ready) == hipSuccess) {
       P.ready_done.store(true, std::memory_order_release);
@@ -1080,11 +1112,12 @@ bool cached_split_parts(const Plan& P, const Plan::Launch& L, bool skip_uniform,
 // jit: run the plan's compiled programs (jit_use said so) instead of the interpreter. With
 // `finalize`, the range's last kernel (k_compact for records, k_finalize for raw outputs) then hands
 // the call's flags to their pinned words.
-// With `clear` (record mode), the workspace's group marks and per-pair totals are cleared right
-// before the discover launch, once every argument of that launch is ready on the host.
+// counters (record mode): the range's group marks and totals, a plan's counter set or the
+// workspace's own. With `clear` they are cleared right before the discover launch, once every
+// argument of that launch is ready on the host.
 // flags: the call's device flag words (error bits, largest count); flags_host: their pinned words
 // (device view) for that hand-over.
-// turn: which of the workspace's two sets of totals the range uses (the other is cleared for the
+// turn: which of the counters' two sets of totals the range uses (the other is cleared for the
 // next call).
 // may_alloc: the call may allocate on first use: the thread's launch profiling (its events) and
 // the launch's chunk schedule apply (off for the allocation-free call, which runs its chunks
@@ -1094,7 +1127,7 @@ bool cached_split_parts(const Plan& P, const Plan::Launch& L, bool skip_uniform,
 // round-robin.
 emr_status launch_range(const emr_population* pop, const Plan& P, const CallTables& T,
                         float theta, const emr_result* out, float* raw, void* workspace,
-                        hipStream_t s, int64_t tile_lo, int64_t n_tiles, bool jit,
+                        char* counters, hipStream_t s, int64_t tile_lo, int64_t n_tiles, bool jit,
                         uint32_t* flags, uint32_t* flags_host, bool finalize, bool clear,
                         bool may_alloc = true, int64_t* host_counts = nullptr,
                         uint32_t turn = 0) {
@@ -1104,6 +1137,7 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
   const uint32_t geo_rows = T.geo_rows;
   const int cus = device_cu_count();
   const bool records = out != nullptr && raw == nullptr;
+  char* totals = records ? counters + (P.off_ptotal - P.off_nz) : nullptr;
   const int mode = records ? emr::kModeRecords : emr::kModeRaw;
   // a raw call's only flag is its error word, which its kernels raise in the pinned word itself
   const bool hand_over = records || !finalize;
@@ -1136,11 +1170,11 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     a.groups = jit ? P.jit->d_groups : (const emr::Group*)(tables + P.t_groups);
     a.bias_tab = T.bias;
     a.status = (uint64_t*)(ws + P.off_status);
-    a.nz = (uint64_t*)(ws + P.off_nz);
+    a.nz = (uint64_t*)counters;
     a.err = hand_over ? flags : flags_host;
     a.pool_parent = pool_parent;
     a.pool_w4 = pool_w4;
-    a.pair_total = records ? (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride) : nullptr;
+    a.pair_total = records ? (uint32_t*)(totals + turn * P.ptotal_stride) : nullptr;
     a.raw = raw;
     a.cap = cap;
     a.n_pos = emr::n_positions(P.depth);
@@ -1185,7 +1219,7 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     hipEvent_t e0 = timed ? prof.events[2 * (rec0 + li)] : nullptr;
     hipEvent_t e1 = timed ? prof.events[2 * (rec0 + li) + 1] : nullptr;
     if (li == 0 && clear && records)
-      HIP_OR_FAIL(emr_launch_fill(ws + P.off_nz, P.clear_words, 0u, s));
+      HIP_OR_FAIL(emr_launch_fill(counters, P.clear_words, 0u, s));
     if (jit) {
       emr_status js = jit_launch(P, a, mode, blocks, s, e0, e1);
       if (js != EMR_OK) return js;
@@ -1211,11 +1245,11 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
   }
   if (timed_call) prof.calls++;
   if (clear && records && P.launches.empty())
-    HIP_OR_FAIL(emr_launch_fill(ws + P.off_nz, P.clear_words, 0u, s));
+    HIP_OR_FAIL(emr_launch_fill(counters, P.clear_words, 0u, s));
   if (records && P.n_pairs > 0) {
     emr::ScanArgs S{};
-    S.pair_total = (uint32_t*)(ws + P.off_ptotal + turn * P.ptotal_stride);
-    S.clear_total = (uint32_t*)(ws + P.off_ptotal + (1 - turn) * P.ptotal_stride);
+    S.pair_total = (uint32_t*)(totals + turn * P.ptotal_stride);
+    S.clear_total = (uint32_t*)(totals + (1 - turn) * P.ptotal_stride);
     S.buckets = (emr::PairBucket*)(ws + P.off_buckets);
     S.pair_count = out->pair_count;
     S.pair_offset = out->pair_offset;
@@ -1229,7 +1263,7 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
     M.pool_w4 = pool_w4;
     M.parent = out->parent;
     M.w4 = out->w4;
-    M.nz = (uint64_t*)(ws + P.off_nz);
+    M.nz = (uint64_t*)counters;
     M.skip = skip_uniform ? (const uint8_t*)(tables + P.t_uniform) : nullptr;
     M.cap = cap;
     M.tiles = (uint32_t)n_tiles;
@@ -1254,51 +1288,94 @@ emr_status call_tables(const emr_population* pop, const Plan& P, const CallFlags
   return tile_geo_table(P.depth, &T->geo, &T->geo_rows);
 }
 
-// Workspaces whose counters a record call left cleared: its compaction zeroes every tile-group mark
-// and the pair totals that the next record call will use (its own, or the other of two sets, taken
-// in turn), so the next record call of the same plan on the same stream (stream order puts it
-// after those kernels) needs no clearing launch. Any other call with the workspace forgets it. (A
-// few entries: the latest workspaces of the process.)
-struct CleanWorkspace {
-  const void* ws;
-  uint64_t plan;
-  hipStream_t s;
-  int64_t capacity;
-  uint32_t turn;  // the set of totals that the next call uses
-};
-std::mutex g_clean_mu;
-std::vector<CleanWorkspace> g_clean;
-constexpr size_t kCleanEntries = 64;
-
-bool workspace_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity,
-                     uint32_t* turn) {
-  std::lock_guard<std::mutex> lock(g_clean_mu);
-  *turn = 0;
-  for (const CleanWorkspace& c : g_clean)
-    if (c.ws == ws && c.plan == P.id && c.s == s && c.capacity == capacity) {
-      *turn = c.turn;
-      return true;
-    }
+// Whether the call of a flag slot (its number seq) has completed.
+bool call_done(FlagRing* R, int slot, uint64_t seq) {
+  std::lock_guard<std::mutex> lock(g_ring_mu);
+  if (R->seq[slot] != seq) return true;  // (a slot is taken again only after its last call)
+  if (!R->pending[slot]) return false;
+  if (hipEventQuery(R->done[slot]) == hipSuccess) return true;
+  (void)hipGetLastError();  // (not ready is no error of the caller's)
   return false;
 }
-void workspace_forget(const void* ws) {
-  std::lock_guard<std::mutex> lock(g_clean_mu);
-  for (size_t i = 0; i < g_clean.size(); ++i)
-    if (g_clean[i].ws == ws) {
-      g_clean.erase(g_clean.begin() + (std::ptrdiff_t)i);
-      return;
+
+// A record call's counters, given back when the call is enqueued.
+struct CallCounters {
+  const Plan* P = nullptr;
+  size_t set = 0;
+  char* d = nullptr;
+  bool clear = true;   // the call has to clear them first
+  uint32_t turn = 0;
+  bool ok = false;     // the compaction that leaves them cleared is enqueued
+  CallCounters() = default;
+  CallCounters(const CallCounters&) = delete;
+  CallCounters& operator=(const CallCounters&) = delete;
+  ~CallCounters() {
+    if (!P) return;
+    std::lock_guard<std::mutex> lock(P->counters_mu);
+    CounterSet& x = P->counters[set];
+    x.busy = false;
+    x.clean = ok;
+    x.turn = 1 - turn;
+  }
+};
+
+// Counters for a record call on stream s with the flags f: the plan's set that the stream used last
+// (stream order then puts this call after that one's compaction), else one whose last call has
+// completed, else a new one, else one whose last call the stream waits for. Where that is not
+// possible (a capture, whose replays would run beside the plan's later calls; no memory; every set
+// busy) the call uses the workspace's own and clears them.
+emr_status take_counters(const Plan& P, void* workspace, hipStream_t s, const CallFlags& f,
+                         CallCounters* c) {
+  c->d = (char*)workspace + P.off_nz;
+  c->clear = true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return EMR_OK;
+  std::lock_guard<std::mutex> lock(P.counters_mu);
+  const size_t n = P.counters.size();
+  size_t use = n;
+  bool wait = false;
+  // (one handle stands for a stream of every thread: its calls are ordered by their events)
+  if (s != hipStreamPerThread)
+    for (size_t k = 0; k < n && use == n; ++k)
+      if (!P.counters[k].busy && P.counters[k].ring && P.counters[k].s == s) use = k;
+  for (size_t k = 0; k < n && use == n; ++k) {
+    const CounterSet& x = P.counters[k];
+    if (!x.busy && (!x.ring || call_done(x.ring, x.slot, x.seq))) use = k;
+  }
+  if (use == n && n < kCounterSets) {
+    CounterSet x;
+    x.own = true;
+    if (hipMalloc((void**)&x.d, P.counter_bytes()) == hipSuccess)
+      P.counters.push_back(x);
+    else
+      (void)hipGetLastError();
+  }
+  for (size_t k = 0; k < n && use == P.counters.size(); ++k)
+    if (!P.counters[k].busy) {
+      use = k;
+      wait = true;
     }
-}
-void workspace_mark_clean(const void* ws, const Plan& P, hipStream_t s, int64_t capacity,
-                          uint32_t turn) {
-  std::lock_guard<std::mutex> lock(g_clean_mu);
-  for (CleanWorkspace& c : g_clean)
-    if (c.ws == ws) {
-      c = CleanWorkspace{ws, P.id, s, capacity, turn};
-      return;
+  if (use == P.counters.size()) return EMR_OK;
+  CounterSet& x = P.counters[use];
+  if (wait) {
+    std::lock_guard<std::mutex> ring(g_ring_mu);
+    if (x.ring->seq[x.slot] == x.seq) {
+      if (!x.ring->pending[x.slot]) return EMR_OK;  // (its event could not be recorded)
+      HIP_OR_FAIL(hipStreamWaitEvent(s, x.ring->done[x.slot], 0));
     }
-  if (g_clean.size() >= kCleanEntries) g_clean.erase(g_clean.begin());
-  g_clean.push_back(CleanWorkspace{ws, P.id, s, capacity, turn});
+  }
+  x.busy = true;
+  c->P = &P;
+  c->set = use;
+  c->d = x.d;
+  c->clear = !x.clean;
+  c->turn = x.turn;
+  x.s = s;
+  x.ring = f.ring;
+  x.slot = f.slot;
+  x.seq = f.seq;
+  return EMR_OK;
 }
 
 // Enqueue a whole call: take a flag slot, then every tile of every pair.
@@ -1307,6 +1384,7 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   emr_status st = check_call_workspace(workspace, workspace_bytes,
                                        (int64_t)workspace_need(P, out ? out->capacity : 0));
   if (st != EMR_OK) return st;
+  CallCounters c;  // (given back after the flags: their event is recorded by then)
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
   CallTables T;
@@ -1314,14 +1392,11 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   bool jit = false;
   if ((st = jit_use(pop, P, plan_slots(P), &jit)) != EMR_OK) return st;
   const bool records = out != nullptr && raw == nullptr;
-  const int64_t capacity = records ? out->capacity : -1;
-  uint32_t turn = 0;
-  const bool clean = records && workspace_clean(workspace, P, s, capacity, &turn);
-  workspace_forget(workspace);
-  st = launch_range(pop, P, T, theta, out, raw, workspace, s, 0, P.tiles, jit, f.dev, f.host_dev,
-                    true, !clean, true, nullptr, turn);
+  if (records && (st = take_counters(P, workspace, s, f, &c)) != EMR_OK) return st;
+  st = launch_range(pop, P, T, theta, out, raw, workspace, c.d, s, 0, P.tiles, jit, f.dev,
+                    f.host_dev, true, c.clear, true, nullptr, c.turn);
   if (st != EMR_OK) return st;
-  if (records) workspace_mark_clean(workspace, P, s, capacity, 1 - turn);
+  c.ok = true;
   f.ok = true;
   return EMR_OK;
 }
@@ -1645,7 +1720,7 @@ emr_status emr_eval_raw_noalloc(const emr_population* pop, const emr_source* sou
                                   (uint32_t)geo_rows, s));
   const emr::BindArgs bind = bind_args(pop, P, scr, (float*)(scr + off_bias), err_dev);
   HIP_OR_FAIL(emr_launch_bind(&bind, s));
-  return launch_range(pop, P, T, 0.0f, nullptr, out_dev, ws, s, 0, P.tiles, false, err_dev,
+  return launch_range(pop, P, T, 0.0f, nullptr, out_dev, ws, nullptr, s, 0, P.tiles, false, err_dev,
                       nullptr, false, false, false);
 }
 
@@ -1930,7 +2005,8 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
                          R.ws_bytes};
     // k_compact also writes the chunk's counts and the call's error bits to the pinned words
     // (each chunk's compaction clears the marks and the other set of totals for the next chunk)
-    emr_status e = launch_range(pop, P, T, theta, &chunk_out, nullptr, R.ws, R.s, tile_lo, n, jit,
+    emr_status e = launch_range(pop, P, T, theta, &chunk_out, nullptr, R.ws,
+                                (char*)R.ws + P.off_nz, R.s, tile_lo, n, jit,
                                 f.dev, f.host_dev, c == n_chunks - 1, !cleared, true,
                                 R.counts_h_dev[b], turn);
     cleared = true;

@@ -1,7 +1,8 @@
-"""A workspace reused by consecutive record calls: a call leaves its counters cleared and the next
-call of the same plan, capacity and stream does not clear them again. Every call's records must
-equal those of a call on a fresh workspace, bit for bit, across changes of theta, interleaved raw
-calls, another plan on the same workspace and a capacity overflow."""
+"""A workspace reused by consecutive record calls: the counters that a call leaves cleared for the
+next one lie with the plan, not in the workspace. Every call's records must equal those of a call on
+a fresh workspace, bit for bit, across changes of theta, interleaved raw calls, another plan on the
+same workspace, a capacity overflow, anything written into the workspace between two calls, and more
+streams than the plan keeps counters for."""
 
 import numpy as np
 import pytest
@@ -148,3 +149,72 @@ def test_calls_in_flight_on_their_own_streams(emr, depth, n, in_flight):
     assert emr.emr_jit_info(pop)["state"] == 1
     for g in got:
         same(g, want)
+
+
+@pytest.mark.parametrize("depth,n", [(6, 300), (8, 100)])
+def test_workspace_written_between_calls(emr, depth, n):
+    """The memory of a workspace belongs to its caller: what is written into it between two calls, or
+    by another tensor in a block that the allocator hands out again, changes nothing."""
+    import torch
+    pop = emr.emr_pack_population(W.population(74, n, 20, 60))
+    sources = W.xor_sources()
+    theta = np.float32(0.03).item()
+    res = emr.emr_discover_all(pop, sources, depth, theta)
+    want = host(emr, res)
+    for byte in (1, 255):
+        res["workspace"].fill_(byte)
+        emr.emr_discover(pop, sources, depth, theta, res=res)
+        emr.emr_result_check(res)
+        same(host(emr, res), want)
+    size = res["workspace"].numel()
+    del res
+    torch.empty(size, dtype=torch.uint8, device="cuda").fill_(1)
+    same(host(emr, emr.emr_discover_all(pop, sources, depth, theta)), want)
+
+
+def test_builds_of_one_population_around_another(emr):
+    """Builds without hidden phases keep the population's plan: a second build, after another
+    population's build used the library's buffers, gives the same networks."""
+    def nets(pop):
+        return emr.emr_build_networks(pop, sources, 6, theta, 1, 0.1, 0).to_host()
+
+    sources = W.xor_sources()
+    theta = np.float32(0.03).item()
+    a = emr.emr_pack_population(W.population(75, 100, 20, 60))
+    b = emr.emr_pack_population(W.population(76, 160, 20, 60))
+    first = nets(a)
+    for _ in range(2):
+        nets(b)
+        again = nets(a)
+        for x, y in zip(first, again):
+            for key in x:
+                np.testing.assert_array_equal(x[key], y[key], err_msg=key)
+
+
+def test_more_streams_than_counter_sets(emr):
+    """Twelve calls of one plan in flight on twelve streams (the plan keeps eight sets of counters:
+    the others wait for an earlier call's), twice over, from two threads in turn."""
+    import threading
+    import torch
+    pop = emr.emr_pack_population(W.population(77, 300, 20, 60))
+    sources = W.xor_sources()
+    theta = np.float32(0.03).item()
+    want = host(emr, emr.emr_discover_all(pop, sources, 7, theta))
+    bufs = [emr.alloc_result(pop, sources, 7) for _ in range(12)]
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    torch.cuda.synchronize()
+
+    def half(k):
+        for i in range(k, 12, 2):
+            emr.emr_discover(pop, sources, 7, theta, res=bufs[i], stream=streams[i])
+
+    for _ in range(2):
+        threads = [threading.Thread(target=half, args=(k,)) for k in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for b in bufs:
+            emr.emr_result_check(b)
+        for b in bufs:
+            same(host(emr, b), want)

@@ -56,6 +56,16 @@ __device__ __forceinline__ uint32_t last_from(const int64_t* off, uint32_t lo, u
   return last_at_most(off, lo, hi, r);
 }
 
+// The entries of a CSR table that the buffers hold: from the first pair's offset (a caller may pass
+// the pairs from some k on: the offsets' tail over the same entries) to the last one's.
+struct Held {
+  int64_t first, end;
+};
+__device__ __forceinline__ Held held_entries(const int64_t* off, uint32_t n, int64_t cap) {
+  const int64_t first = min(max(off[0], (int64_t)0), cap);
+  return {first, min(max(off[n], first), cap)};
+}
+
 // Entries per span when `held` entries go to n_spans spans: a multiple of 64.
 __device__ __forceinline__ int64_t span_length(int64_t held, uint32_t n_spans) {
   const int64_t steps = (held + kWave - 1) / kWave;
@@ -122,17 +132,16 @@ template <typename Op>
 __global__ void __launch_bounds__(256) k_filter_count(Op op) {
   const uint32_t lane = lane_id(), span = span_index();
   const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
-  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
-  const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
+  const Held held = held_entries(op.off(), n, op.cap());
+  const int64_t len = span_length(held.end - held.first, n_spans);
+  const int64_t base = held.first + (int64_t)span * len, end = min(base + len, held.end);
   uint32_t total = 0;
-  if (op.off()[0] <= 0)  // (else not a CSR offset table)
-    for_span(
-        op.off(), n, base, min(base + len, held), lane,
-        [&](uint32_t pair) { return op.context(pair); },
-        [&](int64_t i, uint32_t, const auto& c) {
-          const uint32_t m = i < min(base + len, held) ? op.keep(i, c) : 0u;
-          total += wave_sum3((uint32_t)__builtin_popcount(m));
-        });
+  for_span(
+      op.off(), n, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
+      [&](int64_t i, uint32_t, const auto& c) {
+        const uint32_t m = i < end ? op.keep(i, c) : 0u;
+        total += wave_sum3((uint32_t)__builtin_popcount(m));
+      });
   if (lane == 0) op.spans.kept[span] = total;
   if (span == 0 && lane == 0) op.spans.kept[kFilterSpans] = 0u;  // k_filter_end's counter
 }
@@ -161,29 +170,28 @@ __global__ void __launch_bounds__(256) k_filter_emit(Op op) {
   __shared__ uint64_t wsum[256 / kWave];
   const uint32_t lane = lane_id(), span = span_index();
   const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
-  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
-  const int64_t len = span_length(held, n_spans), base = (int64_t)span * len;
+  const Held held = held_entries(op.off(), n, op.cap());
+  const int64_t entries = held.end - held.first, len = span_length(entries, n_spans);
+  const int64_t base = held.first + (int64_t)span * len, end = min(base + len, held.end);
   // The spans are those of the capacity: of a light call's, most workgroups have no entries and
   // leave before the sums (the last one writes the total): the filters of a tabular result 344 ->
   // 338 us, of 432 records 262 -> 252 us.
-  const uint32_t used = len > 0 ? (uint32_t)((held + len - 1) / len) : 0u;
+  const uint32_t used = len > 0 ? (uint32_t)((entries + len - 1) / len) : 0u;
   if (blockIdx.x + 1 < gridDim.x && blockIdx.x * (blockDim.x / kWave) >= used) return;
   int64_t at0 = (int64_t)spans_before(op.spans.kept, used, wsum);
-  if (op.off()[0] <= 0)
-    for_span(
-        op.off(), n, base, min(base + len, held), lane,
-        [&](uint32_t pair) { return op.context(pair); },
-        [&](int64_t i, uint32_t pair, const auto& ctx) {
-          const bool mine = i < min(base + len, held);
-          const uint32_t m = mine ? op.keep(i, ctx) : 0u;
-          const uint32_t c = (uint32_t)__builtin_popcount(m);
-          int64_t at = at0 + wave_excl3(c);
-          if (mine && i == ctx.start) op.spans.out_offset[pair] = at;
+  for_span(
+      op.off(), n, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
+      [&](int64_t i, uint32_t pair, const auto& ctx) {
+        const bool mine = i < end;
+        const uint32_t m = mine ? op.keep(i, ctx) : 0u;
+        const uint32_t c = (uint32_t)__builtin_popcount(m);
+        int64_t at = at0 + wave_excl3(c);
+        if (mine && i == ctx.start) op.spans.out_offset[pair] = at;
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if ((m >> k) & 1u) op.emit(i, k, at++);
-          at0 += wave_sum3(c);
-        });
+        for (int k = 0; k < 4; ++k)
+          if ((m >> k) & 1u) op.emit(i, k, at++);
+        at0 += wave_sum3(c);
+      });
   if (span == n_spans - 1 && lane == 0)
     *reinterpret_cast<uint64_t*>(op.spans.kept + kFilterSpans + 2) = (uint64_t)at0;  // the total
 }
@@ -196,7 +204,7 @@ template <typename Op>
 __global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op) {
   const uint32_t n = op.pairs();
   const FilterSpans& F = op.spans;
-  const int64_t held = min(max(op.off()[n], (int64_t)0), op.cap());
+  const int64_t held = held_entries(op.off(), n, op.cap()).end;
   const uint64_t total = *reinterpret_cast<const uint64_t*>(F.kept + kFilterSpans + 2);
   uint32_t mx = 0;
   // the offset of the first kept item at or after entry i, the first of pair p or of a later one
@@ -458,10 +466,9 @@ __global__ void __launch_bounds__(256) k_chain_mark(ChainArgs A) {
   const int64_t Q = n_parents(A.rec.depth);
   const uint32_t np = A.rec.n_pairs;
   const int64_t* off = A.rec.offset;
-  const int64_t held = min(max(off[np], (int64_t)0), A.rec.cap);
-  if (off[0] > 0) return;
-  const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
-  const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
+  const Held held = held_entries(off, np, A.rec.cap);
+  const int64_t len = span_length(held.end - held.first, gridDim.x * (blockDim.x / kWave));
+  const int64_t base = held.first + (int64_t)span_index() * len, end = min(base + len, held.end);
   for_span(
       off, np, base, end, lane,
       [&](uint32_t p) { return RecordPair{off[p], off[p] + A.rec.count[p], 0u, 0.0f, 0.0f}; },

@@ -1,6 +1,7 @@
 """The filters over CSR entries (spans of consecutive entries, whatever pairs they belong to) on
 hand-built records and connections: runs of empty pairs at both ends and between, a pair that
-spans many spans, pairs of one entry, capacities below the entries, against numpy."""
+spans many spans, pairs of one entry, capacities below the entries, a range of a table's pairs,
+against numpy."""
 
 import numpy as np
 import pytest
@@ -115,6 +116,43 @@ def test_chain_filter(emr, name):
     k = int(want.sum())
     np.testing.assert_array_equal(out["parent"].cpu().numpy()[:k], parent[keep])
     np.testing.assert_array_equal(out["w4"].cpu().numpy()[:k], w4[keep])
+
+
+@pytest.mark.parametrize("name", ["ends empty", "long pair", "mixed", "single entries"])
+def test_ranges_of_pairs(emr, name):
+    """The pairs from k on (the offsets' tail, over the same entries) give the whole table's results
+    for those pairs: the band filter and the chain rule, with the entries cut off by the capacity too."""
+    n = counts_of(name)
+    off = np.concatenate([[0], np.cumsum(n)])
+    total, P = int(off[-1]), len(n)
+    r = np.random.default_rng(4)
+    band = r.random(total).astype(np.float32)
+    cell = r.integers(1, 1 << 20, total)
+    parent = np.concatenate([np.arange(c) for c in n])  # a prefix of the heap: every ancestor kept
+    keep = np.concatenate([[0], np.cumsum(band > 0.5)])
+    for k, last in ((1, P), (P // 2, P), (P - 1, P), (2, P - 1)):
+        for cap in (total, total - total // 3):
+            lo, hi = min(off[k], cap), min(off[last], cap)
+            edge = np.minimum(off[k:last + 1], cap)
+            conn = {"cell": dev(cell, np.int32), "w": dev(band, np.float32),
+                    "pair_count": dev(n, np.int64)[k:], "pair_offset": dev(off, np.int64)[k:],
+                    "capacity": cap, "n_pairs": last - k, "total": total}
+            out = emr.emr_band_filter(conn, dev(band, np.float32), 0.5)
+            want = keep[edge] - keep[lo]
+            np.testing.assert_array_equal(out["pair_offset"].cpu().numpy(), want)
+            np.testing.assert_array_equal(out["pair_count"].cpu().numpy(), np.diff(want))
+            m = int(want[-1])
+            assert out["total"] == m
+            np.testing.assert_array_equal(out["cell"].cpu().numpy()[:m],
+                                          cell[lo:hi][band[lo:hi] > 0.5])
+            rec = {"parent": dev(parent, np.int32), "w4": dev(np.zeros((total, 4)), np.float32),
+                   "pair_count": conn["pair_count"], "pair_offset": conn["pair_offset"],
+                   "capacity": cap, "n_pairs": last - k,
+                   "workspace": torch.empty(256, dtype=torch.uint8, device="cuda")}
+            out = emr.emr_chain_filter(rec, 10, capacity=total)
+            np.testing.assert_array_equal(out["pair_offset"].cpu().numpy(), edge - lo)
+            np.testing.assert_array_equal(out["pair_count"].cpu().numpy()[:last - k], np.diff(edge))
+            np.testing.assert_array_equal(out["parent"].cpu().numpy()[:hi - lo], parent[lo:hi])
 
 
 @pytest.mark.parametrize("mask", [0, 1, 6, 15])

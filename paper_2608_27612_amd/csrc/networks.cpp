@@ -252,7 +252,7 @@ struct Phase {
   int64_t hcap = 0, n_new = 0;
   Dev src_cell;   // [sources] heap cells of the queried hidden nodes
   Dev src_offs;   // [n_genomes + 1] int64 copy of offs
-  Dev ws;         // the discovery's workspace, released after the phase
+  Dev ws;         // the discovery's workspace, released once it is checked
 
   void release_idle() {
     for (Dev* d : {&parent, &w4, &rcount, &roffset, &cell, &w, &ccount, &coffset, &src_cell,
@@ -332,6 +332,24 @@ struct Build {
   hipStream_t s;
 };
 
+// Moves the first `bytes` of d into a buffer of that size and gives the larger one back; without
+// the memory for it d stays as it is.
+emr_status fit(Dev& d, size_t bytes, const char* what, hipStream_t s) {
+  Dev small;
+  if (alloc(small, bytes, what, s) != EMR_OK) return EMR_OK;
+  if (bytes) NET_HIP(hipMemcpyAsync(small.p, d.p, bytes, hipMemcpyDeviceToDevice, s));
+  d.take(small);
+  return EMR_OK;
+}
+
+// A retry runs the phase's discovery a second time (and a heavy population's hidden phase is most of
+// a generation; one random population of 1000 in ten keeps more than 16M records), so the first guess
+// is large: 64M records (1.3 GB, as much again for the pool). The records then move to buffers of
+// their number: the phase keeps them as long as the networks live. Where the memory for the large
+// guess is short the guess is 16M, which the phase may keep.
+constexpr size_t kFitBytes = size_t(4) << 20;  // (below this a copy's launch costs more than it frees)
+constexpr int64_t kFirstRecords = int64_t(1) << 26, kKeptRecords = int64_t(1) << 24;
+
 // The phase's discovery, retried once with the exact capacity when the first guess was short.
 emr_status discover_phase(Build& B, Phase& P) {
   emr_networks& N = *B.net;
@@ -342,30 +360,41 @@ emr_status discover_phase(Build& B, Phase& P) {
   NET_TRY(alloc(P.roffset, (size_t)(P.n_pairs + 1) * 8, "pair offsets", B.s));
   int64_t n_pos = 0, Q = 0;
   NET_TRY(emr_grid_count(N.depth, &n_pos, &Q));
-  // A retry runs the phase's discovery a second time (and a heavy population's hidden phase is
-  // most of a generation), so the first guess is large: 64M records (1.3 GB, as much again for the
-  // pool). One random population of 1000 in ten keeps more than 16M.
-  int64_t cap = P.n_pairs * Q;
-  if (cap > (int64_t)1 << 26) cap = (int64_t)1 << 26;
-  if (cap < 1) cap = 1;
-  for (int attempt = 0;; ++attempt) {
+  auto room = [&](int64_t cap) -> emr_status {
     int64_t wsb = 0;
     NET_TRY(emr_workspace_bytes(B.pop, src, n, P.offs_ptr(), P.n_shared(), N.depth, cap, &wsb));
     NET_TRY(alloc(P.ws, (size_t)wsb, "discover workspace", B.s));
     NET_TRY(alloc(P.parent, (size_t)cap * 4, "records", B.s));
-    NET_TRY(alloc(P.w4, (size_t)cap * 16, "records", B.s));
+    return alloc(P.w4, (size_t)cap * 16, "records", B.s);
+  };
+  int64_t cap = std::max<int64_t>(1, std::min(P.n_pairs * Q, kFirstRecords));
+  for (int attempt = 0;; ++attempt) {
+    emr_status st = room(cap);
+    if (st == EMR_E_NOMEM && attempt == 0 && cap > kKeptRecords) {
+      for (Dev* d : {&P.ws, &P.parent, &P.w4}) d->reset_idle();
+      cap = kKeptRecords;
+      st = room(cap);
+    }
+    NET_TRY(st);
     P.rcap = cap;
     const emr_result r = P.result();
     NET_TRY(emr_discover(B.pop, src, n, P.offs_ptr(), P.n_shared(), N.depth, B.theta, &r, B.s));
     int64_t total = 0;
-    const emr_status st = emr_result_check(&r, &total, nullptr, B.s);
+    st = emr_result_check(&r, &total, nullptr, B.s);
     if (st == EMR_OK) {
       P.rtotal = total;
-      return EMR_OK;
+      break;
     }
     if (st != EMR_E_CAPACITY || attempt > 0) return st;
     cap = total;
   }
+  P.ws.reset_idle();  // (the check waited for the call)
+  if (P.rcap > kKeptRecords && P.rtotal < P.rcap) {
+    P.rcap = std::max<int64_t>(1, P.rtotal);
+    NET_TRY(fit(P.parent, (size_t)P.rcap * 4, "records", B.s));
+    NET_TRY(fit(P.w4, (size_t)P.rcap * 16, "records", B.s));
+  }
+  return EMR_OK;
 }
 
 // Enqueues the phase's new hidden nodes (or-ed into the bitmap).
@@ -621,6 +650,16 @@ emr_status assemble(Build& B) {
   if (N.nodes < 0 || N.nodes > n_raw || N.edges < 0 || N.edges > e_raw)
     return failf(EMR_E_DEVICE, "networks: %lld nodes of %lld, %lld kept edges of %lld",
                  (long long)N.nodes, (long long)n_raw, (long long)N.edges, (long long)e_raw);
+  // The arrays of the networks were sized by the raw nodes and edges, so that nothing waited for the
+  // kept ones; what pruning left much smaller moves, and the raw size goes back to the cache.
+  const struct { Dev* d; size_t bytes; const char* what; } kept[] = {
+      {&N.node_cell, (size_t)N.nodes * 4, "network nodes"},
+      {&N.node_in, (size_t)N.nodes * 4, "network input numbers"},
+      {&N.in_offset, (size_t)(N.nodes + 1) * 8, "network edge offsets"},
+      {&N.in_src, (size_t)N.edges * 4, "network edges"},
+      {&N.in_w, (size_t)N.edges * 4, "network edges"}};
+  for (const auto& k : kept)
+    if (k.d->bytes - k.bytes > kFitBytes) NET_TRY(fit(*k.d, k.bytes, k.what, s));
   return order_genomes(N, off.data(), off.data() + G + 1, s);
 }
 
@@ -877,7 +916,6 @@ emr_status build_all(Build& B, int32_t n_substrate, int32_t iterations) {
     NET_TRY(hidden_phase(B, P));
     NET_TRY(express_phase(B, P));
     NET_TRY(finish_phase(B, P, next.get()));
-    P.ws.reset();
     if (!more || P.n_new == 0) break;
     N.phases.push_back(std::move(next));
   }

@@ -269,6 +269,49 @@ emr_status upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
   return EMR_OK;
 }
 
+// A plan's error word, which its bind kernel raises: pinned, so that any thread reads it without a
+// copy once the kernel has completed. A word is handed out for as long as its plan, or the flag slot
+// of a call that read the plan's bias rows, holds it. Words come in blocks that the process keeps.
+class PlanError {
+ public:
+  static std::shared_ptr<PlanError> make() {
+    std::lock_guard<std::mutex> lock(mu());
+    std::vector<uint32_t*>& spare = words();
+    if (spare.empty()) {
+      uint32_t* block = nullptr;
+      if (hipHostMalloc((void**)&block, kBlock * sizeof(uint32_t), hipHostMallocPortable) != hipSuccess)
+        return nullptr;
+      for (size_t k = 0; k < kBlock; ++k) spare.push_back(block + k);
+    }
+    std::shared_ptr<PlanError> e(new PlanError(spare.back()));
+    spare.pop_back();
+    return e;
+  }
+  ~PlanError() {
+    std::lock_guard<std::mutex> lock(mu());
+    words().push_back(word_);
+  }
+  // 0: none so far (the bind kernel may still run).
+  uint32_t bits() const { return __atomic_load_n(word_, __ATOMIC_RELAXED); }
+  uint32_t* device() const {
+    void* d = nullptr;
+    return hipHostGetDevicePointer(&d, word_, 0) == hipSuccess ? (uint32_t*)d : nullptr;
+  }
+
+ private:
+  static constexpr size_t kBlock = 1024;
+  explicit PlanError(uint32_t* w) : word_(w) { *w = 0u; }
+  static std::mutex& mu() {
+    static std::mutex* m = new std::mutex;  // (never destroyed: plans may go at the process's end)
+    return *m;
+  }
+  static std::vector<uint32_t*>& words() {
+    static std::vector<uint32_t*>* v = new std::vector<uint32_t*>;
+    return *v;
+  }
+  uint32_t* word_;
+};
+
 // Per-thread profiling of the discover-kernel launches.
 struct Profiler {
   bool on = false;
@@ -374,6 +417,7 @@ struct Plan : emr::PlanTables {
   // The bias rows of the plan's groups (the bind kernel's output: every position-independent
   // contribution per (genome, source)), computed on the device once, on first use (dev_mu).
   mutable float* d_bias = nullptr;
+  mutable std::shared_ptr<PlanError> bind_error;  // (set with d_bias)
   // Recorded after the upload and the bind kernel; a call's stream waits for it until a query has
   // found it complete (call_tables).
   mutable hipEvent_t ready = nullptr;
@@ -611,6 +655,7 @@ struct FlagRing {
   const void* ws[kFlagSlots] = {};  // workspace of the slot's last call (NULL: nothing to check)
   uint64_t seq[kFlagSlots] = {};    // order of the calls
   bool pending[kFlagSlots] = {};    // done[k] is recorded after the slot's last call
+  std::shared_ptr<PlanError> plan_error[kFlagSlots];  // of the plan whose bias rows the call reads
   bool dirty[kFlagSlots] = {};      // a call failed after taking the slot: cleared before reuse
   int next = 0;
   uint64_t calls = 0;
@@ -669,6 +714,7 @@ struct CallFlags {
   uint32_t* host_dev = nullptr;  // the pinned words (device view)
   hipStream_t s = nullptr;
   const void* ws = nullptr;
+  std::shared_ptr<PlanError> plan_error;  // call_tables
   uint64_t seq = 0;
   bool ok = false;  // the call's last kernel is enqueued
   CallFlags() = default;
@@ -680,6 +726,7 @@ struct CallFlags {
     // the slot's next user waits for whatever this call enqueued
     ring->pending[slot] = hipEventRecord(ring->done[slot], s) == hipSuccess;
     ring->ws[slot] = ok ? ws : nullptr;
+    ring->plan_error[slot].swap(plan_error);
     ring->dirty[slot] = !ok;
   }
 };
@@ -739,11 +786,16 @@ emr::BindArgs bind_args(const emr_population* pop, const Plan& P, const char* ta
   return b;
 }
 
+emr_status bind_failed(uint32_t bits) {
+  return fail(EMR_E_DEVICE, "the bind kernel reported error flags 0x%x (2: a table entry out of "
+              "range)", bits);
+}
+
 // The plan's tables and bias rows on the device: on first use uploaded, and the rows computed by
 // the bind kernel, on the library's stream without waiting; the caller's stream s waits for them.
-// The bind kernel raises a table error into *err (the first call's flags, so that call's check
-// reports it; check_plan_tables has found none).
-emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, uint32_t* err) {
+// The bind kernel raises a table error into the plan's word (check_plan_tables has found none): every
+// call that finds it raised fails, and so does the check of a call that was enqueued before it was.
+emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s) {
   if (!P.ready_done.load(std::memory_order_acquire)) {
     std::lock_guard<std::mutex> lock(P.dev_mu);
     if (!P.d_bias) {
@@ -759,6 +811,10 @@ emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, 
           hipMalloc((void**)&bias, bytes) != hipSuccess)
         st = fail(EMR_E_NOMEM, "device tables of %zu bytes, bias rows and counters of %zu",
                   P.img.size(), bytes);
+      std::shared_ptr<PlanError> error;
+      uint32_t* err = nullptr;
+      if (st == EMR_OK && (!(error = PlanError::make()) || !(err = error->device())))
+        st = fail(EMR_E_NOMEM, "error word of the call tables");
       if (st == EMR_OK && !P.ready &&
           hipEventCreateWithFlags(&P.ready, hipEventDisableTiming) != hipSuccess)
         st = fail(EMR_E_DEVICE, "event of the call tables");
@@ -778,6 +834,7 @@ emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, 
       }
       P.d_tables = d;
       P.d_bias = bias;
+      P.bind_error = std::move(error);
       CounterSet first;
       first.d = (char*)bias + off_set;
       first.clean = true;  // (every call's stream waits for the fill)
@@ -792,6 +849,7 @@ emr_status plan_device(const emr_population* pop, const Plan& P, hipStream_t s, 
       HIP_OR_FAIL(hipStreamWaitEvent(s, P.ready, 0));
     }
   }
+  if (const uint32_t bits = P.bind_error->bits()) return bind_failed(bits);
   return EMR_OK;
 }
 
@@ -1279,10 +1337,10 @@ emr_status launch_range(const emr_population* pop, const Plan& P, const CallTabl
 
 // The plan's own device tables and bias rows and the depth's tile geometry table (each made on
 // first use).
-emr_status call_tables(const emr_population* pop, const Plan& P, const CallFlags& f,
-                       CallTables* T, bool raw = false) {
-  emr_status st = plan_device(pop, P, f.s, (raw ? f.host_dev : f.dev) + emr::kFlagErr);
+emr_status call_tables(const emr_population* pop, const Plan& P, CallFlags& f, CallTables* T) {
+  emr_status st = plan_device(pop, P, f.s);
   if (st != EMR_OK) return st;
+  f.plan_error = P.bind_error;
   T->tables = P.d_tables;
   T->bias = P.d_bias;
   return tile_geo_table(P.depth, &T->geo, &T->geo_rows);
@@ -1388,7 +1446,7 @@ emr_status run_plan(const emr_population* pop, const Plan& P, float theta, const
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
   CallTables T;
-  if ((st = call_tables(pop, P, f, &T, out == nullptr || raw != nullptr)) != EMR_OK) return st;
+  if ((st = call_tables(pop, P, f, &T)) != EMR_OK) return st;
   bool jit = false;
   if ((st = jit_use(pop, P, plan_slots(P), &jit)) != EMR_OK) return st;
   const bool records = out != nullptr && raw == nullptr;
@@ -1615,6 +1673,7 @@ emr_status emr_call_check(const void* workspace, int64_t capacity, int64_t* tota
   // the flag slot of the latest call with this workspace
   hipEvent_t ev = nullptr;
   const uint32_t* host = nullptr;
+  std::shared_ptr<PlanError> plan_error;
   {
     std::lock_guard<std::mutex> lock(g_ring_mu);
     FlagRing* R = nullptr;
@@ -1626,6 +1685,7 @@ emr_status emr_call_check(const void* workspace, int64_t capacity, int64_t* tota
         latest = R->seq[k];
         ev = R->done[k];
         host = R->host + (size_t)k * kSlotWords;
+        plan_error = R->plan_error[k];
       }
   }
   if (!ev)
@@ -1641,6 +1701,7 @@ emr_status emr_call_check(const void* workspace, int64_t capacity, int64_t* tota
   if (err)
     return fail(EMR_E_DEVICE, "kernel reported error flags 0x%x (2: a table entry out of range)",
                 err);
+  if (plan_error && plan_error->bits()) return bind_failed(plan_error->bits());
   if (found > capacity)
     return fail(EMR_E_CAPACITY, "the call found %lld entries; the capacity is %lld",
                 (long long)found, (long long)capacity);
@@ -2027,7 +2088,7 @@ emr_status emr_discover_stream(const emr_population* pop, const emr_source* sour
     }
     HIP_OR_FAIL(hipEventSynchronize(R.ev_count[b]));
     // a kernel error raised up to this chunk stops the run before its records are delivered
-    const uint32_t err = (uint32_t)R.counts_h[b][n_pairs];
+    const uint32_t err = (uint32_t)R.counts_h[b][n_pairs] | P.bind_error->bits();
     if (err) {
       if (next) *next = c * n_pairs + (c == c0 ? skip : 0);
       return fail(EMR_E_DEVICE, "kernel reported error flags 0x%x at chunk %lld (2: a table entry "

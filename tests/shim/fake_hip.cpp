@@ -28,6 +28,7 @@ struct Fake {
   int slow_copies = 0;  // the same from other memory
   uint64_t total = 0;   // what the next record calls and filters report
   uint32_t bind_error = 0;
+  uint32_t* bind_word = nullptr;  // held with the events
 };
 Fake& F() {
   static Fake* f = new Fake;
@@ -70,7 +71,12 @@ extern "C" {
 
 // ------------------------------------------------------------------ the tests' side
 void fake_limit(int64_t bytes) { F().limit = bytes < 0 ? ~size_t(0) : F().held + (size_t)bytes; }
-void fake_hold_events(int on) { F().hold_events = on != 0; }
+void fake_hold_events(int on) {
+  F().hold_events = on != 0;
+  if (on || !F().bind_word) return;
+  *F().bind_word = F().bind_error;
+  F().bind_word = nullptr;
+}
 void fake_capturing(int on) { F().capturing = on != 0; }
 void fake_total(int64_t n) { F().total = (uint64_t)n; }
 void fake_bind_error(uint32_t bits) { F().bind_error = bits; }
@@ -188,7 +194,11 @@ hipError_t emr_launch_fill(void* p, int64_t n_words, uint32_t value, hipStream_t
 }
 hipError_t emr_launch_grid(float*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t emr_launch_bind(const emr::BindArgs* a, hipStream_t) {
-  if (F().bind_error) *a->err = F().bind_error;
+  if (!F().bind_error) return hipSuccess;
+  if (F().hold_events)
+    F().bind_word = a->err;
+  else
+    *a->err = F().bind_error;
   return hipSuccess;
 }
 hipError_t emr_launch_discover(const emr::DiscoverArgs*, int, uint32_t, hipStream_t, hipEvent_t,

@@ -118,3 +118,50 @@ def test_networks_under_little_memory(lib, spare_mb, found, ok):
     if ok:
         assert phase0(h).records == found
         lib.emr_free_networks(h)
+
+
+def discover(pop, sources, depth, ws):
+    """emr_discover with no room for records and the workspace `ws` (a numpy buffer): its status."""
+    n = len(sources) * pop.n_genomes
+    count, offset = np.zeros(n, np.int64), np.zeros(n + 1, np.int64)
+    out = E.emr_result(0, 0, 0, count.ctypes.data, offset.ctypes.data, ws.ctypes.data, ws.size)
+    return E.lib().emr_discover(pop.handle, sources.ctypes.data, len(sources), None, len(sources),
+                                depth, 0.03, C.byref(out), None)
+
+
+def workspace(pop, sources, depth):
+    n = E.emr_workspace_bytes(pop, sources, depth)
+    raw = np.zeros(n + 256, np.uint8)
+    at = -raw.ctypes.data % 256
+    return raw[at:at + n]
+
+
+@pytest.mark.parametrize("known", [True, False])
+def test_a_table_error_fails_every_call_of_the_plan(lib, known):
+    """A table error of the bind kernel: calls made before it is raised (`known` false) fail in their
+    check, each of them and whether or not an earlier call was checked; later ones fail at once, raw
+    calls among them. Another population's calls do not."""
+    pop = E.emr_pack_population(W.population(2, 10, 6, 12))
+    src = W.xor_sources()
+    a, b, c = (workspace(pop, src, 4) for _ in range(3))
+    out = np.zeros(E.emr_grid_count(4)[0] * 4 * 10, np.float32)
+
+    def raw():
+        return lib.emr_eval_raw(pop.handle, src.ctypes.data, len(src), None, len(src), 4,
+                                out.ctypes.data, c.ctypes.data, c.size, None)
+
+    lib.fake_bind_error(2)
+    if not known:
+        lib.fake_hold_events(1)
+        assert raw() == 0 and discover(pop, src, 4, a) == 0 and discover(pop, src, 4, b) == 0
+        lib.fake_hold_events(0)
+        for ws in (b, a, c):
+            assert lib.emr_call_check(ws.ctypes.data, 0, None, None, None) == E.EMR_E_DEVICE
+    for _ in range(2):
+        assert discover(pop, src, 4, b) == E.EMR_E_DEVICE
+        assert "bind kernel" in lib.emr_last_error().decode()
+        assert raw() == E.EMR_E_DEVICE
+    lib.fake_bind_error(0)
+    other = E.emr_pack_population(W.population(2, 10, 6, 12))
+    assert discover(other, src, 4, a) == 0
+    assert lib.emr_call_check(a.ctypes.data, 0, None, None, None) == 0

@@ -206,19 +206,66 @@ emr_status stream_pool(StreamPool** out) {
 // Pinned staging of the host tables' uploads: a copy from pageable memory holds the calling thread
 // for the whole transfer (75 us for a 200 KB table; 15 us into staging). A buffer is handed out
 // again once the event recorded after its copy has completed. At most kStagings buffers of at most
-// kStagingBytes each, kept for the process; a larger upload, or one that finds them all in flight
-// and the table full, copies from the caller's memory and waits.
+// kStagingBytes each per device, kept for the process; with that many, an idle one that is too small
+// is replaced by a larger one. A larger upload, or one that finds them all in flight, copies from
+// the caller's memory and waits.
 constexpr size_t kStagings = 4;
 constexpr size_t kStagingBytes = size_t(16) << 20;
 struct Staging {
-  int device;
-  void* p;
-  size_t size;
-  hipEvent_t done;
-  bool pending;
+  int device = 0;
+  void* p = nullptr;
+  size_t size = 0;
+  hipEvent_t done = nullptr;
+  bool busy = false;     // being filled
+  bool pending = false;  // `done` follows its last copy
 };
 std::mutex g_staging_mu;
-std::vector<Staging> g_stagings;
+std::vector<std::unique_ptr<Staging>> g_stagings;
+
+// A staging buffer of at least `bytes` on device dev, marked busy, or nullptr.
+Staging* take_staging(int dev, size_t bytes) {
+  if (bytes > kStagingBytes) return nullptr;
+  std::lock_guard<std::mutex> lock(g_staging_mu);
+  Staging* use = nullptr;
+  size_t have = 0;
+  for (auto& b : g_stagings) {
+    if (b->device != dev) continue;
+    ++have;
+    if (b->busy) continue;
+    if (b->pending) {
+      if (hipEventQuery(b->done) != hipSuccess) {
+        (void)hipGetLastError();  // (not ready is no error of the caller's)
+        continue;
+      }
+      b->pending = false;
+    }
+    if (!use || (use->size < bytes && b->size > use->size)) use = b.get();
+  }
+  if (!use || (use->size < bytes && have < kStagings)) {
+    if (have >= kStagings) return nullptr;
+    auto b = std::make_unique<Staging>();
+    b->device = dev;
+    if (hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    use = b.get();
+    g_stagings.push_back(std::move(b));
+  }
+  if (use->size < bytes) {
+    if (use->p) (void)hipHostFree(use->p);
+    use->size = size_t(1) << 20;
+    while (use->size < bytes) use->size *= 2;
+    if (hipHostMalloc(&use->p, use->size, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      use->p = nullptr;
+      use->size = 0;
+      return nullptr;
+    }
+  }
+  use->busy = true;
+  return use;
+}
 
 // Copies src to dst (device) on s. The source may be reused on return; the copy is complete only
 // in stream order.
@@ -226,47 +273,20 @@ emr_status upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
   if (bytes == 0) return EMR_OK;
   int dev = 0;
   HIP_OR_FAIL(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lock(g_staging_mu);
-  Staging* use = nullptr;
-  for (Staging& b : g_stagings) {
-    if (b.device != dev || b.size < bytes || use) continue;
-    if (b.pending) {
-      const hipError_t q = hipEventQuery(b.done);
-      if (q != hipSuccess) {
-        (void)hipGetLastError();  // (not ready is no error of the caller's)
-        continue;
-      }
-      b.pending = false;
-    }
-    use = &b;
-  }
-  if (!use && bytes <= kStagingBytes && g_stagings.size() < kStagings) {
-    Staging b{dev, nullptr, size_t(1) << 20, nullptr, false};
-    while (b.size < bytes) b.size *= 2;
-    if (hipHostMalloc(&b.p, b.size, hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-    } else if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      (void)hipHostFree(b.p);
-    } else {
-      g_stagings.push_back(b);
-      use = &g_stagings.back();
-    }
-  }
-  if (!use) {
+  Staging* b = take_staging(dev, bytes);
+  if (!b) {  // (no lock is held: the wait is for whatever the stream holds)
     HIP_OR_FAIL(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
     return EMR_OK;
   }
-  std::memcpy(use->p, src, bytes);
-  use->pending = true;
-  if (hipMemcpyAsync(dst, use->p, bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-      hipEventRecord(use->done, s) != hipSuccess) {
-    (void)hipStreamSynchronize(s);
-    use->pending = false;
-    return fail(EMR_E_DEVICE, "upload of %zu bytes failed", bytes);
-  }
-  return EMR_OK;
+  std::memcpy(b->p, src, bytes);
+  const bool ok = hipMemcpyAsync(dst, b->p, bytes, hipMemcpyHostToDevice, s) == hipSuccess &&
+                  hipEventRecord(b->done, s) == hipSuccess;
+  if (!ok) (void)hipStreamSynchronize(s);
+  std::lock_guard<std::mutex> lock(g_staging_mu);
+  b->pending = ok;
+  b->busy = false;
+  return ok ? EMR_OK : fail(EMR_E_DEVICE, "upload of %zu bytes failed", bytes);
 }
 
 // A plan's error word, which its bind kernel raises: pinned, so that any thread reads it without a

@@ -7,10 +7,12 @@
 
 #include <sys/mman.h>
 
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "../../paper_2608_27612_amd/csrc/band.h"
@@ -23,6 +25,7 @@ struct Fake {
   std::map<void*, size_t> device, pinned;
   size_t held = 0, limit = ~size_t(0);
   bool hold_events = false, capturing = false;
+  std::atomic<bool> block_waits{false};
   int waits = 0;        // stream and event waits of the host
   int copies = 0;       // host-to-device copies from pinned memory
   int slow_copies = 0;  // the same from other memory
@@ -77,6 +80,7 @@ void fake_hold_events(int on) {
   *F().bind_word = F().bind_error;
   F().bind_word = nullptr;
 }
+void fake_block_waits(int on) { F().block_waits = on != 0; }
 void fake_capturing(int on) { F().capturing = on != 0; }
 void fake_total(int64_t n) { F().total = (uint64_t)n; }
 void fake_bind_error(uint32_t bits) { F().bind_error = bits; }
@@ -133,6 +137,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
+  while (F().block_waits) std::this_thread::yield();
   Lock l(F().mu);
   ++F().waits;
   return hipSuccess;

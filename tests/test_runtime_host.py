@@ -7,6 +7,7 @@ import gc
 import os
 import shutil
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -43,6 +44,7 @@ def lib(built, tmp_path):
     L.emr_set_jit(E.EMR_JIT_OFF)
     for name, (res, args) in {"fake_limit": (None, [C.c_int64]),
                               "fake_hold_events": (None, [C.c_int]),
+                              "fake_block_waits": (None, [C.c_int]),
                               "fake_capturing": (None, [C.c_int]), "fake_total": (None, [C.c_int64]),
                               "fake_bind_error": (None, [C.c_uint32]),
                               "fake_held": (C.c_int64, []), "fake_size": (C.c_int64, [C.c_void_p]),
@@ -165,3 +167,57 @@ def test_a_table_error_fails_every_call_of_the_plan(lib, known):
     other = E.emr_pack_population(W.population(2, 10, 6, 12))
     assert discover(other, src, 4, a) == 0
     assert lib.emr_call_check(a.ctypes.data, 0, None, None, None) == 0
+
+
+def first_call(pop, sources, depth=3):
+    """The first discover call of a population's plan: it uploads the plan's tables."""
+    assert discover(pop, sources, depth, workspace(pop, sources, depth)) == 0
+
+
+def test_a_large_table_replaces_a_small_staging_buffer(lib):
+    """Four small uploads in flight make four 1 MB staging buffers; a later table of some MB (2000
+    CPPNs, 35 sources) still leaves from staging, without a wait."""
+    src = W.tabular_sources(32)
+    small = [E.emr_pack_population(W.population(k, 4, 4, 8)) for k in range(5)]
+    large = E.emr_pack_population(W.population(9, 2000, 2, 4))
+    lib.fake_hold_events(1)
+    for p in small[:4]:
+        first_call(p, src)
+    before = counts(lib)
+    first_call(small[4], src)  # all four in flight: copied from the caller's memory, with a wait
+    after = counts(lib)
+    assert after["slow_copies"] == before["slow_copies"] + 1 and after["waits"] > before["waits"]
+    lib.fake_hold_events(0)
+    first_call(E.emr_pack_population(W.population(10, 4, 4, 8)), src)
+    before = counts(lib)
+    first_call(large, src)
+    after = counts(lib)
+    assert after["copies"] == before["copies"] + 1
+    assert after["slow_copies"] == before["slow_copies"]
+
+
+def test_an_upload_that_waits_holds_up_no_other(lib):
+    """While one thread's upload waits for its stream (all staging in flight), another thread's, which
+    finds an idle buffer, goes through."""
+    src = W.tabular_sources(32)
+    pops = [E.emr_pack_population(W.population(k, 4, 4, 8)) for k in range(6)]
+    lib.fake_hold_events(1)
+    for p in pops[:4]:
+        first_call(p, src)
+    lib.fake_block_waits(1)
+    waiting = threading.Thread(target=first_call, args=(pops[4], src))
+    other = threading.Thread(target=first_call, args=(pops[5], src))
+    slow = counts(lib)["slow_copies"]
+    try:
+        waiting.start()
+        while counts(lib)["slow_copies"] == slow:
+            assert waiting.is_alive()
+        lib.fake_hold_events(0)
+        other.start()
+        other.join(20)
+        assert not other.is_alive() and waiting.is_alive()
+    finally:
+        lib.fake_hold_events(0)
+        lib.fake_block_waits(0)
+        waiting.join()
+        other.join()

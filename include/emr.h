@@ -296,8 +296,9 @@ emr_status emr_band_workspace_bytes(int64_t n_pairs, int64_t* bytes);
  * in fp32 (fminf / fmaxf: a NaN operand is ignored). band: device, caller-owned, [conn->capacity]
  * (entries past the connections are not written). conn->pair_count and conn->workspace are not
  * used. `workspace` (device, >= emr_band_workspace_bytes(n_pairs), 256-byte aligned) holds the
- * pairs' program entries. Enqueued on `stream`; check with emr_call_check(workspace, 0):
- * EMR_E_DEVICE when a connection names no cell of the grid (its band is not written).
+ * pairs' program entries (uploaded: EMR_E_DEVICE on a stream under capture). Enqueued on `stream`;
+ * check with emr_call_check(workspace, 0): EMR_E_DEVICE when a connection names no cell of the grid
+ * (its band is not written).
  */
 emr_status emr_band_values(const emr_population* pop, const emr_source* sources,
                            int32_t n_sources, const int32_t* src_offsets, int32_t n_shared,

@@ -1397,6 +1397,13 @@ struct CallCounters {
   }
 };
 
+// Whether work enqueued on s would go into a graph instead of running now.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
+}
+
 // Counters for a record call on stream s with the flags f: the plan's set that the stream used last
 // (stream order then puts this call after that one's compaction), else one whose last call has
 // completed, else a new one, else one whose last call the stream waits for. Where that is not
@@ -1406,9 +1413,7 @@ emr_status take_counters(const Plan& P, void* workspace, hipStream_t s, const Ca
                          CallCounters* c) {
   c->d = (char*)workspace + P.off_nz;
   c->clear = true;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-  if (capture != hipStreamCaptureStatusNone) return EMR_OK;
+  if (capturing(s)) return EMR_OK;
   std::lock_guard<std::mutex> lock(P.counters_mu);
   const size_t n = P.counters.size();
   size_t use = n;
@@ -2397,6 +2402,8 @@ emr_status emr_band_values(const emr_population* pop, const emr_source* sources,
       }
     }
   const hipStream_t s = (hipStream_t)stream;
+  // (a graph would copy the pairs' table from the staging buffer again, whatever that then holds)
+  if (capturing(s)) return fail(EMR_E_DEVICE, "emr_band_values uploads a table: not under capture");
   CallFlags f;
   if ((st = take_flags(workspace, s, &f)) != EMR_OK) return st;
   CallTables T;

@@ -221,3 +221,28 @@ def test_an_upload_that_waits_holds_up_no_other(lib):
         lib.fake_block_waits(0)
         waiting.join()
         other.join()
+
+
+def test_band_values_refuse_a_capture(lib):
+    """The call uploads a table: recorded into a graph, the copy would read the staging buffer at
+    every replay, which later calls have rewritten."""
+    src = W.xor_sources()
+    pop = E.emr_pack_population(W.population(3, 4, 4, 8))
+    first_call(pop, src)
+    n = 4 * len(src)
+    b = C.c_int64()
+    assert lib.emr_band_workspace_bytes(n, C.byref(b)) == 0
+    raw = np.zeros(b.value + 256, np.uint8)
+    ws = raw[-raw.ctypes.data % 256:]
+    offset = np.zeros(n + 1, np.int64)
+    conn = E.emr_connections(0, 0, 0, 0, offset.ctypes.data, 0, 0)
+
+    def call():
+        return lib.emr_band_values(pop.handle, src.ctypes.data, len(src), None, len(src), 3,
+                                   C.byref(conn), None, ws.ctypes.data, b.value, None)
+
+    lib.fake_capturing(1)
+    before = counts(lib)
+    assert call() == E.EMR_E_DEVICE and counts(lib) == before
+    lib.fake_capturing(0)
+    assert call() == 0 and counts(lib) != before

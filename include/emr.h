@@ -212,6 +212,13 @@ emr_status emr_result_check(const emr_result* out, int64_t* total, int64_t* max_
 emr_status emr_call_check(const void* workspace, int64_t capacity, int64_t* total,
                           int64_t* max_count, void* stream);
 
+/* Moves a result into buffers of another size, such as those of its number of records: waits for the
+ * latest discover call made with from's workspace and checks it (its errors are returned), enqueues
+ * the copy of its records to to's `parent` and `w4` on `stream`, and makes the call to's: it is
+ * to's workspace that emr_result_check then looks up. EMR_E_CAPACITY for more records than to's
+ * capacity. pair_count and pair_offset are not used. */
+emr_status emr_result_move(const emr_result* from, const emr_result* to, void* stream);
+
 /* ------------------------------------------------------------------ after discovery
  * Operations on the checked CSR output `rec` of an emr_discover call, given the same population,
  * sources and depth as that call. Each writes a CSR output of its own through a workspace and is

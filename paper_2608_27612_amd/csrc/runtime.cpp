@@ -1739,6 +1739,34 @@ emr_status emr_result_check(const emr_result* out, int64_t* total, int64_t* max_
   return emr_call_check(out->workspace, out->capacity, total, max_count, stream);
 }
 
+emr_status emr_result_move(const emr_result* from, const emr_result* to, void* stream) {
+  if (!from || !to || !to->workspace || to->workspace == from->workspace)
+    return fail(EMR_E_INVAL, "emr_result_move: bad results");
+  int64_t total = 0;
+  const emr_status st = emr_result_check(from, &total, nullptr, nullptr);
+  if (st != EMR_OK) return st;
+  if (total > to->capacity)
+    return fail(EMR_E_CAPACITY, "%lld records for a capacity of %lld", (long long)total,
+                (long long)to->capacity);
+  if (total > 0) {
+    if (!to->parent || !to->w4) return fail(EMR_E_INVAL, "parent/w4 is NULL with records to move");
+    const hipStream_t s = (hipStream_t)stream;
+    HIP_OR_FAIL(hipMemcpyAsync(to->parent, from->parent, (size_t)total * 4, hipMemcpyDeviceToDevice, s));
+    HIP_OR_FAIL(hipMemcpyAsync(to->w4, from->w4, (size_t)total * 16, hipMemcpyDeviceToDevice, s));
+  }
+  std::lock_guard<std::mutex> lock(g_ring_mu);
+  FlagRing* R = nullptr;
+  const emr_status rs = flag_ring(&R);
+  if (rs != EMR_OK) return rs;
+  int latest = -1;
+  for (int k = 0; k < kFlagSlots; ++k) {
+    if (R->ws[k] == to->workspace) R->ws[k] = nullptr;
+    if (R->ws[k] == from->workspace && (latest < 0 || R->seq[k] > R->seq[latest])) latest = k;
+  }
+  if (latest >= 0) R->ws[latest] = to->workspace;
+  return EMR_OK;
+}
+
 emr_status emr_eval_raw(const emr_population* pop, const emr_source* sources, int32_t n_sources,
                         const int32_t* src_offsets, int32_t n_shared, int32_t depth, float* out_dev,
                         void* workspace, int64_t workspace_bytes, void* stream) {

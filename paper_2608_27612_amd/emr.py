@@ -24,7 +24,7 @@ EMR_MAX_DEPTH = 15
 ABI_FUNCTIONS = [
     "emr_last_error", "emr_version", "emr_grid_count", "emr_build_grids", "emr_pack_population",
     "emr_free_population", "emr_population_info", "emr_workspace_bytes", "emr_discover",
-    "emr_result_check", "emr_eval_raw", "emr_discover_cost", "emr_profile_enable",
+    "emr_result_check", "emr_result_move", "emr_eval_raw", "emr_discover_cost", "emr_profile_enable",
     "emr_profile_read", "emr_stream_chunks", "emr_discover_stream", "emr_pack_population_flat",
     "emr_set_jit", "emr_jit_info", "emr_eval_raw_noalloc", "emr_call_check", "emr_cell_words",
     "emr_hidden_workspace_bytes", "emr_hidden_sources", "emr_express_workspace_bytes",
@@ -124,6 +124,7 @@ def lib():
             "emr_workspace_bytes": (I32, [P, P, I32, P, I32, I32, I64, P]),
             "emr_discover": (I32, [P, P, I32, P, I32, I32, F32, P, P]),
             "emr_result_check": (I32, [P, P, P, P]),
+            "emr_result_move": (I32, [P, P, P]),
             "emr_eval_raw": (I32, [P, P, I32, P, I32, I32, P, P, I64, P]),
             "emr_discover_cost": (I32, [P, P, I32, P, I32, I32, F64, P, P, P, P]),
             "emr_profile_enable": (I32, [I32, I32, F64]),
@@ -418,8 +419,8 @@ def emr_result_check(res, stream=None):
 
 # A call of this many parent positions or more runs for milliseconds, and finding more than
 # DEFAULT_CAPACITY records it would run a second time: emr_discover_all gives it room for
-# ROOMY_CAPACITY records (3 GB while it runs, of which the 1.3 GB workspace stays with the result) and
-# then moves the records into buffers of the usual size. Two populations of 100 CPPNs whose hidden nodes at depth 10 find more than that: 37.1 -> 19.8
+# ROOMY_CAPACITY records (3 GB while it runs) and then moves the result into buffers of the usual
+# size. Two populations of 100 CPPNs whose hidden nodes at depth 10 find more than that: 37.1 -> 19.8
 # and 78.5 -> 41.1 ms; one that finds less pays a copy (9.4 -> 9.5 ms). Shorter calls keep the small
 # buffers: their second run is cheap. So do calls on a device with less than ROOMY_FREE bytes to
 # spare (a program that keeps many results).
@@ -428,12 +429,21 @@ ROOMY_CAPACITY = 1 << 26
 ROOMY_FREE = 24 << 30
 
 
+def _device_free():
+    """Bytes that torch can still hand out: the device's free memory, and what torch holds unused."""
+    import torch
+    free = torch.cuda.mem_get_info()[0]
+    if free < ROOMY_FREE:
+        free += torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
+    return free
+
+
 def _roomy_result(pop, sources, depth, src_offsets):
     """A result with room for ROOMY_CAPACITY records, or None: a short call, or no such memory."""
     import torch
     _, q = emr_grid_count(depth)
     cap = n_pairs_of(pop, sources, src_offsets) * q
-    if cap < ROOMY_POSITIONS or torch.cuda.mem_get_info()[0] < ROOMY_FREE:
+    if cap < ROOMY_POSITIONS or _device_free() < ROOMY_FREE:
         return None
     try:
         return alloc_result(pop, sources, depth, src_offsets, min(cap, ROOMY_CAPACITY))
@@ -441,19 +451,22 @@ def _roomy_result(pop, sources, depth, src_offsets):
         return None
 
 
-def _fit_result(res, total):
-    """Moves a checked result's records into buffers of DEFAULT_CAPACITY records, or of `total` where
-    that is more, as a call without the extra room leaves them; done when it returns."""
+def _fit_result(pop, sources, depth, src_offsets, res, total):
+    """A checked result's records and check in buffers (a workspace among them) for DEFAULT_CAPACITY
+    records, or for `total` where that is more, as a call without the extra room leaves them; done
+    when it returns."""
     import torch
     cap = max(total, DEFAULT_CAPACITY)
-    for key in ("parent", "w4"):
-        fit = torch.empty((cap,) + tuple(res[key].shape[1:]), dtype=res[key].dtype, device="cuda")
-        fit[:total].copy_(res[key][:total])
-        res[key] = fit
-    res["capacity"] = cap
-    res.pop("_struct", None)
-    res.pop("_check_args", None)
+    ws = emr_workspace_bytes(pop, sources, depth, src_offsets, cap)
+    fit = dict(res, capacity=cap,
+               parent=torch.empty(cap, dtype=torch.int32, device="cuda"),
+               w4=torch.empty((cap, 4), dtype=torch.float32, device="cuda"),
+               workspace=torch.empty(max(ws, 256), dtype=torch.uint8, device="cuda"))
+    fit.pop("_check_args", None)
+    fit["_struct"] = _result_struct(fit)
+    _check(lib().emr_result_move(C.byref(res["_struct"]), C.byref(fit["_struct"]), _stream_ptr(None)))
     torch.cuda.current_stream().synchronize()
+    return fit
 
 
 def emr_discover_all(pop: Population, sources, depth: int, theta: float, src_offsets=None,
@@ -467,7 +480,7 @@ def emr_discover_all(pop: Population, sources, depth: int, theta: float, src_off
     try:
         total, _ = emr_result_check(res, stream)
         if room is not None:
-            _fit_result(res, total)
+            res = _fit_result(pop, sources, depth, src_offsets, res, total)
     except EmrError as e:
         if e.status != EMR_E_CAPACITY:
             raise

@@ -218,3 +218,35 @@ def test_more_streams_than_counter_sets(emr):
             emr.emr_result_check(b)
         for b in bufs:
             same(host(emr, b), want)
+
+
+@pytest.mark.parametrize("enough", [True, False])
+def test_long_discoveries_leave_buffers_of_the_usual_size(emr, monkeypatch, enough):
+    """emr_discover_all's extra room (a call of many positions): the result has buffers and a workspace
+    of the usual size, whether the room sufficed or not, and is checked and used again like any."""
+    import torch
+    pop = emr.emr_pack_population(W.population(78, 100, 20, 60))
+    sources = W.xor_sources()
+    theta = np.float32(0.03).item()
+    want = host(emr, emr.emr_discover_all(pop, sources, 6, theta))
+    total = int(want[0].sum())
+    monkeypatch.setattr(emr, "DEFAULT_CAPACITY", total // 4)
+    monkeypatch.setattr(emr, "ROOMY_POSITIONS", 1)
+    monkeypatch.setattr(emr, "ROOMY_CAPACITY", 2 * total if enough else total // 2)
+    res = emr.emr_discover_all(pop, sources, 6, theta)
+    assert res["capacity"] == total
+    assert res["workspace"].numel() == emr.emr_workspace_bytes(pop, sources, 6, capacity=total)
+    assert res["parent"].numel() == total and res["w4"].shape == (total, 4)
+    same(host(emr, res), want)
+    biggest = int(want[0].max())
+    assert emr.emr_result_check(res) == (total, biggest)
+    assert emr.emr_call_check(res["workspace"], res["capacity"]) == (total, biggest)
+    emr.emr_discover(pop, sources, 6, theta, res=res)
+    assert emr.emr_result_check(res) == (total, biggest)
+    same(host(emr, res), want)
+    # memory that torch holds without using it counts as free
+    block = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+    monkeypatch.setattr(emr, "ROOMY_FREE", 1 << 62)
+    used = emr._device_free()
+    del block
+    assert emr._device_free() >= used + (1 << 30)

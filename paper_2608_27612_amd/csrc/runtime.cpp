@@ -565,10 +565,11 @@ double chunk_cost(const Plan& P, uint64_t gi, uint32_t S, double tpw, double nt)
   return S * q * nt * (emr::kTile / emr::kWave) + nt / tpw * kSchedWalkSlots + kSchedChunkSlots;
 }
 constexpr size_t kMaxScheds = 16;            // launch shapes a plan keeps lists for
-// Placing a chunk costs the host about 0.4 us, and with hundreds of chunks per workgroup the
-// round-robin shares are balanced by their number alone (227 ms of placement before a launch of
-// 24 ms that did not need it), so larger launches run round-robin.
-constexpr uint64_t kSchedMaxChunks = 1u << 17;
+// A launch beyond this many chunks, or beyond kListLds chunks per workgroup (524,288 on 256 CUs: its
+// lists would not fit the LDS, and placing them took 227 ms), runs round-robin. Below, a plan that runs
+// again pays for the placement once (15 to 25 ms for 200,000 to 350,000 chunks) and its launches gain
+// 2 to 4%: 300 CPPNs at depth 10 0.785 against 0.759 ms, 2000 at depth 9 1.334 against 1.309 ms.
+constexpr uint64_t kSchedMaxChunks = 1u << 22;
 constexpr uint64_t kSchedMaxBytes = 64u << 20;
 
 // The waves' chunk lists of a discover launch with scalars sc on `grid` workgroups, made and

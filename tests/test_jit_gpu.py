@@ -203,3 +203,26 @@ def test_biased_node_of_each_activation_both_tiers(emr, act):
     for policy in (emr.EMR_JIT_OFF, emr.EMR_JIT_ALWAYS):
         emr.emr_set_jit(policy)
         check_raw(emr, [g], W.xor_sources(), 5)
+
+
+def test_a_resident_launch_of_more_than_2_pow_17_chunks_is_listed(emr):
+    """300 CPPNs at depth 10 (about 200,000 chunks): the plan's third call runs from the workgroups'
+    chunk lists, and its records are the first call's bit for bit."""
+    pop = emr.emr_pack_population(W.population(3, 300, 20, 60))
+    sources = W.xor_sources()
+    res = emr.alloc_result(pop, sources, 10, capacity=1 << 24)
+    got = []
+    emr.emr_profile_enable()
+    try:
+        for _ in range(3):
+            emr.emr_discover(pop, sources, 10, 0.03, res=res)
+            total, _ = emr.emr_result_check(res)
+            got.append([res["pair_offset"].cpu().numpy(), res["parent"][:total].cpu().numpy(),
+                        res["w4"][:total].cpu().numpy().view(np.uint32)])
+        launches = emr.emr_profile_read()
+    finally:
+        emr.emr_profile_enable(False)
+    assert launches[-1]["listed"] and launches[-1]["compiled"]
+    for g in got[1:]:
+        for x, y in zip(g, got[0]):
+            np.testing.assert_array_equal(x, y)

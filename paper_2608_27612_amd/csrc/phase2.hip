@@ -44,16 +44,47 @@ __device__ __forceinline__ uint32_t last_at_most(const int64_t* off, uint32_t lo
   }
   return lo;
 }
-// The last q >= lo with off[q] <= r, given off[lo] <= r: a gallop, then a search.
-__device__ __forceinline__ uint32_t last_from(const int64_t* off, uint32_t lo, uint32_t n,
-                                              int64_t r) {
-  uint32_t step = 1u, hi = lo + 1u;
-  while (hi < n && off[hi] <= r) {
-    lo = hi;
-    step = step < (1u << 30) ? 2u * step : step;
-    hi = n - lo > step ? lo + step : n;
+// The same for an r of the whole wave, 64 places at a time: two or three trips to memory where the
+// halving above takes 13 (5000 pairs), each of them most of a microsecond.
+__device__ __forceinline__ uint32_t wave_last(const int64_t* off, uint32_t lo, uint32_t hi, int64_t r,
+                                              uint32_t lane) {
+  while (hi - lo > 1u) {
+    const uint32_t step = (hi - lo - 1u) / kWave + 1u;
+    const uint64_t q = (uint64_t)lo + (uint64_t)lane * step;
+    const uint32_t le = popc64(ballot(q < hi && (lane == 0u || off[q] <= r)));
+    lo += (le - 1u) * step;
+    hi = hi - lo > step ? lo + step : hi;
   }
-  return last_at_most(off, lo, hi, r);
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+// The last q >= lo with off[q] <= r (the wave's), given off[lo] <= r: mostly close to lo.
+__device__ __forceinline__ uint32_t wave_last_from(const int64_t* off, uint32_t lo, uint32_t n,
+                                                   int64_t r, uint32_t lane) {
+  const uint64_t q = (uint64_t)lo + lane;
+  const uint32_t le = popc64(ballot(q < n && (lane == 0u || off[q] <= r)));
+  return le < (uint32_t)kWave ? __builtin_amdgcn_readfirstlane(lo + le - 1u)
+                              : wave_last(off, lo + kWave - 1u, n, r, lane);
+}
+// Each lane's last q with off[q] <= r (off[p] <= r <= the last lane's r), v being off[p + lane]: 64
+// places between p and the last lane's q are searched between the lanes; only where there are more
+// (a step of 64 entries over many empty pairs) does a lane then halve the rest in memory.
+__device__ __forceinline__ uint32_t lane_last(const int64_t* off, uint32_t p, uint32_t n, int64_t v,
+                                              int64_t r, int64_t r_last, uint32_t lane) {
+  uint32_t step = 1u, hi = n;
+  if (ballot(v > r_last) == 0ull) {
+    hi = wave_last(off, p + kWave - 1u, n, r_last, lane) + 1u;
+    step = (hi - p - 1u) / kWave + 1u;
+    const uint64_t q = (uint64_t)p + (uint64_t)lane * step;
+    v = q < hi ? off[q] : INT64_MAX;
+  }
+  uint32_t k = 0;  // the last place with v <= r
+#pragma unroll
+  for (uint32_t d = kWave / 2; d >= 1u; d >>= 1) {
+    const int64_t u = __shfl(v, (int)(k + d), kWave);
+    if (u <= r) k += d;
+  }
+  const uint32_t lo = p + k * step;
+  return step == 1u ? lo : last_at_most(off, lo, hi - lo > step ? lo + step : hi, r);
 }
 
 // The entries of a CSR table that the buffers hold: from the first pair's offset (a caller may pass
@@ -72,36 +103,52 @@ __device__ __forceinline__ int64_t span_length(int64_t held, uint32_t n_spans) {
   return (steps + n_spans - 1) / n_spans * kWave;
 }
 
-// Calls f(i, pair, ctx) for the wave's entries [base, end) of a CSR table (off[n + 1]), 64 at a
-// time, every lane of the wave taking part (i < end is the lane's own test): pair is the entry's
-// and ctx = make(pair) what its entries need of it. Most steps lie inside one pair, which the wave
-// then follows without a search or another load of its context (a step that loaded it again took
-// five trips to memory, one after the other); in the others each lane searches on from the pair of
-// the step's first entry.
+// 64 of the n offsets, spread over all of them: the first round of a span's search, read before its
+// first entry is known.
+__device__ __forceinline__ int64_t span_pivot(const int64_t* off, uint32_t n, uint32_t lane) {
+  const uint64_t q = (uint64_t)lane * ((n - 1u) / kWave + 1u);
+  return q < n ? off[q] : INT64_MAX;
+}
+
+// Calls f(i, pair, ctx) for the wave's entries [base, end) of a CSR table (off[n + 1], n > 0), 64 at
+// a time, every lane of the wave taking part (i < end is the lane's own test): pair is the entry's
+// and ctx = make(pair) what its entries need of it. The wave holds the offsets of 64 pairs, from
+// its step's first on. Most steps lie inside one pair, which the wave then follows without a search
+// or another load of its context; in the others each lane finds its pair among the 64. (What bounds
+// a call of few entries is the trips to memory, one after the other: with a search by halves here,
+// a gallop per lane and a fence in k_filter_end, the filters of 432 records took 56 / 40 / 65 us,
+// expression / band / chain, now 51 / 36 / 57; of 63,000 records 64 / 49 / 75, now 57 / 42 / 67.)
 template <typename M, typename F>
-__device__ __forceinline__ void for_span(const int64_t* off, uint32_t n, int64_t base, int64_t end,
-                                         uint32_t lane, M&& make, F&& f) {
+__device__ __forceinline__ void for_span(const int64_t* off, uint32_t n, int64_t pivot, int64_t base,
+                                         int64_t end, uint32_t lane, M&& make, F&& f) {
   if (base >= end) return;
-  uint32_t p = __builtin_amdgcn_readfirstlane(last_at_most(off, 0u, n, base));
-  int64_t p1 = off[p + 1];
-  auto ctx = make(p);
+  const uint32_t step = (n - 1u) / kWave + 1u;
+  uint32_t p = (popc64(ballot(lane == 0u || pivot <= base)) - 1u) * step;
+  p = wave_last(off, p, n - p > step ? p + step : n, base, lane);
+  auto window = [&] {
+    const uint64_t q = (uint64_t)p + lane;
+    return q < n ? off[q] : INT64_MAX;
+  };
+  int64_t v = window(), p1 = __shfl(v, 1, kWave);
+  bool have = false;
+  decltype(make(p)) ctx{};
   for (int64_t b = base; b < end; b += kWave) {
     if (b >= p1) {
-      p = __builtin_amdgcn_readfirstlane(last_from(off, p, n, b));
-      p1 = off[p + 1];
-      ctx = make(p);
+      const uint32_t le = popc64(ballot(lane == 0u || v <= b));
+      p = le < (uint32_t)kWave ? __builtin_amdgcn_readfirstlane(p + le - 1u)
+                               : wave_last(off, p + kWave - 1u, n, b, lane);
+      v = window();
+      p1 = __shfl(v, 1, kWave);
+      have = false;
     }
-    const int64_t i = b + lane;
-    if (p1 >= (b + kWave < end ? b + kWave : end)) {
+    const int64_t i = b + lane, last = min(b + kWave, end) - 1;
+    if (p1 > last) {
+      if (!have) ctx = make(p);
+      have = true;
       f(i, p, ctx);
     } else {
-      uint32_t q = p;
-      auto c = ctx;
-      if (i >= p1 && i < end) {
-        q = last_from(off, p, n, i);
-        c = make(q);
-      }
-      f(i, q, c);
+      const uint32_t q = lane_last(off, p, n, v, i < last ? i : last, last, lane);
+      f(i, q, make(q));
     }
   }
 }
@@ -132,12 +179,13 @@ template <typename Op>
 __global__ void __launch_bounds__(256) k_filter_count(Op op) {
   const uint32_t lane = lane_id(), span = span_index();
   const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
+  const int64_t pivot = span_pivot(op.off(), n, lane);
   const Held held = held_entries(op.off(), n, op.cap());
   const int64_t len = span_length(held.end - held.first, n_spans);
   const int64_t base = held.first + (int64_t)span * len, end = min(base + len, held.end);
   uint32_t total = 0;
   for_span(
-      op.off(), n, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
+      op.off(), n, pivot, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
       [&](int64_t i, uint32_t, const auto& c) {
         const uint32_t m = i < end ? op.keep(i, c) : 0u;
         total += wave_sum3((uint32_t)__builtin_popcount(m));
@@ -148,39 +196,42 @@ __global__ void __launch_bounds__(256) k_filter_count(Op op) {
 
 // The kept entries of the spans before this one (n_spans at most kFilterSpans, read by the
 // workgroup: 32 loads per thread at most; the spans from `used` on hold no entries).
+constexpr uint32_t kFilterWaves = 4;  // of the counting and emitting workgroups
 __device__ __forceinline__ uint64_t spans_before(const uint32_t* kept, uint32_t used,
                                                  uint64_t* wsum) {
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, waves = blockDim.x / kWave;
-  const uint32_t first = blockIdx.x * waves, read = min(first, used);
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  const uint32_t first = blockIdx.x * kFilterWaves, read = min(first, used);
+  const uint4 own = *reinterpret_cast<const uint4*>(kept + first);
   uint64_t sum = 0;
-  for (uint32_t k = threadIdx.x; k < read; k += blockDim.x) sum += kept[k];
+  for (uint32_t k = threadIdx.x; k < read; k += kFilterWaves * kWave) sum += kept[k];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
   if (lane == 0) wsum[wv] = sum;
   __syncthreads();
   uint64_t t = 0;
-  for (uint32_t k = 0; k < waves; ++k) t += wsum[k];
-  for (uint32_t k = first; k < first + wv; ++k) t += kept[k];
-  return t;
+#pragma unroll
+  for (uint32_t k = 0; k < kFilterWaves; ++k) t += wsum[k];
+  return t + (wv > 0u ? own.x : 0u) + (wv > 1u ? own.y : 0u) + (wv > 2u ? own.z : 0u);
 }
 
 // Writes the kept items in order, and the offset of every pair whose first entry the span holds.
 template <typename Op>
 __global__ void __launch_bounds__(256) k_filter_emit(Op op) {
-  __shared__ uint64_t wsum[256 / kWave];
+  __shared__ uint64_t wsum[kFilterWaves];
   const uint32_t lane = lane_id(), span = span_index();
   const uint32_t n = op.pairs(), n_spans = gridDim.x * (blockDim.x / kWave);
+  const int64_t pivot = span_pivot(op.off(), n, lane);
   const Held held = held_entries(op.off(), n, op.cap());
   const int64_t entries = held.end - held.first, len = span_length(entries, n_spans);
   const int64_t base = held.first + (int64_t)span * len, end = min(base + len, held.end);
   // The spans are those of the capacity: of a light call's, most workgroups have no entries and
-  // leave before the sums (the last one writes the total): the filters of a tabular result 344 ->
-  // 338 us, of 432 records 262 -> 252 us.
+  // leave before the sums (the last one writes the total).
   const uint32_t used = len > 0 ? (uint32_t)((entries + len - 1) / len) : 0u;
-  if (blockIdx.x + 1 < gridDim.x && blockIdx.x * (blockDim.x / kWave) >= used) return;
-  int64_t at0 = (int64_t)spans_before(op.spans.kept, used, wsum);
+  if (blockIdx.x + 1 < gridDim.x && blockIdx.x * kFilterWaves >= used) return;
+  // (few spans are summed whole: these reads then go out with the offsets', not after them)
+  int64_t at0 = (int64_t)spans_before(op.spans.kept, n_spans <= 1024u ? n_spans : used, wsum);
   for_span(
-      op.off(), n, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
+      op.off(), n, pivot, base, end, lane, [&](uint32_t pair) { return op.context(pair); },
       [&](int64_t i, uint32_t pair, const auto& ctx) {
         const bool mine = i < end;
         const uint32_t m = mine ? op.keep(i, ctx) : 0u;
@@ -197,47 +248,60 @@ __global__ void __launch_bounds__(256) k_filter_emit(Op op) {
 }
 
 // After k_filter_emit: the offsets of the empty pairs (their next pair's that has an entry) and of
-// those whose entries lie beyond the ones held (the total), and every pair's count; the workgroup
-// that ends last hands the call's flags over (see k_scan).
-constexpr int kEndThreads = 256;
+// those whose entries lie beyond the ones held (the total), and every pair's count, 64 consecutive
+// pairs per wave; the workgroup that ends last hands the call's flags over (see k_scan).
+constexpr int kEndThreads = 1024;
 template <typename Op>
 __global__ void __launch_bounds__(kEndThreads) k_filter_end(Op op) {
-  const uint32_t n = op.pairs();
+  __shared__ uint32_t wmax[kEndThreads / kWave];
+  const uint32_t n = op.pairs(), lane = lane_id();
   const FilterSpans& F = op.spans;
-  const int64_t held = held_entries(op.off(), n, op.cap()).end;
-  const uint64_t total = *reinterpret_cast<const uint64_t*>(F.kept + kFilterSpans + 2);
+  const int64_t* off = op.off();
+  const uint32_t err = __hip_atomic_load(F.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int64_t held = held_entries(off, n, op.cap()).end;
+  const int64_t total = (int64_t)*reinterpret_cast<const uint64_t*>(F.kept + kFilterSpans + 2);
   uint32_t mx = 0;
-  // the offset of the first kept item at or after entry i, the first of pair p or of a later one
-  auto offset_at = [&](int64_t i, uint32_t p) {
-    return i >= held ? (int64_t)total : F.out_offset[last_from(op.off(), p, n, i)];
-  };
-  for (uint32_t p = blockIdx.x * kEndThreads + threadIdx.x; p < n; p += gridDim.x * kEndThreads) {
-    const int64_t i0 = op.off()[p], i1 = op.off()[p + 1];
-    int64_t c = 0;
-    if (i0 < i1 && i0 < held) {
-      const int64_t o0 = F.out_offset[p];
-      const int64_t o1 = p + 1 == n ? (int64_t)total : offset_at(i1, p + 1);
-      c = o1 > o0 ? o1 - o0 : 0;
-    } else {
-      F.out_offset[p] = offset_at(i0, p);
+  const uint32_t waves = gridDim.x * (kEndThreads / kWave);
+  for (uint32_t w = span_index(); w <= (n - 1u) / kWave; w += waves) {
+    const uint32_t p0 = w * kWave, p = p0 + lane;
+    const uint32_t p1 = n - p0 > (uint32_t)kWave ? p0 + kWave : n;  // the wave's pairs end here
+    const int64_t i0 = p < p1 ? off[p] : 0, i1 = p < p1 ? off[p + 1] : 0, i_end = off[p1];
+    const bool has = i0 < i1 && i0 < held;
+    const uint64_t m = ballot(has);
+    int64_t o = has ? F.out_offset[p] : 0;
+    // the offset of the first entry after the wave's pairs
+    int64_t after = total;
+    if (i_end < held) after = F.out_offset[wave_last_from(off, p1 - 1u, n, i_end, lane)];
+    const uint64_t later = lane == kWave - 1 ? 0ull : m >> (lane + 1u);
+    const int64_t ahead = __shfl(o, later ? (int)(lane + 1u + (uint32_t)__builtin_ctzll(later)) : 0, kWave);
+    const int64_t next = later ? ahead : after;
+    if (p < p1) {
+      if (!has) F.out_offset[p] = next;
+      const int64_t c = has && next > o ? next - o : 0;
+      F.out_count[p] = c;
+      mx = max(mx, (uint32_t)min(c, (int64_t)0xFFFFFFFFll));
     }
-    F.out_count[p] = c;
-    mx = max(mx, (uint32_t)min(c, (int64_t)0xFFFFFFFFll));
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
-  if (lane_id() == 0 && mx != 0u) raise_max(F.flags + kFlagMax, mx);
-  __threadfence();  // (the raised word before the count below)
+  if (lane == 0) wmax[threadIdx.x / kWave] = mx;
   __syncthreads();
-  if (threadIdx.x != 0 || atomicAdd(F.kept + kFilterSpans, 1u) != gridDim.x - 1u) return;
-  __threadfence();
-  F.out_offset[n] = (int64_t)total;
-  F.host[kFlagErr] =
-      __hip_atomic_load(F.flags + kFlagErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  F.host[kFlagMax] =
-      __hip_atomic_load(F.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int k = 1; k < kEndThreads / kWave; ++k) mx = max(mx, wmax[k]);
+  if (gridDim.x > 1u) {
+    // the workgroup's largest is raised before the workgroup is counted: the value that the first
+    // atomic returns has to be there before the second (a fence would write the L2 back)
+    const uint32_t before = atomicMax(F.flags + kFlagMax, mx);
+    asm volatile("" ::"v"(before) : "memory");
+    if (atomicAdd(F.kept + kFilterSpans, 1u) != gridDim.x - 1u) return;
+    mx = __hip_atomic_load(F.flags + kFlagMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  F.out_offset[n] = total;
+  F.host[kFlagErr] = err;
+  F.host[kFlagMax] = mx;
   F.host[kFlagTotal] = (uint32_t)total;
-  F.host[kFlagTotal + 1] = (uint32_t)(total >> 32);
+  F.host[kFlagTotal + 1] = (uint32_t)((uint64_t)total >> 32);
 #pragma unroll
   for (int k = 0; k < kFlagWords; ++k)
     __hip_atomic_store(F.flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -264,7 +328,7 @@ __global__ void __launch_bounds__(256) k_hidden_mark(HiddenArgs A) {
   const int64_t len = span_length(held, gridDim.x * (blockDim.x / kWave));
   const int64_t base = (int64_t)span_index() * len, end = min(base + len, held);
   for_span(
-      off, np, base, end, lane,
+      off, np, span_pivot(off, np, lane), base, end, lane,
       [&](uint32_t p) {
         return RecordPair{off[p], off[p] + A.rec.count[p], A.rec.pair_info[2 * p], 0.0f, 0.0f};
       },
@@ -416,12 +480,11 @@ struct ExpressOp : ExpressArgs {
             rec.src_xy[2 * j + 1]};
   }
   __device__ uint32_t keep(int64_t i, const RecordPair& c) const {
-    if (i < c.start || i >= c.end) return 0u;
-    const uint32_t P = rec.parent[i];
-    if ((int64_t)P >= n_parents(rec.depth)) return 0u;
+    const uint32_t P = rec.parent[i];  // (these reads go out with the pair's)
+    const float4 w = reinterpret_cast<const float4*>(rec.w4)[i];
+    if (i < c.start || i >= c.end || (int64_t)P >= n_parents(rec.depth)) return 0u;
     const bool incoming = (c.info & 1u) != 0u;
     const float sx = c.sx, sy = c.sy;
-    const float4 w = reinterpret_cast<const float4*>(rec.w4)[i];
     const float wk[4] = {w.x, w.y, w.z, w.w};
     // Eq. 1: the four children are one aligned quad of their level
     float x0, y0;
@@ -470,12 +533,12 @@ __global__ void __launch_bounds__(256) k_chain_mark(ChainArgs A) {
   const int64_t len = span_length(held.end - held.first, gridDim.x * (blockDim.x / kWave));
   const int64_t base = held.first + (int64_t)span_index() * len, end = min(base + len, held.end);
   for_span(
-      off, np, base, end, lane,
+      off, np, span_pivot(off, np, lane), base, end, lane,
       [&](uint32_t p) { return RecordPair{off[p], off[p] + A.rec.count[p], 0u, 0.0f, 0.0f}; },
       [&](int64_t i, uint32_t p, const RecordPair& c) {
-        if (i >= end || i < c.start || i >= c.end) return;
-        const uint32_t P = A.rec.parent[i];
-        if ((int64_t)P < Q) atomicOr(A.member + (int64_t)p * A.qwords + P / 32u, 1u << (P % 32u));
+        const uint32_t P = i < end ? A.rec.parent[i] : 0u;
+        if (i < c.end && i >= c.start && i < end && (int64_t)P < Q)
+          atomicOr(A.member + (int64_t)p * A.qwords + P / 32u, 1u << (P % 32u));
       });
 }
 
@@ -490,13 +553,17 @@ struct ChainOp : ChainArgs {
     return {start, start + rec.count[pair], pair, 0.0f, 0.0f};  // (info: the pair itself)
   }
   __device__ uint32_t keep(int64_t i, const RecordPair& c) const {
-    if (i < c.start || i >= c.end) return 0u;
     uint32_t P = rec.parent[i];
-    if ((int64_t)P >= n_parents(rec.depth)) return 0u;
+    if (i < c.start || i >= c.end || (int64_t)P >= n_parents(rec.depth)) return 0u;
     const uint32_t* bits = member + (int64_t)c.info * qwords;
-    while (P > 0u) {
-      P = (P - 1u) / 4u;
-      if (((bits[P / 32u] >> (P % 32u)) & 1u) == 0u) return 0u;
+    while (P > 0u) {  // four ancestors at a time, their reads in flight together (the root: its own)
+      uint32_t all = 1u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        P = P > 0u ? (P - 1u) / 4u : 0u;
+        all &= bits[P / 32u] >> (P % 32u);
+      }
+      if ((all & 1u) == 0u) return 0u;
     }
     return 1u;
   }
@@ -544,7 +611,7 @@ hipError_t launch_filter(const Op& op, int64_t cap, hipStream_t s) {
   hipLaunchKernelGGL(emr::k_filter_count<Op>, dim3(blocks), dim3(256), 0, s, op);
   hipLaunchKernelGGL(emr::k_filter_emit<Op>, dim3(blocks), dim3(256), 0, s, op);
   const uint32_t ends = (op.pairs() + emr::kEndThreads - 1) / emr::kEndThreads;
-  hipLaunchKernelGGL(emr::k_filter_end<Op>, dim3(ends < 256u ? ends : 256u), dim3(emr::kEndThreads), 0,
+  hipLaunchKernelGGL(emr::k_filter_end<Op>, dim3(ends < 64u ? ends : 64u), dim3(emr::kEndThreads), 0,
                      s, op);
   return hipGetLastError();
 }

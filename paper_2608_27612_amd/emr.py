@@ -723,8 +723,14 @@ def emr_cell_words(depth: int) -> int:
     return w.value
 
 
-def _rec_struct(rec):
-    return rec.get("_struct") or _result_struct(rec)
+def _rec_struct(rec, total=None):
+    """The result as a filter's input; `total`, where the caller knows it, sizes the filter's launch by
+    the records instead of by the buffers that hold them."""
+    st = rec.get("_struct") or _result_struct(rec)
+    if total is None or total >= st.capacity:
+        return st
+    return emr_result(st.parent, st.w4, total, st.pair_count, st.pair_offset, st.workspace,
+                      st.workspace_bytes)
 
 
 def emr_hidden_sources(pop: Population, sources, depth: int, rec, src_offsets=None, known=None,
@@ -783,7 +789,8 @@ def emr_express(pop: Population, sources, depth: int, rec, type_mask: int = EMR_
     returns dict(cell, w, pair_count, pair_offset device tensors, total)."""
     import torch
     n_pairs = rec["n_pairs"]
-    cap = int(capacity) if capacity is not None else 4 * int(rec["pair_offset"][-1].item())
+    total = int(rec["pair_offset"][-1].item()) if capacity is None else None
+    cap = int(capacity) if capacity is not None else 4 * total
     wsb = C.c_int64()
     _check(lib().emr_express_workspace_bytes(n_pairs, C.byref(wsb)))
     ws = torch.empty(max(wsb.value, 256), dtype=torch.uint8, device="cuda")
@@ -799,7 +806,7 @@ def emr_express(pop: Population, sources, depth: int, rec, type_mask: int = EMR_
     _check(lib().emr_express(pop.handle, src.ctypes.data, len(sources),
                              None if offs is None else offs.ctypes.data,
                              0 if offs is not None else len(sources), depth,
-                             C.byref(_rec_struct(rec)), int(type_mask), C.c_float(w_min),
+                             C.byref(_rec_struct(rec, total)), int(type_mask), C.c_float(w_min),
                              C.byref(st), _stream_ptr(stream)))
     out["total"], _ = emr_call_check(ws, cap, stream)
     out["n_pairs"] = n_pairs
@@ -863,7 +870,8 @@ def emr_chain_filter(rec, depth: int, capacity=None, stream=None):
     form (checked)."""
     import torch
     n_pairs = rec["n_pairs"]
-    cap = int(rec["pair_offset"][-1].item()) if capacity is None else int(capacity)
+    total = int(rec["pair_offset"][-1].item()) if capacity is None else None
+    cap = total if capacity is None else int(capacity)
     wsb = C.c_int64()
     _check(lib().emr_chain_workspace_bytes(n_pairs, depth, C.byref(wsb)))
     out = {"parent": torch.empty(max(cap, 1), dtype=torch.int32, device="cuda"),
@@ -874,7 +882,7 @@ def emr_chain_filter(rec, depth: int, capacity=None, stream=None):
            "capacity": cap, "n_pairs": n_pairs}
     st = _result_struct(out)
     out["_struct"] = st
-    _check(lib().emr_chain_filter(C.byref(_rec_struct(rec)), n_pairs, depth, C.byref(st),
+    _check(lib().emr_chain_filter(C.byref(_rec_struct(rec, total)), n_pairs, depth, C.byref(st),
                                   _stream_ptr(stream)))
     emr_result_check(out, stream)
     return out

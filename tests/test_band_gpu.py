@@ -64,6 +64,26 @@ def test_band_values_match_oracle(emr, seed, n, D, biases):
     check_band(genomes, sources, D, conn_h, band[:len(conn_h["cell"])].cpu().numpy())
 
 
+def test_band_values_do_not_depend_on_the_pairs_beside(emr):
+    """Waves past a pair's first part get a pair each up to 1024 pairs and several above: 1200 pairs,
+    some with thousands of connections, against the same genomes 500 pairs at a time, bit for bit."""
+    genomes = W.population(61, 300, 20, 60)
+    sources = W.xor_sources()
+    D = 6
+    _, conn, band = run_band(emr, genomes, sources, D, 0.003)
+    whole = conn_to_host(conn)
+    assert whole["pair_count"].max() > 4 * 64 * 6 and (whole["pair_count"] < 64).any()
+    got = band[:len(whole["cell"])].cpu().numpy()
+    for g in range(0, 300, 125):
+        _, conn, band = run_band(emr, genomes[g:g + 125], sources, D, 0.003)
+        part = conn_to_host(conn)
+        lo = whole["pair_offset"][4 * g]
+        n = len(part["cell"])
+        np.testing.assert_array_equal(part["w"], whole["w"][lo:lo + n])
+        np.testing.assert_array_equal(band[:n].cpu().numpy().view(np.uint32),
+                                      got[lo:lo + n].view(np.uint32))
+
+
 def test_band_values_wide_programs(emr):
     """The tabular population's larger CPPNs need the wider register windows."""
     genomes = W.population(21, 40, 40, 120)

@@ -32,6 +32,14 @@ COUNTS = {
     "single entries": [1] * 5000,
     "long pair": [2, 0, 300000, 0, 0, 7, 63],
     "mixed": None,
+    # a step of 64 entries over 63, 64, 65 and 5000 pairs, and tables of 64, 65, 4096 and 4097 pairs
+    "63 pairs a step": [32, 32] + [0] * 61 + [1] * 3,
+    "64 pairs": [5] + [0] * 62 + [70],
+    "65 pairs": [0] * 63 + [70, 5],
+    "4096 pairs": [64] + [0] * 4094 + [64],
+    "4097 pairs": [0] + [1] + [0] * 4094 + [130],
+    "sparse": [1 if k % 173 == 5 else 0 for k in range(20000)],
+    "dense then sparse": [7] * 200 + [1 if k % 90 == 0 else 0 for k in range(9000)] + [500],
 }
 
 
@@ -118,7 +126,8 @@ def test_chain_filter(emr, name):
     np.testing.assert_array_equal(out["w4"].cpu().numpy()[:k], w4[keep])
 
 
-@pytest.mark.parametrize("name", ["ends empty", "long pair", "mixed", "single entries"])
+@pytest.mark.parametrize("name", ["ends empty", "long pair", "mixed", "single entries", "sparse",
+                                  "dense then sparse", "4097 pairs"])
 def test_ranges_of_pairs(emr, name):
     """The pairs from k on (the offsets' tail, over the same entries) give the whole table's results
     for those pairs: the band filter and the chain rule, with the entries cut off by the capacity too."""

@@ -90,7 +90,7 @@ __device__ __forceinline__ void hand_over_flags(uint32_t* flags, uint32_t* host)
     __hip_atomic_store(flags + k, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The call's last kernel when k_compact does not hand over its flags (raw outputs, streamed calls).
+// The last kernel of a call that no other kernel ends: band values, calls without pairs.
 __global__ void k_finalize(uint32_t* flags, uint32_t* host) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   hand_over_flags(flags, host);

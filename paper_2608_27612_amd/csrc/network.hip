@@ -840,9 +840,8 @@ dim3 list_grid(const emr::NetList& L, uint32_t x, uint32_t pblocks) {
 // Steps: 0 rank, 1 layout, 2 pairs of a phase, 3 its edges, 4 flags, 5 reach pass, 6 kept counts
 // and their sums, 7 nodes, 8 keys; after the sort, 14 offsets and edges. Activation: 9 initial
 // state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns by value, 13 all steps in LDS.
-extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, hipStream_t s) {
+extern "C" hipError_t emr_launch_net(int step, const void* args, hipStream_t s) {
   using namespace emr;
-  (void)work;
   const dim3 blk(kNetThreads);
   switch (step) {
     case 0: {

@@ -30,7 +30,7 @@
 namespace emr {
 emr_status set_error(emr_status st, const std::string& msg);
 }
-extern "C" hipError_t emr_launch_net(int step, const void* args, int64_t work, hipStream_t s);
+extern "C" hipError_t emr_launch_net(int step, const void* args, hipStream_t s);
 extern "C" hipError_t emr_net_sort(void* tmp, size_t* bytes, const uint32_t* kin, uint32_t* kout,
                                    const uint64_t* vin, uint64_t* vout, uint32_t n, int bits,
                                    hipStream_t s);
@@ -529,7 +529,7 @@ emr_status assemble(Build& B) {
   const uint8_t* d_dir = reinterpret_cast<const uint8_t*>(d_tab.as<uint64_t>() + 2 * K);
   emr::NetRankArgs ra{N.known.as<uint32_t>(), rank.as<uint32_t>(), hidden.as<uint32_t>(), N.words,
                       G};
-  NET_HIP(emr_launch_net(0, &ra, 0, s));
+  NET_HIP(emr_launch_net(0, &ra, s));
   emr::NetLayoutArgs la{};
   la.hidden = hidden.as<uint32_t>();
   la.conn_offset = d_tab.as<const int64_t*>();
@@ -543,7 +543,7 @@ emr_status assemble(Build& B) {
   la.n_sub = (uint32_t)N.n_sub;
   la.n_genomes = G;
   la.err = d_err;
-  NET_HIP(emr_launch_net(1, &la, 0, s));
+  NET_HIP(emr_launch_net(1, &la, s));
   for (size_t k = 0; k < K; ++k) {
     Phase& P = *N.phases[k];
     Dev pairs;
@@ -571,14 +571,14 @@ emr_status assemble(Build& B) {
     ea.ew = ew.as<float>();
     ea.e_raw = e_raw;
     ea.err = d_err;
-    NET_HIP(emr_launch_net(2, &ea, 0, s));
-    NET_HIP(emr_launch_net(3, &ea, 0, s));
+    NET_HIP(emr_launch_net(2, &ea, s));
+    NET_HIP(emr_launch_net(3, &ea, s));
   }
   // pruning: flags, then passes over every edge until one changes nothing
   emr::NetFlagArgs fa{d_dir, raw_node.as<int64_t>(), flags.as<uint16_t>(), kept_n.as<uint32_t>(),
                       N.node_offset.as<int64_t>(), (uint32_t)N.n_sub, G,
                       reinterpret_cast<int64_t*>(d_err + 2 + emr::kNetPasses)};
-  NET_HIP(emr_launch_net(4, &fa, 0, s));
+  NET_HIP(emr_launch_net(4, &fa, s));
   emr::NetReachArgs rr{eu.as<uint32_t>(), ev.as<uint32_t>(), flags.as<uint16_t>(), d_err + 1, 0u,
                        e_raw, n_raw};
   // a pass that changes something sets at least one more flag: 2 n_raw passes bound the loop
@@ -591,8 +591,8 @@ emr_status assemble(Build& B) {
   // the wait that looks at the passes then brings the kept node count too.
   int64_t kept_nodes = (int64_t)G * N.n_sub;  // (without edges nothing but the substrate is kept)
   if (e_raw == 0) {
-    NET_HIP(emr_launch_net(6, &fa, 0, s));
-    NET_HIP(emr_launch_net(7, &na, 0, s));
+    NET_HIP(emr_launch_net(6, &fa, s));
+    NET_HIP(emr_launch_net(7, &na, s));
   }
   for (int64_t pass = 0; e_raw > 0; pass += emr::kNetPasses) {
     if (pass > max_pass)
@@ -600,9 +600,9 @@ emr_status assemble(Build& B) {
                    (long long)max_pass);
     if (pass > 0) NET_HIP(hipMemsetAsync(d_err + 1, 0, 4 * emr::kNetPasses, s));
     for (rr.pass = 0; rr.pass < (uint32_t)emr::kNetPasses; ++rr.pass)
-      NET_HIP(emr_launch_net(5, &rr, 0, s));
-    NET_HIP(emr_launch_net(6, &fa, 0, s));
-    NET_HIP(emr_launch_net(7, &na, 0, s));
+      NET_HIP(emr_launch_net(5, &rr, s));
+    NET_HIP(emr_launch_net(6, &fa, s));
+    NET_HIP(emr_launch_net(7, &na, s));
     struct { uint32_t changed, unused; int64_t kept; } seen;
     static_assert(sizeof seen == 16, "the last pass word, a word between, the count");
     NET_TRY(to_host(&seen, d_err + emr::kNetPasses, sizeof seen, s));
@@ -626,7 +626,7 @@ emr_status assemble(Build& B) {
     emr::NetKeyArgs ka{eu.as<uint32_t>(), ev.as<uint32_t>(), ew.as<float>(), flags.as<uint16_t>(),
                        gid.as<uint32_t>(), keys.as<uint32_t>(), vals.as<uint64_t>(), e_raw, n_raw,
                        sentinel, d_err};
-    NET_HIP(emr_launch_net(8, &ka, 0, s));
+    NET_HIP(emr_launch_net(8, &ka, s));
     int bits = 1;
     while (bits < 32 && ((uint64_t)1 << bits) <= (uint64_t)sentinel) ++bits;  // keys <= sentinel
     size_t tb = 0;
@@ -639,7 +639,7 @@ emr_status assemble(Build& B) {
   emr::NetSplitArgs sa{skeys.as<uint32_t>(), svals.as<uint64_t>(), N.node_offset.as<int64_t>(),
                        N.in_offset.as<int64_t>(), sum.as<int64_t>(), N.in_src.as<uint32_t>(),
                        N.in_w.as<float>(), e_raw, n_raw, sentinel, G, d_err};
-  NET_HIP(emr_launch_net(14, &sa, 0, s));
+  NET_HIP(emr_launch_net(14, &sa, s));
   std::vector<int64_t> off(2 * ((size_t)G + 1) + 1);
   NET_TRY(to_host(off.data(), sum.p, off.size() * 8, s));
   if (off.back() != 0)
@@ -725,7 +725,7 @@ emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
     a.n = (uint32_t)(n_pat + n_tgt);
     std::memcpy(a.v, patterns, n_pat * 4);
     if (n_tgt) std::memcpy(a.v + n_pat, targets, n_tgt * 4);
-    NET_HIP(emr_launch_net(12, &a, 0, s));
+    NET_HIP(emr_launch_net(12, &a, s));
     return EMR_OK;
   }
   if (!M.pin_done) NET_HIP(hipEventCreateWithFlags(&M.pin_done, hipEventDisableTiming));
@@ -839,7 +839,7 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
     }
     if (blocks > 0x7FFFFFFFull)
       return failf(EMR_E_LIMIT, "networks: too many genomes x patterns");
-    if (blocks > 0) NET_HIP(emr_launch_net(13, &ra, 0, s));
+    if (blocks > 0) NET_HIP(emr_launch_net(13, &ra, s));
   }
   if (list.total > 0) {
     // two state buffers of [pblocks][nodes] float4
@@ -864,14 +864,14 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
       emr::NetStateArgs sa{list, N->node_offset.as<int64_t>(), N->node_in.as<int32_t>(),
                            M.patterns.as<float>(), buf[0], N->nodes, (uint32_t)N->n_in,
                            (uint32_t)n_patterns, (uint32_t)pblocks};
-      NET_HIP(emr_launch_net(9, &sa, 0, s));
+      NET_HIP(emr_launch_net(9, &sa, s));
       int cur = 0;
       for (int32_t t = 0; t < steps; ++t, cur ^= 1) {
         emr::NetStepArgs st{list, N->node_offset.as<int64_t>(), N->node_in.as<int32_t>(),
                             N->in_offset.as<int64_t>(), N->in_src.as<uint32_t>(),
                             N->in_w.as<float>(), buf[cur], buf[cur ^ 1], N->nodes,
                             (uint32_t)pblocks};
-        NET_HIP(emr_launch_net(10, &st, 0, s));
+        NET_HIP(emr_launch_net(10, &st, s));
       }
       emr::NetOutArgs oa{};
       oa.list = list;
@@ -884,7 +884,7 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
       oa.nodes = N->nodes;
       oa.n_outputs = (uint32_t)N->n_out;
       oa.n_patterns = (uint32_t)n_patterns;
-      NET_HIP(emr_launch_net(11, &oa, 0, s));
+      NET_HIP(emr_launch_net(11, &oa, s));
     }
   }
   if (!M.done) NET_HIP(hipEventCreateWithFlags(&M.done, hipEventDisableTiming));

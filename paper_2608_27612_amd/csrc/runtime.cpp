@@ -661,10 +661,11 @@ emr_status plan_schedule(const Plan& P, const emr::DiscoverScalars& sc, uint32_t
 // ------------------------------------------------------------------ call flags
 // Each call's kernels raise their error bits (word 0) and largest pair count (word 1) into a slot
 // of a library-owned ring in device memory. A slot is zero when a call takes it; the call's last
-// kernel (k_compact for a record call, k_finalize otherwise) writes the words to the slot's pinned
-// host words and clears them again. So
-// no copy of the flags goes either way, and the caller's workspace keeps no state from one call
-// to the next.
+// kernel (k_compact for a record call, the last chunk's for a streamed one, k_filter_end or k_scan
+// after discovery, k_finalize for band values and calls without pairs) writes the words to the
+// slot's pinned host words and clears them again. A raw call's kernels raise its one word in the
+// pinned words themselves. So no copy of the flags goes either way, and the caller's workspace keeps
+// no state from one call to the next.
 constexpr int kFlagSlots = 256;
 constexpr int kSlotWords = 16;  // the kFlag* words, then padding
 
@@ -1189,8 +1190,8 @@ bool cached_split_parts(const Plan& P, const Plan::Launch& L, bool skip_uniform,
 // records go to `out` pair after pair (pair_offset, pair_count), its capacity also bounding the
 // pool in the workspace; raw outputs go to raw[r * N(D) + p].
 // jit: run the plan's compiled programs (jit_use said so) instead of the interpreter. With
-// `finalize`, the range's last kernel (k_compact for records, k_finalize for raw outputs) then hands
-// the call's flags to their pinned words.
+// `finalize`, the range ends the call: k_compact then hands the flags to their pinned words
+// (k_finalize where there are no pairs), and raw outputs raise their errors there.
 // counters (record mode): the range's group marks and totals, a plan's counter set or the
 // workspace's own. With `clear` they are cleared right before the discover launch, once every
 // argument of that launch is ready on the host.

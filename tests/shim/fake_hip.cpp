@@ -231,7 +231,7 @@ hipError_t emr_discover_setup(const emr::DiscoverArgs*, uint32_t, int, int, emr:
                               uint32_t*) {
   return hipErrorNotSupported;
 }
-hipError_t emr_launch_net(int, const void*, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t emr_launch_net(int, const void*, hipStream_t) { return hipSuccess; }
 hipError_t emr_net_sort(void*, size_t* bytes, const uint32_t*, uint32_t*, const uint64_t*, uint64_t*,
                         uint32_t, int, hipStream_t) {
   *bytes = 256;

@@ -102,6 +102,15 @@ struct NetFlagArgs {
   int64_t* total;           // node_offset[n_genomes] once more, beside the pass words
 };
 
+// Copies of the first 16-byte units of buffers to others, in one launch.
+constexpr int kNetFits = 5;
+struct NetFitArgs {
+  const void* src[kNetFits];
+  void* dst[kNetFits];
+  int64_t units[kNetFits];
+  uint32_t count;
+};
+
 constexpr int kNetPasses = 6;  // reach passes enqueued before the host looks at them
 
 struct NetReachArgs {

@@ -819,6 +819,15 @@ __global__ void __launch_bounds__(kNetThreads) k_net_out(NetOutArgs A) {
   }
 }
 
+// The copies of a build's buffers to buffers of their contents' size, a row of workgroups each
+// (a copy call per buffer held the host for 8 to 15 us each).
+__global__ void __launch_bounds__(kNetThreads) k_net_fit(NetFitArgs A) {
+  const uint4* src = static_cast<const uint4*>(A.src[blockIdx.y]);
+  uint4* dst = static_cast<uint4*>(A.dst[blockIdx.y]);
+  const int64_t n = A.units[blockIdx.y];
+  for (int64_t i = grid_thread(); i < n; i += grid_threads()) dst[i] = src[i];
+}
+
 // After every other kernel of the build: the error word to the host's summary.
 __global__ void k_net_end(NetSplitArgs A) { A.summary[2 * ((int64_t)A.n_genomes + 1)] = *A.err; }
 
@@ -839,7 +848,8 @@ dim3 list_grid(const emr::NetList& L, uint32_t x, uint32_t pblocks) {
 
 // Steps: 0 rank, 1 layout, 2 pairs of a phase, 3 its edges, 4 flags, 5 reach pass, 6 kept counts
 // and their sums, 7 nodes, 8 keys; after the sort, 14 offsets and edges. Activation: 9 initial
-// state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns by value, 13 all steps in LDS.
+// state, 10 one step, 11 outputs / fitness (stepwise), 12 patterns by value, 13 all steps in LDS. 15
+// copies into buffers of the contents' size.
 extern "C" hipError_t emr_launch_net(int step, const void* args, hipStream_t s) {
   using namespace emr;
   const dim3 blk(kNetThreads);
@@ -951,6 +961,16 @@ extern "C" hipError_t emr_launch_net(int step, const void* args, hipStream_t s) 
       if (b == 0) return hipSuccess;
       if (b > 0x7FFFFFFFull || A.lds_bytes > kNetRunLds) return hipErrorInvalidValue;
       hipLaunchKernelGGL(k_net_run, dim3((uint32_t)b), dim3(kNetRunThreads), A.lds_bytes, s, A);
+      break;
+    }
+    case 15: {
+      const auto& A = *static_cast<const NetFitArgs*>(args);
+      int64_t most = 0;
+      for (uint32_t k = 0; k < A.count && k < (uint32_t)kNetFits; ++k)
+        most = A.units[k] > most ? A.units[k] : most;
+      if (most == 0) return hipSuccess;
+      const uint32_t b = stride_blocks(most);
+      hipLaunchKernelGGL(k_net_fit, dim3(b < 2048u ? b : 2048u, A.count), blk, 0, s, A);
       break;
     }
     default:

@@ -417,6 +417,15 @@ def emr_result_check(res, stream=None):
     return total.value, mx.value
 
 
+def emr_result_move(res, to, stream=None):
+    """Moves a result's records and its check into the buffers of `to` (see emr_result_move in
+    include/emr.h): waits for the call, enqueues the copies."""
+    to["_struct"] = _result_struct(to)
+    to.pop("_check_args", None)
+    _check(lib().emr_result_move(C.byref(res.get("_struct") or _result_struct(res)),
+                                 C.byref(to["_struct"]), _stream_ptr(stream)))
+
+
 # A call of this many parent positions or more runs for milliseconds, and finding more than
 # DEFAULT_CAPACITY records it would run a second time: emr_discover_all gives it room for
 # ROOMY_CAPACITY records (3 GB while it runs) and then moves the result into buffers of the usual
@@ -462,9 +471,7 @@ def _fit_result(pop, sources, depth, src_offsets, res, total):
                parent=torch.empty(cap, dtype=torch.int32, device="cuda"),
                w4=torch.empty((cap, 4), dtype=torch.float32, device="cuda"),
                workspace=torch.empty(max(ws, 256), dtype=torch.uint8, device="cuda"))
-    fit.pop("_check_args", None)
-    fit["_struct"] = _result_struct(fit)
-    _check(lib().emr_result_move(C.byref(res["_struct"]), C.byref(fit["_struct"]), _stream_ptr(None)))
+    emr_result_move(res, fit)
     torch.cuda.current_stream().synchronize()
     return fit
 

@@ -259,3 +259,28 @@ def test_refusals(emr):
         net.xor_fitness(1, -1)
     with pytest.raises(emr.EmrError):
         net.activate(np.zeros((0, 3)), 1)
+
+
+def test_records_that_move_into_smaller_buffers(emr):
+    """300 genomes, whose hidden phase could find more than 16M records (its first buffers; what it
+    finds moves out of them), against the same genomes 30 at a time, which keep theirs."""
+    genomes = W.population(79, 300, 20, 60)
+    subs = W.xor_sources()
+    whole = emr.emr_build_networks(emr.emr_pack_population(genomes), subs, 6, 0.01, 15, 0.1, 1)
+    nets, ph = whole.to_host(), whole.phase(1)
+    Q = emr.emr_grid_count(6)[1]
+    assert len(ph["sources"]) * Q > 1 << 24
+    at = 0
+    for g in range(0, 300, 30):
+        part = emr.emr_build_networks(emr.emr_pack_population(genomes[g:g + 30]), subs, 6, 0.01, 15,
+                                      0.1, 1)
+        for x, y in zip(part.to_host(), nets[g:g + 30]):
+            for key in x:
+                np.testing.assert_array_equal(x[key], y[key], err_msg=key)
+        p1 = part.phase(1)
+        assert len(p1["sources"]) * Q < 1 << 24
+        n = len(p1["records"]["parent"])
+        for key in ("parent", "w4"):
+            np.testing.assert_array_equal(p1["records"][key], ph["records"][key][at:at + n])
+        at += n
+    assert at == len(ph["records"]["parent"])

@@ -29,6 +29,7 @@ struct Fake {
   int waits = 0;        // stream and event waits of the host
   int copies = 0;       // host-to-device copies from pinned memory
   int slow_copies = 0;  // the same from other memory
+  const void* totals = nullptr;  // of the last discover launch
   uint64_t total = 0;   // what the next record calls and filters report
   uint32_t bind_error = 0;
   uint32_t* bind_word = nullptr;  // held with the events
@@ -84,6 +85,7 @@ void fake_block_waits(int on) { F().block_waits = on != 0; }
 void fake_capturing(int on) { F().capturing = on != 0; }
 void fake_total(int64_t n) { F().total = (uint64_t)n; }
 void fake_bind_error(uint32_t bits) { F().bind_error = bits; }
+const void* fake_totals(void) { return F().totals; }
 int64_t fake_held(void) { return (int64_t)F().held; }
 int64_t fake_size(const void* p) {
   auto it = F().device.find(const_cast<void*>(p));
@@ -206,11 +208,15 @@ hipError_t emr_launch_bind(const emr::BindArgs* a, hipStream_t) {
     *a->err = F().bind_error;
   return hipSuccess;
 }
-hipError_t emr_launch_discover(const emr::DiscoverArgs*, int, uint32_t, hipStream_t, hipEvent_t,
+hipError_t emr_launch_discover(const emr::DiscoverArgs* a, int, uint32_t, hipStream_t, hipEvent_t,
                                hipEvent_t) {
+  F().totals = a->pair_total;
+  for (uint32_t r = 0; r < a->n_pairs && a->pair_total; ++r)
+    if (a->pair_total[r] != 0u) return hipErrorInvalidValue;  // (a record call's totals start at 0)
   return hipSuccess;
 }
 hipError_t emr_launch_compact(const emr::ScanArgs* S, const emr::MoveArgs*, hipStream_t) {
+  for (uint32_t r = 0; r < S->n_pairs; ++r) S->pair_total[r] = 1u, S->clear_total[r] = 0u;
   hand_over(S->host);
   return hipSuccess;
 }

@@ -47,6 +47,7 @@ def lib(built, tmp_path):
                               "fake_block_waits": (None, [C.c_int]),
                               "fake_capturing": (None, [C.c_int]), "fake_total": (None, [C.c_int64]),
                               "fake_bind_error": (None, [C.c_uint32]),
+                              "fake_totals": (C.c_void_p, []),
                               "fake_held": (C.c_int64, []), "fake_size": (C.c_int64, [C.c_void_p]),
                               "fake_counts": (None, [C.c_void_p])}.items():
         fn = getattr(L, name)
@@ -246,3 +247,39 @@ def test_band_values_refuse_a_capture(lib):
     assert call() == E.EMR_E_DEVICE and counts(lib) == before
     lib.fake_capturing(0)
     assert call() == 0 and counts(lib) != before
+
+
+def test_counters_lie_with_the_plan(lib):
+    """A record call's totals lie in the plan's memory and start at zero whatever the workspace holds
+    (the stand-in's launch checks that, and leaves totals behind); calls on other streams, with the
+    earlier ones in flight, have sets of their own; a capture, which may be replayed beside later
+    calls, has the workspace's, cleared by the call."""
+    src = W.xor_sources()
+    pop = E.emr_pack_population(W.population(4, 50, 6, 12))
+    ws = workspace(pop, src, 5)
+
+    def call(stream=None):
+        ws.fill(0xAB)
+        n = len(src) * pop.n_genomes
+        count, offset = np.zeros(n, np.int64), np.zeros(n + 1, np.int64)
+        out = E.emr_result(0, 0, 0, count.ctypes.data, offset.ctypes.data, ws.ctypes.data, ws.size)
+        assert lib.emr_discover(pop.handle, src.ctypes.data, len(src), None, len(src), 5, 0.03,
+                                C.byref(out), stream) == 0, lib.emr_last_error()
+        at = lib.fake_totals()
+        return at, ws.ctypes.data <= at < ws.ctypes.data + ws.size
+
+    own = [call() for _ in range(4)]
+    assert not any(inside for _, inside in own)
+    assert own[0][0] == own[2][0] != own[1][0] == own[3][0]  # two sets of totals in turn
+    lib.fake_hold_events(1)
+    seen = set()
+    for k in range(12):  # eight sets; the other calls' streams wait for an earlier call's
+        a, inside = call(C.c_void_p(1000 + k))
+        assert not inside
+        seen.add(a)
+    assert 8 <= len(seen) <= 12
+    lib.fake_hold_events(0)
+    lib.fake_capturing(1)
+    assert all(call()[1] for _ in range(2))
+    lib.fake_capturing(0)
+    assert not call()[1]

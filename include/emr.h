@@ -433,8 +433,9 @@ emr_status emr_record_file_close(emr_record_file* file, int64_t* records, int64_
  * and at each step takes sigmoid(sum of w * the source node's previous value) = 1/(1+e^-z) over
  * its incoming edges, in fp32: edge k of the node's list goes to partial sum k mod 64 (an fmaf
  * chain in list order), and the 64 partial sums are added in a fixed butterfly, so every run
- * gives the same bits. A genome whose node states fit the LDS runs all its steps in one launch; the
- * others (and those of many edges on few patterns) run one launch per step, with the same bits. */
+ * gives the same bits. A genome whose node states fit the LDS can run all its steps in one launch; the
+ * others, and those for which that is estimated to take longer, run one launch per step, with the same
+ * bits. */
 typedef struct emr_networks emr_networks;
 
 #define EMR_SUBSTRATE_NODE 0xFFFFFFFFu /* node_cell of a substrate node */

@@ -172,19 +172,19 @@ struct NetSplitArgs {
   uint32_t* err;
 };
 
-// Synchronous activation. A genome whose node states fit the LDS runs all its steps in one
-// workgroup per block of 4 Q patterns (k_net_run); the others, and those whose edges would keep one
-// workgroup busy long after the rest of the chip, run one launch per step over state buffers
-// [pblocks][nodes] of float4 (4 patterns per block), swapped after each step.
+// Synchronous activation. A genome whose node states fit the LDS can run all its steps in one
+// workgroup per block of 4 Q patterns (k_net_run); the others, and those for which the host estimates
+// that to take longer, run one launch per step over state buffers [pblocks][nodes] of float4 (4
+// patterns per block), swapped after each step.
 constexpr int kNetRunThreads = 1024;          // 16 waves: two workgroups fill a CU
 constexpr uint32_t kNetRunMaxQ = 4;           // float4 pattern groups of a workgroup, at most
 constexpr uint32_t kNetRunLds = 160u * 1024u;
 // LDS of a genome of n nodes: two state buffers of n * q float4 and n + 1 edge offsets.
 inline constexpr uint32_t net_run_lds(uint32_t n, uint32_t q) { return n * (32u * q + 4u) + 4u; }
 constexpr int kNetRanges = 8;                 // classes of genomes in a launch, at most
-constexpr uint32_t kNetStageFloats = 256;     // patterns and targets small enough for the kernarg
+constexpr uint32_t kNetStageFloats = 256;     // patterns small enough for the kernarg
 
-// Patterns and targets passed by value to the device buffer the kernels read.
+// Patterns passed by value to the device buffer the kernels read.
 struct NetStageArgs {
   float* dst;
   uint32_t n;
@@ -199,7 +199,7 @@ struct NetRunArgs {
   const uint32_t* in_src;
   const float* in_w;
   const float* patterns;       // [n_patterns * n_inputs]
-  const float* targets;        // [n_patterns] or NULL (fitness: one output, at most 4 patterns)
+  float target[4];             // (fitness: one output, at most 4 patterns)
   const int32_t* out_node;     // [n_outputs] substrate index of output o
   float* outputs;              // [n_genomes * n_patterns * n_outputs] or NULL
   float* fitness;              // [n_genomes] or NULL
@@ -212,7 +212,8 @@ struct NetRunArgs {
   uint32_t first[kNetRanges], count[kNetRanges], blocks[kNetRanges], q[kNetRanges];
 };
 
-// The genomes of a stepwise launch: up to kNetRanges runs of `order`.
+// The genomes of a stepwise launch: up to kNetRanges runs of `order`, or (order NULL, one run from 0)
+// all of them.
 struct NetList {
   const uint32_t* order;
   uint32_t first[kNetRanges];  // run r: order[first[r]] ..
@@ -226,12 +227,13 @@ struct NetStateArgs {
   NetList list;
   const int64_t* node_offset;
   const int32_t* node_in;   // [nodes]
-  const float* patterns;    // [n_patterns * n_inputs]
+  const float* patterns;    // [n_patterns * n_inputs], or NULL: v
   float* state;             // [pblocks * nodes * 4]
   int64_t nodes;
   uint32_t n_inputs;
   uint32_t n_patterns;
   uint32_t pblocks;
+  float v[kNetStageFloats];
 };
 
 struct NetStepArgs {
@@ -252,7 +254,7 @@ struct NetOutArgs {
   const int64_t* node_offset;  // [n_genomes + 1]
   const int32_t* out_node;     // [n_outputs] substrate index of output o
   const float* state;          // the final state
-  const float* targets;        // [n_patterns] or NULL (fitness: one output, 4 patterns)
+  float target[4];             // (fitness: one output, 4 patterns)
   float* outputs;              // [n_genomes * n_patterns * n_outputs] or NULL
   float* fitness;              // [n_genomes] or NULL
   int64_t nodes;

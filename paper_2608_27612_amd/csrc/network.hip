@@ -8,8 +8,8 @@
 // genome with a high-frequency CPPN can hold a large share of the population's edges), so no
 // step may give one genome to one workgroup when its cost grows with the genome's edges beyond
 // its share of the chip. Steps whose cost follows a genome's node count (its bitmap, its node
-// numbering) run one workgroup per genome, and activation one per (genome, pattern block) while
-// that block's edges stay below the chip's share (the rule is in networks.cpp). Numbering and
+// numbering) run one workgroup per genome, and activation one per (genome, pattern block) where
+// that takes less than a launch per step (the estimate is in networks.cpp). Numbering and
 // layouts: network.h.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -516,15 +516,16 @@ __global__ void __launch_bounds__(kNetThreads) k_net_stage(NetStageArgs A) {
   if (threadIdx.x < A.n) A.dst[threadIdx.x] = A.v[threadIdx.x];
 }
 
-// Four patterns (block pb) of input slot `slot`.
-__device__ __forceinline__ float4 pattern4(const float* patterns, uint32_t n_patterns,
-                                           uint32_t n_inputs, int32_t slot, uint32_t pb) {
+// Four patterns (block pb) of input slot `slot`, of values at(i).
+template <typename P>
+__device__ __forceinline__ float4 pattern4(P&& at, uint32_t n_patterns, uint32_t n_inputs, int32_t slot,
+                                           uint32_t pb) {
   float c[4] = {0.f, 0.f, 0.f, 0.f};
   if (slot >= 0 && (uint32_t)slot < n_inputs) {
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
       const uint32_t p = 4u * pb + k;
-      c[k] = p < n_patterns ? patterns[(int64_t)p * n_inputs + (uint32_t)slot] : 0.0f;
+      c[k] = p < n_patterns ? at((int64_t)p * n_inputs + (uint32_t)slot) : 0.0f;
     }
   }
   return make_float4(c[0], c[1], c[2], c[3]);
@@ -673,7 +674,8 @@ __device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_
   uint32_t* first = reinterpret_cast<uint32_t*>(lds + 2u * n * Q);
   for (uint32_t i = threadIdx.x; i < n * Q; i += kNetRunThreads) {
     const float4 v =
-        pattern4(A.patterns, A.n_patterns, A.n_inputs, A.node_in[n0 + i / Q], block * Q + i % Q);
+        pattern4([&](int64_t j) { return A.patterns[j]; }, A.n_patterns, A.n_inputs,
+                 A.node_in[n0 + i / Q], block * Q + i % Q);
     cur[i] = v;
     nxt[i] = v;
   }
@@ -713,7 +715,7 @@ __device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_
   if (A.fitness && threadIdx.x == 0 && (uint32_t)A.out_node[0] < n) {
     float se = 0.0f;
     for (uint32_t k = 0; k < A.n_patterns && k < 4u; ++k) {
-      const float d = c[(uint32_t)A.out_node[0] * 4u * Q + k] - A.targets[k];
+      const float d = c[(uint32_t)A.out_node[0] * 4u * Q + k] - A.target[k];
       se = fmaf(d, d, se);
     }
     A.fitness[g] = 1.0f - se / (float)A.n_patterns;
@@ -742,6 +744,7 @@ __global__ void __launch_bounds__(kNetRunThreads, 8) k_net_run(NetRunArgs A) {
 
 // The k-th genome of a list (k < total).
 __device__ __forceinline__ uint32_t list_genome(const NetList& L, uint32_t k) {
+  if (L.order == nullptr) return k;
 #pragma unroll
   for (int r = 0; r < kNetRanges; ++r) {
     if (k < L.count[r]) return L.order[L.first[r] + k];
@@ -750,44 +753,51 @@ __device__ __forceinline__ uint32_t list_genome(const NetList& L, uint32_t k) {
   return L.n_genomes;
 }
 
-// The stepwise kernels: blockIdx.y is the list's genome, blockIdx.z the block of four patterns.
+// The stepwise kernels: blockIdx.y is the list's genome (0: all nodes as they lie, when the list is
+// every genome: a step then waits for no list, order and offset; 4.8 -> 4.2 us), blockIdx.z the block
+// of four patterns.
 // Initial state: input nodes hold their pattern values, every other node 0.
 __global__ void __launch_bounds__(kNetThreads) k_net_state(NetStateArgs A) {
-  const uint32_t g = list_genome(A.list, blockIdx.y);
+  const bool all = A.list.order == nullptr;
+  const uint32_t g = all ? 0u : list_genome(A.list, blockIdx.y);
   if (g >= A.list.n_genomes) return;
   float4* st = reinterpret_cast<float4*>(A.state);
-  const int64_t n1 = A.node_offset[g + 1];
-  for (int64_t i = A.node_offset[g] + grid_thread(); i < n1; i += grid_threads())
+  const int64_t n0 = all ? 0 : A.node_offset[g], n1 = all ? A.nodes : A.node_offset[g + 1];
+  for (int64_t i = n0 + grid_thread(); i < n1; i += grid_threads())
     for (uint32_t pb = blockIdx.z; pb < A.pblocks; pb += gridDim.z)
-      st[(int64_t)pb * A.nodes + i] =
-          pattern4(A.patterns, A.n_patterns, A.n_inputs, A.node_in[i], pb);
+      st[(int64_t)pb * A.nodes + i] = pattern4(
+          [&](int64_t j) { return A.patterns ? A.patterns[j] : A.v[j]; }, A.n_patterns, A.n_inputs,
+          A.node_in[i], pb);
 }
 
 // One synchronous step: one wave per (node, pattern block).
 __global__ void __launch_bounds__(kNetThreads) k_net_step(NetStepArgs A) {
-  const uint32_t g = list_genome(A.list, blockIdx.y);
+  const bool all = A.list.order == nullptr;
+  const uint32_t g = all ? 0u : list_genome(A.list, blockIdx.y);
   if (g >= A.list.n_genomes) return;
   const uint32_t lane = threadIdx.x % kWave;
-  const int64_t n0 = A.node_offset[g];
-  const uint32_t n = (uint32_t)(A.node_offset[g + 1] - n0);
-  const uint32_t k = blockIdx.x * (kNetThreads / kWave) +
-                     __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (k >= n) return;
-  const int64_t i = n0 + k;
-  for (uint32_t pb = blockIdx.z; pb < A.pblocks; pb += gridDim.z) {
-    const float4* cur = reinterpret_cast<const float4*>(A.cur) + (int64_t)pb * A.nodes;
-    float4* nxt = reinterpret_cast<float4*>(A.nxt) + (int64_t)pb * A.nodes;
-    if (A.node_in[i] >= 0) {
-      if (lane == 0) nxt[i] = cur[i];
-      continue;
+  const int64_t n0 = all ? 0 : A.node_offset[g];
+  const int64_t n = (all ? A.nodes : A.node_offset[g + 1]) - n0;
+  const int64_t waves = (int64_t)gridDim.x * (kNetThreads / kWave);
+  for (int64_t k = (int64_t)blockIdx.x * (kNetThreads / kWave) +
+                   __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+       k < n; k += waves) {
+    const int64_t i = n0 + k;
+    for (uint32_t pb = blockIdx.z; pb < A.pblocks; pb += gridDim.z) {
+      const float4* cur = reinterpret_cast<const float4*>(A.cur) + (int64_t)pb * A.nodes;
+      float4* nxt = reinterpret_cast<float4*>(A.nxt) + (int64_t)pb * A.nodes;
+      if (A.node_in[i] >= 0) {
+        if (lane == 0) nxt[i] = cur[i];
+        continue;
+      }
+      const int64_t e0 = A.in_offset[i];
+      const float z = node_sum<1, true>(
+          [&](uint32_t s) {
+            return (int64_t)s < A.nodes ? cur[s] : make_float4(0.f, 0.f, 0.f, 0.f);
+          },
+          A.in_src + e0, A.in_w + e0, (uint32_t)(A.in_offset[i + 1] - e0), lane);
+      if (lane % 16u == 0u) reinterpret_cast<float*>(nxt + i)[lane / 16u] = sigmoid_f(z);
     }
-    const int64_t e0 = A.in_offset[i];
-    const float z = node_sum<1, true>(
-        [&](uint32_t s) {
-          return (int64_t)s < A.nodes ? cur[s] : make_float4(0.f, 0.f, 0.f, 0.f);
-        },
-        A.in_src + e0, A.in_w + e0, (uint32_t)(A.in_offset[i + 1] - e0), lane);
-    if (lane % 16u == 0u) reinterpret_cast<float*>(nxt + i)[lane / 16u] = sigmoid_f(z);
   }
 }
 
@@ -812,7 +822,7 @@ __global__ void __launch_bounds__(kNetThreads) k_net_out(NetOutArgs A) {
     const float4 v = st[node];
     float se = 0.0f;
     for (uint32_t q = 0; q < A.n_patterns && q < 4u; ++q) {
-      const float d = comp(v, q) - A.targets[q];
+      const float d = comp(v, q) - A.target[q];
       se = fmaf(d, d, se);
     }
     A.fitness[g] = 1.0f - se / (float)A.n_patterns;
@@ -843,6 +853,13 @@ uint32_t stride_blocks(int64_t n) {
 // (x: the caller's, y: the list's genomes, z: pattern blocks, at most 65535 with a stride loop)
 dim3 list_grid(const emr::NetList& L, uint32_t x, uint32_t pblocks) {
   return dim3(x < 1 ? 1 : x, L.total, pblocks < 65535u ? pblocks : 65535u);
+}
+// Workgroups of `per` nodes each over the nodes of a list's genomes (a row each), or over all nodes; the
+// kernels stride over what 2^22 of them leave.
+dim3 node_grid(const emr::NetList& L, int64_t nodes, uint32_t per, uint32_t pblocks) {
+  const int64_t n = L.order ? (int64_t)L.max_nodes : nodes, x = (n + per - 1) / per;
+  return dim3((uint32_t)(x < 1 ? 1 : (x > (1 << 22) ? 1 << 22 : x)), L.order ? L.total : 1u,
+              pblocks < 65535u ? pblocks : 65535u);
 }
 }  // namespace
 
@@ -921,17 +938,13 @@ extern "C" hipError_t emr_launch_net(int step, const void* args, hipStream_t s) 
     }
     case 9: {
       const auto& A = *static_cast<const NetStateArgs*>(args);
-      hipLaunchKernelGGL(k_net_state, list_grid(A.list, (A.list.max_nodes + kNetThreads - 1) /
-                                                            kNetThreads, A.pblocks),
-                         blk, 0, s, A);
+      hipLaunchKernelGGL(k_net_state, node_grid(A.list, A.nodes, kNetThreads, A.pblocks), blk, 0, s, A);
       break;
     }
     case 10: {
       const auto& A = *static_cast<const NetStepArgs*>(args);
       constexpr uint32_t waves = kNetThreads / kWave;
-      hipLaunchKernelGGL(k_net_step,
-                         list_grid(A.list, (A.list.max_nodes + waves - 1) / waves, A.pblocks), blk,
-                         0, s, A);
+      hipLaunchKernelGGL(k_net_step, node_grid(A.list, A.nodes, waves, A.pblocks), blk, 0, s, A);
       break;
     }
     case 11: {

@@ -290,11 +290,13 @@ struct emr_networks {
   Dev d_out_node;  // [n_out] substrate index of output o
   int64_t nodes = 0, edges = 0;
   Dev state, patterns;
-  // genomes in the order of the activation launches (order_genomes), with their node and edge counts
+  // genomes in the order of the activation launches (order_genomes): their loads and node counts, the
+  // sums over those before each, and the most nodes of those before each in its class
   Dev order;
-  std::vector<int64_t> order_edges;
-  std::vector<uint32_t> order_host, order_nodes, class_first;
-  // pinned staging of an activation's patterns and targets, and the event of its last copy
+  std::vector<double> order_load, batches_before;
+  std::vector<int64_t> nodes_before, edges_before;
+  std::vector<uint32_t> order_host, order_nodes, most_before, class_first;
+  // pinned staging of an activation's patterns, and the event of its last copy
   void* pin = nullptr;
   size_t pin_bytes = 0;
   hipEvent_t pin_done = nullptr;
@@ -682,7 +684,7 @@ emr_status assemble(Build& B) {
 }
 
 // The genomes in the order of the activation launches: by class of node count (the classes of
-// run_forward), the most edges first inside a class.
+// run_forward), the largest load first inside a class.
 struct RunClass {
   uint32_t lds;  // LDS of the class's genomes, at most
   uint32_t q;    // float4 pattern groups of a workgroup, at most
@@ -693,6 +695,10 @@ struct RunClass {
 constexpr RunClass kRunClass[] = {{80u << 10, 4}, {80u << 10, 2},
                                   {80u << 10, 1}, {160u << 10, 1}, {0xFFFFFFFFu, 1}};
 constexpr int kRunClasses = sizeof kRunClass / sizeof kRunClass[0];
+// The batches of 64 edges of a genome's nodes beyond one each, as the two totals let them be estimated.
+double run_batches(int64_t nodes, int64_t edges) {
+  return std::max(0.0, (double)edges / 64.0 - 0.5 * (double)nodes);
+}
 static_assert(kRunClasses <= emr::kNetRanges && kRunClass[kRunClasses - 2].lds == emr::kNetRunLds,
               "a range per class");
 
@@ -713,15 +719,28 @@ emr_status order_genomes(emr_networks& N, const int64_t* node_off, const int64_t
     cls[g] = (uint8_t)c;
   }
   auto edges = [&](uint32_t g) { return edge_off[g + 1] - edge_off[g]; };
+  auto nodes = [&](uint32_t g) { return node_off[g + 1] - node_off[g]; };
+  auto load = [&](uint32_t g) {  // (a batch costs about three quarters of a node)
+    return (double)nodes(g) + 0.75 * run_batches(nodes(g), edges(g));
+  };
   std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
-    return cls[a] != cls[b] ? cls[a] < cls[b] : edges(a) > edges(b);
+    return cls[a] != cls[b] ? cls[a] < cls[b] : load(a) > load(b);
   });
-  N.order_edges.resize(G);
+  N.order_load.resize(G);
   N.order_nodes.resize(G);
+  N.nodes_before.assign(G + 1, 0);
+  N.edges_before.assign(G + 1, 0);
+  N.batches_before.assign(G + 1, 0.0);
+  N.most_before.assign(G + 1, 0);
   N.class_first.assign(kRunClasses + 1, 0);
   for (uint32_t k = 0; k < G; ++k) {
-    N.order_edges[k] = edges(order[k]);
-    N.order_nodes[k] = (uint32_t)(node_off[order[k] + 1] - node_off[order[k]]);
+    N.order_load[k] = load(order[k]);
+    N.order_nodes[k] = (uint32_t)nodes(order[k]);
+    N.nodes_before[k + 1] = N.nodes_before[k] + nodes(order[k]);
+    N.edges_before[k + 1] = N.edges_before[k] + edges(order[k]);
+    N.batches_before[k + 1] = N.batches_before[k] + run_batches(nodes(order[k]), edges(order[k]));
+    const bool first = k == 0 || cls[order[k]] != cls[order[k - 1]];
+    N.most_before[k + 1] = std::max(N.order_nodes[k], first ? 0u : N.most_before[k]);
     ++N.class_first[cls[order[k]] + 1];
   }
   for (int c = 0; c < kRunClasses; ++c) N.class_first[c + 1] += N.class_first[c];
@@ -729,20 +748,17 @@ emr_status order_genomes(emr_networks& N, const int64_t* node_off, const int64_t
   return to_device(N.order.p, order.data(), (size_t)G * 4, s);
 }
 
-// The patterns (and targets) on the device: small ones as kernel arguments, others staged in
-// pinned memory and copied on the stream (the staging is rewritten only after the previous
-// call's copy has completed).
-emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
-                          const float* targets, size_t n_tgt, hipStream_t s) {
-  const size_t need = (n_pat + n_tgt) * 4;
+// The patterns on the device: small ones as kernel arguments, others staged in pinned memory and copied
+// on the stream (the staging is rewritten only after the previous call's copy has completed).
+emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat, hipStream_t s) {
+  const size_t need = n_pat * 4;
   if (M.patterns.bytes < need || !M.patterns.p)
     NET_TRY(alloc(M.patterns, need, "input patterns", s));
-  if (n_pat + n_tgt <= emr::kNetStageFloats) {
+  if (n_pat <= emr::kNetStageFloats) {
     emr::NetStageArgs a{};
     a.dst = M.patterns.as<float>();
-    a.n = (uint32_t)(n_pat + n_tgt);
-    std::memcpy(a.v, patterns, n_pat * 4);
-    if (n_tgt) std::memcpy(a.v + n_pat, targets, n_tgt * 4);
+    a.n = (uint32_t)n_pat;
+    std::memcpy(a.v, patterns, need);
     NET_HIP(emr_launch_net(12, &a, s));
     return EMR_OK;
   }
@@ -760,20 +776,88 @@ emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
     }
     M.pin_bytes = need;
   }
-  std::memcpy(M.pin, patterns, n_pat * 4);
-  if (n_tgt) std::memcpy(static_cast<float*>(M.pin) + n_pat, targets, n_tgt * 4);
+  std::memcpy(M.pin, patterns, need);
   NET_HIP(hipMemcpyAsync(M.patterns.p, M.pin, need, hipMemcpyHostToDevice, s));
   NET_HIP(hipEventRecord(M.pin_done, s));
   M.pin_pending = true;
   return EMR_OK;
 }
 
-// Smallest edge count that sends a genome to the stepwise kernels (below it the launches of the
-// steps cost more than one workgroup's longer run), and the most steps of a fused run (one launch
-// stays well below a second).
-constexpr int64_t kStepwiseEdges = 6144;
-constexpr int32_t kFusedSteps = 1024;
-constexpr int64_t kFusedWorkgroups = 256;  // half of those that the chip holds
+// Times of an activation's parts, in us, measured on networks of 8 to 2484 nodes alone and on 30 to
+// 1000 networks together. A fused run takes kLaunch and the longer of its longest workgroup (per step
+// kStep, kNode[q] a node, q = 1, 2 and 4 pattern groups, and kBatch a further batch of 64 edges) and of
+// all of them over the kSlots that the chip holds. The stepwise kernels take kSteps and per step
+// kStepLaunch, or the time of their nodes and edges for all pattern blocks; a launch over some of the
+// genomes has a row of workgroups as long as the largest for each (kStepSlot a node's place). The two
+// follow each other on the stream.
+struct RunTimes {
+  static constexpr double kLaunch = 3.0, kStep = 0.8, kNode[3] = {0.028, 0.036, 0.045};
+  static constexpr double kBatch = 0.026, kSlots = 512.0;
+  static constexpr double kSteps = 12.0, kStepLaunch = 4.2, kStepNode = 2.5e-4, kStepEdge = 1.3e-6,
+                          kStepSlot = 4e-5;
+  static constexpr double kLongest = 2.5e5;  // a longer workgroup is not fused
+};
+constexpr int32_t kFusedSteps = 1024;  // nor are more steps (one launch stays below a second)
+
+// Where each class's fused genomes begin (those before, its largest loads, run stepwise): the least
+// estimated time over cuts at a load, from none stepwise but those that have to be to all.
+struct RunCut {
+  uint32_t first[kRunClasses];
+  double us;
+};
+RunCut cut_at(const emr_networks& N, double load, int64_t pblocks, const uint32_t* q_of, double steps) {
+  using T = RunTimes;
+  RunCut r{};
+  double longest = 0.0, work = 0.0, step_nodes = 0.0, step_edges = 0.0, stepwise = 0.0, most = 0.0;
+  for (int c = 0; c < kRunClasses; ++c) {
+    const uint32_t k0 = N.class_first[c], k1 = N.class_first[c + 1];
+    const int qi = q_of[c] == 1 ? 0 : (q_of[c] == 2 ? 1 : 2);
+    const double limit = std::min(load, (T::kLongest / std::max(steps, 1.0) - T::kStep) / T::kNode[qi]);
+    uint32_t k = k1;
+    if (c + 1 < kRunClasses && steps <= kFusedSteps)
+      k = (uint32_t)(std::partition_point(N.order_load.begin() + k0, N.order_load.begin() + k1,
+                                          [&](double l) { return l > limit; }) -
+                     N.order_load.begin());
+    r.first[c] = k;
+    if (k > k0) {
+      step_nodes += (double)(N.nodes_before[k] - N.nodes_before[k0]);
+      step_edges += (double)(N.edges_before[k] - N.edges_before[k0]);
+      stepwise += (double)(k - k0);
+      most = std::max(most, (double)N.most_before[k]);
+    }
+    if (k == k1) continue;
+    longest = std::max(longest, T::kStep + T::kNode[qi] * (double)N.order_nodes[k] +
+                                    T::kBatch * (N.batches_before[k + 1] - N.batches_before[k]));
+    work += (double)((pblocks + q_of[c] - 1) / q_of[c]) *
+            (T::kStep * (double)(k1 - k) +
+             T::kNode[qi] * (double)(N.nodes_before[k1] - N.nodes_before[k]) +
+             T::kBatch * (N.batches_before[k1] - N.batches_before[k]));
+  }
+  if (longest > 0.0) r.us += T::kLaunch + steps * std::max(longest, work / T::kSlots);
+  if (stepwise > 0.0) {
+    const double slots = stepwise < (double)N.n_genomes ? stepwise * most : step_nodes;
+    r.us += T::kSteps +
+            steps * std::max(T::kStepLaunch,
+                             (double)pblocks * (T::kStepNode * step_nodes + T::kStepEdge * step_edges +
+                                                T::kStepSlot * (slots - step_nodes)));
+  }
+  return r;
+}
+RunCut best_cut(const emr_networks& N, int64_t pblocks, const uint32_t* q_of, int32_t steps) {
+  double largest = 0.0;
+  for (int c = 0; c + 1 < kRunClasses; ++c)
+    if (N.class_first[c] < N.class_first[c + 1])
+      largest = std::max(largest, N.order_load[N.class_first[c]]);
+  RunCut best = cut_at(N, largest, pblocks, q_of, steps);
+  // (nothing is shorter than the launches of the stepwise kernels)
+  if (best.us <= RunTimes::kSteps + steps * RunTimes::kStepLaunch) return best;
+  for (int j = 0; j < 9; ++j) {
+    largest = j < 8 ? 0.5 * largest : 0.0;
+    const RunCut r = cut_at(N, largest, pblocks, q_of, steps);
+    if (r.us < best.us) best = r;
+  }
+  return best;
+}
 
 emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_patterns,
                        int32_t steps, float* outputs, float* fitness, const float* targets,
@@ -787,7 +871,6 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
   if (pblocks * (N->nodes ? N->nodes : 1) > ((int64_t)1 << 40))
     return failf(EMR_E_LIMIT, "networks: too many nodes x patterns");
   const size_t n_pat = (size_t)n_patterns * (size_t)N->n_in;
-  NET_TRY(stage_patterns(M, patterns, n_pat, targets, targets ? (size_t)n_patterns : 0, s));
   // A class's pattern groups per workgroup, no more than there are.
   uint32_t q_of[kRunClasses];
   for (int c = 0; c < kRunClasses; ++c) {
@@ -795,31 +878,27 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
     while (q < kRunClass[c].q && (int64_t)q < pblocks) q *= 2;
     q_of[c] = q;
   }
-  // One workgroup runs a (genome, pattern block). A genome whose edges exceed twice the mean load
-  // of the workgroups that the chip holds would outlast all others, so it runs stepwise, spread
-  // over the chip (a prefix of its class, which is in descending edge order).
-  int64_t work = 0;
-  for (int c = 0; c < kRunClasses; ++c)
-    for (uint32_t k = N->class_first[c]; k < N->class_first[c + 1]; ++k)
-      work += N->order_edges[k] * ((pblocks + q_of[c] - 1) / q_of[c]);
-  const int64_t most = std::max(kStepwiseEdges, work / kFusedWorkgroups);
+  const RunCut cut = best_cut(*N, pblocks, q_of, steps);
+  const uint32_t* fused_first = cut.first;
   emr::NetList list{};
   list.order = N->order.as<uint32_t>();
   list.n_genomes = (uint32_t)N->n_genomes;
-  uint32_t fused_first[kRunClasses];
   for (int c = 0; c < kRunClasses; ++c) {
-    const uint32_t k0 = N->class_first[c], k1 = N->class_first[c + 1];
-    uint32_t k = k0;
-    while (k < k1 && (c == kRunClasses - 1 || steps > kFusedSteps || N->order_edges[k] > most)) {
-      list.max_nodes = std::max(list.max_nodes, N->order_nodes[k]);
-      ++k;
-    }
+    const uint32_t k0 = N->class_first[c], k1 = fused_first[c];
+    for (uint32_t k = k0; k < k1; ++k) list.max_nodes = std::max(list.max_nodes, N->order_nodes[k]);
     list.first[c] = k0;
-    list.count[c] = k - k0;
-    list.total += k - k0;
-    fused_first[c] = k;
+    list.count[c] = k1 - k0;
+    list.total += k1 - k0;
   }
-  const float* d_targets = targets ? M.patterns.as<float>() + n_pat : nullptr;
+  // every genome stepwise: the kernels take the nodes as they lie, without the list
+  if (list.total == list.n_genomes && list.total <= 65535u) {
+    list.order = nullptr;
+    for (int c = 0; c < kRunClasses; ++c) list.first[c] = list.count[c] = 0;
+    list.count[0] = list.total;
+  }
+  // (few patterns of stepwise kernels alone are the initial state's arguments: a launch fewer)
+  const bool by_value = list.order == nullptr && n_pat <= emr::kNetStageFloats;
+  if (!by_value) NET_TRY(stage_patterns(M, patterns, n_pat, s));
   emr::NetRunArgs ra{};
   ra.order = N->order.as<uint32_t>();
   ra.node_offset = N->node_offset.as<int64_t>();
@@ -828,7 +907,7 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
   ra.in_src = N->in_src.as<uint32_t>();
   ra.in_w = N->in_w.as<float>();
   ra.patterns = M.patterns.as<float>();
-  ra.targets = d_targets;
+  if (targets) std::memcpy(ra.target, targets, sizeof ra.target);
   ra.out_node = N->d_out_node.as<int32_t>();
   ra.outputs = outputs;
   ra.fitness = fitness;
@@ -880,8 +959,9 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
         left -= n;
       }
       emr::NetStateArgs sa{list, N->node_offset.as<int64_t>(), N->node_in.as<int32_t>(),
-                           M.patterns.as<float>(), buf[0], N->nodes, (uint32_t)N->n_in,
-                           (uint32_t)n_patterns, (uint32_t)pblocks};
+                           by_value ? nullptr : M.patterns.as<float>(), buf[0], N->nodes,
+                           (uint32_t)N->n_in, (uint32_t)n_patterns, (uint32_t)pblocks, {}};
+      if (by_value) std::memcpy(sa.v, patterns, n_pat * 4);
       NET_HIP(emr_launch_net(9, &sa, s));
       int cur = 0;
       for (int32_t t = 0; t < steps; ++t, cur ^= 1) {
@@ -896,7 +976,7 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
       oa.node_offset = N->node_offset.as<int64_t>();
       oa.out_node = N->d_out_node.as<int32_t>();
       oa.state = buf[cur];
-      oa.targets = d_targets;
+      if (targets) std::memcpy(oa.target, targets, sizeof oa.target);
       oa.outputs = outputs;
       oa.fitness = fitness;
       oa.nodes = N->nodes;

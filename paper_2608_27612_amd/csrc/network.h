@@ -199,7 +199,7 @@ struct NetRunArgs {
   const uint32_t* in_src;
   const float* in_w;
   const float* patterns;       // [n_patterns * n_inputs]
-  float target[4];             // (fitness: one output, at most 4 patterns)
+  const float* targets;        // (fitness: one output, at most 4 patterns)
   const int32_t* out_node;     // [n_outputs] substrate index of output o
   float* outputs;              // [n_genomes * n_patterns * n_outputs] or NULL
   float* fitness;              // [n_genomes] or NULL

@@ -674,7 +674,7 @@ __device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_
   uint32_t* first = reinterpret_cast<uint32_t*>(lds + 2u * n * Q);
   for (uint32_t i = threadIdx.x; i < n * Q; i += kNetRunThreads) {
     const float4 v =
-        pattern4([&](int64_t j) { return A.patterns[j]; }, A.n_patterns, A.n_inputs,
+        pattern4([p = A.patterns](int64_t j) { return p[j]; }, A.n_patterns, A.n_inputs,
                  A.node_in[n0 + i / Q], block * Q + i % Q);
     cur[i] = v;
     nxt[i] = v;
@@ -715,7 +715,7 @@ __device__ __forceinline__ void net_run(const NetRunArgs& A, uint32_t g, uint32_
   if (A.fitness && threadIdx.x == 0 && (uint32_t)A.out_node[0] < n) {
     float se = 0.0f;
     for (uint32_t k = 0; k < A.n_patterns && k < 4u; ++k) {
-      const float d = c[(uint32_t)A.out_node[0] * 4u * Q + k] - A.target[k];
+      const float d = c[(uint32_t)A.out_node[0] * 4u * Q + k] - A.targets[k];
       se = fmaf(d, d, se);
     }
     A.fitness[g] = 1.0f - se / (float)A.n_patterns;

@@ -296,7 +296,7 @@ struct emr_networks {
   std::vector<double> order_load, batches_before;
   std::vector<int64_t> nodes_before, edges_before;
   std::vector<uint32_t> order_host, order_nodes, most_before, class_first;
-  // pinned staging of an activation's patterns, and the event of its last copy
+  // pinned staging of an activation's patterns and targets, and the event of its last copy
   void* pin = nullptr;
   size_t pin_bytes = 0;
   hipEvent_t pin_done = nullptr;
@@ -748,17 +748,20 @@ emr_status order_genomes(emr_networks& N, const int64_t* node_off, const int64_t
   return to_device(N.order.p, order.data(), (size_t)G * 4, s);
 }
 
-// The patterns on the device: small ones as kernel arguments, others staged in pinned memory and copied
-// on the stream (the staging is rewritten only after the previous call's copy has completed).
-emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat, hipStream_t s) {
-  const size_t need = n_pat * 4;
+// The patterns (and targets) on the device: small ones as kernel arguments, others staged in
+// pinned memory and copied on the stream (the staging is rewritten only after the previous
+// call's copy has completed).
+emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat,
+                          const float* targets, size_t n_tgt, hipStream_t s) {
+  const size_t need = (n_pat + n_tgt) * 4;
   if (M.patterns.bytes < need || !M.patterns.p)
     NET_TRY(alloc(M.patterns, need, "input patterns", s));
-  if (n_pat <= emr::kNetStageFloats) {
+  if (n_pat + n_tgt <= emr::kNetStageFloats) {
     emr::NetStageArgs a{};
     a.dst = M.patterns.as<float>();
-    a.n = (uint32_t)n_pat;
-    std::memcpy(a.v, patterns, need);
+    a.n = (uint32_t)(n_pat + n_tgt);
+    std::memcpy(a.v, patterns, n_pat * 4);
+    if (n_tgt) std::memcpy(a.v + n_pat, targets, n_tgt * 4);
     NET_HIP(emr_launch_net(12, &a, s));
     return EMR_OK;
   }
@@ -776,7 +779,8 @@ emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat, 
     }
     M.pin_bytes = need;
   }
-  std::memcpy(M.pin, patterns, need);
+  std::memcpy(M.pin, patterns, n_pat * 4);
+  if (n_tgt) std::memcpy(static_cast<float*>(M.pin) + n_pat, targets, n_tgt * 4);
   NET_HIP(hipMemcpyAsync(M.patterns.p, M.pin, need, hipMemcpyHostToDevice, s));
   NET_HIP(hipEventRecord(M.pin_done, s));
   M.pin_pending = true;
@@ -793,7 +797,7 @@ emr_status stage_patterns(emr_networks& M, const float* patterns, size_t n_pat, 
 struct RunTimes {
   static constexpr double kLaunch = 3.0, kStep = 0.8, kNode[3] = {0.028, 0.036, 0.045};
   static constexpr double kBatch = 0.026, kSlots = 512.0;
-  static constexpr double kSteps = 12.0, kStepLaunch = 4.2, kStepNode = 2.5e-4, kStepEdge = 1.3e-6,
+  static constexpr double kSteps = 12.0, kStepLaunch = 4.2, kStepNode = 2e-4, kStepEdge = 9.5e-7,
                           kStepSlot = 4e-5;
   static constexpr double kLongest = 2.5e5;  // a longer workgroup is not fused
 };
@@ -898,7 +902,8 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
   }
   // (few patterns of stepwise kernels alone are the initial state's arguments: a launch fewer)
   const bool by_value = list.order == nullptr && n_pat <= emr::kNetStageFloats;
-  if (!by_value) NET_TRY(stage_patterns(M, patterns, n_pat, s));
+  if (!by_value)
+    NET_TRY(stage_patterns(M, patterns, n_pat, targets, targets ? (size_t)n_patterns : 0, s));
   emr::NetRunArgs ra{};
   ra.order = N->order.as<uint32_t>();
   ra.node_offset = N->node_offset.as<int64_t>();
@@ -907,7 +912,7 @@ emr_status run_forward(const emr_networks* N, const float* patterns, int32_t n_p
   ra.in_src = N->in_src.as<uint32_t>();
   ra.in_w = N->in_w.as<float>();
   ra.patterns = M.patterns.as<float>();
-  if (targets) std::memcpy(ra.target, targets, sizeof ra.target);
+  ra.targets = targets ? M.patterns.as<float>() + n_pat : nullptr;
   ra.out_node = N->d_out_node.as<int32_t>();
   ra.outputs = outputs;
   ra.fitness = fitness;
